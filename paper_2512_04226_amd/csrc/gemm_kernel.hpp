@@ -87,7 +87,7 @@ typedef float f32x16 __attribute__((ext_vector_type(16)));
 // layout of the paper's own runs, Section V): B is then staged and read exactly like A.
 // FT_ (16-bit inputs only): 0 bf16 in / bf16 out, 1 IEEE fp16 in / fp16 out (the precision of the
 // paper's runs); the data path is the same, only the MFMA instruction and the output rounding differ.
-// LF_: form of the K loop, one of seven source arrangements of the same work between which the
+// LF_: form of the K loop, one of eight source arrangements of the same work between which the
 // compiler's instruction schedule, and with it the time per slab, differs by up to 15 % either
 // way; which one a variant uses is measured (8192^3, the forms interleaved) and recorded
 // in the variant table.  0: one loop over all slabs, the part up to the next barrier under a
@@ -112,6 +112,13 @@ typedef float f32x16 __attribute__((ext_vector_type(16)));
 // read three (k-step, column) blocks ahead of the MFMAs, and the slab's barrier follows the last fragment read of
 // the stage, not its last MFMA.  Fewer live registers than form 5 (the eight-wave 256x256x64 tiles keep no spills);
 // needs three or more column blocks per wave and a multiple of four blocks per slab, else the tile runs form 0.
+// 7: the pipelined loop of the 256x256 tiles on four waves (128x128 wave tiles, accumulators in AGPRs).  One wave per SIMD
+// means that nothing hides a stall, so the loop is arranged to have none: A and B slabs share a ring of five 32 KB units
+// (all 160 KB of LDS; A(s) and B(s) are neighbours, two slabs and a half are resident or in flight), the loads of a slab
+// are spread evenly over a WHOLE slab of MFMAs (B's in the second k-step, A's in the next slab's first, A one slab further
+// ahead), the slab is unrolled five times so that every ring offset is a constant, the loads' advance along K is the
+// instruction's scalar offset, and fragment rows are instruction offsets: between two MFMAs there is hardly ever more than
+// one other instruction.  See the comment at the loop for what each of these measured.
 // Building with -DG355_FORCE_LOOP_FORM=k gives every variant form k (how the forms are compared).
 // Timing-only diagnostic builds (their RESULTS ARE WRONG; every access stays in bounds and every wait ends):
 // -DG355_DIAG_SKIP_FILL leaves the refills out of the K loop (the ring keeps its first NS slabs),
@@ -140,7 +147,7 @@ struct Tile {
 #else
     static constexpr int LF_ASKED = LF_;
 #endif
-    static_assert(LF_ASKED >= 0 && LF_ASKED <= 6, "unknown K-loop form");
+    static_assert(LF_ASKED >= 0 && LF_ASKED <= 7, "unknown K-loop form");
     static_assert(FT == 0 || ES == 2, "fp16 is a 16-bit input type");
     static constexpr int NW = WM * WN;
     static constexpr int NT = WM * WN * 64;
@@ -159,13 +166,17 @@ struct Tile {
     static constexpr int KG = 64 / MI;                      // lane groups along k
     static constexpr int KL = KI / KG;                      // k elements held by one lane
     static constexpr int KSTEPS = BK / KI;
-    // form 6 needs at least three B fragments per k-step and a whole number of four-slot ring turns per slab;
-    // a tile that has neither runs form 0 when form 6 is forced on every tile
-    static constexpr int LF = (LF_ASKED == 6 && !(TN >= 3 && (KSTEPS * TN) % 4 == 0 && KSTEPS >= 2)) ? 0 : LF_ASKED;
+    // form 6 needs at least three B fragments per k-step and a whole number of four-slot ring turns per slab, form 7 the
+    // 256x256 tile on four waves with 128-byte slab rows; a tile that has neither runs form 0 when the form is forced on
+    // every tile
+    static constexpr bool FITS6 = TN >= 3 && (KSTEPS * TN) % 4 == 0 && KSTEPS >= 2;
+    static constexpr bool FITS7 = BM == 256 && BN == 256 && WM == 2 && WN == 2 && BK * ES == 128 && KSTEPS == 2 && RG == 0 && ST == 0;
+    static constexpr int LF = ((LF_ASKED == 6 && !FITS6) || (LF_ASKED == 7 && !FITS7)) ? 0 : LF_ASKED;
     static constexpr int RA = BK * ES;                      // bytes per A row in LDS
     static constexpr int RB = (BL == 0) ? BN * ES : BK * ES; // bytes per B row in LDS (a k row, or an n row when K-contiguous)
     static constexpr int A_BYTES = BM * RA, B_BYTES = BK * BN * ES;
     static constexpr int STAGE = A_BYTES + B_BYTES;
+    static constexpr int LDS_BYTES = (LF == 7) ? 5 * A_BYTES : NS * STAGE;
     static constexpr int ACH = A_BYTES / 16, BCH = B_BYTES / 16;  // 16-byte chunks per slab
     static constexpr int CA = RA / 16, CB = RB / 16;              // chunks per row
     // a direct-to-LDS load instruction of one wave fills one 1 KB unit (64 lanes x 16 bytes)
@@ -291,11 +302,35 @@ __device__ __forceinline__ void sched_spread_fills()
     }
 }
 
+// f(integral_constant<I>) for I in [I0, N): the index is a constant in the body, so that register arrays indexed with it
+// stay in registers whatever the unroller decides about a loop of hundreds of instructions.
+template <int I, int N, class F>
+__device__ __forceinline__ void static_for(F f)
+{
+    if constexpr (I < N) {
+        f(std::integral_constant<int, I>{});
+        static_for<I + 1, N>(f);
+    }
+}
+
+// s_waitcnt for at most VM vector-memory operations in flight (and, with LGKM0, no LDS operation), then the workgroup's
+// barrier.  Through the builtins and not as text: the compiler's own wait insertion then knows that the LDS reads before
+// it have returned; with the same wait as inline asm it waited for every LDS read in flight, the youngest included, at the
+// first use of a fragment in each k-step.
+template <int VM, bool LGKM0>
+__device__ __forceinline__ void wait_and_barrier()
+{
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_waitcnt((VM & 15) | ((VM >> 4) << 14) | (7 << 4) | (LGKM0 ? 0 : 15 << 8));
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+}
+
 template <class T>
 __global__ __launch_bounds__(T::NT) void gemm_kernel(const KernelArgs args)
 {
     constexpr int ES = T::ES, BM = T::BM, BN = T::BN, BK = T::BK, MI = T::MI;
-    __shared__ __attribute__((aligned(1024))) uint8_t smem[T::NS * T::STAGE];
+    __shared__ __attribute__((aligned(1024))) uint8_t smem[T::LDS_BYTES];
 
     // Work of this workgroup: one (tile, K slice) for a data-parallel or split-K launch, up to
     // two (tile, slab range) segments for a stream-K worker.
@@ -833,6 +868,135 @@ __global__ __launch_bounds__(T::NT) void gemm_kernel(const KernelArgs args)
             constexpr unsigned MIN_PITCH = BM <= 32 ? 8192 : 16384;
             rot = (k_len % BK == 0 && pitch >= MIN_PITCH && (pitch & (pitch - 1)) == 0) ? tn % kt_count : 0;
         }
+#if defined(__HIP_DEVICE_COMPILE__)
+        if constexpr (LF == 7) {
+            // Ring unit u holds one operand's slab; A(s) sits in unit 2s mod 5, B(s) in the one after it.  From the
+            // barrier in the middle of slab s (its k-step-1 fragments are in registers) the units of A(s) and B(s) are
+            // free: B(s+2) goes into A(s)'s during this k-step, A(s+3) into B(s)'s during the first k-step of slab s+1.
+            // That barrier waits for all but the youngest A slab's loads, so A has between two and three k-steps to
+            // land and B between one and two.
+            // What bounds it: the chip's power on data that toggles the matrix cores (1.77-1.84 GHz under this loop,
+            // 2.38 on zeros).  8192^3 bf16, one box each: row-major B 742 -> 671 us (zeros 685 -> 556), K-contiguous
+            // 739 -> 670 (655 -> 550) against the eight-wave forms 4 and 6.  Measured on the way (K-contiguous, N(0,1) /
+            // zeros): five units and B's and A's loads in one k-step 728 / 646; the loads spread over both k-steps
+            // 717 / 574; unrolled over the ring 672 / 553.  A burst of loads costs most (half a k-step: 791 / 740):
+            // a CU's vector-memory path takes 64 bytes per clock, and a wave whose load waits for it issues no MFMA.
+            static_assert(T::A_BYTES == T::B_BYTES && T::A_UNITS % T::NW == 0 && T::B_UNITS % T::NW == 0, "five equal units");
+            static_assert((MI / T::A_ROWS_PER_WIN) % (T::A_KEY_MASK + 1) == 0, "MFMA tiles down a wave tile share one swizzle key");
+            static_assert(T::TM % 2 == 0 && T::TN % 2 == 0, "2x2 blocks of MFMA tiles");
+            constexpr int U = T::A_BYTES;
+            typedef std::integral_constant<int, 0> K0;
+            typedef std::integral_constant<int, 1> K1;
+            // byte offsets of the lane's chunk of a K-contiguous operand in a unit, per k-step; rows of MFMA tile u are
+            // u * MI further on (fp8: a fragment's second chunk is the swizzled neighbour)
+            int fa_off[2], fb_off[2];
+#pragma unroll
+            for (int k = 0; k < 2; ++k) {
+                fa_off[k] = T::a_off(a_row, (k * T::KI + a_kg * T::KL) / EPC);
+                fb_off[k] = T::a_off(bk_row, (k * T::KI + a_kg * T::KL) / EPC);
+            }
+            auto kc_frag = [&](frag_t &dst, const G355_LDS uint8_t *p, int off, int rows) __attribute__((always_inline)) {
+                if constexpr (ES == 2) {
+                    dst = *(const G355_LDS frag_t *)(p + off + rows * T::RA);
+                } else {
+                    const i32x4 lo = *(const G355_LDS i32x4 *)(p + off + rows * T::RA);
+                    const i32x4 hi = *(const G355_LDS i32x4 *)(p + (off ^ 16) + rows * T::RA);
+                    dst = __builtin_bit_cast(frag_t, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
+                }
+            };
+            auto frag = [&](const G355_LDS uint8_t *pa, const G355_LDS uint8_t *pb, int k, int u) __attribute__((always_inline)) {
+                if (u < T::TM)
+                    kc_frag(af[k][u], pa, fa_off[k], u * MI);
+                else if (T::BL == 1)
+                    kc_frag(bfr[k][u - T::TM], pb, fb_off[k], (u - T::TM) * MI);
+                else
+                    load_frag(pb - T::A_BYTES, k, k, u);
+            };
+            // one load instruction of A's (B's) slab at K position kk; a slab wholly inside the K range needs no test and
+            // its position is the scalar offset
+            auto load_a = [&](auto tail, int i, int kk, G355_LDS uint8_t *unit) __attribute__((always_inline)) {
+                G355_LDS void *const dst = (G355_LDS void *)(unit + (i * T::NW + wave) * 1024);
+                if constexpr (decltype(tail)::value) {
+                    const unsigned off = (a_kcol[i] + kk < k_len) ? a_voff[i] + (unsigned)(kk * ES) : OOB_OFFSET;
+                    __builtin_amdgcn_raw_ptr_buffer_load_lds(rsA, dst, 16, off, 0, 0, G355_LOAD_DEFAULT);
+                } else {
+                    __builtin_amdgcn_raw_ptr_buffer_load_lds(rsA, dst, 16, a_voff[i], kk * ES, 0, G355_LOAD_DEFAULT);
+                }
+            };
+            auto load_b = [&](auto tail, int i, int kk, G355_LDS uint8_t *unit) __attribute__((always_inline)) {
+                G355_LDS void *const dst = (G355_LDS void *)(unit + (i * T::NW + wave) * 1024);
+                const unsigned adv = (T::BL == 0) ? (unsigned)kk * (unsigned)(pldb * ES) : (unsigned)(kk * ES);
+                if constexpr (decltype(tail)::value) {
+                    const unsigned off = (T::BL == 0 || b_kcol[i] + kk < k_len) ? b_voff[i] + adv : OOB_OFFSET;
+                    __builtin_amdgcn_raw_ptr_buffer_load_lds(rsB, dst, 16, off, 0, 0, G355_LOAD_DEFAULT);
+                } else {
+                    __builtin_amdgcn_raw_ptr_buffer_load_lds(rsB, dst, 16, b_voff[i], (int)adv, 0, G355_LOAD_DEFAULT);
+                }
+            };
+            // MFMA number m of a k-step: 2x2 blocks of MFMA tiles, walked as a U, so that every MFMA but one in four
+            // shares an operand with the one before (1 % on N(0,1) data against rows of eight: fewer operand changes)
+            auto mma_at = [&](int buf, int m) __attribute__((always_inline)) {
+                const int b = m / 4, q = m % 4;
+                mma_one(buf, b / (T::TM / 2) * 2 + q / 2, b % (T::TM / 2) * 2 + (q == 1 || q == 2));
+            };
+            // One k-step on the fragments in buffer KB.  Slot m: its share of the other buffer's fragment reads (from
+            // pa / pb, spread over the first three quarters), MFMA m, its share of the slab's loads of one operand.
+            constexpr int HR = MN * 3 / 4;
+            auto kstep7 = [&](auto kb, const G355_LDS uint8_t *pa, const G355_LDS uint8_t *pb, auto load) __attribute__((always_inline)) {
+                constexpr int KB = decltype(kb)::value;
+                static_for<0, MN>([&](auto mc) __attribute__((always_inline)) {
+                    constexpr int m = decltype(mc)::value, LPS = T::A_LOADS;
+                    constexpr int u0 = (m * NF + HR - 1) / HR, u1 = ((m + 1) * NF + HR - 1) / HR;
+                    static_for<(u0 < NF ? u0 : NF), (u1 < NF ? u1 : NF)>(
+                        [&](auto u) __attribute__((always_inline)) { frag(pa, pb, KB ^ 1, decltype(u)::value); });
+                    mma_at(KB, m);
+                    static_for<(m * LPS + MN - 1) / MN, ((m + 1) * LPS + MN - 1) / MN>(load);
+                    __builtin_amdgcn_sched_barrier(0);
+                });
+            };
+            // from the barrier of slab s to the barrier of slab s + 1 (ua, ub: the units of A(s) and B(s))
+            auto slab7 = [&](auto tail, G355_LDS uint8_t *__restrict__ ua, G355_LDS uint8_t *__restrict__ ub,
+                             const G355_LDS uint8_t *__restrict__ na, const G355_LDS uint8_t *__restrict__ nb, int s)
+                             __attribute__((always_inline)) {
+                kstep7(K1{}, na, nb, [&](auto l) __attribute__((always_inline)) { load_b(tail, decltype(l)::value, (s + 2) * BK, ua); });
+                kstep7(K0{}, na, nb, [&](auto l) __attribute__((always_inline)) { load_a(tail, decltype(l)::value, (s + 3) * BK, ub); });
+                wait_and_barrier<T::A_LOADS, true>();
+            };
+            const std::true_type tested{};
+            const std::false_type inside{};
+            static_for<0, 5>([&](auto uc) __attribute__((always_inline)) {
+                constexpr int u = decltype(uc)::value;
+                static_for<0, T::A_LOADS>([&](auto l) __attribute__((always_inline)) {
+                    if constexpr (u % 2 == 0)
+                        load_a(tested, decltype(l)::value, u / 2 * BK, lds + u * U);
+                    else
+                        load_b(tested, decltype(l)::value, u / 2 * BK, lds + u * U);
+                });
+            });
+            wait_and_barrier<3 * T::A_LOADS, false>();
+            static_for<0, NF>([&](auto u) __attribute__((always_inline)) { frag(lds, lds + U, 0, decltype(u)::value); });
+            kstep7(K0{}, lds, lds + U, [](auto) {});
+            wait_and_barrier<T::A_LOADS, true>();
+            int s = 0;
+            const int end = kt_count - 1;
+            const int whole = k_len / BK - 3;      // slabs below this one load only slabs that lie inside the K range
+            for (; s + 5 <= whole; s += 5)
+                static_for<0, 5>([&](auto ic) __attribute__((always_inline)) {
+                    constexpr int i = decltype(ic)::value;
+                    slab7(inside, lds + 2 * i % 5 * U, lds + (2 * i + 1) % 5 * U, lds + (2 * i + 2) % 5 * U,
+                          lds + (2 * i + 3) % 5 * U, s + i);
+                });
+            int ua = 0;
+            auto wrap = [](int x) { return x >= 5 ? x - 5 : x; };
+            for (; s < end; ++s) {
+                const int na = wrap(ua + 2);
+                slab7(tested, lds + ua * U, lds + wrap(ua + 1) * U, lds + na * U, lds + wrap(ua + 3) * U, s);
+                ua = na;
+            }
+            static_for<0, MN>([&](auto mc) __attribute__((always_inline)) { mma_at(1, decltype(mc)::value); });
+            return;
+        }
+#endif
 #pragma unroll
         for (int s = 0; s < T::NS; ++s)
 #pragma unroll
@@ -970,7 +1134,7 @@ __global__ __launch_bounds__(T::NT) void gemm_kernel(const KernelArgs args)
     typedef typename std::conditional<T::FT == 1, f16x8, bf16x8>::type out8_t;
     constexpr int ST_ROW = T::WTN * 4 + 16;                 // bytes per staged row
     constexpr int ST_CPR = T::WTN / 8;                      // 8-float chunks per row
-    static_assert(T::NW * MI * ST_ROW <= T::NS * T::STAGE, "the staging rows of all waves must fit the LDS ring");
+    static_assert(T::NW * MI * ST_ROW <= T::LDS_BYTES, "the staging rows of all waves must fit the LDS ring");
     const float alpha = args.alpha, beta = args.beta;
     // every wave's requests towards LDS have landed (above) and every wave is past its last fragment read
     __syncthreads();

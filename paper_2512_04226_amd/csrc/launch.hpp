@@ -11,7 +11,8 @@ struct VariantFns {
     OccupancyFn occupancy;   // the runtime's resident-workgroups-per-CU figure for the instantiation
 };
 // (variant index inside the translation unit's list, storage of B: 0 row-major K x N, 1 K-contiguous N x K,
-//  1 for the instantiation that handles an N or K that is not a whole number of 16-byte chunks)
+//  instantiation: 0 plain, 1 for an N or K that is not a whole number of 16-byte chunks, 2 weight-streaming,
+//  3 pipelined -- its launch is null for a tile that has none)
 const VariantFns &kLaunchBf16_0(int, int, int),
     &kLaunchBf16_1(int, int, int),
     &kLaunchBf16_2(int, int, int),

@@ -171,7 +171,8 @@ int scratch_of_current_device(void **out)
     return GEMM_OK;
 }
 
-const VariantFns &launcher_of(int dtype, int id, int bl, int ragged)
+// which: the instantiation of the variant (see kernels.inc)
+const VariantFns &launcher_of(int dtype, int id, int bl, int which)
 {
 #define G355_COUNT(...) +1
     constexpr int n_b0 = 0 G355_VARIANTS_BF16_0(G355_COUNT);
@@ -183,33 +184,47 @@ const VariantFns &launcher_of(int dtype, int id, int bl, int ragged)
 #undef G355_COUNT
     if (dtype == GEMM_FP16) {
         if (id < n_b0)
-            return kLaunchFp16_0(id, bl, ragged);
+            return kLaunchFp16_0(id, bl, which);
         if (id < n_b0 + n_b1)
-            return kLaunchFp16_1(id - n_b0, bl, ragged);
+            return kLaunchFp16_1(id - n_b0, bl, which);
         if (id < n_b0 + n_b1 + n_b2)
-            return kLaunchFp16_2(id - n_b0 - n_b1, bl, ragged);
+            return kLaunchFp16_2(id - n_b0 - n_b1, bl, which);
         if (id < n_b0 + n_b1 + n_b2 + n_b3)
-            return kLaunchFp16_3(id - n_b0 - n_b1 - n_b2, bl, ragged);
+            return kLaunchFp16_3(id - n_b0 - n_b1 - n_b2, bl, which);
         if (id < n_b0 + n_b1 + n_b2 + n_b3 + n_b4)
-            return kLaunchFp16_4(id - n_b0 - n_b1 - n_b2 - n_b3, bl, ragged);
-        return kLaunchFp16_5(id - n_b0 - n_b1 - n_b2 - n_b3 - n_b4, bl, ragged);
+            return kLaunchFp16_4(id - n_b0 - n_b1 - n_b2 - n_b3, bl, which);
+        return kLaunchFp16_5(id - n_b0 - n_b1 - n_b2 - n_b3 - n_b4, bl, which);
     }
     if (dtype == GEMM_BF16) {
         if (id < n_b0)
-            return kLaunchBf16_0(id, bl, ragged);
+            return kLaunchBf16_0(id, bl, which);
         if (id < n_b0 + n_b1)
-            return kLaunchBf16_1(id - n_b0, bl, ragged);
+            return kLaunchBf16_1(id - n_b0, bl, which);
         if (id < n_b0 + n_b1 + n_b2)
-            return kLaunchBf16_2(id - n_b0 - n_b1, bl, ragged);
+            return kLaunchBf16_2(id - n_b0 - n_b1, bl, which);
         if (id < n_b0 + n_b1 + n_b2 + n_b3)
-            return kLaunchBf16_3(id - n_b0 - n_b1 - n_b2, bl, ragged);
+            return kLaunchBf16_3(id - n_b0 - n_b1 - n_b2, bl, which);
         if (id < n_b0 + n_b1 + n_b2 + n_b3 + n_b4)
-            return kLaunchBf16_4(id - n_b0 - n_b1 - n_b2 - n_b3, bl, ragged);
-        return kLaunchBf16_5(id - n_b0 - n_b1 - n_b2 - n_b3 - n_b4, bl, ragged);
+            return kLaunchBf16_4(id - n_b0 - n_b1 - n_b2 - n_b3, bl, which);
+        return kLaunchBf16_5(id - n_b0 - n_b1 - n_b2 - n_b3 - n_b4, bl, which);
     }
     if (id < n_f0)
-        return kLaunchFp8_0(id, bl, ragged);
-    return kLaunchFp8_1(id - n_f0, bl, ragged);
+        return kLaunchFp8_0(id, bl, which);
+    return kLaunchFp8_1(id - n_f0, bl, which);
+}
+
+// The instantiation of a variant that a launch runs.  The pipelined one (four waves, K-loop form 7) has the faster loop
+// and, with half the waves, the slower prologue and store stage (about 2 us in 16-bit types): it pays from about twenty
+// K slabs per workgroup.  Plain -> pipelined, M = N = 4096 bf16, K-contiguous B: K = 512 21.7 -> 22.9 us, 1024 32.9 -> 33.3,
+// 1536 44.5 -> 43.6, 2048 56.9 -> 54.1, 4096 106.1 -> 94.8; fp8 (whose plain tile has four waves too): level up to
+// K = 2048, 56.1 -> 55.0 at 4096.
+constexpr int64_t kPipelinedSlabs = 20;
+const VariantFns &kernel_of(int dtype, int id, int bl, bool ragged, bool streaming, int64_t slabs)
+{
+    if (ragged || streaming)
+        return launcher_of(dtype, id, bl, ragged ? 1 : 2);
+    const VariantFns &pipelined = launcher_of(dtype, id, bl, 3);
+    return (pipelined.launch && slabs >= kPipelinedSlabs) ? pipelined : launcher_of(dtype, id, bl, 0);
 }
 
 inline int64_t cdiv64(int64_t a, int64_t b) { return (a + b - 1) / b; }
@@ -348,8 +363,11 @@ static int run_impl(const gemm_cfg *cfg, const void *A, const void *B, void *C, 
     // (B's loads non-temporal, K walked in a rotated order where the weights' pitch asks for it).  Weights that fit
     // that cache are left to it: a caller that multiplies by the same weights again soon finds them there (fp8
     // M = 64, N = 28672, K = 8192, 235 MB, in a loop: 40 us cached, 48 us streamed).
-    const int streaming = (!ragged && tiles_m == 1 && (double)cfg->N * (double)cfg->K * es > hw.mall_bytes) ? 2 : 0;
-    if (launcher_of(dtype, cfg->kernel_id, cfg->b_layout, ragged ? 1 : streaming).launch(a, stream) != hipSuccess) {
+    const int streaming = (!ragged && tiles_m == 1 && (double)cfg->N * (double)cfg->K * es > hw.mall_bytes) ? 1 : 0;
+    // K slabs a workgroup walks: its slice of K, or a Stream-K worker's share where no tile is whole
+    const int64_t slabs = (sk.workers > 0 && sk.dp_tiles == 0) ? sk.iters / sk.workers : kps / v.block_k;
+    const VariantFns &fns = kernel_of(dtype, cfg->kernel_id, cfg->b_layout, ragged, streaming, slabs);
+    if (fns.launch(a, stream) != hipSuccess) {
         (void)hipGetLastError();
         return GEMM_ERR_HIP;
     }
@@ -441,6 +459,7 @@ extern "C" int gemm_run_grouped(const gemm_cfg *cfg, int n_groups, const gemm_gr
         return GEMM_ERR_ALIGN;
     const int X = grouped_xcds(cfg);
     int64_t slots = 0;
+    int64_t tiles = 0, tile_slabs = 0;
     int ragged = 0;   // one group with a ragged N or K sends the whole launch through the trimming instantiation
     const int per16 = 16 / elem_bytes(cfg->dtype);
     for (int i = 0; i < n_groups; ++i) {
@@ -452,6 +471,9 @@ extern "C" int gemm_run_grouped(const gemm_cfg *cfg, int n_groups, const gemm_gr
             return GEMM_ERR_SHAPE;
         if (host_table[i].M > 0 && (host_table[i].N % per16 || host_table[i].K % per16))
             ragged = 1;
+        const int64_t t = (int64_t)host_table[i].tiles_m * host_table[i].tiles_n;
+        tiles += t;
+        tile_slabs += t * cdiv64(host_table[i].K, cfg->block_k);
     }
     if (slots == 0)
         return GEMM_OK;   // every group is empty
@@ -470,7 +492,9 @@ extern "C" int gemm_run_grouped(const gemm_cfg *cfg, int n_groups, const gemm_gr
     a.batch = 1;
     a.groups = (const GroupRec *)dev_table;
     a.n_groups = n_groups;
-    if (launcher_of(cfg->dtype, cfg->kernel_id, cfg->b_layout, ragged).launch(a, (hipStream_t)hip_stream) != hipSuccess) {
+    // one kernel for all groups: the mean slab count over the tiles decides
+    if (kernel_of(cfg->dtype, cfg->kernel_id, cfg->b_layout, ragged, false, tile_slabs / tiles).launch(a, (hipStream_t)hip_stream) !=
+        hipSuccess) {
         (void)hipGetLastError();
         return GEMM_ERR_HIP;
     }
