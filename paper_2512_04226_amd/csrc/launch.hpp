@@ -11,8 +11,8 @@ struct VariantFns {
     OccupancyFn occupancy;   // the runtime's resident-workgroups-per-CU figure for the instantiation
 };
 // (variant index inside the translation unit's list, storage of B: 0 row-major K x N, 1 K-contiguous N x K,
-//  instantiation: 0 plain, 1 for an N or K that is not a whole number of 16-byte chunks, 2 weight-streaming,
-//  3 pipelined -- its launch is null for a tile that has none)
+//  instantiation: 0 plain, 1 for an N or K that is not a whole number of 16-byte chunks, 2 weight-streaming, 3 pipelined,
+//  4 pipelined and ragged -- 3 and 4: launch is null for a tile that has none)
 const VariantFns &kLaunchBf16_0(int, int, int),
     &kLaunchBf16_1(int, int, int),
     &kLaunchBf16_2(int, int, int),

@@ -221,10 +221,10 @@ const VariantFns &launcher_of(int dtype, int id, int bl, int which)
 constexpr int64_t kPipelinedSlabs = 20;
 const VariantFns &kernel_of(int dtype, int id, int bl, bool ragged, bool streaming, int64_t slabs)
 {
-    if (ragged || streaming)
-        return launcher_of(dtype, id, bl, ragged ? 1 : 2);
-    const VariantFns &pipelined = launcher_of(dtype, id, bl, 3);
-    return (pipelined.launch && slabs >= kPipelinedSlabs) ? pipelined : launcher_of(dtype, id, bl, 0);
+    if (streaming)
+        return launcher_of(dtype, id, bl, 2);
+    const VariantFns &pipelined = launcher_of(dtype, id, bl, ragged ? 4 : 3);
+    return (pipelined.launch && slabs >= kPipelinedSlabs) ? pipelined : launcher_of(dtype, id, bl, ragged ? 1 : 0);
 }
 
 inline int64_t cdiv64(int64_t a, int64_t b) { return (a + b - 1) / b; }
@@ -357,7 +357,7 @@ static int run_impl(const gemm_cfg *cfg, const void *A, const void *B, void *C, 
 
     hipStream_t stream = (hipStream_t)hip_stream;
     const int f16 = (dtype == GEMM_FP16) ? 1 : 0;
-    // an N or K that is not a whole number of 16-byte chunks runs the instantiation that trims in registers
+    // an N or K that is not a whole number of 16-byte chunks runs the instantiation that trims its last slab
     const int ragged = (cfg->N % per16 || cfg->K % per16) ? 1 : 0;
     // A grid of one tile row over weights larger than the memory-side cache runs the weight-streaming instantiation
     // (B's loads non-temporal, K walked in a rotated order where the weights' pitch asks for it).  Weights that fit
