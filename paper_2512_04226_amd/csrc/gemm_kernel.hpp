@@ -1079,80 +1079,119 @@ __global__ __launch_bounds__(T::NT) void gemm_kernel(const KernelArgs args)
 
     // ---- epilogue: a lane holds, per MFMA tile, output row m = lane % MI and columns
     //      n = 8*(r/4) + 4*(lane/32) + r%4 (32x32) or n = 4*(lane/16) + r (16x16).  Stored from
-    //      there, one instruction would write 16- or 32-byte pieces of many rows; instead every
-    //      wave passes its accumulators through a private piece of the (now free) LDS ring, one
-    //      MFMA row block (MI rows of its wave tile) at a time, and stores whole row segments of
-    //      its tile: 128 bytes and more per row.  Staged rows are padded by 16 bytes so that the
-    //      16-byte writes of a column of lanes spread over the banks. ----
+    //      there, one instruction would write 8- to 32-byte pieces of many rows; instead every
+    //      wave passes its results through a private piece of the (now free) LDS ring and stores
+    //      whole row segments of its tile: 128 bytes and more per row.  Staged rows are padded by
+    //      16 bytes so that the writes of a column of lanes spread over the banks.
+    //      What bounds it is latency (write, read back, store, one after the other, with few
+    //      waves on the CU), so as many MFMA row blocks as fit go through LDS at a time; and a
+    //      result that needs neither the old C nor a later summation is scaled and rounded before
+    //      it is staged, which halves the LDS traffic.  STORE_STAGE_FIGURES ----
     typedef typename std::conditional<T::FT == 1, _Float16, __bf16>::type out_t;
     typedef typename std::conditional<T::FT == 1, f16x8, bf16x8>::type out8_t;
-    constexpr int ST_ROW = T::WTN * 4 + 16;                 // bytes per staged row
-    constexpr int ST_CPR = T::WTN / 8;                      // 8-float chunks per row
-    static_assert(T::NW * MI * ST_ROW <= T::LDS_BYTES, "the staging rows of all waves must fit the LDS ring");
+    typedef typename std::conditional<T::FT == 1, f16x4, bf16x4>::type out4_t;
+    constexpr int ST_CPR = T::WTN / 8;                      // chunks of 8 columns per row of the wave tile
+    constexpr int ST_RPI = 64 / ST_CPR;                     // rows one instruction of a wave covers
+    static_assert(64 % ST_CPR == 0, "a lane keeps its column chunk");
+    constexpr int ST_ROW32 = T::WTN * 4 + 16, ST_ROW16 = T::WTN * 2 + 16;   // bytes per staged row
+    static_assert(T::NW * MI * ST_ROW32 <= T::LDS_BYTES, "the staging rows of all waves must fit the LDS ring");
+    // row blocks at a time, rounded and as fp32
+    constexpr int ST_FIT = T::LDS_BYTES / (T::NW * MI * ST_ROW16), ST_FIT32 = T::LDS_BYTES / (T::NW * MI * ST_ROW32);
+    constexpr int ST_G = (ST_FIT >= 4 && T::TM % 4 == 0) ? 4 : (ST_FIT >= 2 && T::TM % 2 == 0) ? 2 : 1;
+    constexpr int ST_G32 = ST_FIT32 >= ST_G ? ST_G : (ST_FIT32 >= 2 && ST_G % 2 == 0) ? 2 : 1;
     const float alpha = args.alpha, beta = args.beta;
     // every wave's requests towards LDS have landed (above) and every wave is past its last fragment read
     __syncthreads();
-    G355_LDS uint8_t *stg = lds + wave * (MI * ST_ROW);
-    const int st_w = (lane % MI) * ST_ROW + 16 * (lane / MI);      // this lane's row and 4-column group
-    const int row0 = m0 + wm * T::WTM, col0 = n0 + wn * T::WTN;    // origin of the wave tile
+    const int row0 = m0 + wm * T::WTM, n = n0 + wn * T::WTN + lane % ST_CPR * 8;   // first row of the wave tile, the lane's columns
+    auto c_at = [&](int m) { return (out_t *)pC + bz * args.stride_c + (size_t)m * pldc + n; };
+    auto store8 = [&](out_t *dst, out8_t o) __attribute__((always_inline)) {
+        if (!T::RG || n + 8 <= pN) {
+            *(out8_t *)dst = o;
+        } else {
+            // ragged edge of C: nothing beyond column N - 1 is written
 #pragma unroll
-    for (int i = 0; i < T::TM; ++i) {
-#pragma unroll
-        for (int j = 0; j < T::TN; ++j)
-#pragma unroll
-            for (int q = 0; q < T::ACC / 4; ++q) {
-                f32x4 v;
-#pragma unroll
-                for (int r = 0; r < 4; ++r)
-                    v[r] = acc[j][i][q * 4 + r];
-                *(G355_LDS f32x4 *)(stg + st_w + (j * MI + q * 8) * 4) = v;
-            }
-        // the wave reads back what it wrote itself (LDS operations of one wave complete in order):
-        // 8 consecutive columns per lane, so that a 16-bit result leaves as one 16-byte store
-#pragma unroll
-        for (int c0 = 0; c0 < MI * ST_CPR; c0 += 64) {
-            const int c = c0 + lane;
-            const int m = row0 + i * MI + c / ST_CPR, n = col0 + (c % ST_CPR) * 8;
-            if ((MI * ST_CPR % 64 != 0 && c >= MI * ST_CPR) || m >= pM || n >= pN)
-                continue;
-            const G355_LDS uint8_t *src = stg + (c / ST_CPR) * ST_ROW + (c % ST_CPR) * 32;
-            const f32x4 lo = *(const G355_LDS f32x4 *)src, hi = *(const G355_LDS f32x4 *)(src + 16);
-            if (out_mode != 0) {
-                // split-K slabs have rows of N rounded up to 8 floats (whole 32-byte stores also at a ragged edge)
-                const size_t nw = T::RG ? (size_t)(pN + 7) / 8 * 8 : (size_t)pN;   // (N is a multiple of 8 otherwise)
-                float *dst = (out_mode == 1)
-                                 ? args.ws + ((bz * args.split_k + ks) * pM + m) * nw + n
-                                 : args.ws + ((size_t)(2 * blockIdx.x + seg) * BM + (m - m0)) * BN + (n - n0);
-                *(f32x4 *)dst = lo;
-                *(f32x4 *)(dst + 4) = hi;
-            } else {
-                out_t *dst = (out_t *)pC + bz * args.stride_c + (size_t)m * pldc + n;
-                out8_t o;
-                if (beta != 0.f) {
-                    const out8_t cin = *(const out8_t *)dst;
-#pragma unroll
-                    for (int r = 0; r < 4; ++r) {
-                        o[r] = (out_t)__builtin_fmaf(beta, (float)cin[r], lo[r] * alpha);
-                        o[r + 4] = (out_t)__builtin_fmaf(beta, (float)cin[r + 4], hi[r] * alpha);
-                    }
-                } else {
-#pragma unroll
-                    for (int r = 0; r < 4; ++r) {
-                        o[r] = (out_t)(lo[r] * alpha);
-                        o[r + 4] = (out_t)(hi[r] * alpha);
-                    }
-                }
-                if (!T::RG || n + 8 <= pN) {
-                    *(out8_t *)dst = o;
-                } else {
-                    // ragged edge of C: nothing beyond column N - 1 is written
-#pragma unroll
-                    for (int r = 0; r < 8; ++r)
-                        if (n + r < pN)
-                            dst[r] = o[r];
-                }
-            }
+            for (int r = 0; r < 8; ++r)
+                if (n + r < pN)
+                    dst[r] = o[r];
         }
+    };
+    // MFMA row blocks i0 .. i0 + G - 1 of the wave tile, staged as fp32 (wide) or scaled and rounded
+    auto store_blocks = [&](auto wide, auto gc, int i0, auto put) __attribute__((always_inline)) {
+        constexpr bool F32 = decltype(wide)::value;
+        constexpr int G = decltype(gc)::value, ROWB = F32 ? ST_ROW32 : ST_ROW16, EB = F32 ? 4 : 2, ROWS = G * MI;
+        G355_LDS uint8_t *const stg = lds + wave * (ROWS * ROWB);
+        const int st_w = (lane % MI) * ROWB + 4 * EB * (lane / MI);      // this lane's row and 4-column group
+#pragma unroll
+        for (int i = 0; i < G; ++i)
+#pragma unroll
+            for (int j = 0; j < T::TN; ++j) {
+                // a 128x128 wave tile's accumulators live in AGPRs: said here, or the register allocator copies all 256
+                // of them to VGPRs at the end of the K loop and from there to scratch
+                if constexpr (BM * BN / T::NT >= 256)
+                    asm volatile("" : "+a"(acc[j][i0 + i]));
+#pragma unroll
+                for (int q = 0; q < T::ACC / 4; ++q) {
+                    f32x4 v;
+#pragma unroll
+                    for (int r = 0; r < 4; ++r)
+                        v[r] = acc[j][i0 + i][q * 4 + r];
+                    G355_LDS uint8_t *const w = stg + st_w + i * (MI * ROWB) + (j * MI + q * 8) * EB;
+                    if constexpr (F32) {
+                        *(G355_LDS f32x4 *)w = v;
+                    } else {
+                        out4_t o;
+#pragma unroll
+                        for (int r = 0; r < 4; ++r)
+                            o[r] = (out_t)(v[r] * alpha);
+                        *(G355_LDS out4_t *)w = o;
+                    }
+                }
+            }
+        // the wave reads back what it wrote itself (LDS operations of one wave complete in order)
+        const int lrow = lane / ST_CPR;
+        const G355_LDS uint8_t *const src = stg + lrow * ROWB + lane % ST_CPR * (8 * EB);
+#pragma unroll
+        for (int t = 0; t < ROWS; t += ST_RPI) {
+            const int m = row0 + i0 * MI + t + lrow;
+            if ((ROWS % ST_RPI == 0 || t + lrow < ROWS) && m < pM && n < pN)
+                put(m, src + t * ROWB);
+        }
+    };
+    const bool narrow = out_mode == 0 && beta == 0.f;
+#pragma unroll
+    for (int i0 = 0; i0 < T::TM; i0 += ST_G) {
+        if (narrow) {
+            store_blocks(std::false_type{}, std::integral_constant<int, ST_G>{}, i0,
+                         [&](int m, const G355_LDS uint8_t *src) __attribute__((always_inline)) {
+                             store8(c_at(m), *(const G355_LDS out8_t *)src);
+                         });
+            continue;
+        }
+#pragma unroll
+        for (int i = i0; i < i0 + ST_G; i += ST_G32)
+            store_blocks(std::true_type{}, std::integral_constant<int, ST_G32>{}, i,
+                         [&](int m, const G355_LDS uint8_t *src) __attribute__((always_inline)) {
+                             const f32x4 lo = *(const G355_LDS f32x4 *)src, hi = *(const G355_LDS f32x4 *)(src + 16);
+                             if (out_mode != 0) {
+                                 // split-K slabs have rows of N rounded up to 8 floats (whole 32-byte stores also at a ragged edge)
+                                 const size_t nw = T::RG ? (size_t)(pN + 7) / 8 * 8 : (size_t)pN;   // (N is a multiple of 8 otherwise)
+                                 float *dst = (out_mode == 1)
+                                                  ? args.ws + ((bz * args.split_k + ks) * pM + m) * nw + n
+                                                  : args.ws + ((size_t)(2 * blockIdx.x + seg) * BM + (m - m0)) * BN + (n - n0);
+                                 *(f32x4 *)dst = lo;
+                                 *(f32x4 *)(dst + 4) = hi;
+                             } else {
+                                 out_t *const dst = c_at(m);
+                                 const out8_t cin = *(const out8_t *)dst;
+                                 out8_t o;
+#pragma unroll
+                                 for (int r = 0; r < 4; ++r) {
+                                     o[r] = (out_t)__builtin_fmaf(beta, (float)cin[r], lo[r] * alpha);
+                                     o[r + 4] = (out_t)__builtin_fmaf(beta, (float)cin[r + 4], hi[r] * alpha);
+                                 }
+                                 store8(dst, o);
+                             }
+                         });
     }
     }   // segments
 }
