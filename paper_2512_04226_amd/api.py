@@ -7,6 +7,8 @@ computation runs in libgemm355.so.
     C = matmul(A, B)                       # A (M, K), B (K, N): bf16, fp16 or float8_e4m3fn
     C = matmul(X, W, b_k_contiguous=True)  # W stored (N, K), as an nn.Linear weight
 """
+import ctypes
+
 import torch
 
 from . import binding as g
@@ -17,6 +19,8 @@ if hasattr(torch, "float8_e4m3fn"):
 
 _cfg_cache = {}       # (M, N, K, dtype, b_layout) -> cfg; the selector is deterministic, so this is exact
 _workspace = {}       # device index -> tensor
+_plans = {}           # (M, N, K, dtype, b_layout, lda, ldb, ldc) -> _Plan
+_MAX_PLANS = 4096     # a program with more shapes than this starts over
 
 
 def select(M, N, K, dtype, b_layout=g.GEMM_B_ROW_MAJOR):
@@ -28,10 +32,29 @@ def select(M, N, K, dtype, b_layout=g.GEMM_B_ROW_MAJOR):
     return cfg
 
 
-def _ensure_workspace(cfg, device):
-    need = g.gemm_workspace_bytes(cfg)
-    if not need:
-        return
+class _Plan:
+    """What one launch needs beside its pointers: the pick with the tensors' leading dimensions, alpha = 1 and beta = 0
+    (never changed after it is made, so threads share it), and its workspace size."""
+    __slots__ = ("base", "cfg", "ref", "need")
+
+    def __init__(self, base, lda, ldb, ldc):
+        self.base, self.cfg = base, base.copy()
+        self.cfg.lda, self.cfg.ldb, self.cfg.ldc = lda, ldb, ldc
+        self.cfg.alpha, self.cfg.beta = 1.0, 0.0
+        self.ref = ctypes.byref(self.cfg)
+        self.need = g.gemm_workspace_bytes(self.cfg)
+
+
+def _plan(base, key):
+    plan = _plans.get(key)
+    if plan is None or plan.base is not base:      # (another base: the memo of picks was emptied since)
+        if len(_plans) >= _MAX_PLANS:
+            _plans.clear()
+        plan = _plans[key] = _Plan(base, *key[5:])
+    return plan
+
+
+def _ensure_workspace(need, device):
     idx = device.index if device.index is not None else torch.cuda.current_device()
     cur = _workspace.get(idx)
     if cur is None or cur.numel() * 4 < need:
@@ -48,30 +71,50 @@ def _ensure_workspace(cfg, device):
 def matmul(A, B, out=None, alpha=1.0, beta=0.0, b_k_contiguous=False, stream=None):
     """out = alpha * A @ B + beta * out.  A: (M, K) row-major; B: (K, N) row-major, or (N, K)
     row-major with b_k_contiguous=True.  bf16 / fp8 inputs give a bf16 result, fp16 gives fp16."""
-    if A.dtype not in _DTYPES or B.dtype != A.dtype:
+    a_dtype, device = A.dtype, A.device
+    dtype = _DTYPES.get(a_dtype)
+    if dtype is None or B.dtype != a_dtype:
         raise TypeError("matmul takes two tensors of one dtype out of %s" % sorted(str(d) for d in _DTYPES))
-    if A.dim() != 2 or B.dim() != 2 or not A.is_cuda or not B.is_cuda or A.device != B.device:
+    if A.dim() != 2 or B.dim() != 2 or not A.is_cuda or not B.is_cuda or device != B.device:
         raise ValueError("matmul takes two 2-D tensors on one GPU")
-    if A.stride(1) != 1 or B.stride(1) != 1:
+    (lda, a_step), (ldb, b_step) = A.stride(), B.stride()
+    if a_step != 1 or b_step != 1:
         raise ValueError("rows of A and B must be contiguous (leading dimensions are free)")
     M, K = A.shape
-    N = B.shape[0] if b_k_contiguous else B.shape[1]
-    if (B.shape[1] if b_k_contiguous else B.shape[0]) != K:
+    N, K_b = B.shape if b_k_contiguous else B.shape[::-1]
+    if K_b != K:
         raise ValueError("inner dimensions differ")
-    dtype = _DTYPES[A.dtype]
     out_dtype = torch.float16 if dtype == g.GEMM_FP16 else torch.bfloat16
     if out is None:
         if beta != 0.0:
             raise ValueError("beta != 0 needs out")
         # rows of C start on 16-byte boundaries: a ragged N gets a padded row stride (the result is a view)
-        out = torch.empty((M, -(-N // 8) * 8), dtype=out_dtype, device=A.device)[:, :N]
-    elif out.shape != (M, N) or out.dtype != out_dtype or out.stride(1) != 1 or out.device != A.device:
-        raise ValueError("out must be a (%d, %d) %s tensor with contiguous rows" % (M, N, out_dtype))
+        ldc = -(-N // 8) * 8
+        out = torch.empty((M, ldc), dtype=out_dtype, device=device)
+        if ldc != N:
+            out = out[:, :N]
+    else:
+        if out.shape != (M, N) or out.dtype != out_dtype or out.stride(1) != 1 or out.device != device:
+            raise ValueError("out must be a (%d, %d) %s tensor with contiguous rows" % (M, N, out_dtype))
+        ldc = out.stride(0)
     layout = g.GEMM_B_K_CONTIGUOUS if b_k_contiguous else g.GEMM_B_ROW_MAJOR
-    cfg = select(M, N, K, dtype, layout).copy()
-    cfg.lda, cfg.ldb, cfg.ldc = A.stride(0), B.stride(0), out.stride(0)
-    cfg.alpha, cfg.beta = alpha, beta
-    with torch.cuda.device(A.device):
-        _ensure_workspace(cfg, A.device)
-        g.gemm_run(cfg, A, B, out, stream)
+    plan = _plan(select(M, N, K, dtype, layout), (M, N, K, dtype, layout, lda, ldb, ldc))
+    cfg_ref = plan.ref
+    if alpha != 1.0 or beta != 0.0:
+        cfg = plan.cfg.copy()
+        cfg.alpha, cfg.beta = alpha, beta
+        cfg_ref = ctypes.byref(cfg)
+    if torch.cuda.current_device() == device.index:
+        _launch(plan.need, cfg_ref, A, B, out, device, stream)
+    else:
+        with torch.cuda.device(device):
+            _launch(plan.need, cfg_ref, A, B, out, device, stream)
     return out
+
+
+def _launch(need, cfg_ref, A, B, out, device, stream):
+    """gemm_run with the tensors' device current: no error paths, no Python objects made per argument."""
+    if need:
+        _ensure_workspace(need, device)
+    stream = g.current_stream_handle(device.index) if stream is None else g._stream_handle(stream)
+    g._check(g._lib.gemm_run(cfg_ref, A.data_ptr(), B.data_ptr(), out.data_ptr(), stream), "gemm_run")

@@ -219,9 +219,21 @@ def gemm_probe_stream(buf, scratch, stream=None):
     return out.value
 
 
+# torch's own accessor of the current stream's handle where it has one (what its compiler emits for launches): a tenth of
+# the cost of building a Stream object per call
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
+def current_stream_handle(device_index):
+    """Raw handle of torch's current stream on a device."""
+    if _raw_stream is not None:
+        return _raw_stream(device_index)
+    return torch.cuda.current_stream(device_index).cuda_stream
+
+
 def _stream_handle(stream):
     if stream is None:
-        return torch.cuda.current_stream().cuda_stream
+        return current_stream_handle(torch.cuda.current_device())
     return stream.cuda_stream if hasattr(stream, "cuda_stream") else stream
 
 
@@ -379,14 +391,13 @@ def gemm_set_workspace(tensor):
 
 
 def _ptr(t):
-    return ctypes.c_void_p(t.data_ptr()) if t is not None else None
+    return t.data_ptr() if t is not None else None
 
 
 def gemm_run(cfg, A, B, C, stream=None):
     """Enqueue C = alpha * A * B + beta * C (cfg.batch problems, cfg.stride_* apart).  stream: a torch.cuda.Stream, a raw hipStream_t int, or
     None for torch's current stream."""
-    _check(_lib.gemm_run(ctypes.byref(cfg), _ptr(A), _ptr(B), _ptr(C), ctypes.c_void_p(_stream_handle(stream))),
-           "gemm_run")
+    _check(_lib.gemm_run(ctypes.byref(cfg), _ptr(A), _ptr(B), _ptr(C), _stream_handle(stream)), "gemm_run")
 
 
 def gemm_run_noalloc(cfg, A, B, C, stream=None):
