@@ -114,3 +114,35 @@ def test_pipelined_batch_group_and_beta(oracle, bl):
                 dC.fill_(0x7FC0)
         n += 1
     assert n >= 2
+
+
+@pytest.mark.parametrize("M,N,K,batch,dtype,bl", [(4100, 4360, 72, 1, BF16, 0), (4100, 4360, 1288, 1, BF16, 1), (260, 264, 200, 141, BF16, 1),
+                                                  (4100, 4360, 272, 1, E4M3, 1)])
+def test_resident_launch_takes_every_work_item(oracle, M, N, K, batch, dtype, bl):
+    """More work items than the device holds workgroups (306 tiles of 256x256, 1155 of 128x128; 564 to 1269 of a batch whose
+    item count is no multiple of the grid): every tile of every problem is written, bit for bit, whatever order the
+    workgroups take them in.  Sampled rows of the product against the oracle; every row against a second configuration."""
+    from gpu_util import to_dev
+    from paper_2512_04226_amd import binding as g
+    A, B = _operands(oracle, batch * M, N, K, dtype)
+    per16 = 16 if dtype == E4M3 else 8
+    pad = lambda x: np.pad(x, ((0, 0), (0, -x.shape[1] % per16)))
+    dA, dB = to_dev(pad(A)), to_dev(pad(np.ascontiguousarray(B.T) if bl else B))
+    dBs = dB.repeat(batch, 1)
+    rows = np.unique(np.concatenate([np.arange(0, batch * M, 997), [M - 1, batch * M - 1]]))
+    ref16, _ = oracle.gemm_rows(A, B, rows, dtype)
+    first, n = None, 0
+    for idx in range(g.gemm_cfg_count(dtype)):
+        c = g.gemm_cfg_at_batched(idx, M, N, K, batch, dtype, bl)
+        if c is None or c.split_k > 1 or c.stream_k or c.block_m * c.block_n < 128 * 128:
+            continue
+        dC = torch.full((batch * M, c.ldc), 0x7FC0, dtype=torch.int16, device="cuda")
+        c.stride_a, c.stride_b, c.stride_c = M * c.lda, dB.shape[0] * c.ldb, M * c.ldc
+        g.gemm_run(c, dA, dBs, dC)
+        torch.cuda.synchronize()
+        out = dC.cpu().numpy().view(np.uint16)[:, :N]
+        assert np.array_equal(out[rows], ref16), c.describe()
+        first = out if first is None else first
+        assert np.array_equal(out, first), c.describe()
+        n += 1
+    assert n >= 4
