@@ -842,7 +842,7 @@ __global__ __launch_bounds__(T::NT) void gemm_kernel(const KernelArgs args)
             // That barrier waits for all but the youngest A slab's loads, so A has between two and three k-steps to
             // land and B between one and two.
             // What bounds it: the chip's power on data that toggles the matrix cores (1.77-1.84 GHz under this loop,
-            // 2.38 on zeros).  8192^3 bf16, one box each: row-major B 742 -> 671 us (zeros 685 -> 556), K-contiguous
+            // 2.38 on zeros).  8192^3 bf16, both forms on one card: row-major B 742 -> 671 us (zeros 685 -> 556), K-contiguous
             // 739 -> 670 (655 -> 550) against the eight-wave forms 4 and 6.  Measured on the way (K-contiguous, N(0,1) /
             // zeros): five units and B's and A's loads in one k-step 728 / 646; the loads spread over both k-steps
             // 717 / 574; unrolled over the ring 672 / 553.  A burst of loads costs most (half a k-step: 791 / 740):

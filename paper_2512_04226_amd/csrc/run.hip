@@ -214,10 +214,10 @@ const VariantFns &launcher_of(int dtype, int id, int bl, int which)
 }
 
 // The instantiation of a variant that a launch runs.  The pipelined one (four waves, K-loop form 7) has the faster loop
-// and, with half the waves, the slower prologue and store stage (about 2 us in 16-bit types): it pays from about twenty
-// K slabs per workgroup.  Plain -> pipelined, M = N = 4096 bf16, K-contiguous B: K = 512 21.7 -> 22.9 us, 1024 32.9 -> 33.3,
-// 1536 44.5 -> 43.6, 2048 56.9 -> 54.1, 4096 106.1 -> 94.8.  (The four-wave fp8 tile runs form 7 at every K: level with
-// form 5 up to K = 2048.)
+// and, with half the waves, the slower prologue and store stage (about 1 us in 16-bit types): it pays from about twenty
+// K slabs per workgroup.  Plain -> pipelined, M = N = 4096 bf16, K-contiguous B: K = 512 20.3 -> 21.4 us, 1024 31.1 -> 31.6,
+// 1152 34.0 -> 33.6; and, before the store stage took several row blocks at a time, 1536 44.5 -> 43.6, 2048 56.9 -> 54.1,
+// 4096 106.1 -> 94.8.  (The four-wave fp8 tile runs form 7 at every K: level with form 5 up to K = 2048.)
 constexpr int64_t kPipelinedSlabs = 20;
 const VariantFns &kernel_of(int dtype, int id, int bl, bool ragged, bool streaming, int64_t slabs)
 {
