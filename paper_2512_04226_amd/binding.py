@@ -400,6 +400,14 @@ def gemm_run(cfg, A, B, C, stream=None):
     _check(_lib.gemm_run(ctypes.byref(cfg), _ptr(A), _ptr(B), _ptr(C), _stream_handle(stream)), "gemm_run")
 
 
+def open_library(path):
+    """Another build of the library (for comparisons), gemm_run typed as in this one: an untyped foreign function takes a
+    Python int for a 32-bit C int and would cut off the upper half of a device address."""
+    lib = ctypes.CDLL(path)
+    lib.gemm_run.restype, lib.gemm_run.argtypes = _lib.gemm_run.restype, _lib.gemm_run.argtypes
+    return lib
+
+
 def gemm_run_noalloc(cfg, A, B, C, stream=None):
     """gemm_run with the library's own built-in workspace (at most GEMM_NOALLOC_WORKSPACE_BYTES); allocates nothing."""
     _check(_lib.gemm_run_noalloc(ctypes.byref(cfg), _ptr(A), _ptr(B), _ptr(C), ctypes.c_void_p(_stream_handle(stream))),

@@ -150,27 +150,27 @@ def measure_slab_clk(dtype, n, b_layout=0, passes=5):
     return rows
 
 
+def run_in(lib, cfg, A, B, C):
+    """gemm_run of a library that g.open_library opened, on torch's current stream."""
+    rc = lib.gemm_run(ctypes.byref(cfg), g._ptr(A), g._ptr(B), g._ptr(C), g._stream_handle(None))
+    if rc != 0:
+        raise RuntimeError("gemm_run returned %d" % rc)
+
+
 def compare_loop_forms(lib_paths, n=8192, passes=7):
     """Times every variant of every datatype and B layout in each of the given builds of the
     library (the same cfg, plain launches, the builds and variants interleaved in shuffled
     passes, median) and prints one line per variant: microseconds per build and the ratios to
     the first.  The outputs of the builds are compared bit for bit first."""
-    libs = [ctypes.CDLL(p) for p in lib_paths]
-    for lib in libs:
-        lib.gemm_run.restype = ctypes.c_int
-
-    def run(lib, cfg, A, B, C):
-        rc = lib.gemm_run(ctypes.byref(cfg), g._ptr(A), g._ptr(B), g._ptr(C), ctypes.c_void_p(g._stream_handle(None)))
-        if rc != 0:
-            raise RuntimeError("gemm_run returned %d" % rc)
+    libs = [g.open_library(p) for p in lib_paths]
 
     def time_one(lib, cfg, A, B, C, launches=6):
         for _ in range(2):
-            run(lib, cfg, A, B, C)
+            run_in(lib, cfg, A, B, C)
         e0, e1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
         e0.record()
         for _ in range(launches):
-            run(lib, cfg, A, B, C)
+            run_in(lib, cfg, A, B, C)
         e1.record()
         e1.synchronize()
         return e0.elapsed_time(e1) * 1e3 / launches
@@ -193,7 +193,7 @@ def compare_loop_forms(lib_paths, n=8192, passes=7):
                 outs = []
                 for lib in libs:
                     C.zero_()
-                    run(lib, c, A, B, C)
+                    run_in(lib, c, A, B, C)
                     torch.cuda.synchronize()
                     outs.append(C.clone())
                 if any(not torch.equal(outs[0], o) for o in outs[1:]):
@@ -232,20 +232,15 @@ def decompose(lib_paths, n=8192):
     (LIB_FULL LIB_SKIP_FILL LIB_SKIP_FRAG LIB_SKIP_BOTH, all built with the same forced K-loop form), on
     N(0,1)-like and on all-zero operands (the latter take the power limit out of the picture)."""
     names = ("full", "no fill", "no fragment reads", "neither")
-    libs = [ctypes.CDLL(p) for p in lib_paths]
-    for lib in libs:
-        lib.gemm_run.restype = ctypes.c_int
+    libs = [g.open_library(p) for p in lib_paths]
 
     def settled(lib, cfg, A, B, C):
-        def run():
-            if lib.gemm_run(ctypes.byref(cfg), g._ptr(A), g._ptr(B), g._ptr(C), ctypes.c_void_p(g._stream_handle(None))) != 0:
-                raise RuntimeError("gemm_run failed")
         for _ in range(40):
-            run()
+            run_in(lib, cfg, A, B, C)
         e0, e1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
         e0.record()
         for _ in range(30):
-            run()
+            run_in(lib, cfg, A, B, C)
         e1.record()
         e1.synchronize()
         return e0.elapsed_time(e1) * 1e3 / 30
@@ -275,20 +270,15 @@ def compare_builds(named_libs, n=8192):
     libs = []
     for a in named_libs:
         name, path = a.split("=", 1)
-        lib = ctypes.CDLL(path)
-        lib.gemm_run.restype = ctypes.c_int
-        libs.append((name, lib))
+        libs.append((name, g.open_library(path)))
 
     def settled(lib, cfg, A, B, C):
-        def run():
-            if lib.gemm_run(ctypes.byref(cfg), g._ptr(A), g._ptr(B), g._ptr(C), ctypes.c_void_p(g._stream_handle(None))) != 0:
-                raise RuntimeError("gemm_run failed")
         for _ in range(30):
-            run()
+            run_in(lib, cfg, A, B, C)
         e0, e1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
         e0.record()
         for _ in range(20):
-            run()
+            run_in(lib, cfg, A, B, C)
         e1.record()
         e1.synchronize()
         return e0.elapsed_time(e1) * 1e3 / 20

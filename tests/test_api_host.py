@@ -1,6 +1,8 @@
 """Argument checks of api.matmul that need no GPU, the sweep tool's summary of its own records, and the
 calibration tool's reading of the variant table."""
+import ctypes
 import json
+import subprocess
 
 import pytest
 import torch
@@ -58,6 +60,30 @@ def test_variant_table_loop_form_columns_cover_every_compiled_variant():
                 seen.add((sect, c.block_m, c.block_n, c.block_k, c.waves_m, c.waves_n, c.mfma, c.stages))
         assert seen == set(rows)
     assert all(lf in range(7) and lf_kc in range(7) for lf, lf_kc in forms.values())
+
+
+def test_a_second_build_of_the_library_gets_whole_pointers(tmp_path, monkeypatch):
+    """The calibration tool runs other builds of the library through handles of its own.  A stand-in built here hands back
+    the arguments its gemm_run received: addresses above 32 bits have to arrive whole."""
+    from paper_2512_04226_amd import binding as g, calibrate
+
+    src, lib = tmp_path / "echo.c", tmp_path / "echo.so"
+    src.write_text("#include <stdint.h>\nuintptr_t seen[4];\n"
+                   "int gemm_run(const void *cfg, void *a, void *b, void *c, void *s)\n"
+                   "{ seen[0] = (uintptr_t)a; seen[1] = (uintptr_t)b; seen[2] = (uintptr_t)c; seen[3] = (uintptr_t)s; return cfg == 0; }\n")
+    subprocess.run(["gcc", "-shared", "-fPIC", "-o", str(lib), str(src)], check=True)
+
+    class Tensor:
+        def __init__(self, address):
+            self.data_ptr = lambda: address
+
+    addresses = (0x7F1234567890, 0x7F12F4567890, 0x8000000000)
+    monkeypatch.setattr(g, "_stream_handle", lambda stream: 0x55AA12345678)
+    handle = g.open_library(str(lib))
+    calibrate.run_in(handle, g.gemm_cfg(), *(Tensor(a) for a in addresses))
+    assert tuple((ctypes.c_size_t * 4).in_dll(handle, "seen")) == addresses + (0x55AA12345678,)
+    # and the tool opens its libraries in no other way
+    assert "CDLL" not in open(calibrate.__file__).read()
 
 
 def test_uniform128_shapes_follow_the_papers_recipe():
