@@ -271,6 +271,16 @@ int gemm_run_grouped(const gemm_cfg *cfg, int n_groups, const gemm_group_rec *ho
 int gemm_run(const gemm_cfg *cfg, const void *A, const void *B, void *C, void *hip_stream);
 
 /*
+ * gemm_run with the split-K / Stream-K workspace as an argument: workspace[0, workspace_bytes), device memory,
+ * 16-byte aligned, at least gemm_workspace_bytes(cfg) (else GEMM_ERR_WORKSPACE; it may be NULL where that is 0).  The
+ * registered workspace is neither used nor changed, so that threads and streams that each bring their own need no order
+ * among themselves.  The buffer belongs to the call until its last kernel has finished: calls that share one must be
+ * stream-ordered, and the two launches of a call must not have another call's between them.
+ */
+int gemm_run_ws(const gemm_cfg *cfg, const void *A, const void *B, void *C, void *hip_stream, void *workspace,
+                size_t workspace_bytes);
+
+/*
  * gemm_run for callers that cannot allocate or register device memory (code under HIP graph capture,
  * tight serving loops, harnesses that forbid hipMalloc): the same launch, but split-K slabs and Stream-K
  * partial tiles go to a buffer of GEMM_NOALLOC_WORKSPACE_BYTES that is part of the library's code object

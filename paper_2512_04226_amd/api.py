@@ -1,13 +1,17 @@
 """`matmul`: the call a user of the paper's library makes -- hand over two tensors, get the product,
 with the kernel chosen analytically for the shape (Section V-C: selection costs microseconds and
 is cached per shape, no tuning run).  A thin convenience layer over `binding`: it looks up or
-makes the cfg, keeps one workspace tensor per device and calls gemm_run; every step of the
-computation runs in libgemm355.so.
+makes the cfg, keeps one workspace tensor per stream and launches; every step of the computation
+runs in libgemm355.so.  Calls on several streams and from several threads need no order among
+themselves.  (Graphs captured on one stream share its workspace: replays of two of them are to
+be ordered.)
 
     C = matmul(A, B)                       # A (M, K), B (K, N): bf16, fp16 or float8_e4m3fn
     C = matmul(X, W, b_k_contiguous=True)  # W stored (N, K), as an nn.Linear weight
 """
+import collections
 import ctypes
+import threading
 
 import torch
 
@@ -18,7 +22,10 @@ if hasattr(torch, "float8_e4m3fn"):
     _DTYPES[torch.float8_e4m3fn] = g.GEMM_FP8_E4M3
 
 _cfg_cache = {}       # (M, N, K, dtype, b_layout) -> cfg; the selector is deterministic, so this is exact
-_workspace = {}       # device index -> tensor
+_workspaces = collections.OrderedDict()     # (device index, stream handle, thread) -> _Workspace, least recently used first
+_MAX_WORKSPACES = 32  # torch hands out 32 pooled streams per device; beyond that the oldest that no graph holds goes
+_pinned = []          # outgrown buffers whose addresses captured graphs may hold
+_workspace_lock = threading.RLock()    # (re-entered only by a finaliser that multiplies)
 _plans = {}           # (M, N, K, dtype, b_layout, lda, ldb, ldc) -> _Plan
 _MAX_PLANS = 4096     # a program with more shapes than this starts over
 
@@ -54,18 +61,39 @@ def _plan(base, key):
     return plan
 
 
-def _ensure_workspace(need, device):
-    idx = device.index if device.index is not None else torch.cuda.current_device()
-    cur = _workspace.get(idx)
-    if cur is None or cur.numel() * 4 < need:
-        # A larger buffer replaces the old one.  Launches enqueued earlier -- on whatever stream the caller
-        # gave them -- may still be using the old one, and the allocator only knows about torch's current
-        # stream: wait for the device before the old buffer can be handed out again.  (Rare: the buffer
-        # only ever grows.)
-        if cur is not None:
-            torch.cuda.synchronize(device)
-        cur = _workspace[idx] = torch.empty((need + 3) // 4, dtype=torch.float32, device=device)
-    g.gemm_set_workspace(cur)
+class _Workspace:
+    """A buffer of one stream.  `pinned`: a graph may have been captured with its address."""
+    __slots__ = ("tensor", "pinned")
+
+    def __init__(self, tensor):
+        self.tensor, self.pinned = tensor, False
+
+
+def _allocate(nbytes, device):
+    return torch.empty((nbytes + 15) // 16 * 4, dtype=torch.float32, device=device)
+
+
+def _workspace_for(need, device, stream):
+    """The stream's workspace of at least `need` bytes (with _workspace_lock held and `stream` torch's current one, so that
+    the allocator hands a buffer that is replaced or dropped only to later work of the same stream: nothing has to be
+    waited for).  A buffer that a capture has seen is never given up, as replays write to it; it is replaced by one of
+    at least twice its size, so that a stream holds at most twice what its largest call needs."""
+    # handle 2 is the per-thread default stream: another stream in every thread
+    key = (device.index, stream, threading.get_ident() if stream == 2 else 0)
+    ws = _workspaces.get(key)
+    if ws is None or ws.tensor.numel() * 4 < need:
+        if ws is not None and ws.pinned:
+            _pinned.append(ws.tensor)
+            need = max(need, 8 * ws.tensor.numel())
+        ws = _workspaces[key] = _Workspace(_allocate(need, device))
+        if len(_workspaces) > _MAX_WORKSPACES:
+            for old in [k for k, w in _workspaces.items() if not w.pinned and k != key][:1]:
+                del _workspaces[old]
+    else:
+        _workspaces.move_to_end(key)
+    if torch.cuda.is_current_stream_capturing():
+        ws.pinned = True
+    return ws.tensor
 
 
 def matmul(A, B, out=None, alpha=1.0, beta=0.0, b_k_contiguous=False, stream=None):
@@ -113,8 +141,21 @@ def matmul(A, B, out=None, alpha=1.0, beta=0.0, b_k_contiguous=False, stream=Non
 
 
 def _launch(need, cfg_ref, A, B, out, device, stream):
-    """gemm_run with the tensors' device current: no error paths, no Python objects made per argument."""
-    if need:
-        _ensure_workspace(need, device)
-    stream = g.current_stream_handle(device.index) if stream is None else g._stream_handle(stream)
-    g._check(g._lib.gemm_run(cfg_ref, A.data_ptr(), B.data_ptr(), out.data_ptr(), stream), "gemm_run")
+    """One launch with the tensors' device current: no Python objects made per argument."""
+    current = g.current_stream_handle(device.index)
+    stream = current if stream is None else g._stream_handle(stream)
+    if not need:
+        g._check(g._lib.gemm_run(cfg_ref, A.data_ptr(), B.data_ptr(), out.data_ptr(), stream), "gemm_run")
+    elif stream == current:
+        _launch_with_workspace(need, cfg_ref, A, B, out, device, stream)
+    else:
+        with torch.cuda.stream(torch.cuda.ExternalStream(stream, device) if stream else torch.cuda.default_stream(device)):
+            _launch_with_workspace(need, cfg_ref, A, B, out, device, stream)
+
+
+def _launch_with_workspace(need, cfg_ref, A, B, out, device, stream):
+    # a call is two kernels: no other thread may put its own on the stream between them
+    with _workspace_lock:
+        ws = _workspace_for(need, device, stream)
+        g._check(g._lib.gemm_run_ws(cfg_ref, A.data_ptr(), B.data_ptr(), out.data_ptr(), stream, ws.data_ptr(), ws.numel() * 4),
+                 "gemm_run_ws")

@@ -105,6 +105,8 @@ _lib.gemm_cfg_at_ex.restype = _int
 _lib.gemm_cfg_at_ex.argtypes = [_int, _i64, _i64, _i64, _int, _int, ctypes.POINTER(gemm_cfg)]
 _lib.gemm_run.restype = _int
 _lib.gemm_run.argtypes = [ctypes.POINTER(gemm_cfg), _vp, _vp, _vp, _vp]
+_lib.gemm_run_ws.restype = _int
+_lib.gemm_run_ws.argtypes = [ctypes.POINTER(gemm_cfg), _vp, _vp, _vp, _vp, _vp, ctypes.c_size_t]
 _lib.gemm_run_noalloc.restype = _int
 _lib.gemm_run_noalloc.argtypes = [ctypes.POINTER(gemm_cfg), _vp, _vp, _vp, _vp]
 GEMM_NOALLOC_WORKSPACE_BYTES = 64 << 20
@@ -398,6 +400,13 @@ def gemm_run(cfg, A, B, C, stream=None):
     """Enqueue C = alpha * A * B + beta * C (cfg.batch problems, cfg.stride_* apart).  stream: a torch.cuda.Stream, a raw hipStream_t int, or
     None for torch's current stream."""
     _check(_lib.gemm_run(ctypes.byref(cfg), _ptr(A), _ptr(B), _ptr(C), _stream_handle(stream)), "gemm_run")
+
+
+def gemm_run_ws(cfg, A, B, C, workspace, stream=None):
+    """gemm_run with the workspace (a device tensor, or None where the cfg needs none) as an argument."""
+    nbytes = workspace.numel() * workspace.element_size() if workspace is not None else 0
+    _check(_lib.gemm_run_ws(ctypes.byref(cfg), _ptr(A), _ptr(B), _ptr(C), _stream_handle(stream), _ptr(workspace), nbytes),
+           "gemm_run_ws")
 
 
 def open_library(path):

@@ -412,6 +412,19 @@ extern "C" int gemm_run(const gemm_cfg *cfg, const void *A, const void *B, void 
     return run_impl(cfg, A, B, C, hip_stream, nullptr, 0);
 }
 
+extern "C" int gemm_run_ws(const gemm_cfg *cfg, const void *A, const void *B, void *C, void *hip_stream, void *workspace,
+                           size_t workspace_bytes)
+{
+    if (!cfg)
+        return GEMM_ERR_NULL;
+    if ((uintptr_t)workspace & 15)
+        return GEMM_ERR_ALIGN;
+    // (so that a missing buffer never falls back to the registered one)
+    if (!workspace && (cfg->split_k > 1 || cfg->stream_k))
+        return GEMM_ERR_WORKSPACE;
+    return run_impl(cfg, A, B, C, hip_stream, workspace, workspace_bytes);
+}
+
 extern "C" int gemm_run_noalloc(const gemm_cfg *cfg, const void *A, const void *B, void *C, void *hip_stream)
 {
     if (!cfg)

@@ -3,6 +3,8 @@ calibration tool's reading of the variant table."""
 import ctypes
 import json
 import subprocess
+import threading
+import time
 
 import pytest
 import torch
@@ -60,6 +62,113 @@ def test_variant_table_loop_form_columns_cover_every_compiled_variant():
                 seen.add((sect, c.block_m, c.block_n, c.block_k, c.waves_m, c.waves_n, c.mfma, c.stages))
         assert seen == set(rows)
     assert all(lf in range(7) and lf_kc in range(7) for lf, lf_kc in forms.values())
+
+
+class _Recorder:
+    """Stands in for the library: remembers (stream, workspace range, thread, times) of every launch with a workspace."""
+
+    def __init__(self, seconds=0.0):
+        self.calls, self.seconds = [], seconds
+
+    def gemm_run_ws(self, cfg, a, b, c, stream, ws, nbytes):
+        t0 = time.monotonic()
+        time.sleep(self.seconds)
+        self.calls.append((stream, ws, nbytes, threading.get_ident(), t0, time.monotonic()))
+        return 0
+
+
+class _Buffer:
+    def data_ptr(self):
+        return 4096
+
+
+@pytest.fixture
+def launcher(monkeypatch):
+    """launch(need, stream handle) -> (address, bytes) of the workspace it got; no GPU involved."""
+    from paper_2512_04226_amd import api, binding as g
+    rec, state = _Recorder(), {"capturing": False, "current": 0}
+
+    class Stream:
+        def __init__(self, handle):
+            self.handle = handle
+
+        def __enter__(self):
+            self.before, state["current"] = state["current"], self.handle
+
+        def __exit__(self, *exc):
+            state["current"] = self.before
+
+    allocated_on = {}
+
+    def allocate(nbytes, device):
+        t = torch.empty((nbytes + 15) // 16 * 4, dtype=torch.float32)
+        allocated_on[t.data_ptr()] = state["current"]
+        return t
+
+    monkeypatch.setattr(api, "_workspaces", type(api._workspaces)())
+    monkeypatch.setattr(api, "_pinned", [])
+    monkeypatch.setattr(api, "_allocate", allocate)
+    monkeypatch.setattr(g, "_lib", rec)
+    monkeypatch.setattr(g, "current_stream_handle", lambda index: state["current"])
+    monkeypatch.setattr(torch.cuda, "stream", lambda s: s)
+    monkeypatch.setattr(torch.cuda, "ExternalStream", lambda handle, device: Stream(handle))
+    monkeypatch.setattr(torch.cuda, "default_stream", lambda device: Stream(0))
+    monkeypatch.setattr(torch.cuda, "is_current_stream_capturing", lambda: state["capturing"])
+
+    def launch(need, stream=None):
+        x = _Buffer()
+        api._launch(need, None, x, x, x, torch.device("cuda", 0), stream)
+        handle, ws, nbytes = rec.calls[-1][:3]
+        assert nbytes >= need and ws % 16 == 0 and allocated_on[ws] == handle
+        return ws, nbytes
+
+    launch.rec, launch.state, launch.api = rec, state, api
+    return launch
+
+
+def test_every_stream_has_a_workspace_of_its_own(launcher):
+    """Two K-split calls in flight on two streams must not share their partial sums' buffer, whether the stream is torch's
+    current one or an argument; calls of one stream reuse its buffer; an outgrown one is replaced on its own stream."""
+    a, b, c = launcher(1000), launcher(1000, 77), launcher(1000, 78)
+    assert len({a[0], b[0], c[0]}) == 3
+    assert launcher(900) == a and launcher(1000, 77) == b
+    launcher.state["current"] = 77
+    assert launcher(10) == b and launcher(10, 0) == a
+    assert launcher(5000, 78)[1] >= 5000 and launcher(1000, 78)[1] >= 5000 and launcher(1000) == b
+    for handle in range(100, 200):                                     # bounded
+        launcher(16, handle)
+    assert len(launcher.api._workspaces) <= launcher.api._MAX_WORKSPACES
+
+
+def test_a_workspace_that_a_capture_has_seen_is_kept(launcher):
+    """Replays write to the address that was captured, whatever later calls need."""
+    launcher.state["capturing"] = True
+    a = launcher(1000, 77)
+    launcher.state["capturing"] = False
+    b = launcher(1200, 77)
+    assert b[0] != a[0] and b[1] >= 2000 and [t.data_ptr() for t in launcher.api._pinned] == [a[0]]
+    launcher.state["capturing"] = True
+    c = launcher(1200, 78)
+    launcher.state["capturing"] = False
+    for handle in range(100, 200):
+        launcher(16, handle)
+    assert launcher(1200, 78) == c
+
+
+def test_threads_do_not_interleave_their_launches(launcher):
+    """A call with a workspace is two kernels on one stream: another thread's must not come between them."""
+    launcher.rec.seconds = 0.005
+    threads = [threading.Thread(target=lambda: [launcher.api._launch(64, None, _Buffer(), _Buffer(), _Buffer(), torch.device("cuda", 0), h)
+                                                for h in (0, 77, 2)]) for _ in range(4)]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    calls = sorted(launcher.rec.calls, key=lambda c: c[4])
+    assert len(calls) == 12 and all(x[5] <= y[4] for x, y in zip(calls, calls[1:]))
+    # handle 2 is the per-thread default stream: one buffer per thread
+    assert len({c[1] for c in calls if c[0] == 2}) == len({c[3] for c in calls})
+    assert len({c[1] for c in calls if c[0] == 77}) == 1
 
 
 def test_a_second_build_of_the_library_gets_whole_pointers(tmp_path, monkeypatch):

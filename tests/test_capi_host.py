@@ -102,6 +102,16 @@ def test_cfg_at_enumeration_and_legality():
     assert n - n // 7 <= len(seen) <= n and any(k[2] for k in seen)
 
 
+def test_run_with_a_workspace_argument_never_falls_back_to_the_registered_one():
+    split = next(c for c in (g.gemm_cfg_at(i, 512, 512, 4096, g.GEMM_BF16) for i in range(g.gemm_cfg_count(g.GEMM_BF16)))
+                 if c is not None and c.split_k == 4)
+    need = g.gemm_workspace_bytes(split)
+    run, p = g._lib.gemm_run_ws, 0x1000     # never dereferenced: every case fails validation first
+    assert run(None, p, p, p, None, None, 0) == -1
+    for ws, nbytes, code in ((None, 0, -6), (None, need, -6), (0x10000, need - 4, -6), (0x10008, need, -5)):
+        assert run(ctypes.byref(split), p, p, p, None, ws, nbytes) == code
+
+
 def test_run_rejects_bad_arguments_without_launching():
     cfg = g.gemm_select(512, 512, 512, g.GEMM_BF16)
     run = g._lib.gemm_run

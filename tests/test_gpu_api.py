@@ -57,6 +57,61 @@ def test_matmul_matches_the_oracle_across_dtypes_layouts_and_strides(oracle):
         api.matmul(dA, dB[:-8])
 
 
+def test_k_split_calls_on_two_streams_at_once(oracle):
+    """Two streams, neither waiting for the other, each with its own K-split products: every result exact."""
+    from paper_2512_04226_amd import api, binding as g
+    from gpu_util import to_dev
+    M, N, K = 64, 64, 16384
+    assert api.select(M, N, K, g.GEMM_BF16).split_k > 1
+    ops, refs = [], []
+    for case in range(2):
+        A, B = wl.integer_bf16(M, N, K, seed=97, case=case)
+        ops.append((to_dev(A).view(torch.bfloat16), to_dev(B).view(torch.bfloat16)))
+        refs.append(torch.from_numpy(oracle.gemm(A, B, oracle.BF16)[0].view(np.int16)).cuda())
+    streams = [torch.cuda.Stream() for _ in range(2)]
+    torch.cuda.synchronize()
+    outs = [[], []]
+    for i in range(40):
+        for j, s in enumerate(streams):
+            if i % 2:
+                with torch.cuda.stream(s):
+                    outs[j].append(api.matmul(*ops[j]))
+            else:
+                with torch.cuda.stream(s):
+                    out = torch.empty((M, N), dtype=torch.bfloat16, device="cuda")
+                outs[j].append(api.matmul(*ops[j], out=out, stream=s))
+    torch.cuda.synchronize()
+    for j in range(2):
+        assert all(torch.equal(c.view(torch.int16), refs[j]) for c in outs[j])
+
+
+def test_a_captured_k_split_call_survives_larger_calls(oracle):
+    """The graph's workspace stays its own: replayed after larger calls on the stream it was captured on."""
+    from paper_2512_04226_amd import api
+    from gpu_util import to_dev
+    M, N, K = 64, 64, 16384
+    A, B = wl.integer_bf16(M, N, K, seed=98)
+    ref = torch.from_numpy(oracle.gemm(A, B, oracle.BF16)[0].view(np.int16)).cuda()
+    dA, dB = to_dev(A).view(torch.bfloat16), to_dev(B).view(torch.bfloat16)
+    out = torch.empty((M, N), dtype=torch.bfloat16, device="cuda")
+    s = torch.cuda.Stream()
+    with torch.cuda.stream(s):
+        api.matmul(dA, dB, out=out)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=s):
+        api.matmul(dA, dB, out=out)
+    for _ in range(3):
+        with torch.cuda.stream(s):
+            big = api.matmul(dA.repeat(4, 1), dB.repeat(1, 4))
+            junk = torch.full((1 << 22,), float("nan"), device="cuda")
+            out.zero_()
+            graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(out.view(torch.int16), ref)
+        assert torch.equal(big.view(torch.int16), ref.repeat(4, 4)) and bool(torch.isnan(junk).all())
+
+
 @pytest.mark.parametrize("shape", [(1, 8, 8), (7, 8, 65536), (65537, 8, 8), (300001, 64, 64), (3, 16400, 24), (2049, 8, 4104)])
 def test_extreme_aspect_ratios_bit_exact(oracle, shape):
     """Shapes at the edges of what the tiles were made for: one row, one 8-wide column block, a very
