@@ -5,7 +5,7 @@
 //   A  M x K row-major, B  K x N row-major (or N x K row-major, K-contiguous), C  M x N
 //   row-major bf16 (fp16 for fp16 inputs), or fp32 partials when the reduction of a tile is
 //   shared between workgroups (split-K slabs, Stream-K partial tiles).  blockIdx.y selects
-//   the problem of a strided batch (a resident launch counts it into its work items).
+//   the problem of a strided batch.
 //
 // Data path per K slab: 128-bit buffer loads straight into LDS (A along K, B along N or K,
 // out-of-range chunks arrive as zero; no register staging) -> swizzled LDS ring of NS
@@ -15,8 +15,8 @@
 // The MFMA's row operand is fed from B and its column operand from A, so that a lane ends
 // up with 4 consecutive n of one output row (8- or 16-byte stores).
 //
-// A workgroup computes one (tile, K slice), in a resident launch one after the other, or -- as a Stream-K
-// worker -- up to two (tile, slab range) segments, with the same prologue / K loop / epilogue body.
+// A workgroup computes one (tile, K slice), or -- as a Stream-K worker -- up to two
+// (tile, slab range) segments, with the same prologue / K loop / epilogue body.
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
@@ -53,11 +53,6 @@ struct KernelArgs {
     // above are unused and each workgroup reads its group's record from this device table.
     const GroupRec *groups;
     int n_groups;
-    // Resident launch (n_work > 0; neither stream-K nor grouped): n_work work items -- (problem, tile, K slice), the
-    // problem slowest -- shared by a one-dimensional grid of as many workgroups as the device holds at a time; workgroup
-    // b computes items b, b + gridDim.x, ...  0: one workgroup per item.
-    int n_work;
-    int n_cu;           // (host only) compute units of the device the launch is sized for
 };
 
 typedef short short4_t __attribute__((ext_vector_type(4)));
@@ -180,10 +175,6 @@ struct Tile {
     static constexpr int RB = (BL == 0) ? BN * ES : BK * ES; // bytes per B row in LDS (a k row, or an n row when K-contiguous)
     static constexpr int A_BYTES = BM * RA, B_BYTES = BK * BN * ES;
     static constexpr int STAGE = A_BYTES + B_BYTES;
-    // may run resident (KernelArgs::n_work): not the eight-wave tiles whose 128 accumulators per lane leave the 256 registers
-    // of a wave no room for what the loop over work items keeps (they would spill in the K loop), and not the small tiles,
-    // several of which share a CU (the loop's registers would cost the 128x64 tile one of its three)
-    static constexpr bool RESIDENT = BM * BN >= 128 * 128 && (BM * BN / NT < 128 || NW <= 4);
     static constexpr int LDS_BYTES = (LF == 7) ? 5 * A_BYTES : NS * STAGE;
     static constexpr int ACH = A_BYTES / 16, BCH = B_BYTES / 16;  // 16-byte chunks per slab
     static constexpr int CA = RA / 16, CB = RB / 16;              // chunks per row
@@ -340,8 +331,8 @@ __global__ __launch_bounds__(T::NT) void gemm_kernel(const KernelArgs args)
     constexpr int ES = T::ES, BM = T::BM, BN = T::BN, BK = T::BK, MI = T::MI;
     __shared__ __attribute__((aligned(1024))) uint8_t smem[T::LDS_BYTES];
 
-    // Work of this workgroup: one (tile, K slice) for a data-parallel or split-K launch, or every gridDim.x-th one
-    // of a resident launch; up to two (tile, slab range) segments for a stream-K worker.
+    // Work of this workgroup: one (tile, K slice) for a data-parallel or split-K launch, up to
+    // two (tile, slab range) segments for a stream-K worker.
     const bool sk_worker = (int)blockIdx.x < args.sk.workers;
     SkSegment segs[2];
     int nseg = 1;
@@ -382,11 +373,9 @@ __global__ __launch_bounds__(T::NT) void gemm_kernel(const KernelArgs args)
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);   // wave-uniform, kept scalar
     const int wm = wave / T::WN, wn = wave % T::WN;
 
-    const bool resident = T::RESIDENT && args.n_work > 0;
-    for (int seg = 0; resident || seg < nseg; ++seg) {
+    for (int seg = 0; seg < nseg; ++seg) {
     // out_mode 0: bf16 C;  1: fp32 split-K slab ks;  2: fp32 partial tile of a stream-K segment
     int tm, tn, ks = 0, k_begin, k_len, out_mode;
-    size_t bz = blockIdx.y;     // problem of the batch
     if (sk_worker) {
         const SkSegment sg = (seg == 0) ? segs[0] : segs[1];
         logical_tile(args.tiles_m, args.tiles_n, args.group_m, args.sk.dp_tiles + sg.tile, tm, tn);
@@ -408,19 +397,7 @@ __global__ __launch_bounds__(T::NT) void gemm_kernel(const KernelArgs args)
         out_mode = 0;
     } else {
         const int grid = (args.sk.workers > 0) ? args.sk.dp_tiles : args.tiles_m * args.tiles_n * args.split_k;
-        int item = (int)blockIdx.x - args.sk.workers;
-        if (resident) {
-            item += seg * (int)gridDim.x;
-            if (item >= args.n_work)
-                break;
-            if (args.batch > 1) {
-                bz = (unsigned)item / (unsigned)grid;
-                item -= (int)bz * grid;
-            }
-            if (seg)
-                wait_and_barrier<63, true>();      // every wave has read back its staged rows: the ring is free
-        }
-        tile_coords(args, item, grid, tm, tn, ks);
+        tile_coords(args, (int)blockIdx.x - args.sk.workers, grid, tm, tn, ks);
         k_begin = ks * args.k_per_split;
         k_len = pK - k_begin;
         if (k_len > args.k_per_split)
@@ -437,6 +414,7 @@ __global__ __launch_bounds__(T::NT) void gemm_kernel(const KernelArgs args)
     // belongs in its slot.  Rows past the edge of the matrix (A: m >= M, B: k >= k_len) fall
     // outside the buffer window and arrive as zero; chunk columns past the edge (A: k >= k_len,
     // B: n >= N) are sent outside the window by replacing the offset.
+    const size_t bz = blockIdx.y;     // problem of the batch
 #ifdef G355_DIAG_PANEL
     // timing-only builds: every workgroup (bit 0: of an XCD, with bit 2) reads the A rows of tile row 0,
     // (bit 1) the B columns of tile column 0 -- the results are wrong, the request stream keeps its shape

@@ -354,8 +354,6 @@ static int run_impl(const gemm_cfg *cfg, const void *A, const void *B, void *C, 
     a.stride_c = cfg->batch > 1 ? cfg->stride_c : 0;
     a.groups = nullptr;
     a.n_groups = 0;
-    a.n_work = 0;        // (the launcher decides)
-    a.n_cu = hw.n_cu;
 
     hipStream_t stream = (hipStream_t)hip_stream;
     const int f16 = (dtype == GEMM_FP16) ? 1 : 0;
