@@ -21,6 +21,7 @@ _DTYPES = {torch.bfloat16: g.GEMM_BF16, torch.float16: g.GEMM_FP16}
 if hasattr(torch, "float8_e4m3fn"):
     _DTYPES[torch.float8_e4m3fn] = g.GEMM_FP8_E4M3
 
+_REAL = (float, int)
 _cfg_cache = {}       # (M, N, K, dtype, b_layout) -> cfg; the selector is deterministic, so this is exact
 _workspaces = collections.OrderedDict()     # (device index, stream handle, thread) -> _Workspace, least recently used first
 _MAX_WORKSPACES = 32  # torch hands out 32 pooled streams per device; beyond that the oldest that no graph holds goes
@@ -50,6 +51,14 @@ class _Plan:
         self.cfg.alpha, self.cfg.beta = 1.0, 0.0
         self.ref = ctypes.byref(self.cfg)
         self.need = g.gemm_workspace_bytes(self.cfg)
+
+    def ref_for(self, alpha, beta):
+        # (the fast way only for real numbers: whatever else equals 1 is for the field's own conversion to take or refuse)
+        if type(alpha) in _REAL and type(beta) in _REAL and alpha == 1.0 and beta == 0.0:
+            return self.ref
+        cfg = self.cfg.copy()
+        cfg.alpha, cfg.beta = alpha, beta
+        return ctypes.byref(cfg)
 
 
 def _plan(base, key):
@@ -127,11 +136,7 @@ def matmul(A, B, out=None, alpha=1.0, beta=0.0, b_k_contiguous=False, stream=Non
         ldc = out.stride(0)
     layout = g.GEMM_B_K_CONTIGUOUS if b_k_contiguous else g.GEMM_B_ROW_MAJOR
     plan = _plan(select(M, N, K, dtype, layout), (M, N, K, dtype, layout, lda, ldb, ldc))
-    cfg_ref = plan.ref
-    if alpha != 1.0 or beta != 0.0:
-        cfg = plan.cfg.copy()
-        cfg.alpha, cfg.beta = alpha, beta
-        cfg_ref = ctypes.byref(cfg)
+    cfg_ref = plan.ref_for(alpha, beta)
     if torch.cuda.current_device() == device.index:
         _launch(plan.need, cfg_ref, A, B, out, device, stream)
     else:

@@ -27,6 +27,22 @@ def test_matmul_rejects_what_it_cannot_run_before_touching_the_gpu():
         assert bytes(c) == bytes(ref) and api.select(300, 520, 72, g.GEMM_BF16, layout) is c
 
 
+def test_alpha_and_beta_are_taken_and_refused_by_the_cfg_field():
+    """A number that equals the default without being a real one is still refused; one that converts is still taken."""
+    from fractions import Fraction
+
+    from paper_2512_04226_amd import api, binding as g
+    plan = api._Plan(api.select(64, 64, 64, g.GEMM_BF16), 64, 64, 64)
+    assert plan.ref_for(1.0, 0.0) is plan.ref and plan.ref_for(1, 0) is plan.ref
+    for alpha, beta in ((1 + 0j, 0.0), (1.0, 0j), ("1", 0.0), (None, 0.0)):
+        with pytest.raises(TypeError):
+            plan.ref_for(alpha, beta)
+    for alpha, beta in ((0.5, 0.0), (1.0, 2.0), (Fraction(1, 2), 0), (torch.tensor(0.5), torch.tensor(2.0)), (float("nan"), 0.0)):
+        cfg = plan.ref_for(alpha, beta)._obj
+        assert cfg is not plan.cfg and (cfg.alpha == float(alpha) or alpha != alpha) and cfg.beta == float(beta)
+    assert (plan.cfg.alpha, plan.cfg.beta) == (1.0, 0.0)
+
+
 def test_sweep_summary_of_records(tmp_path, capsys):
     from paper_2512_04226_amd import sweep
     rec = {"M": 64, "N": 128, "K": 256, "dtype": 0, "b_layout": 0, "n_cfgs": 3,
