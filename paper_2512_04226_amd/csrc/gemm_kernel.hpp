@@ -176,6 +176,12 @@ struct Tile {
     static constexpr int A_BYTES = BM * RA, B_BYTES = BK * BN * ES;
     static constexpr int STAGE = A_BYTES + B_BYTES;
     static constexpr int LDS_BYTES = (LF == 7) ? 5 * A_BYTES : NS * STAGE;
+    // Waves per SIMD the registers must leave room for.  What a workgroup needs by itself, except in the ragged instantiation
+    // of the two-stage 128x64 and 64x128 tiles on eight waves: their 48 KB of LDS let three workgroups share a CU, and the
+    // trimming and the element-wise store would take 85-87 registers where three fit up to 80.  Held to that (8-12 bytes of
+    // scratch outside the loop with row-major B, none with K-contiguous): 1501x3003x2005 bf16 row-major 53.6 -> 44.3 us
+    // (128x64) and 42.8 -> 33.5 (64x128), 2047x2049x1023 K-contiguous 21.3 -> 17.4; level where the tiles do not fill three slots.
+    static constexpr int MIN_WAVES = (RG && ES == 2 && NW == 8 && NS == 2 && BM * BN == 128 * 64) ? 6 : (NT > 256 ? NT / 256 : 1);
     static constexpr int ACH = A_BYTES / 16, BCH = B_BYTES / 16;  // 16-byte chunks per slab
     static constexpr int CA = RA / 16, CB = RB / 16;              // chunks per row
     // a direct-to-LDS load instruction of one wave fills one 1 KB unit (64 lanes x 16 bytes)
@@ -326,7 +332,7 @@ __device__ __forceinline__ void wait_and_barrier()
 }
 
 template <class T>
-__global__ __launch_bounds__(T::NT) void gemm_kernel(const KernelArgs args)
+__global__ __launch_bounds__(T::NT, T::MIN_WAVES) void gemm_kernel(const KernelArgs args)
 {
     constexpr int ES = T::ES, BM = T::BM, BN = T::BN, BK = T::BK, MI = T::MI;
     __shared__ __attribute__((aligned(1024))) uint8_t smem[T::LDS_BYTES];

@@ -33,16 +33,38 @@ def _usage(src):
     return rows
 
 
-def _tile(es, bm, bn, bk, wm, wn, mi, ns, bl, ft):
-    """Regular expression for the whole-chunk instantiation of a tile, whatever K-loop form the table gives it."""
-    return "TileI" + "".join("Li%dE" % x for x in (es, bm, bn, bk, wm, wn, mi, ns, bl, ft)) + r"Li\d+ELi0ELi0EEEEE"
+def _tile(es, bm, bn, bk, wm, wn, mi, ns, bl, ft, rg=0):
+    """Regular expression for the whole-chunk (rg = 1: ragged) instantiation of a tile, whatever K-loop form it has."""
+    return "TileI" + "".join("Li%dE" % x for x in (es, bm, bn, bk, wm, wn, mi, ns, bl, ft)) + r"Li\d+ELi%dELi0EEEEE" % rg
+
+
+@pytest.fixture(scope="module")
+def usage():
+    """Resource rows of the kernels in two files: the bf16 tiles with the 16x16 instruction, the larger fp8 tiles."""
+    if shutil.which(HIPCC) is None and not os.path.exists(HIPCC):
+        pytest.skip("needs hipcc")
+    with ThreadPoolExecutor(max_workers=2) as ex:
+        bf16, fp8 = ex.map(_usage, ["kernels_bf16_4.hip", "kernels_fp8_0.hip"])
+    return bf16 + fp8
+
+
+def _find(rows, tag):
+    hit = [r for r in rows if re.search(tag, r["name"])]
+    assert len(hit) == 1, (tag, [r["name"] for r in hit])
+    return hit[0]
+
+
+def test_ragged_tiles_keep_the_third_workgroup_of_a_cu(usage):
+    """Six waves per SIMD: three eight-wave workgroups, which the 48 KB rings of these two tiles leave room for."""
+    for bm, bn in ((128, 64), (64, 128)):
+        for bl in (0, 1):
+            r = _find(usage, _tile(2, bm, bn, 64, 2, 4, 16, 2, bl, 0, rg=1))
+            assert r["waves_per_simd"] >= 6 and r["scratch"] <= 16, r
 
 
 @pytest.mark.skipif(shutil.which(HIPCC) is None and not os.path.exists(HIPCC), reason="needs hipcc")
-def test_headline_kernels_keep_no_spills_and_no_kernel_spills_much():
-    with ThreadPoolExecutor(max_workers=2) as ex:
-        bf16, fp8 = ex.map(_usage, ["kernels_bf16_4.hip", "kernels_fp8_0.hip"])
-    rows = bf16 + fp8
+def test_headline_kernels_keep_no_spills_and_no_kernel_spills_much(usage):
+    rows = usage
     assert len(rows) >= 40
     by_name = {r["name"]: r for r in rows}
 
