@@ -62,6 +62,12 @@ def test_ragged_tiles_keep_the_third_workgroup_of_a_cu(usage):
             assert r["waves_per_simd"] >= 6 and r["scratch"] <= 16, r
 
 
+def test_ragged_256_tiles_on_eight_waves_do_not_spill_where_a_form_avoids_it(usage):
+    for tile in ((2, 256, 256, 64, 2, 4, 16, 2, 0, 0), (1, 256, 256, 128, 2, 4, 32, 2, 1, 0), (2, 256, 256, 64, 4, 2, 16, 2, 0, 0)):
+        r = _find(usage, _tile(*tile, rg=1))
+        assert r["scratch"] == 0, r
+
+
 @pytest.mark.skipif(shutil.which(HIPCC) is None and not os.path.exists(HIPCC), reason="needs hipcc")
 def test_headline_kernels_keep_no_spills_and_no_kernel_spills_much(usage):
     rows = usage
