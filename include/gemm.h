@@ -352,6 +352,21 @@ int gemm_predict(const gemm_cfg *cfg, gemm_prediction *out);
  */
 int gemm_variant_occupancy(int dtype, int variant, int b_layout, int *blocks_per_cu);
 
+/*
+ * Which instantiation of the variant gemm_run (n_groups = 0, host_table ignored) or gemm_run_grouped (the planned records)
+ * launches for cfg, by the rule they use themselves.  Host only.  out4 = {instantiation, waves along m, waves along n,
+ * K-loop form}.  Errors: as gemm_run for a cfg that it refuses before it looks at pointers; GEMM_ERR_CFG_ILLEGAL when cfg
+ * and n_groups do not belong together.
+ */
+typedef enum {
+    GEMM_KERNEL_PLAIN = 0,
+    GEMM_KERNEL_RAGGED = 1,           /* N or K is no whole number of 16-byte chunks */
+    GEMM_KERNEL_STREAMING = 2,        /* one tile row over weights larger than the memory-side cache */
+    GEMM_KERNEL_PIPELINED = 3,        /* 256x256 tiles with 128-byte slab rows, twenty K slabs or more per workgroup */
+    GEMM_KERNEL_PIPELINED_RAGGED = 4
+} gemm_kernel_kind;
+int gemm_launched_kernel(const gemm_cfg *cfg, int n_groups, const gemm_group_rec *host_table, int32_t out4[4]);
+
 /* Hardware descriptor: get a copy / replace it (process-wide; not thread-safe against
  * concurrent gemm_select).  gemm_hw_reset restores the MI355X defaults. */
 int gemm_hw_get(gemm_hw *out);

@@ -449,6 +449,21 @@ _lib.gemm_run_grouped.restype = _int
 _lib.gemm_run_grouped.argtypes = [ctypes.POINTER(gemm_cfg), _int, ctypes.POINTER(gemm_group_rec), _vp, _vp]
 
 
+_lib.gemm_launched_kernel.restype = _int
+_lib.gemm_launched_kernel.argtypes = [ctypes.POINTER(gemm_cfg), _int, ctypes.POINTER(gemm_group_rec),
+                                      ctypes.POINTER(ctypes.c_int32)]
+KERNEL_KINDS = ("plain", "ragged", "streaming", "pipelined", "pipelined ragged")
+
+
+def gemm_launched_kernel(cfg, table=None):
+    """(kind out of KERNEL_KINDS, waves along m, waves along n, K-loop form) of the kernel that gemm_run, or with a table
+    from gemm_grouped_plan gemm_run_grouped, launches for cfg."""
+    out = (ctypes.c_int32 * 4)()
+    _check(_lib.gemm_launched_kernel(ctypes.byref(cfg), len(table) if table is not None else 0, table, out),
+           "gemm_launched_kernel")
+    return (KERNEL_KINDS[out[0]],) + tuple(out[1:])
+
+
 def gemm_variant_count(dtype):
     n = _lib.gemm_variant_count(dtype)
     if n < 0:

@@ -171,7 +171,7 @@ int scratch_of_current_device(void **out)
     return GEMM_OK;
 }
 
-// which: the instantiation of the variant (see kernels.inc)
+// which: a gemm_kernel_kind
 const VariantFns &launcher_of(int dtype, int id, int bl, int which)
 {
 #define G355_COUNT(...) +1
@@ -219,12 +219,14 @@ const VariantFns &launcher_of(int dtype, int id, int bl, int which)
 // 1152 34.0 -> 33.6; and, before the store stage took several row blocks at a time, 1536 44.5 -> 43.6, 2048 56.9 -> 54.1,
 // 4096 106.1 -> 94.8.  (The four-wave fp8 tile runs form 7 at every K: level with form 5 up to K = 2048.)
 constexpr int64_t kPipelinedSlabs = 20;
-const VariantFns &kernel_of(int dtype, int id, int bl, bool ragged, bool streaming, int64_t slabs)
+int kernel_of(int dtype, int id, int bl, bool ragged, bool streaming, int64_t slabs)
 {
     if (streaming)
-        return launcher_of(dtype, id, bl, 2);
-    const VariantFns &pipelined = launcher_of(dtype, id, bl, ragged ? 4 : 3);
-    return (pipelined.launch && slabs >= kPipelinedSlabs) ? pipelined : launcher_of(dtype, id, bl, ragged ? 1 : 0);
+        return GEMM_KERNEL_STREAMING;
+    const int pipelined = ragged ? GEMM_KERNEL_PIPELINED_RAGGED : GEMM_KERNEL_PIPELINED;
+    if (slabs >= kPipelinedSlabs && launcher_of(dtype, id, bl, pipelined).launch)
+        return pipelined;
+    return ragged ? GEMM_KERNEL_RAGGED : GEMM_KERNEL_PLAIN;
 }
 
 inline int64_t cdiv64(int64_t a, int64_t b) { return (a + b - 1) / b; }
@@ -246,13 +248,16 @@ extern "C" int gemm_set_workspace(void *dev_ptr, size_t bytes)
     return GEMM_OK;
 }
 
-// The body of gemm_run and gemm_run_noalloc.  own_ws: nullptr = the workspace registered for the
-// current device, else the buffer of own_ws_bytes bytes to use instead.
-static int run_impl(const gemm_cfg *cfg, const void *A, const void *B, void *C, void *hip_stream, void *own_ws,
-                    size_t own_ws_bytes)
+// What a launch of a cfg that names one problem, or one strided batch, comes to.
+struct Launch {
+    SkPlan sk;                       // workers == 0 unless stream-K
+    int64_t kps, tiles_m, tiles_n;   // K elements per workgroup, tiles
+    int kind;                        // gemm_kernel_kind
+};
+
+// Checks a cfg (aligned: whether its operands start on 16-byte boundaries) and plans its launch.
+static int plan_launch(const gemm_cfg *cfg, bool aligned, Launch *out)
 {
-    if (!cfg || !A || !B || !C)
-        return GEMM_ERR_NULL;
     if (cfg->abi_version != GEMM_ABI_VERSION)
         return GEMM_ERR_ABI;
     int rc = check_problem(cfg->M, cfg->N, cfg->K, cfg->dtype);
@@ -279,15 +284,14 @@ static int run_impl(const gemm_cfg *cfg, const void *A, const void *B, void *C, 
     if (cfg->batch > 1 && cfg->stream_k)
         return GEMM_ERR_CFG_ILLEGAL;
     // stream-K: the plan is rebuilt from the cfg's own worker count and must exist
-    SkPlan sk;
+    SkPlan &sk = out->sk;
     std::memset(&sk, 0, sizeof(sk));
     if (cfg->stream_k && !cfg_stream_k_plan(cfg, &sk))
         return GEMM_ERR_CFG_ILLEGAL;
     if (cfg->lda < cfg->K || cfg->ldb < (cfg->b_layout ? cfg->K : cfg->N) || cfg->ldc < cfg->N)
         return GEMM_ERR_SHAPE;
     const int per16 = 16 / es;
-    if (((uintptr_t)A & 15) || ((uintptr_t)B & 15) || ((uintptr_t)C & 15) || cfg->lda % per16 || cfg->ldb % per16 ||
-        cfg->ldc % 8)
+    if (!aligned || cfg->lda % per16 || cfg->ldb % per16 || cfg->ldc % 8)
         return GEMM_ERR_ALIGN;
     if (cfg->batch > 1) {
         // problems must not overlap and must keep the 16-byte alignment of the first one
@@ -310,6 +314,36 @@ static int run_impl(const gemm_cfg *cfg, const void *A, const void *B, void *C, 
     if ((int64_t)v.block_m * cfg->lda * es >= lim || b_window >= lim ||
         tiles_m * tiles_n * cfg->split_k + cfg->sk_workers >= lim || cfg->M * cfg->N >= ((int64_t)1 << 40))
         return GEMM_ERR_SHAPE;
+
+    // an N or K that is not a whole number of 16-byte chunks runs the instantiation that trims its last slab
+    const int ragged = (cfg->N % per16 || cfg->K % per16) ? 1 : 0;
+    // A grid of one tile row over weights larger than the memory-side cache runs the weight-streaming instantiation
+    // (B's loads non-temporal, K walked in a rotated order where the weights' pitch asks for it).  Weights that fit
+    // that cache are left to it: a caller that multiplies by the same weights again soon finds them there (fp8
+    // M = 64, N = 28672, K = 8192, 235 MB, in a loop: 40 us cached, 48 us streamed).
+    const int streaming = (!ragged && tiles_m == 1 && (double)cfg->N * (double)cfg->K * es > hw.mall_bytes) ? 1 : 0;
+    // K slabs a workgroup walks: its slice of K, or a Stream-K worker's share where no tile is whole
+    const int64_t slabs = (sk.workers > 0 && sk.dp_tiles == 0) ? sk.iters / sk.workers : kps / v.block_k;
+    out->kind = kernel_of(dtype, cfg->kernel_id, cfg->b_layout, ragged, streaming, slabs);
+    out->kps = kps;
+    out->tiles_m = tiles_m;
+    out->tiles_n = tiles_n;
+    return GEMM_OK;
+}
+
+// The body of gemm_run, gemm_run_ws and gemm_run_noalloc.  own_ws: nullptr = the workspace registered for the
+// current device, else the buffer of own_ws_bytes bytes to use instead.
+static int run_impl(const gemm_cfg *cfg, const void *A, const void *B, void *C, void *hip_stream, void *own_ws,
+                    size_t own_ws_bytes)
+{
+    if (!cfg || !A || !B || !C)
+        return GEMM_ERR_NULL;
+    Launch p;
+    const int rc = plan_launch(cfg, !(((uintptr_t)A | (uintptr_t)B | (uintptr_t)C) & 15), &p);
+    if (rc)
+        return rc;
+    const SkPlan &sk = p.sk;
+    const Variant &v = variant_at(cfg->dtype, cfg->kernel_id);
 
     float *ws = nullptr;
     if ((cfg->split_k > 1 || cfg->stream_k) && own_ws) {
@@ -340,13 +374,13 @@ static int run_impl(const gemm_cfg *cfg, const void *A, const void *B, void *C, 
     a.ldc = (int)cfg->ldc;
     a.alpha = cfg->alpha;
     a.beta = cfg->beta;
-    a.tiles_m = (int)tiles_m;
-    a.tiles_n = (int)tiles_n;
+    a.tiles_m = (int)p.tiles_m;
+    a.tiles_n = (int)p.tiles_n;
     a.split_k = cfg->split_k;
-    a.k_per_split = (int)kps;
-    a.group_m = (int)std::min<int64_t>(cfg->group_m, tiles_m);   // a band taller than the grid is the whole grid
+    a.k_per_split = (int)p.kps;
+    a.group_m = (int)std::min<int64_t>(cfg->group_m, p.tiles_m);   // a band taller than the grid is the whole grid
     a.xcd_remap = cfg->xcd_remap ? 1 : 0;
-    a.n_xcd = hw.n_xcd;
+    a.n_xcd = hw_current().n_xcd;
     a.sk = sk;   // workers == 0 unless stream-K
     a.batch = cfg->batch;
     a.stride_a = cfg->batch > 1 ? cfg->stride_a : 0;
@@ -356,18 +390,8 @@ static int run_impl(const gemm_cfg *cfg, const void *A, const void *B, void *C, 
     a.n_groups = 0;
 
     hipStream_t stream = (hipStream_t)hip_stream;
-    const int f16 = (dtype == GEMM_FP16) ? 1 : 0;
-    // an N or K that is not a whole number of 16-byte chunks runs the instantiation that trims its last slab
-    const int ragged = (cfg->N % per16 || cfg->K % per16) ? 1 : 0;
-    // A grid of one tile row over weights larger than the memory-side cache runs the weight-streaming instantiation
-    // (B's loads non-temporal, K walked in a rotated order where the weights' pitch asks for it).  Weights that fit
-    // that cache are left to it: a caller that multiplies by the same weights again soon finds them there (fp8
-    // M = 64, N = 28672, K = 8192, 235 MB, in a loop: 40 us cached, 48 us streamed).
-    const int streaming = (!ragged && tiles_m == 1 && (double)cfg->N * (double)cfg->K * es > hw.mall_bytes) ? 1 : 0;
-    // K slabs a workgroup walks: its slice of K, or a Stream-K worker's share where no tile is whole
-    const int64_t slabs = (sk.workers > 0 && sk.dp_tiles == 0) ? sk.iters / sk.workers : kps / v.block_k;
-    const VariantFns &fns = kernel_of(dtype, cfg->kernel_id, cfg->b_layout, ragged, streaming, slabs);
-    if (fns.launch(a, stream) != hipSuccess) {
+    const int f16 = (cfg->dtype == GEMM_FP16) ? 1 : 0;
+    if (launcher_of(cfg->dtype, cfg->kernel_id, cfg->b_layout, p.kind).launch(a, stream) != hipSuccess) {
         (void)hipGetLastError();
         return GEMM_ERR_HIP;
     }
@@ -460,23 +484,16 @@ static_assert(sizeof(gemm_group_rec) == sizeof(GroupRec) && offsetof(gemm_group_
                   offsetof(gemm_group_rec, group_m) == offsetof(GroupRec, group_m),
               "the public record is the kernel's record");
 
-extern "C" int gemm_run_grouped(const gemm_cfg *cfg, int n_groups, const gemm_group_rec *host_table, const void *dev_table,
-                                void *hip_stream)
+// The workgroups of a grouped launch (0: every group is empty) and its kernel.
+static int plan_grouped(const gemm_cfg *cfg, int n_groups, const gemm_group_rec *host_table, int64_t *total, int *kind)
 {
-    if (!cfg || !host_table || !dev_table)
-        return GEMM_ERR_NULL;
-    int rc = check_grouped_cfg(cfg, n_groups);
-    if (rc)
-        return rc;
-    if ((uintptr_t)dev_table & 15)
-        return GEMM_ERR_ALIGN;
     const int X = grouped_xcds(cfg);
     int64_t slots = 0;
     int64_t tiles = 0, tile_slabs = 0;
     int ragged = 0;   // one group with a ragged N or K sends the whole launch through the trimming instantiation
     const int per16 = 16 / elem_bytes(cfg->dtype);
     for (int i = 0; i < n_groups; ++i) {
-        rc = check_group_rec(cfg, &host_table[i], slots);
+        const int rc = check_group_rec(cfg, &host_table[i], slots);
         if (rc)
             return rc;
         slots += group_slots((int64_t)host_table[i].tiles_m * host_table[i].tiles_n, X);
@@ -488,15 +505,35 @@ extern "C" int gemm_run_grouped(const gemm_cfg *cfg, int n_groups, const gemm_gr
         tiles += t;
         tile_slabs += t * cdiv64(host_table[i].K, cfg->block_k);
     }
-    if (slots == 0)
+    *total = slots * X;
+    // one kernel for all groups: the mean slab count over the tiles decides
+    *kind = kernel_of(cfg->dtype, cfg->kernel_id, cfg->b_layout, ragged, false, tiles ? tile_slabs / tiles : 0);
+    return GEMM_OK;
+}
+
+extern "C" int gemm_run_grouped(const gemm_cfg *cfg, int n_groups, const gemm_group_rec *host_table, const void *dev_table,
+                                void *hip_stream)
+{
+    if (!cfg || !host_table || !dev_table)
+        return GEMM_ERR_NULL;
+    int rc = check_grouped_cfg(cfg, n_groups);
+    if (rc)
+        return rc;
+    if ((uintptr_t)dev_table & 15)
+        return GEMM_ERR_ALIGN;
+    int64_t total = 0;   // the grid: X workgroups per slot
+    int kind = GEMM_KERNEL_PLAIN;
+    rc = plan_grouped(cfg, n_groups, host_table, &total, &kind);
+    if (rc)
+        return rc;
+    if (total == 0)
         return GEMM_OK;   // every group is empty
-    const int64_t total = slots * X;
     const gemm_hw &hw = hw_current();
     KernelArgs a;
     std::memset(&a, 0, sizeof(a));
     a.alpha = cfg->alpha;
     a.beta = cfg->beta;
-    a.tiles_m = (int)total;   // the grid: X workgroups per slot
+    a.tiles_m = (int)total;
     a.tiles_n = 1;
     a.split_k = 1;
     a.group_m = 1;
@@ -505,11 +542,35 @@ extern "C" int gemm_run_grouped(const gemm_cfg *cfg, int n_groups, const gemm_gr
     a.batch = 1;
     a.groups = (const GroupRec *)dev_table;
     a.n_groups = n_groups;
-    // one kernel for all groups: the mean slab count over the tiles decides
-    if (kernel_of(cfg->dtype, cfg->kernel_id, cfg->b_layout, ragged, false, tile_slabs / tiles).launch(a, (hipStream_t)hip_stream) !=
-        hipSuccess) {
+    if (launcher_of(cfg->dtype, cfg->kernel_id, cfg->b_layout, kind).launch(a, (hipStream_t)hip_stream) != hipSuccess) {
         (void)hipGetLastError();
         return GEMM_ERR_HIP;
     }
+    return GEMM_OK;
+}
+
+extern "C" int gemm_launched_kernel(const gemm_cfg *cfg, int n_groups, const gemm_group_rec *host_table, int32_t out4[4])
+{
+    if (!cfg || !out4 || (n_groups != 0 && !host_table))
+        return GEMM_ERR_NULL;
+    int rc, kind = GEMM_KERNEL_PLAIN;
+    if (n_groups != 0) {
+        int64_t total = 0;
+        rc = check_grouped_cfg(cfg, n_groups);
+        if (!rc)
+            rc = plan_grouped(cfg, n_groups, host_table, &total, &kind);
+    } else {
+        Launch p;
+        rc = plan_launch(cfg, true, &p);
+        if (!rc)
+            kind = p.kind;
+    }
+    if (rc)
+        return rc;
+    const VariantFns &fns = launcher_of(cfg->dtype, cfg->kernel_id, cfg->b_layout, kind);
+    out4[0] = kind;
+    out4[1] = fns.waves_m;
+    out4[2] = fns.waves_n;
+    out4[3] = fns.loop_form;
     return GEMM_OK;
 }

@@ -102,6 +102,72 @@ def test_cfg_at_enumeration_and_legality():
     assert n - n // 7 <= len(seen) <= n and any(k[2] for k in seen)
 
 
+def _tile_cfgs(dtype, M, N, K, bl, tile, split_k=1, stream_k=0):
+    for i in range(g.gemm_cfg_count(dtype)):
+        c = g.gemm_cfg_at_ex(i, M, N, K, dtype, bl)
+        if c is not None and (c.block_m, c.block_n, c.block_k, c.stages, c.mfma, c.split_k, c.stream_k) == tile + (split_k, stream_k):
+            yield c
+
+
+def test_which_instantiation_a_launch_runs():
+    """The pipelined kernels from twenty K slabs per workgroup on, ragged ones likewise, for every entry of the 256x256 tiles
+    with 128-byte slab rows; K slices, Stream-K shares and the mean of a group count as a workgroup's slabs."""
+    for dtype, bk, mfma, pick_waves in ((g.GEMM_BF16, 64, 16, {(4, 2), (2, 4)}), (g.GEMM_FP16, 64, 16, {(4, 2), (2, 4)}),
+                                        (g.GEMM_FP8_E4M3, 128, 32, {(2, 2), (2, 4)})):
+        tile = (256, 256, bk, 2, mfma)
+        for bl in (0, 1):
+            for slabs in (19, 20):
+                for short, n_short in ((0, 0), (1, 0), (0, 1)):
+                    seen = set()
+                    for c in _tile_cfgs(dtype, 512, 512 - n_short, slabs * bk - short, bl, tile):
+                        kind, wm, wn, form = g.gemm_launched_kernel(c)
+                        ragged = short or n_short
+                        if slabs == 20:
+                            assert (kind, wm, wn, form) == ("pipelined ragged" if ragged else "pipelined", 2, 2, 7)
+                        else:
+                            assert (kind, wm, wn) == ("ragged" if ragged else "plain", c.waves_m, c.waves_n)
+                            assert (form == 7) == ((wm, wn) == (2, 2))       # the four-wave fp8 tile: at every K
+                        seen.add((c.waves_m, c.waves_n))
+                    assert seen == pick_waves
+    tile = (256, 256, 64, 2, 16)
+    for split, slabs, kind in ((2, 39, "pipelined"), (2, 38, "plain"), (4, 80, "pipelined"), (4, 76, "plain")):
+        for c in _tile_cfgs(g.GEMM_BF16, 512, 512, slabs * 64, 0, tile, split):
+            assert g.gemm_launched_kernel(c)[0] == kind, (split, slabs)
+    # 5 tiles on 256 workers, all of them cut: 5 * slabs / 256 slabs each
+    for slabs, kind in ((1024, "pipelined"), (1000, "plain")):
+        for c in _tile_cfgs(g.GEMM_BF16, 256, 1280, slabs * 64, 0, tile, 1, 1):
+            assert c.sk_workers == 256 and g.gemm_launched_kernel(c)[0] == kind, slabs
+    # other tiles have no pipelined instantiation
+    for c in _tile_cfgs(g.GEMM_BF16, 512, 512, 4096, 0, (256, 256, 32, 4, 32)):
+        assert g.gemm_launched_kernel(c)[0] == "plain"
+    # weights beyond the memory-side cache under one tile row
+    assert g.gemm_launched_kernel(g.gemm_select_ex(16, 28672, 8192, g.GEMM_BF16, 1))[0] == "streaming"
+    assert g.gemm_launched_kernel(g.gemm_select_ex(16, 28671, 8192, g.GEMM_BF16, 0))[0] == "ragged"
+    # a group: the mean over its tiles, and one ragged group makes the launch ragged
+    for shapes, kind in (([(256, 256, 30 * 64), (256, 256, 10 * 64)], "pipelined"), ([(256, 256, 29 * 64), (256, 256, 10 * 64)], "plain"),
+                         ([(256, 256, 30 * 64), (256, 255, 10 * 64)], "pipelined ragged"), ([(0, 256, 64), (256, 256, 20 * 64)], "pipelined")):
+        probs = g.make_problems(shapes)
+        for i, (m, n, k) in enumerate(shapes):
+            probs[i].ldb = probs[i].ldc = 256
+            if m:
+                probs[i].A = probs[i].B = probs[i].C = 0x1000
+        for v in range(g.gemm_variant_count(g.GEMM_BF16)):
+            c = g.gemm_cfg_at_grouped(v, probs, g.GEMM_BF16)
+            if c is not None and (c.block_m, c.block_n, c.block_k, c.stages, c.mfma) == tile:
+                assert g.gemm_launched_kernel(c, g.gemm_grouped_plan(c, probs)[0])[0] == kind, shapes
+    # refused as gemm_run refuses it
+    c = g.gemm_select(512, 512, 512, g.GEMM_BF16)
+    out = (ctypes.c_int32 * 4)()
+    f = g._lib.gemm_launched_kernel
+    assert f(None, 0, None, out) == -1 and f(ctypes.byref(c), 0, None, None) == -1 and f(ctypes.byref(c), 1, None, out) == -1
+    bad = c.copy(); bad.block_m = 12
+    assert f(ctypes.byref(bad), 0, None, out) == -4
+    bad = c.copy(); bad.lda = 511
+    assert f(ctypes.byref(bad), 0, None, out) == -2
+    bad = c.copy(); bad.groups = 2
+    assert f(ctypes.byref(bad), 0, None, out) == -4
+
+
 def test_run_with_a_workspace_argument_never_falls_back_to_the_registered_one():
     split = next(c for c in (g.gemm_cfg_at(i, 512, 512, 4096, g.GEMM_BF16) for i in range(g.gemm_cfg_count(g.GEMM_BF16)))
                  if c is not None and c.split_k == 4)
