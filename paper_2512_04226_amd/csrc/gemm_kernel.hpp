@@ -566,11 +566,10 @@ __global__ __launch_bounds__(T::NT, T::MIN_WAVES) void gemm_kernel(const KernelA
     typedef typename std::conditional<ES == 2, bf16x8, i32x8>::type frag_t;
     frag_t af[2][T::TM], bfr[2][T::TN];
 
-    // Fragment `u` of k-step `kstep` of LDS stage `stage` into register buffer `buf`:
+    // Fragment `u` of k-step `kstep` of the slab at `sA` (A's part) and `sB` into register buffer `buf`:
     // u < TM is the A fragment of MFMA tile row u, otherwise the B fragment of tile column u-TM.
     // (`dslot` >= 0: a B fragment goes to slot dslot of the flat B register array instead of [buf][j]: K-loop form 6)
-    auto load_frag = [&](const G355_LDS uint8_t *sA, int kstep, int buf, int u, int dslot = -1) {
-        const G355_LDS uint8_t *sB = sA + T::A_BYTES;
+    auto frag_from = [&](const G355_LDS uint8_t *sA, const G355_LDS uint8_t *sB, int kstep, int buf, int u, int dslot = -1) {
         const int k0 = kstep * T::KI;
         if (u < T::TM) {
             const int i = u;
@@ -613,6 +612,10 @@ __global__ __launch_bounds__(T::NT, T::MIN_WAVES) void gemm_kernel(const KernelA
                 dst = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
             }
         }
+    };
+    // the same from a stage of the ring, where B's part follows A's
+    auto load_frag = [&](const G355_LDS uint8_t *stage, int kstep, int buf, int u, int dslot = -1) {
+        frag_from(stage, stage + T::A_BYTES, kstep, buf, u, dslot);
     };
     constexpr int NF = T::TM + T::TN;     // fragments per k-step
     // acc[j][i] += B fragment in flat slot `bslot` x A fragment af[abuf][i]
@@ -860,7 +863,7 @@ __global__ __launch_bounds__(T::NT, T::MIN_WAVES) void gemm_kernel(const KernelA
                 else if (T::BL == 1)
                     kc_frag(bfr[k][u - T::TM], pb, fb_off[k], (u - T::TM) * MI);
                 else
-                    load_frag(pb - T::A_BYTES, k, k, u);
+                    frag_from(pa, pb, k, k, u);
             };
             // one load instruction of A's (B's) slab at K position kk; a slab wholly inside the K range needs no test and
             // its position is the scalar offset
