@@ -49,6 +49,8 @@ def test_pipelined_bit_exact(oracle, slabs, short, dtype, bl):
         if c.split_k > 2:
             continue
         c.lda, c.ldb = dA.shape[1], dB.shape[1]
+        if c.split_k == 1:
+            assert g.gemm_launched_kernel(c) == ("pipelined ragged" if K % (16 if dtype == E4M3 else 8) else "pipelined", 2, 2, 7)
         out = run_cfg(c, dA, dB, M, N)
         assert np.array_equal(out, ref16), (c.describe(), int((out != ref16).sum()))
         modes.add((c.split_k, c.stream_k))
@@ -67,6 +69,7 @@ def test_pipelined_stream_k_with_whole_tiles(oracle):
     n = 0
     for c in _cfgs(g, M, N, K, BF16, 0):
         if c.stream_k:
+            assert g.gemm_launched_kernel(c)[0] == "pipelined"
             assert np.array_equal(run_cfg(c, dA, dB, M, N)[rows], ref16), c.describe()
             n += 1
     assert n >= 1
@@ -118,10 +121,9 @@ def test_pipelined_batch_group_and_beta(oracle, bl):
 
 @pytest.mark.parametrize("M,N,K,batch,dtype,bl", [(4100, 4360, 72, 1, BF16, 0), (4100, 4360, 1288, 1, BF16, 1), (260, 264, 200, 141, BF16, 1),
                                                   (4100, 4360, 272, 1, E4M3, 1)])
-def test_resident_launch_takes_every_work_item(oracle, M, N, K, batch, dtype, bl):
-    """More work items than the device holds workgroups (306 tiles of 256x256, 1155 of 128x128; 564 to 1269 of a batch whose
-    item count is no multiple of the grid): every tile of every problem is written, bit for bit, whatever order the
-    workgroups take them in.  Sampled rows of the product against the oracle; every row against a second configuration."""
+def test_more_tiles_than_the_device_holds_workgroups(oracle, M, N, K, batch, dtype, bl):
+    """306 tiles of 256x256, 1155 of 128x128; 564 to 1269 of a batch: every tile of every problem is written, bit for bit,
+    whatever order the workgroups run in.  Sampled rows of the product against the oracle; every row against a second configuration."""
     from gpu_util import to_dev
     from paper_2512_04226_amd import binding as g
     A, B = _operands(oracle, batch * M, N, K, dtype)
@@ -146,3 +148,75 @@ def test_resident_launch_takes_every_work_item(oracle, M, N, K, batch, dtype, bl
         assert np.array_equal(out, first), c.describe()
         n += 1
     assert n >= 4
+
+
+def _padded(x, dtype):
+    """Rows of whole 16-byte chunks, NaN patterns between K (or N) and the pitch."""
+    per16 = 16 if dtype == E4M3 else 8
+    return np.pad(x, ((0, 0), (0, -x.shape[1] % per16)), constant_values=0x7F if dtype == E4M3 else 0x7FC0 if dtype == BF16 else 0x7E00)
+
+
+def _old_c(M, N, dtype):
+    make = wl.integer_fp16 if dtype == FP16 else wl.integer_bf16
+    return make(M, N, 8, seed=23, case=1)[0][:, :1].repeat(N, axis=1)
+
+
+@pytest.mark.parametrize("split", [1, 2])
+@pytest.mark.parametrize("dtype", [BF16, FP16, E4M3])
+@pytest.mark.parametrize("bl", [0, 1])
+def test_pipelined_ragged_batch_with_splits_and_beta(oracle, dtype, bl, split):
+    """Each problem's and each K slice's own last slab, an old C that is read and whose padding is not written."""
+    from gpu_util import to_dev, workspace_for
+    from paper_2512_04226_amd import binding as g
+    M, N, K, batch = 70, 261, 40 * SLAB[dtype] - 13, 3
+    ops = [_operands(oracle, M + i, N, K, dtype) for i in range(batch)]
+    dA = to_dev(np.stack([_padded(a[:M], dtype) for a, _ in ops]))
+    dB = to_dev(np.stack([_padded(np.ascontiguousarray(b.T) if bl else b, dtype) for _, b in ops]))
+    Cin, n = _old_c(M, N, dtype), 0
+    for idx in range(g.gemm_cfg_count(dtype)):
+        c = g.gemm_cfg_at_batched(idx, M, N, K, batch, dtype, bl)
+        if c is None or c.split_k != split or (c.block_m, c.block_n, c.block_k, c.stages, c.mfma) != (
+                256, 256, SLAB[dtype], 2, 32 if dtype == E4M3 else 16):
+            continue
+        c.alpha, c.beta, c.lda, c.ldb, c.ldc = 0.5, 2.0, dA.shape[2], dB.shape[2], 272
+        c.stride_a, c.stride_b, c.stride_c = dA[0].numel(), dB[0].numel(), M * 272
+        assert g.gemm_launched_kernel(c)[0] == "pipelined ragged"
+        workspace_for(c)
+        dC = to_dev(np.stack([np.pad(Cin, ((0, 0), (0, 272 - N)), constant_values=0x7FC0)] * batch))
+        g.gemm_run(c, dA, dB, dC)
+        torch.cuda.synchronize()
+        out = dC.cpu().numpy().view(np.uint16)
+        for i, (a, b) in enumerate(ops):
+            ref16, _ = oracle.accumulate(oracle.gemm(a[:M], b, dtype, alpha=0.5)[1], 2.0, Cin, dtype)
+            assert np.array_equal(out[i][:, :N], ref16), (c.describe(), i)
+        assert (out[:, :, N:] == 0x7FC0).all()
+        n += 1
+    assert n == 2
+
+
+@pytest.mark.parametrize("bl", [0, 1])
+def test_pipelined_stream_k_ragged_with_beta(oracle, bl):
+    """200 tiles on 256 workers, every tile cut, twenty slabs a worker and a second segment for most: the ring is used twice in
+    one workgroup, and the odd last slab is trimmed wherever a segment ends a tile."""
+    from gpu_util import to_dev, workspace_for
+    from paper_2512_04226_amd import binding as g
+    M, N, K = 2047, 6397, 26 * 64 - 13
+    A, B = _operands(oracle, M, N, K, BF16)
+    rows = np.unique(np.concatenate([np.arange(0, M, 173), [255, 256, M - 1]]))
+    Cin = _old_c(M, N, BF16)
+    ref16, _ = oracle.accumulate(oracle.gemm_rows(A, B, rows, BF16)[1], 2.0, Cin[rows], BF16)
+    dA, dB = to_dev(_padded(A, BF16)), to_dev(_padded(np.ascontiguousarray(B.T) if bl else B, BF16))
+    n = 0
+    for idx in range(g.gemm_cfg_count(BF16)):
+        c = g.gemm_cfg_at_ex(idx, M, N, K, BF16, bl)
+        if c is None or not c.stream_k or (c.block_m, c.block_n, c.block_k, c.stages, c.mfma) != (256, 256, 64, 2, 16):
+            continue
+        c.beta, c.lda, c.ldb = 2.0, dA.shape[1], dB.shape[1]
+        assert g.gemm_launched_kernel(c)[0] == "pipelined ragged" and g.gemm_stream_k_plan(c)[2] == 0
+        workspace_for(c)
+        dC = to_dev(np.pad(Cin, ((0, 0), (0, c.ldc - N))))
+        g.gemm_run(c, dA, dB, dC)
+        torch.cuda.synchronize()
+        assert np.array_equal(dC.cpu().numpy().view(np.uint16)[rows][:, :N], ref16), c.describe()
+        n += 1
+    assert n == 2
