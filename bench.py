@@ -302,8 +302,8 @@ def main():
         return settled_us(torch, lambda: g.gemm_run(cfg, dA, dB, dC))
 
     also = {}
-    # the same step in the chip's settled state (the driver's short default run sits in the throttling transient
-    # that follows an idle gap: `value` is what its flags time, this is the sustained rate)
+    # the same step in the chip's settled state (a short run sits in the throttling transient that follows an idle
+    # gap: `value` is what the flags time, this is the sustained rate)
     also["settled_value"] = flops_step / settled_us(torch, step) * 1e-6
     also["settled_8192_kernel_ms"] = settled_us(torch, lambda: g.gemm_run(cfg_big, *dev[big])) * 1e-3
     # GPU time of the warm-up steps: after an idle gap the chip needs 15-20 ms of work to settle under its power
@@ -324,7 +324,8 @@ def main():
                    "select_us": select_us},
         "frac_of_mfma_peak": value / PEAK_TFLOPS["bf16"],
         "roofline": {"bound": "mfma", "achieved": achieved, "peak": PEAK_TFLOPS["bf16"], "unit": "TFLOP/s",
-                     "frac": achieved / PEAK_TFLOPS["bf16"], "kernel": "gemm_kernel<%s> on 8192^3" % cfg_big.describe(),
+                     "frac": achieved / PEAK_TFLOPS["bf16"], "kernel": "gemm_kernel<%s> on 8192^3: the %s instantiation, %dx%d waves, K-loop form %d" % (
+                         (cfg_big.describe(),) + g.gemm_launched_kernel(cfg_big)),
                      "avg_launch_ms": kern_ms, "traffic": read_traffic("gemm_bf16_8192_counters.txt")},
     }
     ceiling = (also.get("mfma_only_bf16_random_tflops") or {}).get("16x16x32" if cfg_big.mfma == 16 else "32x32x16")

@@ -176,7 +176,7 @@ const char *gemm_strerror(int status);
  * chunks (8 16-bit or 16 fp8 elements; ldc: 8 elements); the caller may overwrite them with larger
  * multiples of that.  N and K themselves need not be such multiples: gemm_run then runs the variant's
  * instantiation that clears the ragged ends of the last K slab in LDS and stores C's ragged edge element by
- * element (a per cent or two slower; the model does not price it).  A grid of one tile row (M <= BLOCK_M) over weights larger than the hardware
+ * element (1-5 % slower than whole chunks on most shapes, up to 18 % measured; the model does not price it).  A grid of one tile row (M <= BLOCK_M) over weights larger than the hardware
  * descriptor's mall_bytes runs the variant's weight-streaming instantiation: B's loads carry the non-temporal hint,
  * and K-contiguous weights whose row pitch is a power of two of 16 KiB or more are walked in a K order rotated by
  * tile column (the sum over K is then taken in another order than otherwise: still deterministic).  Whatever lies between a row's end and its leading dimension is never

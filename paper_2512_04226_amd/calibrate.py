@@ -15,7 +15,7 @@ Prints the descriptor fields the probes give and one line per variant (B row-maj
 
 The K-loop form of each variant (LOOP / LOOP_KC columns) is chosen from a comparison of
 builds of the library, one per form (0 .. 6), each with that form forced on every variant (a tile that
-does not fit form 6 runs form 0 in that build):
+does not fit form 6 runs form 0 in that build; the pipelined instantiations, form 7, are not part of such builds):
 
     for k in 0 1 2 3 4 5 6: python -m paper_2512_04226_amd.build --out /tmp/lf$k.so -DG355_FORCE_LOOP_FORM=$k
     python -m paper_2512_04226_amd.calibrate --loop-forms /tmp/lf0.so /tmp/lf1.so /tmp/lf2.so /tmp/lf3.so /tmp/lf4.so /tmp/lf5.so /tmp/lf6.so

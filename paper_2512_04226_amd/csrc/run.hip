@@ -215,9 +215,20 @@ const VariantFns &launcher_of(int dtype, int id, int bl, int which)
 
 // The instantiation of a variant that a launch runs.  The pipelined one (four waves, K-loop form 7) has the faster loop
 // and, with half the waves, the slower prologue and store stage (about 1 us in 16-bit types): it pays from about twenty
-// K slabs per workgroup.  Plain -> pipelined, M = N = 4096 bf16, K-contiguous B: K = 512 20.3 -> 21.4 us, 1024 31.1 -> 31.6,
-// 1152 34.0 -> 33.6; and, before the store stage took several row blocks at a time, 1536 44.5 -> 43.6, 2048 56.9 -> 54.1,
-// 4096 106.1 -> 94.8.  (The four-wave fp8 tile runs form 7 at every K: level with form 5 up to K = 2048.)
+// K slabs per workgroup.  Time of the pipelined kernel over the plain (or ragged) one, 4096 x 4096 (4093 ragged), at
+// 10 / 17 / 20 / 24 / 32 / 48 slabs:
+//   bf16 4x2 grid, row-major B      1.07 1.01 0.99 0.97 0.96 0.92     ragged 1.10 1.04 1.01 1.00 0.98 0.95
+//        4x2 grid, K-contiguous     1.05 1.01 0.98 0.95 0.95 0.92     ragged 1.06 1.01 1.00 0.98 0.97 0.95
+//        2x4 grid, K-contiguous     1.08 1.04 1.03 1.00 1.00 0.96     ragged 1.05 1.03 1.01 1.01 0.99 0.97
+//   fp16 4x2 grid, row-major B      1.06 1.01 0.99 0.97 0.97 0.90     ragged 1.10 1.05 1.02 1.00 0.98 0.96
+//        2x4 grid, K-contiguous     1.07 1.05 1.02 1.00 1.00 0.95     ragged 1.04 1.02 1.00 0.99 1.00 0.97
+//   fp8  2x4 grid, row-major B      1.06 1.00 0.99 0.97 0.96 0.93     ragged 1.07 1.02 1.00 0.99 0.96 0.91
+//        2x4 grid, K-contiguous     1.02 0.97 0.95 0.94 0.94 0.91     ragged 1.01 0.98 0.97 0.95 0.95 0.94
+// and of a group of sixteen products (100 to 2000 rows, N = 2048) at 12 / 16 / 20 / 24 / 32 slabs, equal in all groups or
+// half and one and a half times that in turn (the mean decides): bf16 4x2 row-major 1.07 1.01 0.98 0.97 0.97, mixed
+// 1.07 1.00 0.98 0.95 0.93; 2x4 K-contiguous 1.07 1.04 1.01 0.99 0.99, mixed 1.04 0.99 0.98 0.99 0.97.
+// (One line for all: at twenty the slowest to gain, the 2x4 grid on K-contiguous B, still loses 2-3 %, the others have
+// gained up to 5.  The four-wave fp8 tile runs form 7 at every K: level with form 5 up to K = 2048.)
 constexpr int64_t kPipelinedSlabs = 20;
 int kernel_of(int dtype, int id, int bl, bool ragged, bool streaming, int64_t slabs)
 {

@@ -2,10 +2,14 @@
 // the paper speaks of 75 searched configurations; Section V-E of 50-150 valid tiles per
 // datatype).  One line per instantiation of gemm_kernel<>:
 //   X(BLOCK_M, BLOCK_N, BLOCK_K, WAVES_M, WAVES_N, MFMA, LDS_STAGES, LOOP, LOOP_KC)
-// LOOP / LOOP_KC: the K-loop form (0 to 6, see Tile in gemm_kernel.hpp) the instantiation for
-// row-major / K-contiguous B is compiled with: the fastest of forms 0 to 4 on 8192^3 where one is
-// at least 1.5 % faster than form 0 (bf16 and fp16 timings together for the 16-bit list), else 0;
-// form 5 or 6 where it beat that choice by 3 % (form 6: 2 %) or more.
+// LOOP / LOOP_KC: the K-loop form (0 to 6, see Tile in gemm_kernel.hpp) the plain and the weight-streaming
+// instantiation for row-major / K-contiguous B are compiled with: the fastest of forms 0 to 4 on 8192^3 where
+// one is at least 1.5 % faster than form 0 (bf16 and fp16 timings together for the 16-bit list), else 0;
+// form 5 or 6 where it beat that choice by 3 % (form 6: 2 %) or more.  kernels.inc departs from the columns in
+// three places: the plain and ragged instantiations of the four-wave fp8 256x256x128 tile run form 7, two ragged
+// ones of the eight-wave 256x256 tiles a form that does not spill, and all 256x256 tiles with 128-byte slab rows
+// have a pipelined instantiation beside these (four waves, form 7), which run.hip launches from twenty K slabs
+// per workgroup: WAVES_M x WAVES_N is what runs below that.
 // The table holds no timing: the selector prices a variant from its shape and the hardware
 // descriptor alone (Algorithm 3's instruction count times the measured issue interval, plus the
 // slab's fill and synchronisation cost).
@@ -47,12 +51,10 @@
     X(16, 16, 256, 1, 1, 16, 3, 0, 2)
 // 16x16x32 MFMA on the larger tiles, eight waves: fewer accumulator register bytes per flop than
 // 32x32x16, which is what counts once the chip is power-limited.  The model prices the 4x2 and the 2x4 wave grid of
-// the 256x256x64 tile alike; the 4x2 one measures 3-4 % faster on 8192^3 and is listed first (earlier wins a tie).
-// On K-contiguous B the 2x4 grid in K-loop form 6 is the faster one (8192^3: 767 us against 794 bf16, 794 against 835
-// fp16) and wins that tie there (variant_wins_tie_on_kc below).
-// (A four-wave grid of this tile -- 128x128 wave tiles, accumulators in AGPRs, K-loop form 5 -- is level with the
-// 4x2 grid on 8192^3 with row-major B and 3-4 % ahead with K-contiguous B, but 3-5 % behind on the irregular shapes
-// that pick this tile: not listed.)
+// the 256x256x64 tile alike, and from twenty K slabs on both run the same pipelined kernel.  Below that, 4096 x 4096 at
+// 6 / 10 / 14 / 17 slabs: row-major B 20.5 24.3 29.3 33.6 us (4x2) against 19.0 24.1 29.5 34.0, listed first as the faster
+// of the two near twenty (earlier wins a tie); K-contiguous B 18.6 23.9 29.2 33.4 against 18.2 23.3 28.3 32.5 (2x4, K-loop
+// form 6), which wins the tie there (variant_wins_tie_on_kc below).
 #define G355_VARIANTS_BF16_4(X)    \
     X(256, 256, 64, 4, 2, 16, 2, 4, 2) \
     X(256, 256, 64, 2, 4, 16, 2, 2, 6) \
