@@ -72,10 +72,10 @@ def _plan(base, key):
 
 class _Workspace:
     """A buffer of one stream.  `pinned`: a graph may have been captured with its address."""
-    __slots__ = ("tensor", "pinned")
+    __slots__ = ("tensor", "address", "nbytes", "pinned")
 
     def __init__(self, tensor):
-        self.tensor, self.pinned = tensor, False
+        self.tensor, self.address, self.nbytes, self.pinned = tensor, tensor.data_ptr(), tensor.numel() * 4, False
 
 
 def _allocate(nbytes, device):
@@ -90,10 +90,10 @@ def _workspace_for(need, device, stream):
     # handle 2 is the per-thread default stream: another stream in every thread
     key = (device.index, stream, threading.get_ident() if stream == 2 else 0)
     ws = _workspaces.get(key)
-    if ws is None or ws.tensor.numel() * 4 < need:
+    if ws is None or ws.nbytes < need:
         if ws is not None and ws.pinned:
             _pinned.append(ws.tensor)
-            need = max(need, 8 * ws.tensor.numel())
+            need = max(need, 2 * ws.nbytes)
         ws = _workspaces[key] = _Workspace(_allocate(need, device))
         if len(_workspaces) > _MAX_WORKSPACES:
             for old in [k for k, w in _workspaces.items() if not w.pinned and k != key][:1]:
@@ -102,7 +102,7 @@ def _workspace_for(need, device, stream):
         _workspaces.move_to_end(key)
     if torch.cuda.is_current_stream_capturing():
         ws.pinned = True
-    return ws.tensor
+    return ws
 
 
 def matmul(A, B, out=None, alpha=1.0, beta=0.0, b_k_contiguous=False, stream=None):
@@ -136,7 +136,10 @@ def matmul(A, B, out=None, alpha=1.0, beta=0.0, b_k_contiguous=False, stream=Non
         ldc = out.stride(0)
     layout = g.GEMM_B_K_CONTIGUOUS if b_k_contiguous else g.GEMM_B_ROW_MAJOR
     plan = _plan(select(M, N, K, dtype, layout), (M, N, K, dtype, layout, lda, ldb, ldc))
-    cfg_ref = plan.ref_for(alpha, beta)
+    if type(alpha) is float and alpha == 1.0 and type(beta) is float and beta == 0.0:
+        cfg_ref = plan.ref
+    else:
+        cfg_ref = plan.ref_for(alpha, beta)
     if torch.cuda.current_device() == device.index:
         _launch(plan.need, cfg_ref, A, B, out, device, stream)
     else:
@@ -147,20 +150,21 @@ def matmul(A, B, out=None, alpha=1.0, beta=0.0, b_k_contiguous=False, stream=Non
 
 def _launch(need, cfg_ref, A, B, out, device, stream):
     """One launch with the tensors' device current: no Python objects made per argument."""
-    current = g.current_stream_handle(device.index)
-    stream = current if stream is None else g._stream_handle(stream)
-    if not need:
-        g._check(g._lib.gemm_run(cfg_ref, A.data_ptr(), B.data_ptr(), out.data_ptr(), stream), "gemm_run")
-    elif stream == current:
+    if need:
         _launch_with_workspace(need, cfg_ref, A, B, out, device, stream)
-    else:
-        with torch.cuda.stream(torch.cuda.ExternalStream(stream, device) if stream else torch.cuda.default_stream(device)):
-            _launch_with_workspace(need, cfg_ref, A, B, out, device, stream)
+        return
+    stream = g.current_stream_handle(device.index) if stream is None else g._stream_handle(stream)
+    g._check(g._lib.gemm_run(cfg_ref, A.data_ptr(), B.data_ptr(), out.data_ptr(), stream), "gemm_run")
 
 
 def _launch_with_workspace(need, cfg_ref, A, B, out, device, stream):
+    current = g.current_stream_handle(device.index)
+    stream = current if stream is None else g._stream_handle(stream)
+    if stream != current:
+        with torch.cuda.stream(torch.cuda.ExternalStream(stream, device) if stream else torch.cuda.default_stream(device)):
+            _launch_with_workspace(need, cfg_ref, A, B, out, device, stream)
+        return
     # a call is two kernels: no other thread may put its own on the stream between them
     with _workspace_lock:
         ws = _workspace_for(need, device, stream)
-        g._check(g._lib.gemm_run_ws(cfg_ref, A.data_ptr(), B.data_ptr(), out.data_ptr(), stream, ws.data_ptr(), ws.numel() * 4),
-                 "gemm_run_ws")
+        g._check(g._lib.gemm_run_ws(cfg_ref, A.data_ptr(), B.data_ptr(), out.data_ptr(), stream, ws.address, ws.nbytes), "gemm_run_ws")
