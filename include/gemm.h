@@ -279,6 +279,10 @@ int gemm_run(const gemm_cfg *cfg, const void *A, const void *B, void *C, void *h
 int gemm_run_ws(const gemm_cfg *cfg, const void *A, const void *B, void *C, void *hip_stream, void *workspace,
                 size_t workspace_bytes);
 
+/* *capturing = 1 while hip_stream records a graph (or the runtime cannot tell), else 0: a caller that keeps workspaces must
+ * keep those whose addresses a graph holds.  Error: GEMM_ERR_NULL. */
+int gemm_stream_capturing(void *hip_stream, int *capturing);
+
 /*
  * gemm_run for callers that cannot allocate or register device memory (code under HIP graph capture,
  * tight serving loops, harnesses that forbid hipMalloc): the same launch, but split-K slabs and Stream-K

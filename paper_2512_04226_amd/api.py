@@ -78,15 +78,19 @@ class _Workspace:
         self.tensor, self.address, self.nbytes, self.pinned = tensor, tensor.data_ptr(), tensor.numel() * 4, False
 
 
-def _allocate(nbytes, device):
-    return torch.empty((nbytes + 15) // 16 * 4, dtype=torch.float32, device=device)
+def _allocate(nbytes, device, stream):
+    """Device memory that the allocator knows as the stream's: once it is given up, only later work of the same stream gets
+    it, so that nothing has to be waited for."""
+    if stream == g.current_stream_handle(device.index):
+        return torch.empty((nbytes + 15) // 16 * 4, dtype=torch.float32, device=device)
+    with torch.cuda.stream(torch.cuda.ExternalStream(stream, device) if stream else torch.cuda.default_stream(device)):
+        return torch.empty((nbytes + 15) // 16 * 4, dtype=torch.float32, device=device)
 
 
 def _workspace_for(need, device, stream):
-    """The stream's workspace of at least `need` bytes (with _workspace_lock held and `stream` torch's current one, so that
-    the allocator hands a buffer that is replaced or dropped only to later work of the same stream: nothing has to be
-    waited for).  A buffer that a capture has seen is never given up, as replays write to it; it is replaced by one of
-    at least twice its size, so that a stream holds at most twice what its largest call needs."""
+    """The stream's workspace of at least `need` bytes (with _workspace_lock held).  A buffer that a capture has seen is never
+    given up, as replays write to it; it is replaced by one of at least twice its size, so that a stream holds at most twice
+    what its largest call needs."""
     # handle 2 is the per-thread default stream: another stream in every thread
     key = (device.index, stream, threading.get_ident() if stream == 2 else 0)
     ws = _workspaces.get(key)
@@ -94,13 +98,13 @@ def _workspace_for(need, device, stream):
         if ws is not None and ws.pinned:
             _pinned.append(ws.tensor)
             need = max(need, 2 * ws.nbytes)
-        ws = _workspaces[key] = _Workspace(_allocate(need, device))
+        ws = _workspaces[key] = _Workspace(_allocate(need, device, stream))
         if len(_workspaces) > _MAX_WORKSPACES:
             for old in [k for k, w in _workspaces.items() if not w.pinned and k != key][:1]:
                 del _workspaces[old]
     else:
         _workspaces.move_to_end(key)
-    if torch.cuda.is_current_stream_capturing():
+    if not ws.pinned and g.gemm_stream_capturing(stream):
         ws.pinned = True
     return ws
 
@@ -150,19 +154,9 @@ def matmul(A, B, out=None, alpha=1.0, beta=0.0, b_k_contiguous=False, stream=Non
 
 def _launch(need, cfg_ref, A, B, out, device, stream):
     """One launch with the tensors' device current: no Python objects made per argument."""
-    if need:
-        _launch_with_workspace(need, cfg_ref, A, B, out, device, stream)
-        return
     stream = g.current_stream_handle(device.index) if stream is None else g._stream_handle(stream)
-    g._check(g._lib.gemm_run(cfg_ref, A.data_ptr(), B.data_ptr(), out.data_ptr(), stream), "gemm_run")
-
-
-def _launch_with_workspace(need, cfg_ref, A, B, out, device, stream):
-    current = g.current_stream_handle(device.index)
-    stream = current if stream is None else g._stream_handle(stream)
-    if stream != current:
-        with torch.cuda.stream(torch.cuda.ExternalStream(stream, device) if stream else torch.cuda.default_stream(device)):
-            _launch_with_workspace(need, cfg_ref, A, B, out, device, stream)
+    if not need:
+        g._check(g._lib.gemm_run(cfg_ref, A.data_ptr(), B.data_ptr(), out.data_ptr(), stream), "gemm_run")
         return
     # a call is two kernels: no other thread may put its own on the stream between them
     with _workspace_lock:

@@ -107,6 +107,8 @@ _lib.gemm_run.restype = _int
 _lib.gemm_run.argtypes = [ctypes.POINTER(gemm_cfg), _vp, _vp, _vp, _vp]
 _lib.gemm_run_ws.restype = _int
 _lib.gemm_run_ws.argtypes = [ctypes.POINTER(gemm_cfg), _vp, _vp, _vp, _vp, _vp, ctypes.c_size_t]
+_lib.gemm_stream_capturing.restype = _int
+_lib.gemm_stream_capturing.argtypes = [_vp, ctypes.POINTER(_int)]
 _lib.gemm_run_noalloc.restype = _int
 _lib.gemm_run_noalloc.argtypes = [ctypes.POINTER(gemm_cfg), _vp, _vp, _vp, _vp]
 GEMM_NOALLOC_WORKSPACE_BYTES = 64 << 20
@@ -407,6 +409,13 @@ def gemm_run_ws(cfg, A, B, C, workspace, stream=None):
     nbytes = workspace.numel() * workspace.element_size() if workspace is not None else 0
     _check(_lib.gemm_run_ws(ctypes.byref(cfg), _ptr(A), _ptr(B), _ptr(C), _stream_handle(stream), _ptr(workspace), nbytes),
            "gemm_run_ws")
+
+
+def gemm_stream_capturing(stream):
+    """Whether the stream of this raw handle records a graph."""
+    out = _int()
+    _check(_lib.gemm_stream_capturing(stream, ctypes.byref(out)), "gemm_stream_capturing")
+    return out.value != 0
 
 
 def open_library(path):

@@ -458,6 +458,21 @@ extern "C" int gemm_run_ws(const gemm_cfg *cfg, const void *A, const void *B, vo
     return run_impl(cfg, A, B, C, hip_stream, workspace, workspace_bytes);
 }
 
+extern "C" int gemm_stream_capturing(void *hip_stream, int *capturing)
+{
+    if (!capturing)
+        return GEMM_ERR_NULL;
+    *capturing = 0;
+    if (!hip_stream)
+        return GEMM_OK;   // the default stream cannot record, and asking would disturb a recording of another
+    hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+    const bool known = hipStreamIsCapturing((hipStream_t)hip_stream, &status) == hipSuccess;
+    if (!known)
+        (void)hipGetLastError();
+    *capturing = !known || status != hipStreamCaptureStatusNone;
+    return GEMM_OK;
+}
+
 extern "C" int gemm_run_noalloc(const gemm_cfg *cfg, const void *A, const void *B, void *C, void *hip_stream)
 {
     if (!cfg)

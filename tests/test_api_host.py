@@ -115,21 +115,22 @@ def launcher(monkeypatch):
             state["current"] = self.before
 
     allocated_on = {}
+    empty = torch.empty
 
-    def allocate(nbytes, device):
-        t = torch.empty((nbytes + 15) // 16 * 4, dtype=torch.float32)
+    def on_cpu(*args, device, **kw):
+        t = empty(*args, **kw)
         allocated_on[t.data_ptr()] = state["current"]
         return t
 
     monkeypatch.setattr(api, "_workspaces", type(api._workspaces)())
     monkeypatch.setattr(api, "_pinned", [])
-    monkeypatch.setattr(api, "_allocate", allocate)
+    monkeypatch.setattr(torch, "empty", on_cpu)
     monkeypatch.setattr(g, "_lib", rec)
     monkeypatch.setattr(g, "current_stream_handle", lambda index: state["current"])
     monkeypatch.setattr(torch.cuda, "stream", lambda s: s)
     monkeypatch.setattr(torch.cuda, "ExternalStream", lambda handle, device: Stream(handle))
     monkeypatch.setattr(torch.cuda, "default_stream", lambda device: Stream(0))
-    monkeypatch.setattr(torch.cuda, "is_current_stream_capturing", lambda: state["capturing"])
+    monkeypatch.setattr(g, "gemm_stream_capturing", lambda handle: state["capturing"])
 
     def launch(need, stream=None):
         x = _Buffer()

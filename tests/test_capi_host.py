@@ -178,6 +178,11 @@ def test_run_with_a_workspace_argument_never_falls_back_to_the_registered_one():
         assert run(ctypes.byref(split), p, p, p, None, ws, nbytes) == code
 
 
+def test_stream_capturing_needs_no_gpu_for_the_default_stream():
+    assert g._lib.gemm_stream_capturing(None, None) == -1
+    assert g.gemm_stream_capturing(0) is False
+
+
 def test_run_rejects_bad_arguments_without_launching():
     cfg = g.gemm_select(512, 512, 512, g.GEMM_BF16)
     run = g._lib.gemm_run
