@@ -53,6 +53,7 @@ struct KernelArgs {
     // above are unused and each workgroup reads its group's record from this device table.
     const GroupRec *groups;
     int n_groups;
+    int chain;          // chained kernel only: tiles per workgroup
 };
 
 typedef short short4_t __attribute__((ext_vector_type(4)));
@@ -134,7 +135,8 @@ typedef float f32x16 __attribute__((ext_vector_type(16)));
 // (padding up to the leading dimension, which may be anything, NaN included).  Such chunks are fetched whole like
 // all others, and once the last slab has landed in LDS its workgroup clears those bytes there (see trim_last_slab);
 // results at the ragged edge of C are stored element by element.  Everything else is shared with the plain form.
-// ST_: 1 = the weight-streaming instantiation for grids of one tile row (see STREAMABLE_B in Tile).
+// ST_: 1 = the weight-streaming instantiation for grids of one tile row (see STREAMABLE_B in Tile), 2 = the tile of a
+// chained kernel (chained.hpp).
 template <int ES_, int BM_, int BN_, int BK_, int WM_, int WN_, int MI_, int NS_, int BL_, int FT_ = 0, int LF_ = 0, int RG_ = 0, int ST_ = 0>
 struct Tile {
     static constexpr int ES = ES_, BM = BM_, BN = BN_, BK = BK_, WM = WM_, WN = WN_, MI = MI_, NS = NS_, BL = BL_;
@@ -182,6 +184,9 @@ struct Tile {
     // scratch outside the loop with row-major B, none with K-contiguous): 1501x3003x2005 bf16 row-major 53.6 -> 44.3 us
     // (128x64) and 42.8 -> 33.5 (64x128), 2047x2049x1023 K-contiguous 21.3 -> 17.4; level where the tiles do not fill three slots.
     static constexpr int MIN_WAVES = (RG && ES == 2 && NW == 8 && NS == 2 && BM * BN == 128 * 64) ? 6 : (NT > 256 ? NT / 256 : 1);
+    // chained kernel: as many workgroups on a CU as the LDS has room for
+    static constexpr int CHAIN_WAVES = 160 * 1024 / LDS_BYTES * NW / 4;
+    static constexpr int CHAIN_RESIDENT = 160 * 1024 / LDS_BYTES * 32;      // on the 32 CUs of an XCD
     static constexpr int ACH = A_BYTES / 16, BCH = B_BYTES / 16;  // 16-byte chunks per slab
     static constexpr int CA = RA / 16, CB = RB / 16;              // chunks per row
     // a direct-to-LDS load instruction of one wave fills one 1 KB unit (64 lanes x 16 bytes)

@@ -11,6 +11,7 @@ struct VariantFns {
     LaunchFn launch;
     OccupancyFn occupancy;   // the runtime's resident-workgroups-per-CU figure for the instantiation
     int waves_m, waves_n, loop_form;
+    int resident;            // chained kernels: workgroups that an XCD holds at a time
 };
 // (variant index inside the translation unit's list, storage of B: 0 row-major K x N, 1 K-contiguous N x K,
 //  instantiation: a gemm_kernel_kind; of the pipelined ones launch is null for a tile that has none)
@@ -28,4 +29,8 @@ const VariantFns &kLaunchBf16_0(int, int, int),
     &kLaunchFp16_4(int, int, int),
     &kLaunchBf16_5(int, int, int),
     &kLaunchFp16_5(int, int, int);   // fp16 shares the bf16 variant lists
+
+// The chained kernel of a tile size (ragged: the instantiation that trims), whatever slab depth and wave grid the variant has;
+// launch is null for sizes that have none.
+const VariantFns &chained_bf16(int block_m, int block_n, int b_layout, int ragged), &chained_fp16(int, int, int, int), &chained_fp8(int, int, int, int);
 }  // namespace g355

@@ -174,6 +174,11 @@ int scratch_of_current_device(void **out)
 // which: a gemm_kernel_kind
 const VariantFns &launcher_of(int dtype, int id, int bl, int which)
 {
+    if (which == GEMM_KERNEL_CHAINED || which == GEMM_KERNEL_CHAINED_RAGGED) {
+        const Variant &v = variant_at(dtype, id);
+        const auto of = dtype == GEMM_FP16 ? chained_fp16 : dtype == GEMM_BF16 ? chained_bf16 : chained_fp8;
+        return of(v.block_m, v.block_n, bl, which == GEMM_KERNEL_CHAINED_RAGGED);
+    }
 #define G355_COUNT(...) +1
     constexpr int n_b0 = 0 G355_VARIANTS_BF16_0(G355_COUNT);
     constexpr int n_b1 = 0 G355_VARIANTS_BF16_1(G355_COUNT);
@@ -241,6 +246,46 @@ int kernel_of(int dtype, int id, int bl, bool ragged, bool streaming, int64_t sl
 }
 
 inline int64_t cdiv64(int64_t a, int64_t b) { return (a + b - 1) / b; }
+
+// Tiles per workgroup of a chained launch, 0: the launch is not chained.  `tiles`: of all problems of the launch, `slabs`:
+// 128-byte slabs of K.  A tile of few slabs is bound by the latency of its first loads and by its store stage, and a
+// chained workgroup has the next tile's loads in flight under both; with more slabs the loop counts, which is the plain
+// one of the K-loop forms.  Time of the chained kernel over the others by rounds (tiles over the workgroups the device
+// holds) and slabs, 16384x8192 (8 to 26 rounds) / 8192x4096 (2 to 6), worse layout of B:
+//   16-bit       1 slab       3           8           16          32
+//     256x256    1.01  .95    .94  .93    .95  .94   .99 1.09   1.11 1.13
+//     256x128    .71   .94    .80  .95    .89  .95   .94 1.05   1.04 1.09    (128x256: .68-1.05, .90-1.09)
+//     128x128    .85   .96    .91 1.00    .95 1.02   .96 1.04   1.00  .99    (K-contiguous B .76 .90, .85 .94, .90 .97, .94 .99)
+//     128x64     .71   .83    .83  .88    .90  .94   .96  .95   .95   .98    (64 slabs 1.10 .97; 64x128 alike)
+//     64x64      .55   .68    .69  .73    .84  .90   .91  .94  1.00  1.02    (1.2 rounds .86-.99, 16 slabs 1.02)
+//   fp8          1            4           8           16
+//     256x256    .85   .86    .94  .81    .98  .97   1.05 1.06   K-contiguous B; row-major 1.13 and more (scratch)
+//     256x128    .80  1.01    .88 1.04    .89 1.02   .95 1.08
+//     128x128    .90  1.08   1.02 1.08    .97 1.07   .99 1.07
+//     128x64     .66   .78    .83  .85    .90  .93   .94  .99
+//     64x64      .73   .90    .88  .90    .97  .99  1.00 1.03   (2 to 3 rounds: 1.11 at one slab)
+// The ragged kernels lie within 0.03 of these (no 256x256: its registers spill).
+int64_t chain_of(const Variant &v, int dtype, int bl, int64_t tiles, int64_t slabs, int resident)
+{
+    constexpr int64_t kXcds = 8;      // the chip's, whatever descriptor the selector works with
+    const int64_t slots = kXcds * resident;
+    const int size = v.block_m * v.block_n;
+    const bool many = tiles >= 8 * slots;
+    int64_t most;                     // slabs up to which it pays
+    if (dtype != GEMM_FP8_E4M3)
+        most = size == 256 * 256 ? 8 : size == 256 * 128 ? (many ? 16 : 8) : size == 128 * 128 ? (many ? 16 : bl ? 8 : 2) : size == 128 * 64 ? 32 : 16;
+    else
+        most = size == 256 * 256 ? 8 : size > 128 * 64 ? (many ? 16 : 0) : size == 128 * 64 ? 16 : tiles >= 4 * slots ? 8 : 0;
+    // (the larger tiles from three rounds on: with two, every tile would be dealt out at the start, and beside another
+    // stream's kernel that holds eight CUs 8192x4096x256 with 256x256 tiles takes 46 us instead of 36)
+    const bool enough = size >= 128 * 128 ? tiles >= 3 * slots : size == 64 * 64 ? 4 * tiles >= 5 * slots : tiles >= 2 * slots;
+    if (!enough || slabs > most)
+        return 0;
+    // Half of the tiles are left to the dispatcher, which balances what other work holds CUs; beyond eight tiles nothing is
+    // gained (65536x2048x128, 128x128 tiles, 16 rounds, at 2 / 4 / 8 / 16 tiles: 90 86 85 85 us).
+    const int64_t rounds = cdiv64(tiles, slots);
+    return rounds <= 3 ? 2 : std::min<int64_t>(8, rounds / 2);
+}
 }  // namespace
 
 extern "C" int gemm_set_workspace(void *dev_ptr, size_t bytes)
@@ -263,6 +308,7 @@ extern "C" int gemm_set_workspace(void *dev_ptr, size_t bytes)
 struct Launch {
     SkPlan sk;                       // workers == 0 unless stream-K
     int64_t kps, tiles_m, tiles_n;   // K elements per workgroup, tiles
+    int chain;                       // tiles per workgroup of the chained kernels
     int kind;                        // gemm_kernel_kind
 };
 
@@ -336,6 +382,17 @@ static int plan_launch(const gemm_cfg *cfg, bool aligned, Launch *out)
     // K slabs a workgroup walks: its slice of K, or a Stream-K worker's share where no tile is whole
     const int64_t slabs = (sk.workers > 0 && sk.dp_tiles == 0) ? sk.iters / sk.workers : kps / v.block_k;
     out->kind = kernel_of(dtype, cfg->kernel_id, cfg->b_layout, ragged, streaming, slabs);
+    out->chain = 0;
+    // (beta = 0 only: the chained store stage does not read C; a tile's rows of C are addressed with 32-bit offsets)
+    const int chained = ragged ? GEMM_KERNEL_CHAINED_RAGGED : GEMM_KERNEL_CHAINED;
+    if (!streaming && cfg->split_k == 1 && !cfg->stream_k && cfg->beta == 0.f && (int64_t)v.block_m * cfg->ldc * 2 < lim &&
+        tiles_m * tiles_n * cfg->batch < lim) {
+        const VariantFns &fns = launcher_of(dtype, cfg->kernel_id, cfg->b_layout, chained);
+        if (fns.launch)
+            out->chain = (int)chain_of(v, dtype, cfg->b_layout, tiles_m * tiles_n * cfg->batch, cdiv64(cfg->K * es, 128), fns.resident);
+        if (out->chain)
+            out->kind = chained;
+    }
     out->kps = kps;
     out->tiles_m = tiles_m;
     out->tiles_n = tiles_n;
@@ -399,6 +456,16 @@ static int run_impl(const gemm_cfg *cfg, const void *A, const void *B, void *C, 
     a.stride_c = cfg->batch > 1 ? cfg->stride_c : 0;
     a.groups = nullptr;
     a.n_groups = 0;
+    a.chain = p.chain;
+    if (p.chain) {
+        // The workgroups of an XCD walk its tiles abreast.  Where two of their steps cover a band of the rasterisation, a band
+        // twice as high halves how often new rows of A come from beyond the L2, which takes longest beside the stores
+        // (65536x2048x128: 128x128 tiles 84 -> 78 us, 256x256 76 -> 73; wider grids lose up to a fifth, and so do batches,
+        // whose B changes too: 32 x 2048x2048x128 96 -> 110).
+        const int resident = launcher_of(cfg->dtype, cfg->kernel_id, cfg->b_layout, p.kind).resident;
+        if (a.batch == 1 && p.tiles_n * a.group_m <= 2 * resident)
+            a.group_m = (int)std::min<int64_t>(2 * a.group_m, p.tiles_m);
+    }
 
     hipStream_t stream = (hipStream_t)hip_stream;
     const int f16 = (cfg->dtype == GEMM_FP16) ? 1 : 0;
