@@ -2,7 +2,8 @@
 with the kernel chosen analytically for the shape (Section V-C: selection costs microseconds and
 is cached per shape, no tuning run).  A thin convenience layer over `binding`: it looks up or
 makes the cfg, keeps one workspace tensor per stream and launches; every step of the computation
-runs in libgemm355.so.  Calls on several streams and from several threads need no order among
+runs in libgemm355.so.  A call whose plan is known and needs no workspace goes the short way of a
+compiled extension; all others, mistakes included, the general way below.  Calls on several streams and from several threads need no order among
 themselves.  (Graphs captured on one stream share its workspace: replays of two of them are to
 be ordered.)
 
@@ -15,6 +16,7 @@ import threading
 
 import torch
 
+from . import _fastcall
 from . import binding as g
 
 _DTYPES = {torch.bfloat16: g.GEMM_BF16, torch.float16: g.GEMM_FP16}
@@ -112,6 +114,21 @@ def _workspace_for(need, device, stream):
 def matmul(A, B, out=None, alpha=1.0, beta=0.0, b_k_contiguous=False, stream=None):
     """out = alpha * A @ B + beta * out.  A: (M, K) row-major; B: (K, N) row-major, or (N, K)
     row-major with b_k_contiguous=True.  bf16 / fp8 inputs give a bf16 result, fp16 gives fp16."""
+    result = _fastcall.matmul(A, B, out, alpha, beta, b_k_contiguous, stream)
+    return result if result is not None else _matmul_general(A, B, out, alpha, beta, b_k_contiguous, stream)
+
+
+def _fast_plan(*key):
+    """For the short way: the pick, its key in the memo, the address of the plan's cfg and its workspace size."""
+    base = select(*key[:5])
+    plan = _plan(base, key)
+    return base, key[:5], ctypes.addressof(plan.cfg), plan.need
+
+
+_fastcall.init(ctypes.cast(g._lib.gemm_run, ctypes.c_void_p).value, ctypes.sizeof(g.gemm_cfg), _fast_plan, g._check, globals())
+
+
+def _matmul_general(A, B, out, alpha, beta, b_k_contiguous, stream):
     a_dtype, device = A.dtype, A.device
     dtype = _DTYPES.get(a_dtype)
     if dtype is None or B.dtype != a_dtype:

@@ -16,6 +16,8 @@ HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 HIP_FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Xclang", "-target-feature", "-Xclang",
              "-packed-fp32-ops", "-Wno-unused-command-line-argument"]
 HOST_FLAGS = ["-O2", "-std=c++17", "-fPIC", "-Wall", "-Wextra"]
+EXT_SRC = os.path.join(PKG, "pyext", "fastcall.cpp")
+EXT = os.path.join(PKG, "_fastcall.so")
 
 
 def _sources():
@@ -46,6 +48,28 @@ def _compile(src, force, obj_dir=None, defines=()):
     return obj, True
 
 
+def build_extension(force=False):
+    """The Python extension of api.matmul's short way, against the installed torch."""
+    header = os.path.join(PKG, "..", "include", "gemm.h")
+    if not force and os.path.exists(EXT) and os.path.getmtime(EXT) >= max(os.path.getmtime(EXT_SRC), os.path.getmtime(header)):
+        return EXT
+    import sysconfig
+
+    import torch
+    root = os.path.dirname(torch.__file__)
+    tmp = EXT + ".%d.tmp" % os.getpid()
+    cmd = (["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-D__HIP_PLATFORM_AMD__",
+            "-D_GLIBCXX_USE_CXX11_ABI=%d" % torch.compiled_with_cxx11_abi(), "-isystem", os.path.join(root, "include"), "-isystem",
+            os.path.join(root, "include", "torch", "csrc", "api", "include"), "-isystem", sysconfig.get_paths()["include"], "-isystem",
+            os.path.join(os.path.dirname(os.path.dirname(HIPCC)), "include"), EXT_SRC, "-o", tmp, "-L" + os.path.join(root, "lib")] +
+           ["-l" + x for x in ("c10", "c10_hip", "torch_cpu", "torch", "torch_python")])
+    r = subprocess.run(cmd, capture_output=True, text=True)
+    if r.returncode != 0:
+        raise RuntimeError("extension build failed: %s\n%s" % (" ".join(cmd), r.stderr))
+    os.replace(tmp, EXT)
+    return EXT
+
+
 def build(force=False, jobs=8, out=None, defines=()):
     """out / defines: build another library (always from scratch, objects beside it) with extra
     -D options for the kernels; the in-tree library is the default."""
@@ -55,7 +79,10 @@ def build(force=False, jobs=8, out=None, defines=()):
     os.makedirs(obj_dir, exist_ok=True)
     hip, host = _sources()
     with ThreadPoolExecutor(max_workers=jobs) as ex:
+        extension = None if out else ex.submit(build_extension, force)
         res = list(ex.map(lambda s: _compile(s, force, obj_dir, defines), hip + host))
+    if extension is not None:
+        extension.result()
     objs = [o for o, _ in res]
     if force or any(changed for _, changed in res) or not os.path.exists(lib):
         tmp = lib + ".%d.tmp" % os.getpid()

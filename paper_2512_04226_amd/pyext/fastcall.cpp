@@ -1,0 +1,211 @@
+// The short way of `api.matmul`: a call on two plain CUDA tensors whose plan is known and needs no workspace, without Python
+// objects per argument.  What it does not recognise (subclasses, modes, transforms, other devices, mistakes in the
+// arguments) it leaves to the general way by returning None before anything has been done.
+//
+// Host time of a call (512 x 512 x 512 bf16, whose kernel takes 4.4 us): the general way 7.7 us, this one 4.6, or 4.0 into a
+// given out; with alpha != 1 8.6 and 4.7, with a ragged N 8.8 and 5.1.
+#define PY_SSIZE_T_CLEAN
+#include <Python.h>
+
+#include <ATen/PythonTorchFunctionTLS.h>
+#include <ATen/ops/empty.h>
+#include <c10/core/impl/TorchDispatchModeTLS.h>
+#include <c10/hip/HIPFunctions.h>
+#include <c10/hip/HIPStream.h>
+#include <torch/csrc/Exceptions.h>
+#include <torch/csrc/autograd/python_variable.h>
+
+#include <cstring>
+#include <unordered_map>
+
+#include "../../include/gemm.h"
+
+namespace {
+typedef int (*RunFn)(const gemm_cfg *, const void *, const void *, void *, void *);
+RunFn run_fn = nullptr;
+PyObject *make_plan = nullptr;    // api._fast_plan
+PyObject *check_status = nullptr; // binding._check
+PyObject *api_dict = nullptr;     // the module's namespace: holds the memo of picks
+
+struct Key {
+    int64_t v[8];      // M, N, K, dtype, B's layout, lda, ldb, ldc
+    bool operator==(const Key &o) const { return !std::memcmp(v, o.v, sizeof(v)); }
+};
+struct KeyHash {
+    size_t operator()(const Key &k) const
+    {
+        uint64_t h = 0x9e3779b97f4a7c15ull;
+        for (int64_t x : k.v)
+            h = (h ^ (uint64_t)x) * 0xff51afd7ed558ccdull, h ^= h >> 32;
+        return (size_t)h;
+    }
+};
+struct Plan {
+    PyObject *pick_key, *base;   // the plan holds while the memo of picks holds `base` under `pick_key`
+    gemm_cfg cfg;
+    bool short_way;              // no workspace
+};
+constexpr size_t kMaxPlans = 4096;     // a program with more shapes than this starts over
+std::unordered_map<Key, Plan, KeyHash> plans;   // (guarded by the interpreter lock)
+
+// The plan of a call; nullptr with or without a Python error set: the general way.
+const Plan *plan_of(const Key &key)
+{
+    static PyObject *const memo_name = PyUnicode_InternFromString("_cfg_cache");
+    PyObject *const memo = PyDict_GetItemWithError(api_dict, memo_name);
+    if (!memo || !PyDict_CheckExact(memo))
+        return nullptr;
+    auto it = plans.find(key);
+    if (it != plans.end()) {
+        if (PyDict_GetItemWithError(memo, it->second.pick_key) == it->second.base)
+            return &it->second;
+        Py_DECREF(it->second.pick_key);
+        Py_DECREF(it->second.base);
+        plans.erase(it);
+    }
+    PyObject *const r = PyObject_CallFunction(make_plan, "LLLLLLLL", (long long)key.v[0], (long long)key.v[1], (long long)key.v[2],
+                                              (long long)key.v[3], (long long)key.v[4], (long long)key.v[5], (long long)key.v[6],
+                                              (long long)key.v[7]);
+    if (!r)
+        return nullptr;
+    PyObject *base, *pick_key;
+    unsigned long long address, need;
+    if (!PyArg_ParseTuple(r, "OOKK", &base, &pick_key, &address, &need)) {
+        Py_DECREF(r);
+        return nullptr;
+    }
+    if (plans.size() >= kMaxPlans) {
+        for (auto &p : plans) {
+            Py_DECREF(p.second.pick_key);
+            Py_DECREF(p.second.base);
+        }
+        plans.clear();
+    }
+    Plan p;
+    p.pick_key = pick_key;
+    p.base = base;
+    Py_INCREF(pick_key);
+    Py_INCREF(base);
+    std::memcpy(&p.cfg, (const void *)(uintptr_t)address, sizeof(p.cfg));
+    p.short_way = need == 0;
+    Py_DECREF(r);
+    return &(plans[key] = p);
+}
+
+// A tensor that is nothing but memory on a GPU: no wrapper of a transform, no lazy bit.
+inline bool plain(const at::Tensor &t)
+{
+    constexpr c10::DispatchKeySet known = c10::DispatchKeySet({c10::DispatchKey::CUDA, c10::DispatchKey::ADInplaceOrView}) |
+                                          c10::autograd_dispatch_keyset_with_ADInplaceOrView | c10::autocast_dispatch_keyset;
+    // (the difference of two key sets keeps the backend's bit: what counts is that no functionality is left)
+    return t.is_cuda() && t.layout() == at::kStrided && t.has_storage() &&
+           (t.key_set() - known).highestFunctionalityKey() == c10::DispatchKey::Undefined;
+}
+
+PyObject *matmul(PyObject *, PyObject *const *args, Py_ssize_t n)
+{
+    HANDLE_TH_ERRORS
+    // A, B, out, alpha, beta, b_k_contiguous, stream
+    if (n != 7 || !THPVariable_CheckExact(args[0]) || !THPVariable_CheckExact(args[1]) || !PyFloat_CheckExact(args[3]) ||
+        !PyFloat_CheckExact(args[4]) || !PyBool_Check(args[5]) || args[6] != Py_None ||
+        (args[2] != Py_None && !THPVariable_CheckExact(args[2])) || at::impl::torch_function_mode_enabled() ||
+        c10::impl::dispatch_mode_enabled())
+        Py_RETURN_NONE;
+    const at::Tensor &A = THPVariable_Unpack(args[0]), &B = THPVariable_Unpack(args[1]);
+    if (!plain(A) || !plain(B) || A.dim() != 2 || B.dim() != 2 || A.scalar_type() != B.scalar_type() || A.device() != B.device())
+        Py_RETURN_NONE;
+    int64_t dtype;
+    switch (A.scalar_type()) {
+    case at::kBFloat16: dtype = GEMM_BF16; break;
+    case at::kHalf: dtype = GEMM_FP16; break;
+    case at::kFloat8_e4m3fn: dtype = GEMM_FP8_E4M3; break;
+    default: Py_RETURN_NONE;
+    }
+    const bool kc = args[5] == Py_True;
+    const int64_t M = A.size(0), K = A.size(1), N = B.size(kc ? 0 : 1);
+    const double alpha = PyFloat_AS_DOUBLE(args[3]), beta = PyFloat_AS_DOUBLE(args[4]);
+    if (A.stride(1) != 1 || B.stride(1) != 1 || B.size(kc ? 1 : 0) != K || c10::hip::current_device() != A.device().index())
+        Py_RETURN_NONE;
+    const auto out_type = dtype == GEMM_FP16 ? at::kHalf : at::kBFloat16;
+    int64_t ldc = (N + 7) / 8 * 8;
+    if (args[2] != Py_None) {
+        const at::Tensor &out = THPVariable_Unpack(args[2]);
+        if (!plain(out) || out.dim() != 2 || out.size(0) != M || out.size(1) != N || out.scalar_type() != out_type ||
+            out.stride(1) != 1 || out.device() != A.device())
+            Py_RETURN_NONE;
+        ldc = out.stride(0);
+    } else if (beta != 0.0) {
+        Py_RETURN_NONE;
+    }
+    const Plan *const plan = plan_of({{M, N, K, dtype, kc, A.stride(0), B.stride(0), ldc}});
+    if (!plan) {
+        if (!PyErr_Occurred())
+            Py_RETURN_NONE;
+        PyErr_Clear();        // (the general way meets the same error and raises it)
+        Py_RETURN_NONE;
+    }
+    if (!plan->short_way)
+        Py_RETURN_NONE;
+    gemm_cfg cfg = plan->cfg;
+    cfg.alpha = (float)alpha;
+    cfg.beta = (float)beta;
+    PyObject *result;
+    void *c;
+    if (args[2] != Py_None) {
+        c = THPVariable_Unpack(args[2]).data_ptr();
+        result = args[2];
+        Py_INCREF(result);
+    } else {
+        // rows of C start on 16-byte boundaries: a ragged N gets a padded row stride (the result is a view)
+        at::Tensor out = at::empty({M, ldc}, at::TensorOptions().dtype(out_type).device(A.device()));
+        if (ldc != N)
+            out = out.narrow(1, 0, N);
+        c = out.data_ptr();
+        result = THPVariable_Wrap(std::move(out));
+    }
+    const void *const a = A.data_ptr(), *const b = B.data_ptr();
+    void *const stream = (void *)c10::hip::getCurrentHIPStream(A.device().index()).stream();
+    int status;
+    Py_BEGIN_ALLOW_THREADS
+    status = run_fn(&cfg, a, b, c, stream);
+    Py_END_ALLOW_THREADS
+    if (status != GEMM_OK) {
+        Py_DECREF(result);
+        PyObject *const r = PyObject_CallFunction(check_status, "is", status, "gemm_run");
+        Py_XDECREF(r);
+        if (!r)
+            return nullptr;
+        Py_RETURN_NONE;
+    }
+    return result;
+    END_HANDLE_TH_ERRORS
+}
+
+// (address of gemm_run, sizeof(gemm_cfg) as the caller knows it, api._fast_plan, binding._check, the api module's namespace)
+PyObject *init(PyObject *, PyObject *args)
+{
+    unsigned long long address, cfg_bytes;
+    PyObject *plan, *check, *names;
+    if (!PyArg_ParseTuple(args, "KKOOO!", &address, &cfg_bytes, &plan, &check, &PyDict_Type, &names))
+        return nullptr;
+    if (cfg_bytes != sizeof(gemm_cfg)) {
+        PyErr_SetString(PyExc_ImportError, "_fastcall and the binding disagree about gemm_cfg: build again");
+        return nullptr;
+    }
+    Py_INCREF(plan);
+    Py_INCREF(check);
+    Py_INCREF(names);
+    run_fn = (RunFn)(uintptr_t)address;
+    make_plan = plan;
+    check_status = check;
+    api_dict = names;
+    Py_RETURN_NONE;
+}
+
+PyMethodDef methods[] = {{"matmul", (PyCFunction)(void (*)(void))matmul, METH_FASTCALL, nullptr},
+                         {"init", init, METH_VARARGS, nullptr},
+                         {nullptr, nullptr, 0, nullptr}};
+PyModuleDef module = {PyModuleDef_HEAD_INIT, "_fastcall", nullptr, -1, methods, nullptr, nullptr, nullptr, nullptr};
+}  // namespace
+
+PyMODINIT_FUNC PyInit__fastcall() { return PyModule_Create(&module); }
