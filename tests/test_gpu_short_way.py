@@ -1,0 +1,62 @@
+"""The compiled short way of `api.matmul` against the general one.  (In a file of its own: torch deals its streams
+round-robin onto four hardware queues, so a stream created before the tests of launches beside another stream
+can put those two on one queue.)"""
+import numpy as np
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+
+
+def test_the_short_way_of_matmul_gives_what_the_general_way_gives():
+    """Every form the short way accepts, against the general way bit for bit; every form it has to leave alone."""
+    from paper_2512_04226_amd import api, binding as g
+    gen = torch.Generator(device="cuda").manual_seed(8)
+
+    def operand(r, c, dtype, pad=0):
+        per16 = 16 if dtype == torch.float8_e4m3fn else 8
+        return torch.randn((r, -(-c // per16) * per16 + pad), device="cuda", generator=gen).to(dtype)[:, :c]
+
+    for dtype in (torch.bfloat16, torch.float16, torch.float8_e4m3fn):
+        for M, N, K, pad in ((96, 256, 128, 0), (1, 64, 64, 16), (33, 77, 101, 0), (50, 136, 64, 32)):
+            for kc in (False, True):
+                A, B = operand(M, K, dtype, pad), operand(*((N, K) if kc else (K, N)), dtype, pad)
+                out_dtype = torch.float16 if dtype == torch.float16 else torch.bfloat16
+                for alpha, beta, own in ((1.0, 0.0, False), (0.5, 0.0, False), (0.25, 0.0, True), (1.0, 0.5, True)):
+                    cin = torch.randn((M, -(-N // 8) * 8 + pad), device="cuda", generator=gen).to(out_dtype)
+                    outs = [cin.clone()[:, :N] if own else None for _ in range(2)]
+                    short = api._fastcall.matmul(A, B, outs[0], alpha, beta, kc, None)
+                    assert (short is not None) == (api.select(M, N, K, api._DTYPES[dtype], int(kc)).split_k == 1)
+                    if short is None:
+                        continue
+                    want = api._matmul_general(A, B, outs[1], alpha, beta, kc, None)
+                    assert short.dtype == want.dtype and short.shape == want.shape and short.stride() == want.stride()
+                    assert torch.equal(short.view(torch.int16), want.view(torch.int16))
+                    assert (short is outs[0]) == own and (short._is_view() == want._is_view())
+    A, B = operand(64, 64, torch.bfloat16), operand(64, 64, torch.bfloat16)
+    alike = (A, B, None, 1.0, 0.0, False, None)
+    assert api._fastcall.matmul(*alike) is not None
+
+    class Sub(torch.Tensor):
+        pass
+
+    for i, other in ((0, A.as_subclass(Sub)), (0, A.float()), (0, A.cpu()), (0, A[0]), (0, A.t()), (0, operand(64, 72, torch.bfloat16)),
+                     (2, torch.empty(64, 65, dtype=torch.bfloat16, device="cuda")), (2, torch.empty(64, 64, device="cuda")), (3, 1), (3, np.float64(1)),
+                     (3, 1j), (4, 0.5), (4, 0), (5, 1), (6, torch.cuda.current_stream())):
+        assert api._fastcall.matmul(*(alike[:i] + (other,) + alike[i + 1:])) is None, (i, type(other))
+    with torch.device("cuda"):         # a function mode
+        assert api._fastcall.matmul(*alike) is None
+    torch.func.vmap(lambda x: (torch.testing.assert_close(api._fastcall.matmul(x, B, None, 1.0, 0.0, False, None), None), x)[1])(A.expand(2, 64, 64).clone())
+    # a memo that was emptied: the next call asks for the pick again
+    base = api.select(64, 64, 64, g.GEMM_BF16)
+    api._cfg_cache.clear()
+    assert api._fastcall.matmul(*alike) is not None and api.select(64, 64, 64, g.GEMM_BF16) is not base
+    # launches go to the current stream of the tensors' device
+    s = torch.cuda.Stream()
+    s.wait_stream(torch.cuda.current_stream())
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=s):
+        C = api.matmul(A, B)
+    C.zero_()
+    graph.replay()
+    assert torch.equal(C, api.matmul(A, B))
