@@ -31,10 +31,13 @@ struct TileWalk {
     // false: nothing to do
     __device__ inline bool start(const KernelArgs &a, int resident)
     {
-        const int X = a.xcd_remap ? a.n_xcd : 1, items = a.tiles_m * a.tiles_n * a.batch;
-        const int x = (int)blockIdx.x % X, q = (int)blockIdx.x / X;     // the grid is a multiple of X
-        const int per = items / X, rem = items % X;
-        const int base = x * per + (x < rem ? x : rem), own = per + (x < rem ? 1 : 0);
+        int q = (int)blockIdx.x, base = 0, own = a.tiles_m * a.tiles_n * a.batch;
+        if (a.xcd_remap) {      // the grid is a multiple of n_xcd
+            q = fast_div(q, a.direct.xcds);
+            const int x = (int)blockIdx.x - q * a.n_xcd, rem = a.direct.rem_xcd;
+            base = x * a.direct.per_xcd + (x < rem ? x : rem);
+            own = a.direct.per_xcd + (x < rem ? 1 : 0);
+        }
         const int block = q / resident, first = block * resident * a.chain;   // the block's tiles start here
         const int size = (own - first < resident * a.chain) ? own - first : resident * a.chain;
         step = size < resident ? size : resident;
@@ -48,9 +51,8 @@ struct TileWalk {
     __device__ inline int count() const { return (end - item + step - 1) / step; }
     __device__ inline void locate(const KernelArgs &a)
     {
-        const int tiles = a.tiles_m * a.tiles_n;
-        bz = item / tiles;
-        logical_tile(a.tiles_m, a.tiles_n, a.group_m, item - bz * tiles, tm, tn);
+        bz = fast_div(item, a.direct.tiles);
+        direct_tile(a.direct, a.tiles_m, a.tiles_n, a.group_m, item - bz * (a.tiles_m * a.tiles_n), tm, tn);
     }
     __device__ inline void next(const KernelArgs &a)
     {

@@ -22,6 +22,7 @@
 #include <stdint.h>
 #include <type_traits>
 
+#include "fast_div.hpp"
 #include "grouped.hpp"
 #include "stream_k.hpp"
 
@@ -41,18 +42,24 @@ struct KernelArgs {
     int group_m;
     int xcd_remap;
     int n_xcd;
-    // Stream-K (sk.workers > 0, split_k == 1): workgroups [0, sk.workers) are stream-K workers,
-    // the rest compute the sk.dp_tiles data-parallel tiles; ws then holds the workers' partial
-    // tiles, [2 * workers][BLOCK_M][BLOCK_N] fp32.
-    SkPlan sk;
     // Strided batch: blockIdx.y selects the problem; strides in elements (the workspace of
     // problem b starts at b * split_k * M * N floats).
     long long stride_a, stride_b, stride_c;
     int batch;
-    // Grouped launch (n_groups > 0; split_k == 1, no stream-K, batch == 1): the problem fields
-    // above are unused and each workgroup reads its group's record from this device table.
-    const GroupRec *groups;
-    int n_groups;
+    int general;        // 1: Stream-K or grouped
+    union {
+        struct {
+            // Stream-K (sk.workers > 0, split_k == 1): workgroups [0, sk.workers) are stream-K workers,
+            // the rest compute the sk.dp_tiles data-parallel tiles; ws then holds the workers' partial
+            // tiles, [2 * workers][BLOCK_M][BLOCK_N] fp32.
+            SkPlan sk;
+            // Grouped launch (n_groups > 0; split_k == 1, no stream-K, batch == 1): the problem fields
+            // above are unused and each workgroup reads its group's record from this device table.
+            const GroupRec *groups;
+            int n_groups;
+        };
+        DirectPlan direct;   // general == 0
+    };
     int chain;          // chained kernel only: tiles per workgroup
 };
 
@@ -136,13 +143,20 @@ typedef float f32x16 __attribute__((ext_vector_type(16)));
 // all others, and once the last slab has landed in LDS its workgroup clears those bytes there (see trim_last_slab);
 // results at the ragged edge of C are stored element by element.  Everything else is shared with the plain form.
 // ST_: 1 = the weight-streaming instantiation for grids of one tile row (see STREAMABLE_B in Tile), 2 = the tile of a
-// chained kernel (chained.hpp).
+// chained kernel (chained.hpp), 3 and 4 = 0 and 1 for launches that are neither Stream-K nor grouped (see DIRECT in Tile).
 template <int ES_, int BM_, int BN_, int BK_, int WM_, int WN_, int MI_, int NS_, int BL_, int FT_ = 0, int LF_ = 0, int RG_ = 0, int ST_ = 0>
 struct Tile {
     static constexpr int ES = ES_, BM = BM_, BN = BN_, BK = BK_, WM = WM_, WN = WN_, MI = MI_, NS = NS_, BL = BL_;
     static constexpr int FT = FT_;
     static constexpr int RG = RG_;
     static constexpr int ST = ST_;
+    // Most launches give every workgroup one tile and K slice of one problem.  The kernels that can also be Stream-K workers
+    // or find their group in a table walk through 400 scalar instructions before their first load (the divisions of both,
+    // hoisted out of the loop over segments, and spilled scalars), most of a microsecond in which the workgroup has nothing
+    // in flight.  The instantiations without the two get there in about 150, with tile coordinates by multiplication
+    // (fast_div.hpp).  bf16, row-major B, before and after: 16x64x64 3.1 -> 2.3 us, 512^3 4.4 -> 3.7, 1024^3 7.7 -> 7.0,
+    // 2048x2048x512 8.9 -> 8.5, 1501x3003x2005 31.3 -> 30.0, 4096^3 94.1 -> 92.8; K-contiguous 8x4096x4096 9.8 -> 8.5.
+    static constexpr bool DIRECT = ST >= 3;
 #ifdef G355_FORCE_LOOP_FORM
     static constexpr int LF_ASKED = G355_FORCE_LOOP_FORM;
 #else
@@ -160,7 +174,7 @@ struct Tile {
     // few scalar instructions per slab; as a second copy of the loop inside one kernel either cost the other copy
     // registers or its schedule (128x128x64: a resident workgroup, or 2-12 % on every other shape), so the
     // streaming loop is a kernel of its own.
-    static constexpr bool STREAMABLE_B = ST == 1, STREAMABLE_A = false;
+    static constexpr bool STREAMABLE_B = ST == 1 || ST == 4, STREAMABLE_A = false;
     static constexpr int WTM = BM / WM, WTN = BN / WN;      // wave tile
     static constexpr int TM = WTM / MI, TN = WTN / MI;      // MFMA tiles per wave
     static constexpr int KI = (ES == 2) ? (MI == 32 ? 16 : 32) : (MI == 32 ? 64 : 128);  // MI_K
@@ -171,7 +185,7 @@ struct Tile {
     // 256x256 tile on four waves with 128-byte slab rows; a tile that has neither runs form 0 when the form is forced on
     // every tile
     static constexpr bool FITS6 = TN >= 3 && (KSTEPS * TN) % 4 == 0 && KSTEPS >= 2;
-    static constexpr bool FITS7 = BM == 256 && BN == 256 && WM == 2 && WN == 2 && BK * ES == 128 && KSTEPS == 2 && ST == 0;
+    static constexpr bool FITS7 = BM == 256 && BN == 256 && WM == 2 && WN == 2 && BK * ES == 128 && KSTEPS == 2 && (ST == 0 || ST == 3);
     static constexpr int LF = ((LF_ASKED == 6 && !FITS6) || (LF_ASKED == 7 && !FITS7)) ? 0 : LF_ASKED;
     static constexpr int RA = BK * ES;                      // bytes per A row in LDS
     static constexpr int RB = (BL == 0) ? BN * ES : BK * ES; // bytes per B row in LDS (a k row, or an n row when K-contiguous)
@@ -244,7 +258,7 @@ struct Tile {
 // and inside the tile grid the ids run column-major through bands of group_m tile rows,
 // so the workgroups that share an L2 at one time form a compact group_m x (CUs/group_m)
 // block of output tiles (the cache tile of Algorithms 5 and 6).
-// pid in [0, grid), grid = data-parallel tiles * split_k.
+// pid in [0, grid), grid = data-parallel tiles * split_k.  (direct_coords is the same with the divisors inverted on the host.)
 __device__ inline int logical_id(const KernelArgs &a, int pid, int grid)
 {
     if (!a.xcd_remap)
@@ -344,7 +358,8 @@ __global__ __launch_bounds__(T::NT, T::MIN_WAVES) void gemm_kernel(const KernelA
 
     // Work of this workgroup: one (tile, K slice) for a data-parallel or split-K launch, up to
     // two (tile, slab range) segments for a stream-K worker.
-    const bool sk_worker = (int)blockIdx.x < args.sk.workers;
+    const int sk_workers = T::DIRECT ? 0 : args.sk.workers;
+    const bool sk_worker = !T::DIRECT && (int)blockIdx.x < sk_workers;
     SkSegment segs[2];
     int nseg = 1;
     if (sk_worker)
@@ -355,9 +370,9 @@ __global__ __launch_bounds__(T::NT, T::MIN_WAVES) void gemm_kernel(const KernelA
     void *pC = args.C;
     int pM = args.M, pN = args.N, pK = args.K, plda = args.lda, pldb = args.ldb, pldc = args.ldc;
     int g_tm = 0, g_tn = 0;
-    const bool grouped = args.n_groups > 0;
+    const bool grouped = !T::DIRECT && args.n_groups > 0;
     // one tile row: B is read once; one tile column: A is read once (see Tile::STREAMABLE_*)
-    bool stream_a = args.tiles_n == 1, stream_b = T::ST == 1;
+    bool stream_a = args.tiles_n == 1, stream_b = T::STREAMABLE_B;
     if (grouped) {
         const int X = args.xcd_remap ? args.n_xcd : 1;
         const int x = (int)blockIdx.x % X, q = (int)blockIdx.x / X;
@@ -407,8 +422,14 @@ __global__ __launch_bounds__(T::NT, T::MIN_WAVES) void gemm_kernel(const KernelA
         k_len = pK;
         out_mode = 0;
     } else {
-        const int grid = (args.sk.workers > 0) ? args.sk.dp_tiles : args.tiles_m * args.tiles_n * args.split_k;
-        tile_coords(args, (int)blockIdx.x - args.sk.workers, grid, tm, tn, ks);
+        if constexpr (T::DIRECT) {
+            direct_coords(args.direct, args.tiles_m, args.tiles_n, args.split_k, args.group_m, args.n_xcd, args.xcd_remap, (int)blockIdx.x,
+                          tm, tn, ks);
+        } else {
+            // a data-parallel tile beside Stream-K workers (ks becomes 0; its division stays, as without it the 256x256
+            // tiles spill up to 28 bytes)
+            tile_coords(args, (int)blockIdx.x - sk_workers, args.sk.dp_tiles, tm, tn, ks);
+        }
         k_begin = ks * args.k_per_split;
         k_len = pK - k_begin;
         if (k_len > args.k_per_split)
@@ -455,14 +476,14 @@ __global__ __launch_bounds__(T::NT, T::MIN_WAVES) void gemm_kernel(const KernelA
     int a_kcol[T::A_LOADS], b_kcol[T::B_LOADS];
 #pragma unroll
     for (int i = 0; i < T::A_LOADS; ++i) {
-        const int c = (i * T::NW + wave) * 64 + lane;
+        const unsigned c = (i * T::NW + wave) * 64 + lane;     // (unsigned: its divisions are shifts)
         const int row = c / T::CA, lch = (c % T::CA) ^ T::a_key(row);
         a_kcol[i] = lch * (16 / ES);
         a_voff[i] = (unsigned)(row * plda * ES + lch * 16);
     }
 #pragma unroll
     for (int i = 0; i < T::B_LOADS; ++i) {
-        const int c = (i * T::NW + wave) * 64 + lane;
+        const unsigned c = (i * T::NW + wave) * 64 + lane;
         const int row = c / T::CB;
         if constexpr (T::BL == 0) {
             const int lbyte = ((c % T::CB) * 16) ^ T::b_key(row);

@@ -449,13 +449,16 @@ static int run_impl(const gemm_cfg *cfg, const void *A, const void *B, void *C, 
     a.group_m = (int)std::min<int64_t>(cfg->group_m, p.tiles_m);   // a band taller than the grid is the whole grid
     a.xcd_remap = cfg->xcd_remap ? 1 : 0;
     a.n_xcd = hw_current().n_xcd;
-    a.sk = sk;   // workers == 0 unless stream-K
     a.batch = cfg->batch;
     a.stride_a = cfg->batch > 1 ? cfg->stride_a : 0;
     a.stride_b = cfg->batch > 1 ? cfg->stride_b : 0;
     a.stride_c = cfg->batch > 1 ? cfg->stride_c : 0;
-    a.groups = nullptr;
-    a.n_groups = 0;
+    a.general = sk.workers > 0;
+    if (a.general) {
+        a.sk = sk;
+        a.groups = nullptr;
+        a.n_groups = 0;
+    }
     a.chain = p.chain;
     if (p.chain) {
         // The workgroups of an XCD walk its tiles abreast.  Where two of their steps cover a band of the rasterisation, a band
@@ -466,6 +469,8 @@ static int run_impl(const gemm_cfg *cfg, const void *A, const void *B, void *C, 
         if (a.batch == 1 && p.tiles_n * a.group_m <= 2 * resident)
             a.group_m = (int)std::min<int64_t>(2 * a.group_m, p.tiles_m);
     }
+    if (!a.general)
+        a.direct = direct_plan(a.tiles_m, a.tiles_n, p.chain ? a.batch : a.split_k, a.group_m, a.n_xcd);
 
     hipStream_t stream = (hipStream_t)hip_stream;
     const int f16 = (cfg->dtype == GEMM_FP16) ? 1 : 0;
@@ -633,6 +638,7 @@ extern "C" int gemm_run_grouped(const gemm_cfg *cfg, int n_groups, const gemm_gr
     a.xcd_remap = cfg->xcd_remap ? 1 : 0;
     a.n_xcd = hw.n_xcd;
     a.batch = 1;
+    a.general = 1;
     a.groups = (const GroupRec *)dev_table;
     a.n_groups = n_groups;
     if (launcher_of(cfg->dtype, cfg->kernel_id, cfg->b_layout, kind).launch(a, (hipStream_t)hip_stream) != hipSuccess) {
