@@ -368,7 +368,8 @@ typedef enum {
     GEMM_KERNEL_STREAMING = 2,        /* one tile row over weights larger than the memory-side cache */
     GEMM_KERNEL_PIPELINED = 3,        /* 256x256 tiles with 128-byte slab rows, twenty K slabs or more per workgroup */
     GEMM_KERNEL_PIPELINED_RAGGED = 4,
-    GEMM_KERNEL_CHAINED = 5,          /* many tiles of few K slabs: a workgroup computes several, one after the other */
+    GEMM_KERNEL_CHAINED = 5,          /* many tiles of few K slabs: a workgroup computes several, one after the other
+                                         (named for a C that starts on a 128-byte boundary) */
     GEMM_KERNEL_CHAINED_RAGGED = 6
 } gemm_kernel_kind;
 int gemm_launched_kernel(const gemm_cfg *cfg, int n_groups, const gemm_group_rec *host_table, int32_t out4[4]);

@@ -247,44 +247,102 @@ int kernel_of(int dtype, int id, int bl, bool ragged, bool streaming, int64_t sl
 
 inline int64_t cdiv64(int64_t a, int64_t b) { return (a + b - 1) / b; }
 
-// Tiles per workgroup of a chained launch, 0: the launch is not chained.  `tiles`: of all problems of the launch, `slabs`:
-// 128-byte slabs of K.  A tile of few slabs is bound by the latency of its first loads and by its store stage, and a
-// chained workgroup has the next tile's loads in flight under both; with more slabs the loop counts, which is the plain
-// one of the K-loop forms.  Time of the chained kernel over the others by rounds (tiles over the workgroups the device
-// holds) and slabs, 16384x8192 (8 to 26 rounds) / 8192x4096 (2 to 6), worse layout of B:
-//   16-bit       1 slab       3           8           16          32
-//     256x256    1.01  .95    .94  .93    .95  .94   .99 1.09   1.11 1.13
-//     256x128    .71   .94    .80  .95    .89  .95   .94 1.05   1.04 1.09    (128x256: .68-1.05, .90-1.09)
-//     128x128    .85   .96    .91 1.00    .95 1.02   .96 1.04   1.00  .99    (K-contiguous B .76 .90, .85 .94, .90 .97, .94 .99)
-//     128x64     .71   .83    .83  .88    .90  .94   .96  .95   .95   .98    (64 slabs 1.10 .97; 64x128 alike)
-//     64x64      .55   .68    .69  .73    .84  .90   .91  .94  1.00  1.02    (1.2 rounds .86-.99, 16 slabs 1.02)
-//   fp8          1            4           8           16
-//     256x256    .85   .86    .94  .81    .98  .97   1.05 1.06   K-contiguous B; row-major 1.13 and more (scratch)
-//     256x128    .80  1.01    .88 1.04    .89 1.02   .95 1.08
-//     128x128    .90  1.08   1.02 1.08    .97 1.07   .99 1.07
-//     128x64     .66   .78    .83  .85    .90  .93   .94  .99
-//     64x64      .73   .90    .88  .90    .97  .99  1.00 1.03   (2 to 3 rounds: 1.11 at one slab)
-// The ragged kernels lie within 0.03 of these (no 256x256: its registers spill).
-int64_t chain_of(const Variant &v, int dtype, int bl, int64_t tiles, int64_t slabs, int resident)
+// Tiles per workgroup of a chained launch, 0: the launch is not chained.  `c_bits`: C's address and the distances in bytes of
+// its rows and problems, or-ed.  A tile of few slabs (128 bytes of K) is bound by the latency of its first loads and by its
+// store stage, and a chained workgroup has the next tile's loads in flight under both; with more slabs the loop counts, which
+// is the plain one of the K-loop forms.  Time of the chained kernel over the one that runs otherwise, by rounds (tiles over the
+// workgroups the device holds) and slabs, alone and beside another stream's kernel that holds eight CUs; rows of C on
+// 128-byte boundaries, mean of both layouts of B, of one problem with 32 tile columns, one with 4 and a batch of 256 tiles each:
+//   16-bit             1/4 slab    1          2           4          8          16
+//     256x256    4   1.05 1.21   .94 1.09   .90 1.04   .98 1.09   .99 1.13
+//                8    .91 1.13   .84 1.05   .86 1.05   .89 1.09   .93 1.12
+//               16    .90 1.02   .83  .95   .84  .92   .91  .97   .93 1.02
+//     256x128    4    .92 1.11   .93 1.11   .98 1.18   .98 1.17  1.03 1.23              (128x256 alike)
+//                8    .82  .97   .80  .96   .87 1.00   .91 1.09   .95 1.17  1.00 1.23
+//               16    .76  .83   .77  .85   .82  .90   .91  .99   .94 1.05  1.01 1.11
+//     128x128    4   1.03 1.08  1.03 1.09  1.04 1.09   .97 1.07   .95 1.02
+//                8    .84  .92   .85  .89   .87  .94   .94 1.00   .98 1.05  1.01 1.07
+//               16    .86  .88   .87  .85   .84  .86   .95  .94   .97  .97   .99 1.00
+//     128x64     4    .96 1.00   .96 1.00   .97  .99   .98 1.01  1.02 1.05  1.05 1.11   (64x128 alike)
+//                8    .86  .85   .87  .86   .90  .94   .91  .97   .98  .99  1.05 1.03
+//     64x64   1.25    .95  .99   .95  .99   .95  .96   .93  .92   .95  .96  1.00 1.01
+//                2    .86  .89   .85  .88   .85  .86   .86  .88  1.00  .95  1.09 1.03
+//                8    .66  .69   .71  .71   .79  .79   .80  .82   .90  .88   .97  .97
+//   fp8
+//     256x256    8    .95 1.09   .94 1.07   .94 1.08   .99 1.15  1.02 1.20   (K-contiguous B; the row-major one spills)
+//     256x128    8    .84  .97   .82  .94   .88 1.00   .92 1.08   .96 1.14  1.03 1.25
+//     128x128    8    .90  .96   .93  .95   .93  .99   .98 1.02  1.02 1.08  1.01 1.07   (one problem, 12 rounds: 1.02 at one slab)
+//     128x64     4    .89  .89   .90  .89   .90  .88   .96  .96  1.00 1.00
+//     64x64      4    .91  .95   .91  .94   .92  .93   .94  .95   .99 1.01
+// Among these, from four slabs on the large tiles gain less and lose more beside other work on one problem of 32 columns and
+// more (256x128 at 8 rounds of 8 slabs 1.07 and 1.28 against .92 and 1.11 with 4 columns): the other launch has their
+// panels in the L2.  A batch of problems of some hundred tiles and less gains most: the other launch deals every problem's tiles
+// to all XCDs, the chained walk gives an XCD whole problems (problems of 4 to 64 tiles, from two or three rounds on: .50 to .95).
+// Rows of C that start inside a 128-byte line: two tiles share a line, and the further apart in time they write it the more
+// often the memory behind the L2 gets it in two parts.  16 rounds at 4 and at 2 tiles per workgroup: 16-bit 128x128 one slab
+// 1.03 to 1.19 and .98 to 1.10, two to eight slabs .87 to .95 at both; fp8 128x128 1.00 to 1.29 and 1.00 to 1.19; 128x64 .86 to 1.08 and
+// .82 to 1.02 and 64x64 .67 to 1.05 and .74 to 1.03, of which rows on 64-byte boundaries are level; the wider tiles gain as with
+// whole lines, and so do the smaller ones while C fits well into the memory-side cache, where the parts meet (128x128 one slab,
+// up to 150 MB .79 to .97, from 200 MB 1.10 to 1.41), and batches (.78 to .98).
+// (The ragged kernels lie within 0.03 of these.)
+int64_t chain_of(const Variant &v, int dtype, int64_t tiles_m, int64_t tiles_n, int64_t batch, int64_t k_bytes, int64_t c_bytes, int resident,
+                 uint64_t c_bits)
 {
-    constexpr int64_t kXcds = 8;      // the chip's, whatever descriptor the selector works with
-    const int64_t slots = kXcds * resident;
+    constexpr int64_t kXcds = 8, kMemorySideCache = 256 << 20;      // the chip's, whatever descriptor the selector works with
+    const int64_t slots = kXcds * resident, slabs = cdiv64(k_bytes, 128), tiles = tiles_m * tiles_n * batch;
     const int size = v.block_m * v.block_n;
-    const bool many = tiles >= 8 * slots;
-    int64_t most;                     // slabs up to which it pays
-    if (dtype != GEMM_FP8_E4M3)
-        most = size == 256 * 256 ? 8 : size == 256 * 128 ? (many ? 16 : 8) : size == 128 * 128 ? (many ? 16 : bl ? 8 : 2) : size == 128 * 64 ? 32 : 16;
-    else
-        most = size == 256 * 256 ? 8 : size > 128 * 64 ? (many ? 16 : 0) : size == 128 * 64 ? 16 : tiles >= 4 * slots ? 8 : 0;
-    // (the larger tiles from three rounds on: with two, every tile would be dealt out at the start, and beside another
-    // stream's kernel that holds eight CUs 8192x4096x256 with 256x256 tiles takes 46 us instead of 36)
-    const bool enough = size >= 128 * 128 ? tiles >= 3 * slots : size == 64 * 64 ? 4 * tiles >= 5 * slots : tiles >= 2 * slots;
-    if (!enough || slabs > most)
+    const bool fp8 = dtype == GEMM_FP8_E4M3, thin = k_bytes < 64, lines = c_bits % 128 == 0;
+    // (the tiles with slabs of 64 bytes compute no half slab beyond K, a chained one does: 5320x10560x160, 2.5 slabs, 1.07)
+    const bool half = v.block_k * elem_bytes(dtype) < 128 && (k_bytes - 1) % 128 < 64;
+    const bool cached = c_bytes <= kMemorySideCache / 8 * 5;
+    const bool batched = batch > 1, small = batched && tiles_m * tiles_n <= 128, compact = batched || std::min(tiles_m, tiles_n) <= 8;
+    int64_t most = 0;                 // slabs up to which it pays
+    const auto from = [&](double rounds, int64_t limit) {
+        if ((double)tiles >= rounds * (double)slots)
+            most = std::max(most, limit);
+    };
+    if (size == 256 * 256) {
+        if (small)
+            from(3, fp8 ? 4 : 8);
+        else if (!fp8 && !thin && !half)
+            from(3, 4), from(compact ? 6 : 12, 8);
+    } else if (size == 256 * 128) {
+        if (fp8)
+            from(8, small ? 16 : batched ? 8 : compact ? 4 : 2);
+        else if (small)
+            from(3, 8), from(8, 16);
+        else
+            from(6, compact ? 8 : 2), from(8, 4);
+    } else if (size == 128 * 128) {
+        if (fp8)
+            from(8, batched ? 8 : 0);
+        else if (batched)
+            from(small ? (thin ? 6 : slabs < 2 ? 4 : 3) : 6, 8);
+        else if (lines)
+            from(8, 4);
+        else
+            from(5, cached ? 4 : 0), from(6, slabs >= 2 ? 8 : 0);
+    } else if (size == 128 * 64) {
+        if (small)
+            from(2, fp8 ? 16 : 32);
+        else if (batched)
+            from(lines ? 3 : 2, 2), from(fp8 ? 4 : 3, 8), from(6, 16);
+        else
+            from(lines ? 3 : 2, 2), from(fp8 ? 4 : 6, 4), from(6, fp8 && !compact ? 8 : 0);
+    } else {
+        from(fp8 ? 4 : 1.25, small ? (fp8 ? 8 : 16) : fp8 && batched ? 8 : 4);
+        from(3, fp8 ? 0 : batched ? 16 : 8);
+    }
+    if (slabs > most)
         return 0;
-    // Half of the tiles are left to the dispatcher, which balances what other work holds CUs; beyond eight tiles nothing is
-    // gained (65536x2048x128, 128x128 tiles, 16 rounds, at 2 / 4 / 8 / 16 tiles: 90 86 85 85 us).
-    const int64_t rounds = cdiv64(tiles, slots);
-    return rounds <= 3 ? 2 : std::min<int64_t>(8, rounds / 2);
+    // From four rounds on half of the tiles or more are left to the dispatcher, which balances what other work holds CUs; at three a
+    // third, and at two or less every tile is dealt out at the start, which only the smallest tiles bear (the 64x64 lines above,
+    // beside; a CU holds five of them).  Beyond four tiles per workgroup little is gained alone, and a large tile, of which a CU
+    // holds one at a time, loses beside other work (16 rounds at 2 / 4 / 8 tiles, alone and beside a kernel that holds eight CUs:
+    // 256x256 one slab .88 .83 .82 and 1.00 .95 1.06, 256x128 four slabs .98 .91 .88 and 1.03 .99 1.09).
+    return slabs < 2 && c_bits % (size < 128 * 128 ? 64 : 128) && !cached && !batched && size <= 128 * 128
+               ? 2
+               : std::max<int64_t>(2, std::min<int64_t>(4, cdiv64(tiles, slots) / 2));
 }
 }  // namespace
 
@@ -312,8 +370,9 @@ struct Launch {
     int kind;                        // gemm_kernel_kind
 };
 
-// Checks a cfg (aligned: whether its operands start on 16-byte boundaries) and plans its launch.
-static int plan_launch(const gemm_cfg *cfg, bool aligned, Launch *out)
+// Checks a cfg (aligned: whether its operands start on 16-byte boundaries) and plans its launch.  c_address: where C starts
+// (0: on a boundary of any kind).
+static int plan_launch(const gemm_cfg *cfg, bool aligned, uintptr_t c_address, Launch *out)
 {
     if (cfg->abi_version != GEMM_ABI_VERSION)
         return GEMM_ERR_ABI;
@@ -388,8 +447,10 @@ static int plan_launch(const gemm_cfg *cfg, bool aligned, Launch *out)
     if (!streaming && cfg->split_k == 1 && !cfg->stream_k && cfg->beta == 0.f && (int64_t)v.block_m * cfg->ldc * 2 < lim &&
         tiles_m * tiles_n * cfg->batch < lim) {
         const VariantFns &fns = launcher_of(dtype, cfg->kernel_id, cfg->b_layout, chained);
+        const uint64_t c_bits = c_address | (uint64_t)cfg->ldc * 2 | (cfg->batch > 1 ? (uint64_t)cfg->stride_c * 2 : 0);
         if (fns.launch)
-            out->chain = (int)chain_of(v, dtype, cfg->b_layout, tiles_m * tiles_n * cfg->batch, cdiv64(cfg->K * es, 128), fns.resident);
+            out->chain = (int)chain_of(v, dtype, tiles_m, tiles_n, cfg->batch, cfg->K * es, 2 * cfg->M * cfg->N * cfg->batch,
+                                      fns.resident, c_bits);
         if (out->chain)
             out->kind = chained;
     }
@@ -407,7 +468,7 @@ static int run_impl(const gemm_cfg *cfg, const void *A, const void *B, void *C, 
     if (!cfg || !A || !B || !C)
         return GEMM_ERR_NULL;
     Launch p;
-    const int rc = plan_launch(cfg, !(((uintptr_t)A | (uintptr_t)B | (uintptr_t)C) & 15), &p);
+    const int rc = plan_launch(cfg, !(((uintptr_t)A | (uintptr_t)B | (uintptr_t)C) & 15), (uintptr_t)C, &p);
     if (rc)
         return rc;
     const SkPlan &sk = p.sk;
@@ -660,7 +721,7 @@ extern "C" int gemm_launched_kernel(const gemm_cfg *cfg, int n_groups, const gem
             rc = plan_grouped(cfg, n_groups, host_table, &total, &kind);
     } else {
         Launch p;
-        rc = plan_launch(cfg, true, &p);
+        rc = plan_launch(cfg, true, 0, &p);
         if (!rc)
             kind = p.kind;
     }

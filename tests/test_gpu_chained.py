@@ -116,3 +116,23 @@ def test_where_a_launch_is_chained():
     for M, N, K, kind in ((4096, 12288 - 256, 256, "plain"), (4096, 12288, 9 * 64, "plain"), (4096, 12288, 20 * 64, "pipelined")):
         d = cfg(M, N, K)
         assert g.gemm_launched_kernel(d)[0] == kind, (M, N, K)
+
+
+# What the chained kernel takes longer for: fp8 128x128 tiles of one problem; 128x128 tiles of one slab whose rows of C start
+# inside a line, with more of them than the memory-side cache holds (1.2 to 1.5 times); a fp8 256x256 tile; 2.5 slabs of a tile
+# that computes half slabs; the larger tiles from eight slabs on; two rounds of them.
+@pytest.mark.parametrize("batch,M,N,K,dtype,bl", [
+    (1, 15544, 10064, 32, E4M3, 0), (1, 30152, 10128, 16, E4M3, 1), (1, 22456, 5520, 32, BF16, 0), (1, 18936, 6256, 16, FP16, 1),
+    (1, 11384, 22016, 848, E4M3, 1), (1, 5320, 10560, 160, FP16, 1), (1, 5272, 10320, 480, BF16, 0), (1, 2448, 14336, 112, BF16, 1)])
+def test_launches_that_chaining_slows_are_not_chained(batch, M, N, K, dtype, bl):
+    from paper_2512_04226_amd import binding as g
+    c = g.gemm_select_batched(M, N, K, batch, dtype, bl)
+    assert g.gemm_launched_kernel(c)[0] in ("plain", "ragged"), c.describe()
+
+
+@pytest.mark.parametrize("batch,M,N,K,dtype,bl", [
+    (32, 2048, 2048, 128, BF16, 1), (1, 65536, 2048, 128, BF16, 0), (142, 400, 1056, 64, BF16, 1), (1, 16408, 2960, 64, BF16, 1)])
+def test_launches_that_chaining_speeds_up_are_chained(batch, M, N, K, dtype, bl):
+    from paper_2512_04226_amd import binding as g
+    c = g.gemm_select_batched(M, N, K, batch, dtype, bl)
+    assert g.gemm_launched_kernel(c)[0] == "chained", c.describe()
