@@ -474,16 +474,20 @@ __global__ __launch_bounds__(T::NT, T::MIN_WAVES) void gemm_kernel(const KernelA
 
     unsigned a_voff[T::A_LOADS], b_voff[T::B_LOADS];
     int a_kcol[T::A_LOADS], b_kcol[T::B_LOADS];
+    // Unsigned, the divisions are shifts.  In the kernels that can also be grouped, loop form 0 comes out with the slower
+    // schedule of the two then, the others with the faster (grouped lists, int / unsigned: form 0 64x256x64 200.2 / 202.2 us,
+    // 64x128x128 55.3 / 55.7, 64x64x128 25.5 / 25.6; form 2 376.9 / 375.3, form 5 17.84 / 17.20, form 7 89.4 / 88.5).
+    typedef typename std::conditional<T::DIRECT || T::LF != 0, unsigned, int>::type chunk_t;
 #pragma unroll
     for (int i = 0; i < T::A_LOADS; ++i) {
-        const unsigned c = (i * T::NW + wave) * 64 + lane;     // (unsigned: its divisions are shifts)
+        const chunk_t c = (i * T::NW + wave) * 64 + lane;
         const int row = c / T::CA, lch = (c % T::CA) ^ T::a_key(row);
         a_kcol[i] = lch * (16 / ES);
         a_voff[i] = (unsigned)(row * plda * ES + lch * 16);
     }
 #pragma unroll
     for (int i = 0; i < T::B_LOADS; ++i) {
-        const unsigned c = (i * T::NW + wave) * 64 + lane;
+        const chunk_t c = (i * T::NW + wave) * 64 + lane;
         const int row = c / T::CB;
         if constexpr (T::BL == 0) {
             const int lbyte = ((c % T::CB) * 16) ^ T::b_key(row);
