@@ -48,7 +48,7 @@ struct Plan {
 constexpr size_t kMaxPlans = 4096;     // a program with more shapes than this starts over
 std::unordered_map<Key, Plan, KeyHash> plans;   // (guarded by the interpreter lock)
 
-// The plan of a call; nullptr with or without a Python error set: the general way.
+// The plan of a call; nullptr: a Python error if one is set, else the general way.
 const Plan *plan_of(const Key &key)
 {
     static PyObject *const memo_name = PyUnicode_InternFromString("_cfg_cache");
@@ -138,13 +138,10 @@ PyObject *matmul(PyObject *, PyObject *const *args, Py_ssize_t n)
         Py_RETURN_NONE;
     }
     const Plan *const plan = plan_of({{M, N, K, dtype, kc, A.stride(0), B.stride(0), ldc}});
-    if (!plan) {
-        if (!PyErr_Occurred())
-            Py_RETURN_NONE;
-        PyErr_Clear();        // (the general way meets the same error and raises it)
-        Py_RETURN_NONE;
-    }
-    if (!plan->short_way)
+    // (what making the plan raises, the general way would have raised: its own checks of the arguments have passed above)
+    if (!plan && PyErr_Occurred())
+        return nullptr;
+    if (!plan || !plan->short_way)
         Py_RETURN_NONE;
     gemm_cfg cfg = plan->cfg;
     cfg.alpha = (float)alpha;

@@ -60,3 +60,19 @@ def test_the_short_way_of_matmul_gives_what_the_general_way_gives():
     C.zero_()
     graph.replay()
     assert torch.equal(C, api.matmul(A, B))
+
+
+def _operands(M, N, K):
+    return tuple(torch.randn(s, device="cuda").bfloat16() for s in ((M, K), (K, N)))
+
+
+@pytest.mark.parametrize("error", [KeyboardInterrupt, TimeoutError])
+def test_what_a_signal_raises_while_a_plan_is_made_is_not_lost(error, monkeypatch):
+    """The plan of a new shape is made by Python code, where a signal's handler may raise: whatever the kind, once."""
+    from paper_2512_04226_amd import api
+    A, B = _operands(40, 72, 48)
+    once, select = [error("a handler's")], api.select
+    monkeypatch.setattr(api, "select", lambda *key: select(*key) if not once else (_ for _ in ()).throw(once.pop()))
+    with pytest.raises(error):
+        api.matmul(A, B)
+    assert api._fastcall.matmul(A, B, None, 1.0, 0.0, False, None) is not None
