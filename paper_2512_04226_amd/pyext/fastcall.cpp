@@ -46,50 +46,71 @@ struct Plan {
     bool short_way;              // no workspace
 };
 constexpr size_t kMaxPlans = 4096;     // a program with more shapes than this starts over
-std::unordered_map<Key, Plan, KeyHash> plans;   // (guarded by the interpreter lock)
+typedef std::unordered_map<Key, Plan, KeyHash> Plans;
+Plans plans;                           // (guarded by the interpreter lock)
 
-// The plan of a call; nullptr: a Python error if one is set, else the general way.
-const Plan *plan_of(const Key &key)
+// Gives up the plans of a map that is no longer `plans` (releasing an object may run code that comes back here).
+void release(const Plans &gone)
+{
+    for (const auto &p : gone) {
+        Py_DECREF(p.second.pick_key);
+        Py_DECREF(p.second.base);
+    }
+}
+void drop(Plans::iterator it)
+{
+    Plans gone;
+    gone.insert(*it);
+    plans.erase(it);
+    release(gone);
+}
+
+// The plan of a call: its cfg and whether it goes the short way; false: a Python error if one is set, else the general way.
+bool plan_of(const Key &key, gemm_cfg *cfg, bool *short_way)
 {
     static PyObject *const memo_name = PyUnicode_InternFromString("_cfg_cache");
     PyObject *const memo = PyDict_GetItemWithError(api_dict, memo_name);
     if (!memo || !PyDict_CheckExact(memo))
-        return nullptr;
+        return false;
     auto it = plans.find(key);
     if (it != plans.end()) {
-        if (PyDict_GetItemWithError(memo, it->second.pick_key) == it->second.base)
-            return &it->second;
-        Py_DECREF(it->second.pick_key);
-        Py_DECREF(it->second.base);
-        plans.erase(it);
+        if (PyDict_GetItemWithError(memo, it->second.pick_key) == it->second.base) {
+            *cfg = it->second.cfg;
+            *short_way = it->second.short_way;
+            return true;
+        }
+        drop(it);
     }
     PyObject *const r = PyObject_CallFunction(make_plan, "LLLLLLLL", (long long)key.v[0], (long long)key.v[1], (long long)key.v[2],
                                               (long long)key.v[3], (long long)key.v[4], (long long)key.v[5], (long long)key.v[6],
                                               (long long)key.v[7]);
     if (!r)
-        return nullptr;
-    PyObject *base, *pick_key;
-    unsigned long long address, need;
-    if (!PyArg_ParseTuple(r, "OOKK", &base, &pick_key, &address, &need)) {
-        Py_DECREF(r);
-        return nullptr;
-    }
-    if (plans.size() >= kMaxPlans) {
-        for (auto &p : plans) {
-            Py_DECREF(p.second.pick_key);
-            Py_DECREF(p.second.base);
-        }
-        plans.clear();
-    }
+        return false;
     Plan p;
-    p.pick_key = pick_key;
-    p.base = base;
-    Py_INCREF(pick_key);
-    Py_INCREF(base);
+    unsigned long long address, need;
+    if (!PyArg_ParseTuple(r, "OOKK", &p.base, &p.pick_key, &address, &need)) {
+        Py_DECREF(r);
+        return false;
+    }
+    Py_INCREF(p.pick_key);
+    Py_INCREF(p.base);
     std::memcpy(&p.cfg, (const void *)(uintptr_t)address, sizeof(p.cfg));
     p.short_way = need == 0;
+    *cfg = p.cfg;
+    *short_way = p.short_way;
     Py_DECREF(r);
-    return &(plans[key] = p);
+    it = plans.find(key);     // (another thread, or a call from inside this one, may have made it meanwhile)
+    if (it != plans.end())
+        drop(it);
+    Plans gone;
+    if (plans.size() >= kMaxPlans)
+        gone.swap(plans);
+    if (!plans.emplace(key, p).second) {
+        Py_DECREF(p.pick_key);
+        Py_DECREF(p.base);
+    }
+    release(gone);
+    return true;
 }
 
 // A tensor that is nothing but memory on a GPU: no wrapper of a transform, no lazy bit.
@@ -137,13 +158,13 @@ PyObject *matmul(PyObject *, PyObject *const *args, Py_ssize_t n)
     } else if (beta != 0.0) {
         Py_RETURN_NONE;
     }
-    const Plan *const plan = plan_of({{M, N, K, dtype, kc, A.stride(0), B.stride(0), ldc}});
+    gemm_cfg cfg;
+    bool short_way = false;
     // (what making the plan raises, the general way would have raised: its own checks of the arguments have passed above)
-    if (!plan && PyErr_Occurred())
+    if (!plan_of({{M, N, K, dtype, kc, A.stride(0), B.stride(0), ldc}}, &cfg, &short_way) && PyErr_Occurred())
         return nullptr;
-    if (!plan || !plan->short_way)
+    if (!short_way)
         Py_RETURN_NONE;
-    gemm_cfg cfg = plan->cfg;
     cfg.alpha = (float)alpha;
     cfg.beta = (float)beta;
     PyObject *result;

@@ -76,3 +76,25 @@ def test_what_a_signal_raises_while_a_plan_is_made_is_not_lost(error, monkeypatc
     with pytest.raises(error):
         api.matmul(A, B)
     assert api._fastcall.matmul(A, B, None, 1.0, 0.0, False, None) is not None
+
+
+def test_a_plan_made_twice_at_once_keeps_no_reference_of_the_first(monkeypatch):
+    """A call that comes in while the same shape's plan is being made (another thread's, or one from a finaliser)."""
+    import weakref
+    from paper_2512_04226_amd import api
+    A, B = _operands(56, 88, 64)
+    first, select = [True], api.select
+
+    def interrupted(*key):
+        if first:
+            first.clear()
+            assert api._fastcall.matmul(A, B, None, 1.0, 0.0, False, None) is not None
+        return select(*key)
+    monkeypatch.setattr(api, "select", interrupted)
+    api.matmul(A, B)
+    pick = weakref.ref(select(56, 88, 64, 0))
+    assert pick() is not None
+    api._cfg_cache.clear()
+    api._plans.clear()
+    api.matmul(A, B)                   # (meets the emptied memo and drops what it held of the old pick)
+    assert pick() is None
