@@ -113,6 +113,12 @@ bool plan_of(const Key &key, gemm_cfg *cfg, bool *short_way)
     return true;
 }
 
+// Without the interpreter lock: the launch, and the result's allocation, which may wait for the device.
+struct Unlocked {
+    PyThreadState *const state = PyEval_SaveThread();
+    ~Unlocked() { PyEval_RestoreThread(state); }
+};
+
 // A tensor that is nothing but memory on a GPU: no wrapper of a transform, no lazy bit.
 inline bool plain(const at::Tensor &t)
 {
@@ -167,35 +173,34 @@ PyObject *matmul(PyObject *, PyObject *const *args, Py_ssize_t n)
         Py_RETURN_NONE;
     cfg.alpha = (float)alpha;
     cfg.beta = (float)beta;
-    PyObject *result;
-    void *c;
-    if (args[2] != Py_None) {
-        c = THPVariable_Unpack(args[2]).data_ptr();
-        result = args[2];
-        Py_INCREF(result);
-    } else {
-        // rows of C start on 16-byte boundaries: a ragged N gets a padded row stride (the result is a view)
-        at::Tensor out = at::empty({M, ldc}, at::TensorOptions().dtype(out_type).device(A.device()));
-        if (ldc != N)
-            out = out.narrow(1, 0, N);
-        c = out.data_ptr();
-        result = THPVariable_Wrap(std::move(out));
-    }
-    const void *const a = A.data_ptr(), *const b = B.data_ptr();
-    void *const stream = (void *)c10::hip::getCurrentHIPStream(A.device().index()).stream();
+    const bool own = args[2] == Py_None;
+    at::Tensor made;
     int status;
-    Py_BEGIN_ALLOW_THREADS
-    status = run_fn(&cfg, a, b, c, stream);
-    Py_END_ALLOW_THREADS
+    {
+        Unlocked unlocked;
+        void *c;
+        if (own) {
+            // rows of C start on 16-byte boundaries: a ragged N gets a padded row stride (the result is a view)
+            made = at::empty({M, ldc}, at::TensorOptions().dtype(out_type).device(A.device()));
+            if (ldc != N)
+                made = made.narrow(1, 0, N);
+            c = made.data_ptr();
+        } else {
+            c = THPVariable_Unpack(args[2]).data_ptr();
+        }
+        status = run_fn(&cfg, A.data_ptr(), B.data_ptr(), c, (void *)c10::hip::getCurrentHIPStream(A.device().index()).stream());
+    }
     if (status != GEMM_OK) {
-        Py_DECREF(result);
         PyObject *const r = PyObject_CallFunction(check_status, "is", status, "gemm_run");
         Py_XDECREF(r);
         if (!r)
             return nullptr;
         Py_RETURN_NONE;
     }
-    return result;
+    if (own)
+        return THPVariable_Wrap(std::move(made));
+    Py_INCREF(args[2]);
+    return args[2];
     END_HANDLE_TH_ERRORS
 }
 

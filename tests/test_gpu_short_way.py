@@ -98,3 +98,53 @@ def test_a_plan_made_twice_at_once_keeps_no_reference_of_the_first(monkeypatch):
     api._plans.clear()
     api.matmul(A, B)                   # (meets the emptied memo and drops what it held of the old pick)
     assert pick() is None
+
+
+def test_other_threads_run_while_a_result_is_allocated():
+    """The result's memory comes from cached blocks that have to be given back first, which waits for the device: half a
+    second of work, during which a Python thread has to go on counting."""
+    import threading
+    import time
+    from paper_2512_04226_amd import api
+    M, N = 76800, 4096                 # 600 MB
+    A, B = _operands(M, N, 16)
+    assert api.select(M, N, 16, 0).split_k == 1
+    api.matmul(A[:128], B)
+    torch.cuda.synchronize()
+    torch.cuda.empty_cache()
+    e0, e1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+    e0.record()
+    torch.cuda._sleep(1000000)
+    e1.record()
+    e1.synchronize()
+    cycles = int(500.0 / e0.elapsed_time(e1) * 1000000)
+    blocks = [torch.empty(512 << 20, dtype=torch.uint8, device="cuda") for _ in range(2)]
+    del blocks
+    total = torch.cuda.get_device_properties(0).total_memory
+    gaps, stop = [], threading.Event()
+
+    def count():
+        last = time.perf_counter()
+        while not stop.is_set():
+            time.sleep(0.001)
+            now = time.perf_counter()
+            gaps.append(now - last)
+            last = now
+    thread = threading.Thread(target=count)
+    torch.cuda.set_per_process_memory_fraction((torch.cuda.memory_reserved() + (64 << 20)) / total)
+    try:
+        torch.cuda._sleep(cycles)
+        thread.start()
+        t0 = time.perf_counter()
+        out = api.matmul(A, B)
+        took = time.perf_counter() - t0
+    finally:
+        stop.set()
+        thread.join()
+        torch.cuda.set_per_process_memory_fraction(1.0)
+    torch.cuda.synchronize()
+    assert out.shape == (M, N)
+    print("the call took %.3f s, the thread waited %.3f s at most" % (took, max(gaps)))
+    if took < 0.05:
+        pytest.skip("the allocator did not wait for the device")
+    assert max(gaps) < 0.5 * took, (max(gaps), took)
