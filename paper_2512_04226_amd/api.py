@@ -119,10 +119,11 @@ def matmul(A, B, out=None, alpha=1.0, beta=0.0, b_k_contiguous=False, stream=Non
 
 
 def _fast_plan(*key):
-    """For the short way: the pick, its key in the memo, the address of the plan's cfg and its workspace size."""
+    """For the short way: the pick, its key in the memo, the plan's cfg, that cfg's address and its workspace size.  (The cfg
+    itself, as another thread may empty the plans before its address is used.)"""
     base = select(*key[:5])
     plan = _plan(base, key)
-    return base, key[:5], ctypes.addressof(plan.cfg), plan.need
+    return base, key[:5], plan.cfg, ctypes.addressof(plan.cfg), plan.need
 
 
 _fastcall.init(ctypes.cast(g._lib.gemm_run, ctypes.c_void_p).value, ctypes.sizeof(g.gemm_cfg), _fast_plan, g._check, globals())

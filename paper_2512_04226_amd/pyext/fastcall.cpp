@@ -88,7 +88,8 @@ bool plan_of(const Key &key, gemm_cfg *cfg, bool *short_way)
         return false;
     Plan p;
     unsigned long long address, need;
-    if (!PyArg_ParseTuple(r, "OOKK", &p.base, &p.pick_key, &address, &need)) {
+    PyObject *cfg_object;     // (held by the result: the address stays good until it is released)
+    if (!PyArg_ParseTuple(r, "OOOKK", &p.base, &p.pick_key, &cfg_object, &address, &need)) {
         Py_DECREF(r);
         return false;
     }

@@ -220,3 +220,13 @@ def test_uniform128_shapes_follow_the_papers_recipe():
     assert len(s) == 192 and s == wl.uniform128_shapes()
     assert all(d % 128 == 0 and 128 <= d <= 8192 for shape in s for d in shape)
     assert len({d for shape in s for d in shape}) > 48          # spread over the 64 possible values
+
+
+def test_the_short_ways_plan_keeps_the_cfg_whose_address_it_gives(monkeypatch):
+    """Another thread that empties the plans while one is handed over must not free it: the cfg is part of the result."""
+    from paper_2512_04226_amd import api, binding as g
+    monkeypatch.setattr(api, "_plans", {})
+    given = api._fast_plan(96, 64, 128, g.GEMM_BF16, 0, 128, 64, 64)
+    api._plans.clear()
+    kept = [x for x in given if isinstance(x, g.gemm_cfg) and ctypes.addressof(x) in given]
+    assert len(kept) == 1 and kept[0].ldc == 64 and kept[0].M == 96
