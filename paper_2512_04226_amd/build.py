@@ -70,9 +70,10 @@ def build_extension(force=False):
     return EXT
 
 
-def build(force=False, jobs=8, out=None, defines=()):
+def build(force=False, jobs=8, out=None, defines=(), strict=False):
     """out / defines: build another library (always from scratch, objects beside it) with extra
-    -D options for the kernels; the in-tree library is the default."""
+    -D options for the kernels; the in-tree library is the default.  strict: an extension that cannot be
+    built is an error too (it needs torch's headers, which the library does not), else it is reported."""
     lib = os.path.abspath(out) if out else LIB
     obj_dir = lib + ".obj" if out else OBJ
     force = force or bool(out)
@@ -81,8 +82,6 @@ def build(force=False, jobs=8, out=None, defines=()):
     with ThreadPoolExecutor(max_workers=jobs) as ex:
         extension = None if out else ex.submit(build_extension, force)
         res = list(ex.map(lambda s: _compile(s, force, obj_dir, defines), hip + host))
-    if extension is not None:
-        extension.result()
     objs = [o for o, _ in res]
     if force or any(changed for _, changed in res) or not os.path.exists(lib):
         tmp = lib + ".%d.tmp" % os.getpid()
@@ -91,6 +90,13 @@ def build(force=False, jobs=8, out=None, defines=()):
         if r.returncode != 0:
             raise RuntimeError("link failed: %s\n%s" % (" ".join(cmd), r.stderr))
         os.replace(tmp, lib)
+    if extension is not None:
+        try:
+            extension.result()
+        except Exception as e:
+            if strict:
+                raise
+            print("the library is built, api.matmul's compiled short way is not (its calls go the general way): %s" % e, file=sys.stderr)
     return lib
 
 
