@@ -4,6 +4,7 @@ With --out LIB [-DNAME=VALUE ...] it builds a second library with extra kernel d
 somewhere else, e.g. the builds `calibrate.py --loop-forms` compares:
   python -m paper_2512_04226_amd.build --out /tmp/lf0.so -DG355_FORCE_LOOP_FORM=0"""
 import os
+import shutil
 import subprocess
 import sys
 from concurrent.futures import ThreadPoolExecutor
@@ -48,6 +49,16 @@ def _compile(src, force, obj_dir=None, defines=()):
     return obj, True
 
 
+def _hip_include():
+    """The headers beside the compiler, which HIPCC may name by a path, a link or a name on PATH."""
+    found = shutil.which(HIPCC) or HIPCC
+    for path in (found, os.path.realpath(found)):
+        include = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(path))), "include")
+        if os.path.exists(os.path.join(include, "hip", "hip_runtime.h")):
+            return include
+    return "/opt/rocm/include"
+
+
 def build_extension(force=False):
     """The Python extension of api.matmul's short way, against the installed torch."""
     header = os.path.join(PKG, "..", "include", "gemm.h")
@@ -61,7 +72,7 @@ def build_extension(force=False):
     cmd = (["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-D__HIP_PLATFORM_AMD__",
             "-D_GLIBCXX_USE_CXX11_ABI=%d" % torch.compiled_with_cxx11_abi(), "-isystem", os.path.join(root, "include"), "-isystem",
             os.path.join(root, "include", "torch", "csrc", "api", "include"), "-isystem", sysconfig.get_paths()["include"], "-isystem",
-            os.path.join(os.path.dirname(os.path.dirname(HIPCC)), "include"), EXT_SRC, "-o", tmp, "-L" + os.path.join(root, "lib")] +
+            _hip_include(), EXT_SRC, "-o", tmp, "-L" + os.path.join(root, "lib")] +
            ["-l" + x for x in ("c10", "c10_hip", "torch_cpu", "torch", "torch_python")])
     r = subprocess.run(cmd, capture_output=True, text=True)
     if r.returncode != 0:

@@ -32,3 +32,16 @@ def test_the_library_is_linked_where_the_extension_cannot_be_built(commands, mon
     assert "no torch here" in capsys.readouterr().err
     with pytest.raises(ImportError):
         b.build(force=True, strict=True)
+
+
+@pytest.mark.skipif(not os.path.exists("/opt/rocm/bin/hipcc"), reason="needs hipcc")
+@pytest.mark.parametrize("named", ["path", "name on PATH", "link"])
+def test_hip_headers_are_found_however_the_compiler_is_named(named, commands, monkeypatch, tmp_path):
+    if named == "link":
+        os.symlink("/opt/rocm/bin/hipcc", tmp_path / "hipcc")
+    monkeypatch.setenv("PATH", "/opt/rocm/bin", prepend=os.pathsep)
+    monkeypatch.setattr(b, "HIPCC", {"path": "/opt/rocm/bin/hipcc", "name on PATH": "hipcc", "link": str(tmp_path / "hipcc")}[named])
+    b.build_extension(force=True)
+    cmd = commands[-1]
+    includes = [cmd[i + 1] for i, a in enumerate(cmd) if a == "-isystem"]
+    assert any(os.path.exists(os.path.join(d, "hip", "hip_runtime.h")) for d in includes), includes
