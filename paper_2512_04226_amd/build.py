@@ -7,6 +7,7 @@ import os
 import shutil
 import subprocess
 import sys
+import sysconfig
 from concurrent.futures import ThreadPoolExecutor
 
 PKG = os.path.dirname(os.path.abspath(__file__))
@@ -18,7 +19,7 @@ HIP_FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Xclang", "
              "-packed-fp32-ops", "-Wno-unused-command-line-argument"]
 HOST_FLAGS = ["-O2", "-std=c++17", "-fPIC", "-Wall", "-Wextra"]
 EXT_SRC = os.path.join(PKG, "pyext", "fastcall.cpp")
-EXT = os.path.join(PKG, "_fastcall.so")
+EXT = os.path.join(PKG, "_fastcall" + sysconfig.get_config_var("EXT_SUFFIX"))   # (another Python does not take it for its own)
 
 
 def _sources():
@@ -60,24 +61,28 @@ def _hip_include():
 
 
 def build_extension(force=False):
-    """The Python extension of api.matmul's short way, against the installed torch."""
-    header = os.path.join(PKG, "..", "include", "gemm.h")
-    if not force and os.path.exists(EXT) and os.path.getmtime(EXT) >= max(os.path.getmtime(EXT_SRC), os.path.getmtime(header)):
-        return EXT
-    import sysconfig
-
+    """The Python extension of api.matmul's short way, against the installed torch, whose version it carries.  Built again when
+    its source, the header or the command (torch, Python, paths) is another."""
     import torch
     root = os.path.dirname(torch.__file__)
     tmp = EXT + ".%d.tmp" % os.getpid()
-    cmd = (["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-D__HIP_PLATFORM_AMD__",
+    cmd = (["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-D__HIP_PLATFORM_AMD__", '-DFASTCALL_TORCH="%s"' % torch.__version__,
             "-D_GLIBCXX_USE_CXX11_ABI=%d" % torch.compiled_with_cxx11_abi(), "-isystem", os.path.join(root, "include"), "-isystem",
             os.path.join(root, "include", "torch", "csrc", "api", "include"), "-isystem", sysconfig.get_paths()["include"], "-isystem",
             _hip_include(), EXT_SRC, "-o", tmp, "-L" + os.path.join(root, "lib")] +
            ["-l" + x for x in ("c10", "c10_hip", "torch_cpu", "torch", "torch_python")])
+    header = os.path.join(PKG, "..", "include", "gemm.h")
+    stamp, same = os.path.join(OBJ, "fastcall.cmd"), " ".join(cmd).replace(tmp, EXT)
+    if (not force and os.path.exists(EXT) and os.path.exists(stamp) and open(stamp).read() == same and
+            os.path.getmtime(EXT) >= max(os.path.getmtime(EXT_SRC), os.path.getmtime(header))):
+        return EXT
     r = subprocess.run(cmd, capture_output=True, text=True)
     if r.returncode != 0:
         raise RuntimeError("extension build failed: %s\n%s" % (" ".join(cmd), r.stderr))
     os.replace(tmp, EXT)
+    os.makedirs(OBJ, exist_ok=True)
+    with open(stamp, "w") as f:
+        f.write(same)
     return EXT
 
 

@@ -45,3 +45,25 @@ def test_hip_headers_are_found_however_the_compiler_is_named(named, commands, mo
     cmd = commands[-1]
     includes = [cmd[i + 1] for i, a in enumerate(cmd) if a == "-isystem"]
     assert any(os.path.exists(os.path.join(d, "hip", "hip_runtime.h")) for d in includes), includes
+
+
+def test_the_extension_is_built_again_for_another_torch(commands, monkeypatch):
+    import torch
+    b.build_extension()
+    assert len(commands) == 1
+    b.build_extension()
+    assert len(commands) == 1                   # nothing changed
+    monkeypatch.setattr(torch, "__version__", "9.9.9+other")
+    b.build_extension()
+    assert len(commands) == 2 and any("9.9.9+other" in a for a in commands[-1])
+    b.build_extension()
+    assert len(commands) == 2
+
+
+def test_the_extensions_name_and_contents_say_what_it_is_built_for():
+    import importlib.machinery
+
+    import torch
+    from paper_2512_04226_amd import _fastcall
+    assert b.EXT.endswith(importlib.machinery.EXTENSION_SUFFIXES[0])        # the suffix with Python's own tag
+    assert _fastcall.__file__ == b.EXT and _fastcall.torch_version == torch.__version__
