@@ -3,7 +3,9 @@ with the kernel chosen analytically for the shape (Section V-C: selection costs 
 is cached per shape, no tuning run).  A thin convenience layer over `binding`: it looks up or
 makes the cfg, keeps one workspace tensor per stream and launches; every step of the computation
 runs in libgemm355.so.  A call whose plan is known and needs no workspace goes the short way of a
-compiled extension; all others, mistakes included, the general way below.  Calls on several streams and from several threads need no order among
+compiled extension; all others, mistakes included, the general way below, and every call where the
+extension is not built for this torch and Python (a warning says so; a call then takes some 3 us
+more of host time).  Calls on several streams and from several threads need no order among
 themselves.  (Graphs captured on one stream share its workspace: replays of two of them are to
 be ordered.)
 
@@ -13,11 +15,19 @@ be ordered.)
 import collections
 import ctypes
 import threading
+import warnings
 
 import torch
 
-from . import _fastcall
-from . import binding as g
+from . import binding as g     # (first: it says how to build what is missing)
+
+try:
+    from . import _fastcall
+    if _fastcall.torch_version != torch.__version__:
+        raise ImportError("built for torch %s, this is %s" % (_fastcall.torch_version, torch.__version__))
+except (ImportError, AttributeError) as e:
+    _fastcall = None
+    warnings.warn("no compiled short way of matmul, run `python -m paper_2512_04226_amd.build`: %s" % e, RuntimeWarning)
 
 _DTYPES = {torch.bfloat16: g.GEMM_BF16, torch.float16: g.GEMM_FP16}
 if hasattr(torch, "float8_e4m3fn"):
@@ -114,7 +124,7 @@ def _workspace_for(need, device, stream):
 def matmul(A, B, out=None, alpha=1.0, beta=0.0, b_k_contiguous=False, stream=None):
     """out = alpha * A @ B + beta * out.  A: (M, K) row-major; B: (K, N) row-major, or (N, K)
     row-major with b_k_contiguous=True.  bf16 / fp8 inputs give a bf16 result, fp16 gives fp16."""
-    result = _fastcall.matmul(A, B, out, alpha, beta, b_k_contiguous, stream)
+    result = _short_way(A, B, out, alpha, beta, b_k_contiguous, stream)
     return result if result is not None else _matmul_general(A, B, out, alpha, beta, b_k_contiguous, stream)
 
 
@@ -126,7 +136,12 @@ def _fast_plan(*key):
     return base, key[:5], plan.cfg, ctypes.addressof(plan.cfg), plan.need
 
 
-_fastcall.init(ctypes.cast(g._lib.gemm_run, ctypes.c_void_p).value, ctypes.sizeof(g.gemm_cfg), _fast_plan, g._check, globals())
+if _fastcall is not None:
+    _short_way = _fastcall.matmul
+    _fastcall.init(ctypes.cast(g._lib.gemm_run, ctypes.c_void_p).value, ctypes.sizeof(g.gemm_cfg), _fast_plan, g._check, globals())
+else:
+    def _short_way(*call):
+        return None
 
 
 def _matmul_general(A, B, out, alpha, beta, b_k_contiguous, stream):

@@ -1,10 +1,14 @@
 """The build around the compilers: what a missing or older part of the machine costs, with the compilers stood in for."""
 import os
+import shutil
 import subprocess
+import sys
 
 import pytest
 
 from paper_2512_04226_amd import build as b
+
+ROOT = os.path.dirname(b.PKG)
 
 
 @pytest.fixture
@@ -67,3 +71,35 @@ def test_the_extensions_name_and_contents_say_what_it_is_built_for():
     from paper_2512_04226_amd import _fastcall
     assert b.EXT.endswith(importlib.machinery.EXTENSION_SUFFIXES[0])        # the suffix with Python's own tag
     assert _fastcall.__file__ == b.EXT and _fastcall.torch_version == torch.__version__
+
+
+@pytest.mark.parametrize("before", [
+    "sys.modules['paper_2512_04226_amd._fastcall'] = None",                     # not there, or of another Python
+    "torch.__version__ += '.other'",                                             # of another torch
+    "sys.modules['paper_2512_04226_amd._fastcall'] = types.ModuleType('old')"])  # of before it had a version
+def test_calls_go_the_general_way_without_the_extension(before):
+    code = """
+import sys, types, warnings, torch
+%s
+with warnings.catch_warnings(record=True) as seen:
+    warnings.simplefilter("always")
+    from paper_2512_04226_amd import api
+assert [w for w in seen if "paper_2512_04226_amd.build" in str(w.message)]
+try:
+    api.matmul(torch.zeros(8, 8, dtype=torch.bfloat16), torch.zeros(8, 8, dtype=torch.bfloat16))
+except ValueError as e:
+    assert "one GPU" in str(e)
+else:
+    raise AssertionError("refused nothing")
+""" % before
+    run = subprocess.run([sys.executable, "-c", code], capture_output=True, text=True, cwd=ROOT)
+    assert run.returncode == 0, run.stderr
+
+
+def test_an_unbuilt_tree_says_how_to_build_it(tmp_path):
+    pkg = tmp_path / "paper_2512_04226_amd"
+    pkg.mkdir()
+    for name in ("__init__.py", "api.py", "binding.py"):
+        shutil.copy(os.path.join(b.PKG, name), pkg / name)
+    run = subprocess.run([sys.executable, "-c", "from paper_2512_04226_amd import api"], capture_output=True, text=True, cwd=tmp_path)
+    assert run.returncode != 0 and "libgemm355.so is not built: run" in run.stderr, run.stderr
