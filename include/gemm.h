@@ -350,15 +350,17 @@ int gemm_predict(const gemm_cfg *cfg, gemm_prediction *out);
 /*
  * Diagnostic (needs the GPU, not part of selection): the number of workgroups of compiled variant
  * `variant` in [0, gemm_variant_count(dtype)) that the HIP runtime reports as resident on one CU
- * (registers, LDS and wave slots of the actual code object) -- what gemm_prediction.occupancy
- * estimates on the host.  Errors: GEMM_ERR_NULL, GEMM_ERR_DTYPE, GEMM_ERR_INDEX,
+ * (registers, LDS and wave slots of the actual code object, of the kernel that a launch of one problem
+ * or a strided batch runs; Stream-K and grouped launches run one with the code of both, which can hold one
+ * workgroup fewer) -- what gemm_prediction.occupancy estimates on the host.  Errors: GEMM_ERR_NULL, GEMM_ERR_DTYPE, GEMM_ERR_INDEX,
  * GEMM_ERR_CFG_ILLEGAL (b_layout), GEMM_ERR_HIP.
  */
 int gemm_variant_occupancy(int dtype, int variant, int b_layout, int *blocks_per_cu);
 
 /*
  * Which instantiation of the variant gemm_run (n_groups = 0, host_table ignored) or gemm_run_grouped (the planned records)
- * launches for cfg, by the rule they use themselves.  Host only.  out4 = {instantiation, waves along m, waves along n,
+ * launches for cfg, by the rule they use themselves (each is compiled twice, with and without the code of Stream-K and
+ * grouped launches, and runs as the one or the other).  Host only.  out4 = {instantiation, waves along m, waves along n,
  * K-loop form}.  Errors: as gemm_run for a cfg that it refuses before it looks at pointers; GEMM_ERR_CFG_ILLEGAL when cfg
  * and n_groups do not belong together.
  */

@@ -32,3 +32,13 @@ def test_model_occupancy_equals_the_runtimes_for_the_compiled_variants():
     # the headline tiles hold one workgroup per CU, the 128 x 128 two-stage tile two
     sq = g.gemm_select(8192, 8192, 8192, g.GEMM_BF16)
     assert g.gemm_variant_occupancy(g.GEMM_BF16, sq.kernel_id) == g.gemm_predict(sq).occupancy == 1
+
+
+def test_the_occupancy_is_that_of_the_kernel_a_launch_runs():
+    """The 16-bit 64x128x64 tile of two stages on eight waves, row-major B: the kernel that a launch of one problem runs leaves
+    room for the three workgroups that the LDS has room for; the one that can also be grouped takes registers for two."""
+    from paper_2512_04226_amd import binding as g
+    for dtype in (g.GEMM_BF16, g.GEMM_FP16):
+        cfg = next(c for c in (g.gemm_cfg_at(i, 4096, 4096, 4096, dtype) for i in range(g.gemm_cfg_count(dtype)))
+                   if c is not None and (c.block_m, c.block_n, c.block_k, c.waves_m, c.waves_n, c.stages) == (64, 128, 64, 2, 4, 2))
+        assert g.gemm_variant_occupancy(dtype, cfg.kernel_id) == 3
