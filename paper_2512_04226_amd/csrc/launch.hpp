@@ -9,7 +9,7 @@ typedef hipError_t (*LaunchFn)(const KernelArgs &, hipStream_t);
 typedef hipError_t (*OccupancyFn)(int *blocks_per_cu);
 struct VariantFns {
     LaunchFn launch;
-    OccupancyFn occupancy;   // the runtime's resident-workgroups-per-CU figure for the instantiation
+    OccupancyFn occupancy;   // the runtime's resident-workgroups-per-CU figure for the instantiation (chained ones: none)
     int waves_m, waves_n, loop_form;
     int resident;            // chained kernels: workgroups that an XCD holds at a time
 };

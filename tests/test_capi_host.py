@@ -3,9 +3,12 @@ returns the documented codes, the selector is deterministic and needs no GPU."""
 import ctypes
 import os
 import re
+import subprocess
+import sys
 import threading
 
 import pytest
+import torch
 
 from paper_2512_04226_amd import binding as g
 
@@ -275,3 +278,16 @@ def test_run_rejects_operand_windows_of_2_gib_and_more():
     bad = kc.copy(); bad.ldb = (1 << 31) // (2 * bad.block_n)
     assert run(ctypes.byref(bad), p, p, p, None) == -2
     assert g._lib.gemm_select((1 << 30) + 8, 8, 8, 0, ctypes.byref(cfg)) == -2
+
+
+@pytest.mark.skipif(torch.cuda.is_available(), reason="the launches have to fail for want of a GPU")
+@pytest.mark.parametrize("M,N,K,chained", [(512, 512, 512, False), (65536, 2048, 128, True)])
+def test_a_launch_that_fails_says_which_kernel(M, N, K, chained):
+    """With GEMM355_DEBUG set, on standard error; the call returns GEMM_ERR_HIP."""
+    code = ("import ctypes\nfrom paper_2512_04226_amd import binding as g\n"
+            "c = g.gemm_select(%d, %d, %d, g.GEMM_BF16)\nassert (g.gemm_launched_kernel(c)[0] == 'chained') == %s\n"
+            "print(g._lib.gemm_run(ctypes.byref(c), 4096, 4096, 4096, None), c.block_m, c.block_n)" % (M, N, K, chained))
+    run = subprocess.run([sys.executable, "-c", code], capture_output=True, text=True, cwd=ROOT, env=dict(os.environ, GEMM355_DEBUG="1"))
+    assert run.returncode == 0, run.stderr
+    status, bm, bn = map(int, run.stdout.split())
+    assert status < 0 and "launch of %s%dx%dx" % ("chained " if chained else "", bm, bn) in run.stderr, (run.stdout, run.stderr)
