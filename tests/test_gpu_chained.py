@@ -19,10 +19,10 @@ def _padded(x, per16):
     return out
 
 
-def _problem(batch, M, N, K, dtype, bl, seed=3):
+def _problem(batch, M, N, K, dtype, bl, seed=3, alpha=1.0):
     gen = torch.Generator(device="cuda").manual_seed(seed)
     A, B = (torch.randint(-3, 4, s, device="cuda", generator=gen).float() for s in ((batch, M, K), (batch, K, N)))
-    ref = torch.bmm(A.double(), B.double()).to(torch.float16 if dtype == FP16 else torch.bfloat16)
+    ref = (alpha * torch.bmm(A.double(), B.double())).to(torch.float16 if dtype == FP16 else torch.bfloat16)
     per16 = 16 if dtype == E4M3 else 8
     B = B.transpose(1, 2).contiguous() if bl else B
     return _padded(A, per16).to(IN[dtype]), _padded(B, per16).to(IN[dtype]), ref
@@ -51,6 +51,11 @@ def _per_tile_size(g, M, N, K, batch, dtype, bl):
     return seen
 
 
+def _unchained_256(dtype, bl, ragged, slabs):
+    """The 256x256 tile has no ragged chained kernel, none for fp8 with row-major B, and in fp8 runs it up to four slabs."""
+    return {(256, 256)} if ragged or dtype == E4M3 and (bl == 0 or slabs > 4) else set()
+
+
 # (M, N): tiles with rows and columns missing at both ends; K: part of one slab, one slab, two, five and a rest -- with the
 # ring of two or three stages fewer slabs per tile than stages, as many and more
 @pytest.mark.gpu
@@ -60,7 +65,7 @@ def test_chained_bit_exact_on_a_batch(dtype, bl, slabs, short, ragged_n):
     from paper_2512_04226_amd import binding as g
     M, N, K = 200, 272 - ragged_n, slabs * SLAB[dtype] - short * (2 if dtype == E4M3 and short % 8 == 0 else 1)
     ragged = N % (16 if dtype == E4M3 else 8) or K % (16 if dtype == E4M3 else 8)
-    total = 0
+    chained = set()
     whole = None
     for size, slots in SLOTS.items():
         tiles = -(-M // size[0]) * -(-N // size[1])
@@ -77,20 +82,20 @@ def test_chained_bit_exact_on_a_batch(dtype, bl, slabs, short, ragged_n):
         A, B, ref = (x[:batch] for x in whole)
         out = _run(g, c, A, B, M, N, dtype)
         assert torch.equal(out, ref), (c.describe(), int((out != ref).sum()))
-        total += 1
-    assert total >= 5
+        chained.add(size)
+    assert chained == set(SLOTS) - _unchained_256(dtype, bl, ragged, slabs)
 
 
 # one problem: rounds from two to many (a last block of tiles of its own width), bands of both heights, no XCD
 # renumbering; a tile count that no XCD count divides
 @pytest.mark.gpu
-@pytest.mark.parametrize("M,N,group_m,remap", [(4100, 4208, 0, 1), (20011, 1104, 0, 1), (9000, 3008, 3, 1), (4100, 4208, 1, 0), (3333, 8896, 64, 1)])
+@pytest.mark.parametrize("M,N,group_m,remap", [(4100, 4208, 0, 1), (20011, 1104, 0, 1), (9000, 3008, 3, 1), (4100, 4208, 1, 0), (3333, 8896, 64, 1), (11700, 11296, 0, 1)])
 @pytest.mark.parametrize("dtype,bl", [(BF16, 1), (FP16, 0), (E4M3, 1)])
 def test_chained_walk_covers_every_tile_once(M, N, group_m, remap, dtype, bl):
     from paper_2512_04226_amd import binding as g
     K = SLAB[dtype] + 16
     A, B, ref = _problem(1, M, N, K, dtype, bl)
-    total = 0
+    chained = set()
     for c in _per_tile_size(g, M, N, K, 1, dtype, bl).values():
         if g.gemm_launched_kernel(c)[0] != "chained":
             continue
@@ -99,8 +104,67 @@ def test_chained_walk_covers_every_tile_once(M, N, group_m, remap, dtype, bl):
         c.xcd_remap = remap
         out = _run(g, c, A, B, M, N, dtype)
         assert torch.equal(out, ref), (c.describe(), int((out != ref).sum()))
-        total += 1
-    assert total >= 2
+        chained.add((c.block_m, c.block_n))
+    expected = {(128, 64), (64, 128)}                      # two to four rounds; 64x64 3.4 to 5.8, fp8 from four on
+    if dtype != E4M3 or M != 4100:
+        expected.add((64, 64))
+    if M == 11700:                                         # eight rounds of 256x256 tiles, 16 of their halves
+        expected |= {(256, 128), (128, 256)} | ({(256, 256), (128, 128)} if dtype != E4M3 else set())
+    assert chained == expected
+
+
+# alpha: powers of two, so that the scaled sum has one rounding all the same
+@pytest.mark.gpu
+@pytest.mark.parametrize("dtype,bl", [(d, b) for d in (BF16, FP16, E4M3) for b in (0, 1)])
+@pytest.mark.parametrize("alpha,K,ragged_n", [(0.5, 64, 0), (-2.0, 80, 0), (0.25, 77, 3)])
+def test_chained_scales_by_alpha(dtype, bl, alpha, K, ragged_n):
+    from paper_2512_04226_amd import binding as g
+    M, N = 200, 272 - ragged_n
+    K = K * (2 if dtype == E4M3 and not ragged_n else 1)
+    chained = set()
+    for size, slots in SLOTS.items():
+        batch = -(-8 * slots // (-(-M // size[0]) * -(-N // size[1]))) + 3
+        c = _per_tile_size(g, M, N, K, batch, dtype, bl).get(size)
+        if not g.gemm_launched_kernel(c)[0].startswith("chained"):
+            continue
+        A, B, ref = _problem(batch, M, N, K, dtype, bl, alpha=alpha)
+        c.alpha = alpha
+        out = _run(g, c, A, B, M, N, dtype)
+        assert torch.equal(out, ref), (c.describe(), int((out != ref).sum()))
+        chained.add(size)
+    assert chained == set(SLOTS) - _unchained_256(dtype, bl, ragged_n, -(-K // SLAB[dtype]))
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("dtype,bl", [(d, b) for d in (BF16, FP16, E4M3) for b in (0, 1)])
+@pytest.mark.parametrize("ragged", [0, 1])
+def test_chained_infinities_and_nan_stay_in_their_rows_and_columns(dtype, bl, ragged):
+    """A NaN row and column, and (16-bit) infinities of both signs: what the plain product gives, and the tiles before and
+    after in the same workgroup untouched by them."""
+    from paper_2512_04226_amd import binding as g
+    M, N, K = 200, 272 - 3 * ragged, 2 * SLAB[dtype] - 5 * ragged
+    batch = -(-8 * 1280 // 20) + 3
+    A, B, ref = _problem(batch, M, N, K, dtype, bl)
+    nan, inf = float("nan"), float("nan") if dtype == E4M3 else float("inf")
+    Af = A.float()
+    Bf = B.float()
+    k = (lambda b, kk, n: (b, n, kk)) if bl else (lambda b, kk, n: (b, kk, n))
+    for b in (0, batch // 2, batch - 1):
+        Af[b, 3, K - 1], Af[b, 130, 1], Af[b, M - 1, 5] = nan, inf, -inf
+        Bf[k(b, 2, 65)], Bf[k(b, K - 1, N - 1)], Bf[k(b, 0, 0)] = nan, inf, -inf
+        left, right = Af[b, :, :K].double(), Bf[b].double()
+        right = right[:, :K].t() if bl else right[:, :N]
+        ref[b] = (left.cpu() @ right.cpu()).to(ref.dtype)
+    A, B = Af.to(A.dtype), Bf.to(B.dtype)
+    sizes = _per_tile_size(g, M, N, K, batch, dtype, bl)
+    for size in ((64, 64), (128, 64), (128, 128), (256, 128)):
+        c = sizes[size]
+        if not g.gemm_launched_kernel(c)[0].startswith("chained"):
+            assert size in ((128, 128), (256, 128)), c.describe()        # (fewer than eight rounds of them here)
+            continue
+        out = _run(g, c, A, B, M, N, dtype)
+        same = (out == ref) | (out.isnan() & ref.isnan())
+        assert bool(same.all()), (c.describe(), int((~same).sum()))
 
 
 def test_where_a_launch_is_chained():

@@ -34,9 +34,10 @@ def _usage(src):
     return rows
 
 
-def _tile(es, bm, bn, bk, wm, wn, mi, ns, bl, ft, rg=0):
-    """Regular expression for the whole-chunk (rg = 1: ragged) instantiation of a tile, whatever K-loop form it has."""
-    return "TileI" + "".join("Li%dE" % x for x in (es, bm, bn, bk, wm, wn, mi, ns, bl, ft)) + r"Li\d+ELi%dELi0EEEEE" % rg
+def _tile(es, bm, bn, bk, wm, wn, mi, ns, bl, ft, rg=0, st=0):
+    """Regular expression for the whole-chunk (rg = 1: ragged) instantiation of a tile, whatever K-loop form it has.
+    st = 0: the kernel of Stream-K and grouped launches, 3: of launches of one problem (direct)."""
+    return "TileI" + "".join("Li%dE" % x for x in (es, bm, bn, bk, wm, wn, mi, ns, bl, ft)) + r"Li\d+ELi%dELi%dEEEEE" % (rg, st)
 
 
 @pytest.fixture(scope="module")
@@ -73,7 +74,8 @@ def test_headline_kernels_keep_no_spills_and_no_kernel_spills_much(usage):
     rows = usage
     assert len(rows) >= 40
     # The bf16 256x256x64 tile on a 4x2 wave grid (row-major B) and on a 2x4 grid (K-contiguous B), fp8 256x256x128 on
-    # four waves: the plain instantiations, which run at 8192^3's extents below twenty K slabs
+    # four waves: the plain instantiations, which run at 8192^3's extents below twenty K slabs (of Stream-K and grouped
+    # launches; the direct ones further down)
     for tag in (_tile(2, 256, 256, 64, 4, 2, 16, 2, 0, 0), _tile(2, 256, 256, 64, 2, 4, 16, 2, 1, 0),
                 _tile(1, 256, 256, 128, 2, 2, 32, 2, 0, 0), _tile(1, 256, 256, 128, 2, 2, 32, 2, 1, 0)):
         r = _find(rows, tag)
@@ -84,8 +86,8 @@ def test_headline_kernels_keep_no_spills_and_no_kernel_spills_much(usage):
 
 
 def test_pipelined_kernels_have_no_scratch_and_the_spills_of_the_others_are_known(usage):
-    """The four-wave kernels of the 256x256 tiles (K-loop form 7; what 8192^3 runs) hide nothing: no scratch, plain and
-    ragged, both storages of B.  The kernels that do spill are listed, so that another one, or more of it, is noticed."""
+    """The four-wave kernels of the 256x256 tiles (K-loop form 7; what grouped launches of 8192^3's extents run, its own
+    direct ones further down) hide nothing: no scratch, plain and ragged, both storages of B.  The kernels that do spill are listed, so that another one, or more of it, is noticed."""
     pipelined = [r for r in usage if re.search(r"TileI.*Li7ELi[01]ELi0EEEEE", r["name"])]
     assert len(pipelined) == 12             # {bf16, fp16, fp8} x storage of B x {plain, ragged}
     for r in pipelined:
@@ -99,3 +101,36 @@ def test_pipelined_kernels_have_no_scratch_and_the_spills_of_the_others_are_know
     for r in usage:
         allowed = [b for tag, b in known.items() if re.search(tag, r["name"])]
         assert r.get("scratch", 0) <= (allowed[0] if allowed else 0), r
+
+
+def test_direct_kernels_keep_no_spills_and_the_third_workgroup(usage):
+    """What launches of one problem run: no scratch in any of them (8192^3 runs the pipelined ones, the extents below twenty
+    K slabs the plain ones of the other tests), and three eight-wave workgroups on a CU for the two-stage 128x64 and 64x128
+    tiles, ragged and with row-major B whole."""
+    direct = [r for r in usage if re.search(r"11gemm_kernelI.*Li[34]EEEEE", r["name"])]
+    assert 2 * len(direct) == len([r for r in usage if "11gemm_kernelI" in r["name"]]) >= 80      # each kernel twice
+    for r in direct:
+        assert r["scratch"] == 0, r
+    assert len([r for r in direct if re.search(r"Li7ELi[01]ELi3EEEEE", r["name"])]) == 12         # the pipelined ones
+    for ft in (0, 1):
+        for bm, bn in ((128, 64), (64, 128)):
+            for bl in (0, 1):
+                r = _find(usage, _tile(2, bm, bn, 64, 2, 4, 16, 2, bl, ft, rg=1, st=3))
+                assert r["waves_per_simd"] >= 6, r
+            r = _find(usage, _tile(2, bm, bn, 64, 2, 4, 16, 2, 0, ft, st=3))
+            assert r["waves_per_simd"] >= 6, r
+
+
+@pytest.mark.skipif(shutil.which(HIPCC) is None and not os.path.exists(HIPCC), reason="needs hipcc")
+def test_chained_kernels_fill_the_cu_as_their_walk_assumes():
+    """The walk of a chained launch counts on as many resident workgroups as the LDS has room for; one has scratch."""
+    with ThreadPoolExecutor(max_workers=3) as ex:
+        rows = sum(ex.map(_usage, ["chained_bf16.hip", "chained_fp16.hip", "chained_fp8.hip"]), [])
+    rows = [r for r in rows if "chained_kernel" in r["name"]]
+    assert len(rows) == 77
+    for r in rows:
+        es, bm, bn, bk, wm, wn, mi, ns = map(int, re.search("TileI" + r"Li(\d+)E" * 8, r["name"]).groups())
+        on_a_cu = 160 * 1024 // (ns * (bm + bn) * bk * es)
+        assert r["waves_per_simd"] >= on_a_cu * wm * wn // 4, r
+        spills = (es, bm, bn) == (1, 256, 256)
+        assert r["scratch"] <= (20 if spills else 0), r
