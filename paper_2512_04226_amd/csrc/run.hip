@@ -277,7 +277,8 @@ inline int64_t cdiv64(int64_t a, int64_t b) { return (a + b - 1) / b; }
 // Among these, from four slabs on the large tiles gain less and lose more beside other work on one problem of 32 columns and
 // more (256x128 at 8 rounds of 8 slabs 1.07 and 1.28 against .92 and 1.11 with 4 columns): the other launch has their
 // panels in the L2.  A batch of problems of some hundred tiles and less gains most: the other launch deals every problem's tiles
-// to all XCDs, the chained walk gives an XCD whole problems (problems of 4 to 64 tiles, from two or three rounds on: .50 to .95).
+// to all XCDs, the chained walk gives an XCD whole problems (problems of 4 to 64 tiles, from two or three rounds on: .50 to .95;
+// 52 x 808x1720x576 fp16 on 128x128 tiles, nine slabs, 152 -> 138 us).
 // Rows of C that start inside a 128-byte line: two tiles share a line, and the further apart in time they write it the more
 // often the memory behind the L2 gets it in two parts.  16 rounds at 4 and at 2 tiles per workgroup: 16-bit 128x128 one slab
 // 1.03 to 1.19 and .98 to 1.10, two to eight slabs .87 to .95 at both; fp8 128x128 1.00 to 1.29 and 1.00 to 1.19; 128x64 .86 to 1.08 and
@@ -304,7 +305,7 @@ int64_t chain_of(const Variant &v, int dtype, int64_t tiles_m, int64_t tiles_n, 
     if (size == 256 * 256) {
         if (small)
             from(3, fp8 ? 4 : 8);
-        else if (!fp8 && !thin && !half)
+        else if (!fp8 && !thin && (batched || !half))
             from(3, 4), from(compact ? 6 : 12, 8);
     } else if (size == 256 * 128) {
         if (fp8)
@@ -315,9 +316,9 @@ int64_t chain_of(const Variant &v, int dtype, int64_t tiles_m, int64_t tiles_n, 
             from(6, compact ? 8 : 2), from(8, 4);
     } else if (size == 128 * 128) {
         if (fp8)
-            from(8, batched ? 8 : 0);
+            from(8, batched ? 16 : 0);
         else if (batched)
-            from(small ? (thin ? 6 : slabs < 2 ? 4 : 3) : 6, 8);
+            from(small ? (thin ? 6 : slabs < 2 ? 4 : 3) : 6, 8), from(8, 16);
         else if (lines)
             from(8, 4);
         else

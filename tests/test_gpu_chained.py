@@ -195,7 +195,8 @@ def test_launches_that_chaining_slows_are_not_chained(batch, M, N, K, dtype, bl)
 
 
 @pytest.mark.parametrize("batch,M,N,K,dtype,bl", [
-    (32, 2048, 2048, 128, BF16, 1), (1, 65536, 2048, 128, BF16, 0), (142, 400, 1056, 64, BF16, 1), (1, 16408, 2960, 64, BF16, 1)])
+    (32, 2048, 2048, 128, BF16, 1), (1, 65536, 2048, 128, BF16, 0), (142, 400, 1056, 64, BF16, 1), (1, 16408, 2960, 64, BF16, 1),
+    (52, 808, 1720, 576, FP16, 0), (9, 4048, 3088, 352, FP16, 1)])
 def test_launches_that_chaining_speeds_up_are_chained(batch, M, N, K, dtype, bl):
     from paper_2512_04226_amd import binding as g
     c = g.gemm_select_batched(M, N, K, batch, dtype, bl)
