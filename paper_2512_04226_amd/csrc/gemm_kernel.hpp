@@ -230,6 +230,8 @@ struct Tile {
     // ds_read_b128 sixteen lanes at a time, so sixteen consecutive rows must land on sixteen
     // different 16-byte slots of the 256-byte bank window: the chunk index is XORed with a key
     // that counts 256-byte windows of rows.
+    // (The fragment reads of gemm_kernel and of chained.hpp both follow these layouts and b_off's below: a change of one is a
+    // change of all three.)
     static constexpr int A_ROWS_PER_WIN = (RA >= 256) ? 1 : 256 / RA;
     static constexpr int A_KEY_MASK = ((CA < 16) ? CA : 16) - 1;
     __device__ static inline int a_key(int row) { return (row / A_ROWS_PER_WIN) & A_KEY_MASK; }
