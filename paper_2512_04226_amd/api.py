@@ -124,8 +124,11 @@ def _workspace_for(need, device, stream):
 def matmul(A, B, out=None, alpha=1.0, beta=0.0, b_k_contiguous=False, stream=None):
     """out = alpha * A @ B + beta * out.  A: (M, K) row-major; B: (K, N) row-major, or (N, K)
     row-major with b_k_contiguous=True.  bf16 / fp8 inputs give a bf16 result, fp16 gives fp16."""
-    result = _short_way(A, B, out, alpha, beta, b_k_contiguous, stream) if stream is None else None
-    return result if result is not None else _matmul_general(A, B, out, alpha, beta, b_k_contiguous, stream)
+    if stream is None:
+        result = _short_way(A, B, out, alpha, beta, b_k_contiguous, stream)
+        if result is not None:
+            return result
+    return _matmul_general(A, B, out, alpha, beta, b_k_contiguous, stream)
 
 
 def _fast_plan(*key):
