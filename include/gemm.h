@@ -368,13 +368,21 @@ typedef enum {
     GEMM_KERNEL_PLAIN = 0,
     GEMM_KERNEL_RAGGED = 1,           /* N or K is no whole number of 16-byte chunks */
     GEMM_KERNEL_STREAMING = 2,        /* one tile row over weights larger than the memory-side cache */
-    GEMM_KERNEL_PIPELINED = 3,        /* 256x256 tiles with 128-byte slab rows, twenty K slabs or more per workgroup */
+    GEMM_KERNEL_PIPELINED = 3,        /* 256x256 tiles with 128-byte slab rows, twenty K slabs or more per workgroup; or a tile
+                                         in place of the cfg's, see gemm_launched_tile */
     GEMM_KERNEL_PIPELINED_RAGGED = 4,
     GEMM_KERNEL_CHAINED = 5,          /* many tiles of few K slabs: a workgroup computes several, one after the other
                                          (named for a C that starts on a 128-byte boundary) */
     GEMM_KERNEL_CHAINED_RAGGED = 6
 } gemm_kernel_kind;
 int gemm_launched_kernel(const gemm_cfg *cfg, int n_groups, const gemm_group_rec *host_table, int32_t out4[4]);
+
+/*
+ * BLOCK_M, BLOCK_N and the number of K slices that gemm_run launches for a cfg of one problem or strided batch: the cfg's own,
+ * or those of a pipelined kernel that fills the chip better (at most the cfg's K slices, so that its workspace holds them).
+ * Errors: as gemm_launched_kernel.
+ */
+int gemm_launched_tile(const gemm_cfg *cfg, int32_t out3[3]);
 
 /* Hardware descriptor: get a copy / replace it (process-wide; not thread-safe against
  * concurrent gemm_select).  gemm_hw_reset restores the MI355X defaults. */

@@ -473,6 +473,17 @@ def gemm_launched_kernel(cfg, table=None):
     return (KERNEL_KINDS[out[0]],) + tuple(out[1:])
 
 
+_lib.gemm_launched_tile.restype = _int
+_lib.gemm_launched_tile.argtypes = [ctypes.POINTER(gemm_cfg), ctypes.c_int32 * 3]
+
+
+def gemm_launched_tile(cfg):
+    """(BLOCK_M, BLOCK_N, K slices) that gemm_run launches for the cfg: its own, or those of a pipelined kernel in its place."""
+    out = (ctypes.c_int32 * 3)()
+    _check(_lib.gemm_launched_tile(ctypes.byref(cfg), out), "gemm_launched_tile")
+    return tuple(out)
+
+
 def gemm_variant_count(dtype):
     n = _lib.gemm_variant_count(dtype)
     if n < 0:

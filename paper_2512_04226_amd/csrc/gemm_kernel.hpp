@@ -120,11 +120,11 @@ typedef float f32x16 __attribute__((ext_vector_type(16)));
 // read three (k-step, column) blocks ahead of the MFMAs, and the slab's barrier follows the last fragment read of
 // the stage, not its last MFMA.  Fewer live registers than form 5 (the eight-wave 256x256x64 tiles keep no spills);
 // needs three or more column blocks per wave and a multiple of four blocks per slab, else the tile runs form 0.
-// 7: the pipelined loop of the 256x256 tiles on four waves (128x128 wave tiles, accumulators in AGPRs).  One wave per SIMD
-// means that nothing hides a stall, so the loop is arranged to have none: A and B slabs share a ring of five 32 KB units
-// (all 160 KB of LDS; A(s) and B(s) are neighbours, two slabs and a half are resident or in flight), the loads of a slab
-// are spread evenly over a WHOLE slab of MFMAs (B's in the second k-step, A's in the next slab's first, A one slab further
-// ahead), the slab is unrolled five times so that every ring offset is a constant, the loads' advance along K is the
+// 7: the pipelined loop of the tiles on four waves, 2x2 (256x256: 128x128 wave tiles, accumulators in AGPRs; smaller ones, see
+// retile.hpp, alike).  One wave per SIMD means that nothing hides a stall, so the loop is arranged to have none: the ring takes
+// most of the LDS (256x256: A and B slabs share five 32 KB units, all 160 KB, two slabs and a half resident or in flight; smaller
+// tiles have three to six slabs of each), the loads of a slab are spread evenly over a WHOLE slab of MFMAs (B's in the second
+// k-step, A's in the next slab's first), the loop is unrolled over the ring so that every offset is a constant, the loads' advance along K is the
 // instruction's scalar offset, and fragment rows are instruction offsets: between two MFMAs there is hardly ever more than
 // one other instruction.  See the comment at the loop for what each of these measured.
 // Building with -DG355_FORCE_LOOP_FORM=k gives every variant form k (how the forms are compared).
@@ -181,17 +181,20 @@ struct Tile {
     static constexpr int KG = 64 / MI;                      // lane groups along k
     static constexpr int KL = KI / KG;                      // k elements held by one lane
     static constexpr int KSTEPS = BK / KI;
-    // form 6 needs at least three B fragments per k-step and a whole number of four-slot ring turns per slab, form 7 the
-    // 256x256 tile on four waves with 128-byte slab rows; a tile that has neither runs form 0 when the form is forced on
+    // form 6 needs at least three B fragments per k-step and a whole number of four-slot ring turns per slab, form 7 a
+    // 2x2 grid of waves and 128-byte slab rows; a tile that has neither runs form 0 when the form is forced on
     // every tile
     static constexpr bool FITS6 = TN >= 3 && (KSTEPS * TN) % 4 == 0 && KSTEPS >= 2;
-    static constexpr bool FITS7 = BM == 256 && BN == 256 && WM == 2 && WN == 2 && BK * ES == 128 && KSTEPS == 2 && (ST == 0 || ST == 3);
+    static constexpr bool FITS7 = BM % 64 == 0 && BN % 128 == 0 && WM == 2 && WN == 2 && BK * ES == 128 && KSTEPS == 2 && (ST == 0 || ST == 3);
     static constexpr int LF = ((LF_ASKED == 6 && !FITS6) || (LF_ASKED == 7 && !FITS7)) ? 0 : LF_ASKED;
     static constexpr int RA = BK * ES;                      // bytes per A row in LDS
     static constexpr int RB = (BL == 0) ? BN * ES : BK * ES; // bytes per B row in LDS (a k row, or an n row when K-contiguous)
     static constexpr int A_BYTES = BM * RA, B_BYTES = BK * BN * ES;
     static constexpr int STAGE = A_BYTES + B_BYTES;
-    static constexpr int LDS_BYTES = (LF == 7) ? 5 * A_BYTES : NS * STAGE;
+    // form 7: slabs of A and of B that the ring holds, and whether they share five units
+    static constexpr int RING_B = (160 * 1024 / STAGE >= 3) ? (160 * 1024 / STAGE < 6 ? 160 * 1024 / STAGE : 6) : 2, RING_A = RING_B > 2 ? RING_B : 3;
+    static constexpr bool RING_SHARED = RING_B == 2 && A_BYTES == B_BYTES;
+    static constexpr int LDS_BYTES = (LF == 7) ? RING_A * A_BYTES + RING_B * B_BYTES : NS * STAGE;
     // Waves per SIMD the registers must leave room for.  What a workgroup needs by itself, except in the ragged instantiation
     // of the two-stage 128x64 and 64x128 tiles on eight waves: their 48 KB of LDS let three workgroups share a CU, and the
     // trimming and the element-wise store would take 85-87 registers where three fit up to 80.  Held to that (8-12 bytes of
@@ -855,21 +858,23 @@ __global__ __launch_bounds__(T::NT, T::MIN_WAVES) void gemm_kernel(const KernelA
         }
 #if defined(__HIP_DEVICE_COMPILE__)
         if constexpr (LF == 7) {
-            // Ring unit u holds one operand's slab; A(s) sits in unit 2s mod 5, B(s) in the one after it.  From the
-            // barrier in the middle of slab s (its k-step-1 fragments are in registers) the units of A(s) and B(s) are
-            // free: B(s+2) goes into A(s)'s during this k-step, A(s+3) into B(s)'s during the first k-step of slab s+1.
-            // That barrier waits for all but the youngest A slab's loads, so A has between two and three k-steps to
-            // land and B between one and two.
+            // The ring holds NA slabs of A and NB of B (a_at, b_at: where).  From the barrier in the middle of slab s (its
+            // k-step-1 fragments are in registers) the places of A(s) and B(s) are free: B(s+NB) is loaded during this
+            // k-step, A(s+NA) during the first k-step of slab s+1.  That barrier waits for all but the loads younger than
+            // slab s+2's: of a 256x256 tile (three slabs of A, two of B), which A has between two and three k-steps to land
+            // and B between one and two, all but A's youngest.
             // What bounds it: the chip's power on data that toggles the matrix cores (1.77-1.84 GHz under this loop,
             // 2.38 on zeros).  8192^3 bf16, both forms on one card: row-major B 742 -> 671 us (zeros 685 -> 556), K-contiguous
             // 739 -> 670 (655 -> 550) against the eight-wave forms 4 and 6.  Measured on the way (K-contiguous, N(0,1) /
             // zeros): five units and B's and A's loads in one k-step 728 / 646; the loads spread over both k-steps
             // 717 / 574; unrolled over the ring 672 / 553.  A burst of loads costs most (half a k-step: 791 / 740):
             // a CU's vector-memory path takes 64 bytes per clock, and a wave whose load waits for it issues no MFMA.
-            static_assert(T::A_BYTES == T::B_BYTES && T::A_UNITS % T::NW == 0 && T::B_UNITS % T::NW == 0, "five equal units");
+            static_assert(T::A_UNITS % T::NW == 0 && T::B_UNITS % T::NW == 0, "every wave issues every load");
             static_assert((MI / T::A_ROWS_PER_WIN) % (T::A_KEY_MASK + 1) == 0, "MFMA tiles down a wave tile share one swizzle key");
-            static_assert(T::TM % 2 == 0 && T::TN % 2 == 0, "2x2 blocks of MFMA tiles");
-            constexpr int U = T::A_BYTES;
+            constexpr int NA = T::RING_A, NB = T::RING_B, PERIOD = T::RING_SHARED ? 5 : NA == NB ? NA : NA * NB;
+            G355_LDS uint8_t *const ring_b = lds + NA * T::A_BYTES;
+            auto a_at = [&](int i) __attribute__((always_inline)) { return lds + (T::RING_SHARED ? 2 * i % 5 : i % NA) * T::A_BYTES; };
+            auto b_at = [&](int i) __attribute__((always_inline)) { return T::RING_SHARED ? lds + (2 * i + 1) % 5 * T::B_BYTES : ring_b + i % NB * T::B_BYTES; };
             typedef std::integral_constant<int, 0> K0;
             typedef std::integral_constant<int, 1> K1;
             // byte offsets of the lane's chunk of a K-contiguous operand in a unit, per k-step; rows of MFMA tile u are
@@ -921,16 +926,20 @@ __global__ __launch_bounds__(T::NT, T::MIN_WAVES) void gemm_kernel(const KernelA
             // MFMA number m of a k-step: 2x2 blocks of MFMA tiles, walked as a U, so that every MFMA but one in four
             // shares an operand with the one before (1 % on N(0,1) data against rows of eight: fewer operand changes)
             auto mma_at = [&](int buf, int m) __attribute__((always_inline)) {
-                const int b = m / 4, q = m % 4;
-                mma_one(buf, b / (T::TM / 2) * 2 + q / 2, b % (T::TM / 2) * 2 + (q == 1 || q == 2));
+                if constexpr (T::TM % 2 || T::TN % 2) {
+                    mma_one(buf, m / T::TM, (m / T::TM) % 2 ? T::TM - 1 - m % T::TM : m % T::TM);
+                } else {
+                    const int b = m / 4, q = m % 4;
+                    mma_one(buf, b / (T::TM / 2) * 2 + q / 2, b % (T::TM / 2) * 2 + (q == 1 || q == 2));
+                }
             };
             // One k-step on the fragments in buffer KB.  Slot m: its share of the other buffer's fragment reads (from
             // pa / pb, spread over the first three quarters), MFMA m, its share of the slab's loads of one operand.
             constexpr int HR = MN * 3 / 4;
-            auto kstep7 = [&](auto kb, const G355_LDS uint8_t *pa, const G355_LDS uint8_t *pb, auto load) __attribute__((always_inline)) {
-                constexpr int KB = decltype(kb)::value;
+            auto kstep7 = [&](auto kb, const G355_LDS uint8_t *pa, const G355_LDS uint8_t *pb, auto loads, auto load) __attribute__((always_inline)) {
+                constexpr int KB = decltype(kb)::value, LPS = decltype(loads)::value;
                 static_for<0, MN>([&](auto mc) __attribute__((always_inline)) {
-                    constexpr int m = decltype(mc)::value, LPS = T::A_LOADS;
+                    constexpr int m = decltype(mc)::value;
                     constexpr int u0 = (m * NF + HR - 1) / HR, u1 = ((m + 1) * NF + HR - 1) / HR;
                     static_for<(u0 < NF ? u0 : NF), (u1 < NF ? u1 : NF)>(
                         [&](auto u) __attribute__((always_inline)) { frag(pa, pb, KB ^ 1, decltype(u)::value); });
@@ -939,48 +948,59 @@ __global__ __launch_bounds__(T::NT, T::MIN_WAVES) void gemm_kernel(const KernelA
                     __builtin_amdgcn_sched_barrier(0);
                 });
             };
-            // from the barrier of slab s to the barrier of slab s + 1 (ua, ub: the units of A(s) and B(s))
-            auto slab7 = [&](auto tail, G355_LDS uint8_t *__restrict__ ua, G355_LDS uint8_t *__restrict__ ub,
+            // from the barrier of slab s to the barrier of slab s + 1 (fa, fb: where A(s+NA) and B(s+NB) go; na, nb: A(s+1), B(s+1))
+            typedef std::integral_constant<int, T::A_LOADS> LA;
+            typedef std::integral_constant<int, T::B_LOADS> LB;
+            constexpr int ALLOW7 = (NA - 2) * T::A_LOADS + (NB - 2) * T::B_LOADS;
+            auto slab7 = [&](auto tail, G355_LDS uint8_t *__restrict__ fa, G355_LDS uint8_t *__restrict__ fb,
                              const G355_LDS uint8_t *__restrict__ na, const G355_LDS uint8_t *__restrict__ nb, int s)
                              __attribute__((always_inline)) {
-                kstep7(K1{}, na, nb, [&](auto l) __attribute__((always_inline)) { load_b(tail, decltype(l)::value, (s + 2) * BK, ua); });
-                kstep7(K0{}, na, nb, [&](auto l) __attribute__((always_inline)) { load_a(tail, decltype(l)::value, (s + 3) * BK, ub); });
-                wait_and_barrier<T::A_LOADS, true>();
+                kstep7(K1{}, na, nb, LB{}, [&](auto l) __attribute__((always_inline)) { load_b(tail, decltype(l)::value, (s + NB) * BK, fb); });
+                kstep7(K0{}, na, nb, LA{}, [&](auto l) __attribute__((always_inline)) { load_a(tail, decltype(l)::value, (s + NA) * BK, fa); });
+                wait_and_barrier<ALLOW7, true>();
             };
             const std::true_type tested{};
             const std::false_type inside{};
-            static_for<0, 5>([&](auto uc) __attribute__((always_inline)) {
+            static_for<0, NA>([&](auto uc) __attribute__((always_inline)) {
                 constexpr int u = decltype(uc)::value;
-                static_for<0, T::A_LOADS>([&](auto l) __attribute__((always_inline)) {
-                    if constexpr (u % 2 == 0)
-                        load_a(tested, decltype(l)::value, u / 2 * BK, lds + u * U);
-                    else
-                        load_b(tested, decltype(l)::value, u / 2 * BK, lds + u * U);
-                });
+                static_for<0, T::A_LOADS>([&](auto l) __attribute__((always_inline)) { load_a(tested, decltype(l)::value, u * BK, a_at(u)); });
+                if constexpr (u < NB)
+                    static_for<0, T::B_LOADS>([&](auto l) __attribute__((always_inline)) { load_b(tested, decltype(l)::value, u * BK, b_at(u)); });
             });
-            wait_and_barrier<3 * T::A_LOADS, false>();
+            wait_and_barrier<(NA - 1) * T::A_LOADS + (NB - 1) * T::B_LOADS, false>();
             if (T::RG && kt_count == 1)
-                trim_last_slab(lds, lds + U);
-            static_for<0, NF>([&](auto u) __attribute__((always_inline)) { frag(lds, lds + U, 0, decltype(u)::value); });
-            kstep7(K0{}, lds, lds + U, [](auto) {});
-            wait_and_barrier<T::A_LOADS, true>();
+                trim_last_slab(a_at(0), b_at(0));
+            static_for<0, NF>([&](auto u) __attribute__((always_inline)) { frag(a_at(0), b_at(0), 0, decltype(u)::value); });
+            kstep7(K0{}, a_at(0), b_at(0), std::integral_constant<int, 0>{}, [](auto) {});
+            wait_and_barrier<ALLOW7, true>();
             int s = 0;
             const int end = kt_count - 1;
-            const int whole = k_len / BK - 3;      // slabs below this one load only slabs that lie inside the K range
-            for (; s + 5 <= whole; s += 5)
-                static_for<0, 5>([&](auto ic) __attribute__((always_inline)) {
+            const int whole = k_len / BK - NA;      // slabs below this one load only slabs that lie inside the K range
+            for (; s + PERIOD <= whole; s += PERIOD)
+                static_for<0, PERIOD>([&](auto ic) __attribute__((always_inline)) {
                     constexpr int i = decltype(ic)::value;
-                    slab7(inside, lds + 2 * i % 5 * U, lds + (2 * i + 1) % 5 * U, lds + (2 * i + 2) % 5 * U,
-                          lds + (2 * i + 3) % 5 * U, s + i);
+                    slab7(inside, a_at(i + NA), b_at(i + NB), a_at(i + 1), b_at(i + 1), s + i);
                 });
-            int ua = 0;
-            auto wrap = [](int x) { return x >= 5 ? x - 5 : x; };
+            // (positions of A(s) and B(s) in units of their slabs; of shared units B(s) follows A(s), and A(s+3) takes B(s)'s)
+            int ua = 0, ub = 0;
+            auto next = [](int u, int n) { return u + 1 == n ? 0 : u + 1; };
             for (; s < end; ++s) {
-                const int na = wrap(ua + 2), nb = wrap(ua + 3);
-                if (T::RG && s + 1 == end)
-                    trim_last_slab(lds + na * U, lds + nb * U);
-                slab7(tested, lds + ua * U, lds + wrap(ua + 1) * U, lds + na * U, lds + nb * U, s);
-                ua = na;
+                if constexpr (T::RING_SHARED) {
+                    const int na = ua >= 3 ? ua - 3 : ua + 2;
+                    G355_LDS uint8_t *const pa = lds + na * T::A_BYTES, *const pb = lds + next(na, 5) * T::A_BYTES;
+                    if (T::RG && s + 1 == end)
+                        trim_last_slab(pa, pb);
+                    slab7(tested, lds + next(ua, 5) * T::A_BYTES, lds + ua * T::A_BYTES, pa, pb, s);
+                    ua = na;
+                } else {
+                    const int na = next(ua, NA), nb = next(ub, NB);
+                    G355_LDS uint8_t *const pa = lds + na * T::A_BYTES, *const pb = ring_b + nb * T::B_BYTES;
+                    if (T::RG && s + 1 == end)
+                        trim_last_slab(pa, pb);
+                    slab7(tested, lds + ua * T::A_BYTES, ring_b + ub * T::B_BYTES, pa, pb, s);
+                    ua = na;
+                    ub = nb;
+                }
             }
             static_for<0, MN>([&](auto mc) __attribute__((always_inline)) { mma_at(1, decltype(mc)::value); });
             return;

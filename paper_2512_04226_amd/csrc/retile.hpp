@@ -1,0 +1,95 @@
+// Which tile, and how many K slices, a launch of one problem or strided batch really runs (host only).
+//
+// The selector ranks the variants of its table; their tiles halve and double, and so do its K splits, so that a pick can leave
+// a third of the CUs without work, or compute a fifth of its rows for padding.  The pipelined kernels (K-loop form 7, four
+// waves, one workgroup per CU) exist for tiles between those, and a launch may have any number of K slices that the cfg's
+// workspace holds.  retile() prices all of them and the cfg's own tile by one rule and takes another where that promises at
+// least the margins below; a launch whose cfg names the better tile runs it as before.
+//
+// What a launch costs (us; a slab is 128 bytes of K): per round of 256 workgroups `fixed` + slabs * the slab's time, which is
+// `alone` while the chip has power to spare and grows with the share of busy CUs up to `full` (N(0,1) data: a chip with all
+// matrix cores busy runs at 1.8 GHz instead of 2.4).  Fitted to 1500 launches of 168 drawn problems (16-bit and fp8 slabs take the
+// same time within the fit's error, 14 % rms); the tile it takes is 2 % behind the best of the family in the mean.
+#pragma once
+#include <algorithm>
+#include <cstdint>
+
+namespace g355 {
+struct PipelinedTile {
+    int block_m, block_n;
+    double fixed, alone, full;
+};
+constexpr PipelinedTile kPipelinedTiles[] = {
+    {256, 256, 7.5, 1.20, 1.60}, {192, 256, 4.6, 1.00, 1.38}, {128, 256, 3.0, 0.76, 1.06}, {64, 256, 2.3, 0.55, 0.74},
+    {256, 128, 3.1, 0.77, 1.12}, {192, 128, 3.6, 0.60, 0.84}, {128, 128, 2.8, 0.46, 0.63}, {64, 128, 2.0, 0.29, 0.43}};
+
+struct Retiled {
+    int block_m, block_n, split;      // block_m == 0: the cfg's own
+};
+
+struct RetileProblem {
+    int64_t M, N, batch, slabs;       // slabs: of 128 bytes, in K
+    int block_m, block_n, split;      // the cfg's
+    bool two_resident;                // two workgroups of the cfg's kernel share a CU
+};
+
+inline double pipelined_us(const PipelinedTile &t, const RetileProblem &p, int64_t split, int64_t workgroups, int64_t per_slice)
+{
+    constexpr int64_t kCus = 256;
+    const int64_t rounds = workgroups / kCus, rest = workgroups % kCus;
+    double us = rounds * (t.fixed + per_slice * t.full);
+    if (rest)
+        us += t.fixed + per_slice * std::max(t.alone, t.full * rest / kCus);
+    // the slices' sums are added by a second kernel: 20 bytes per ps
+    return split > 1 ? us + 3.2 + p.batch * p.M * p.N * (4. * split + 2.) * 5e-8 : us;
+}
+
+// Margins, and where the rule does not look, by the measured time over that of the cfg's own kernel (178 drawn launches of
+// these tiles, K-split ones among them; 40 are retiled, to 0.65 - 0.99 of the time and one to 1.02, 0.89 in the mean):
+//  - fewer than kMinSlabs slabs per workgroup: a pipelined workgroup's prologue and store stage stand alone (0.96 - 1.2 below);
+//  - fewer than kMinGrid workgroups: not what the selector picks these tiles for;
+//  - 256x256 below twenty slabs runs an eight-wave kernel that is up to 8 % faster than the pipelined one it is priced as, and
+//    launches priced between 0.85 and 0.95 went either way (0.85 - 1.09);
+//  - two-stage 128x128 and 64x256 tiles, two to a CU, hide each other's store stage: priced at 0.93 one went to 1.04, up to 0.83 all gained;
+//  - smaller tiles than 128x128 have three and more workgroups on a CU: 0.9 - 1.2.
+inline Retiled retile(const RetileProblem &p)
+{
+    constexpr int64_t kMinSlabs = 9, kMinGrid = 64, kMinRetiled = 100;
+    const Retiled own = {0, 0, 0};
+    auto tiles = [&](int bm, int bn) { return (p.M + bm - 1) / bm * ((p.N + bn - 1) / bn) * p.batch; };
+    if (p.block_m * p.block_n < 128 * 128 || p.slabs < kMinSlabs || tiles(p.block_m, p.block_n) * p.split < kMinGrid)
+        return own;
+    const int64_t own_slabs = (p.slabs + p.split - 1) / p.split;
+    double limit = 0;
+    for (const PipelinedTile &t : kPipelinedTiles)
+        if (t.block_m == p.block_m && t.block_n == p.block_n)
+            limit = pipelined_us(t, p, p.split, tiles(t.block_m, t.block_n) * p.split, own_slabs);
+    limit *= (p.block_m * p.block_n == 256 * 256 && own_slabs < 20) ? 0.85 : p.two_resident ? 0.90 : 0.95;
+    Retiled best = own;
+    for (const PipelinedTile &t : kPipelinedTiles) {
+        const int64_t n = tiles(t.block_m, t.block_n);
+        for (int split = 1; split <= p.split; ++split) {
+            const int64_t per_slice = (p.slabs + split - 1) / split;
+            if (per_slice < kMinSlabs)
+                break;
+            if (n * split < kMinRetiled || (p.slabs + per_slice - 1) / per_slice != split)     // (no slice may be empty)
+                continue;
+            const double us = pipelined_us(t, p, split, n * split, per_slice);
+            if (us <= limit) {
+                limit = us;
+                best = {t.block_m, t.block_n, split};
+            }
+        }
+    }
+    return best.block_m == p.block_m && best.block_n == p.block_n && best.split == p.split ? own : best;
+}
+
+// Band height of the rasterisation: the 32 workgroups that an XCD holds cover a region about as high as it is wide.
+inline int64_t retiled_group_m(int block_m, int block_n)
+{
+    int64_t g = 1;
+    while (4 * g * g * block_m <= 64 * block_n)
+        g *= 2;
+    return g;
+}
+}  // namespace g355

@@ -10,6 +10,7 @@
 #include "gemm_kernel.hpp"
 #include "launch.hpp"
 #include "model.hpp"
+#include "retile.hpp"
 
 using namespace g355;
 
@@ -247,6 +248,22 @@ int kernel_of(int dtype, int id, int bl, bool ragged, bool streaming, int64_t sl
 
 inline int64_t cdiv64(int64_t a, int64_t b) { return (a + b - 1) / b; }
 
+// The pipelined kernel of a tile of retile.hpp (nullptr: not built, as in the builds that compare K-loop forms).
+const VariantFns *pipelined_of(int dtype, int block_m, int block_n, int b_layout, int ragged)
+{
+    const VariantFns *f = nullptr;
+    if (block_m == 256 && block_n == 256) {
+        for (int id = 0; id < variant_count(dtype); ++id) {
+            const Variant &v = variant_at(dtype, id);
+            if (v.block_m == 256 && v.block_n == 256 && (!f || !f->launch))
+                f = &launcher_of(dtype, id, b_layout, ragged ? GEMM_KERNEL_PIPELINED_RAGGED : GEMM_KERNEL_PIPELINED);
+        }
+    } else {
+        f = &(dtype == GEMM_FP16 ? pipelined_fp16 : dtype == GEMM_BF16 ? pipelined_bf16 : pipelined_fp8)(block_m, block_n, b_layout, ragged);
+    }
+    return f && f->launch ? f : nullptr;
+}
+
 // Tiles per workgroup of a chained launch, 0: the launch is not chained.  `c_bits`: C's address and the distances in bytes of
 // its rows and problems, or-ed.  A tile of few slabs (128 bytes of K) is bound by the latency of its first loads and by its
 // store stage, and a chained workgroup has the next tile's loads in flight under both; with more slabs the loop counts, which
@@ -365,7 +382,10 @@ extern "C" int gemm_set_workspace(void *dev_ptr, size_t bytes)
 
 // What a launch of a cfg that names one problem, or one strided batch, comes to.
 struct Launch {
+    const VariantFns *fns;
     SkPlan sk;                       // workers == 0 unless stream-K
+    int block_m, block_n, split;     // the cfg's, or a pipelined tile's in its place (retile.hpp)
+    int64_t group_m;
     int64_t kps, tiles_m, tiles_n;   // K elements per workgroup, tiles
     int chain;                       // tiles per workgroup of the chained kernels
     int kind;                        // gemm_kernel_kind
@@ -458,6 +478,33 @@ static int plan_launch(const gemm_cfg *cfg, bool aligned, uintptr_t c_address, L
     out->kps = kps;
     out->tiles_m = tiles_m;
     out->tiles_n = tiles_n;
+    out->block_m = v.block_m;
+    out->block_n = v.block_n;
+    out->split = cfg->split_k;
+    out->group_m = cfg->group_m;
+    out->fns = &launcher_of(dtype, cfg->kernel_id, cfg->b_layout, out->kind);
+    if (streaming || cfg->stream_k || out->chain)
+        return GEMM_OK;
+    const int bk = 128 / es;
+    const Retiled r = retile({cfg->M, cfg->N, cfg->batch, cdiv64(cfg->K, bk), v.block_m, v.block_n, cfg->split_k,
+                              v.block_m * v.block_n == 128 * 128 && v.stages == 2});
+    if (!r.block_m)
+        return GEMM_OK;
+    const VariantFns *const fns = pipelined_of(dtype, r.block_m, r.block_n, cfg->b_layout, ragged);
+    const int64_t r_kps = cdiv64(cdiv64(cfg->K, bk), r.split) * bk;
+    // (its ring asks for at most six slabs more than the slice has; 32-bit offsets as above)
+    if (!fns || (int64_t)r.block_m * cfg->lda * es >= lim ||
+        (cfg->b_layout ? (int64_t)r.block_n : r_kps + 6 * bk) * cfg->ldb * es >= lim)
+        return GEMM_OK;
+    out->fns = fns;
+    out->kind = ragged ? GEMM_KERNEL_PIPELINED_RAGGED : GEMM_KERNEL_PIPELINED;
+    out->kps = r_kps;
+    out->tiles_m = cdiv64(cfg->M, r.block_m);
+    out->tiles_n = cdiv64(cfg->N, r.block_n);
+    out->block_m = r.block_m;
+    out->block_n = r.block_n;
+    out->split = r.split;
+    out->group_m = retiled_group_m(r.block_m, r.block_n);
     return GEMM_OK;
 }
 
@@ -506,9 +553,9 @@ static int run_impl(const gemm_cfg *cfg, const void *A, const void *B, void *C, 
     a.beta = cfg->beta;
     a.tiles_m = (int)p.tiles_m;
     a.tiles_n = (int)p.tiles_n;
-    a.split_k = cfg->split_k;
+    a.split_k = p.split;
     a.k_per_split = (int)p.kps;
-    a.group_m = (int)std::min<int64_t>(cfg->group_m, p.tiles_m);   // a band taller than the grid is the whole grid
+    a.group_m = (int)std::min<int64_t>(p.group_m, p.tiles_m);   // a band taller than the grid is the whole grid
     a.xcd_remap = cfg->xcd_remap ? 1 : 0;
     a.n_xcd = hw_current().n_xcd;
     a.batch = cfg->batch;
@@ -527,7 +574,7 @@ static int run_impl(const gemm_cfg *cfg, const void *A, const void *B, void *C, 
         // twice as high halves how often new rows of A come from beyond the L2, which takes longest beside the stores
         // (65536x2048x128: 128x128 tiles 84 -> 78 us, 256x256 76 -> 73; wider grids lose up to a fifth, and so do batches,
         // whose B changes too: 32 x 2048x2048x128 96 -> 110).
-        const int resident = launcher_of(cfg->dtype, cfg->kernel_id, cfg->b_layout, p.kind).resident;
+        const int resident = p.fns->resident;
         if (a.batch == 1 && p.tiles_n * a.group_m <= 2 * resident)
             a.group_m = (int)std::min<int64_t>(2 * a.group_m, p.tiles_m);
     }
@@ -536,7 +583,7 @@ static int run_impl(const gemm_cfg *cfg, const void *A, const void *B, void *C, 
 
     hipStream_t stream = (hipStream_t)hip_stream;
     const int f16 = (cfg->dtype == GEMM_FP16) ? 1 : 0;
-    if (launcher_of(cfg->dtype, cfg->kernel_id, cfg->b_layout, p.kind).launch(a, stream) != hipSuccess) {
+    if (p.fns->launch(a, stream) != hipSuccess) {
         (void)hipGetLastError();
         return GEMM_ERR_HIP;
     }
@@ -560,7 +607,7 @@ static int run_impl(const gemm_cfg *cfg, const void *A, const void *B, void *C, 
 #undef G355_SUM
         if (hipGetLastError() != hipSuccess)
             return GEMM_ERR_HIP;
-    } else if (cfg->split_k > 1) {
+    } else if (p.split > 1) {
         const size_t quads = (size_t)cfg->M * (size_t)((cfg->N + 3) / 4);
         size_t blocks = (quads + 255) / 256;
         if (blocks > 256 * 8)
@@ -715,23 +762,37 @@ extern "C" int gemm_launched_kernel(const gemm_cfg *cfg, int n_groups, const gem
     if (!cfg || !out4 || (n_groups != 0 && !host_table))
         return GEMM_ERR_NULL;
     int rc, kind = GEMM_KERNEL_PLAIN;
+    Launch p;
     if (n_groups != 0) {
         int64_t total = 0;
         rc = check_grouped_cfg(cfg, n_groups);
         if (!rc)
             rc = plan_grouped(cfg, n_groups, host_table, &total, &kind);
     } else {
-        Launch p;
         rc = plan_launch(cfg, true, 0, &p);
         if (!rc)
             kind = p.kind;
     }
     if (rc)
         return rc;
-    const VariantFns &fns = launcher_of(cfg->dtype, cfg->kernel_id, cfg->b_layout, kind);
+    const VariantFns &fns = n_groups != 0 ? launcher_of(cfg->dtype, cfg->kernel_id, cfg->b_layout, kind) : *p.fns;
     out4[0] = kind;
     out4[1] = fns.waves_m;
     out4[2] = fns.waves_n;
     out4[3] = fns.loop_form;
+    return GEMM_OK;
+}
+
+extern "C" int gemm_launched_tile(const gemm_cfg *cfg, int32_t out3[3])
+{
+    if (!cfg || !out3)
+        return GEMM_ERR_NULL;
+    Launch p;
+    const int rc = plan_launch(cfg, true, 0, &p);
+    if (rc)
+        return rc;
+    out3[0] = p.block_m;
+    out3[1] = p.block_n;
+    out3[2] = p.split;
     return GEMM_OK;
 }

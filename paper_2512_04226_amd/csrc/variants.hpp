@@ -9,7 +9,8 @@
 // three places: the plain and ragged instantiations of the four-wave fp8 256x256x128 tile run form 7, two ragged
 // ones of the eight-wave 256x256 tiles a form that does not spill, and all 256x256 tiles with 128-byte slab rows
 // have a pipelined instantiation beside these (four waves, form 7), which run.hip launches from twenty K slabs
-// per workgroup: WAVES_M x WAVES_N is what runs below that.
+// per workgroup: WAVES_M x WAVES_N is what runs below that.  (And a launch that a pipelined kernel of another tile size does
+// faster runs that one: retile.hpp.)
 // The table holds no timing: the selector prices a variant from its shape and the hardware
 // descriptor alone (Algorithm 3's instruction count times the measured issue interval, plus the
 // slab's fill and synchronisation cost).
