@@ -70,7 +70,7 @@ def build_extension(force=False):
             "-D_GLIBCXX_USE_CXX11_ABI=%d" % torch.compiled_with_cxx11_abi(), "-isystem", os.path.join(root, "include"), "-isystem",
             os.path.join(root, "include", "torch", "csrc", "api", "include"), "-isystem", sysconfig.get_paths()["include"], "-isystem",
             _hip_include(), EXT_SRC, "-o", tmp, "-L" + os.path.join(root, "lib")] +
-           ["-l" + x for x in ("c10", "c10_hip", "torch_cpu", "torch", "torch_python")])
+           ["-l" + x for x in ("c10", "c10_hip", "torch_cpu", "torch_hip", "torch", "torch_python")])
     header = os.path.join(PKG, "..", "include", "gemm.h")
     stamp, same = os.path.join(OBJ, "fastcall.cmd"), " ".join(cmd).replace(tmp, EXT)
     if (not force and os.path.exists(EXT) and os.path.exists(stamp) and open(stamp).read() == same and

@@ -6,6 +6,15 @@
 
 namespace g355 {
 typedef hipError_t (*LaunchFn)(const KernelArgs &, hipStream_t);
+// One launch by the runtime's own entry: the <<<>>> form pushes its configuration, calls a stub that pops it, and leaves its
+// error for another call to fetch.  (An error that an earlier, unrelated runtime call left behind is not ours.)
+template <class A>
+inline hipError_t launch_kernel(void (*kernel)(A), dim3 grid, dim3 block, A args, hipStream_t stream)
+{
+    (void)hipGetLastError();
+    void *list[] = {&args};
+    return hipLaunchKernel((const void *)kernel, grid, block, list, 0, stream);
+}
 typedef hipError_t (*OccupancyFn)(int *blocks_per_cu);
 struct VariantFns {
     LaunchFn launch;
