@@ -373,13 +373,16 @@ typedef enum {
     GEMM_KERNEL_PIPELINED_RAGGED = 4,
     GEMM_KERNEL_CHAINED = 5,          /* many tiles of few K slabs: a workgroup computes several, one after the other
                                          (named for a C that starts on a 128-byte boundary) */
-    GEMM_KERNEL_CHAINED_RAGGED = 6
+    GEMM_KERNEL_CHAINED_RAGGED = 6,
+    GEMM_KERNEL_SLICED = 7,           /* few 16x16 tiles, long K: four waves take a quarter of K each and add up in LDS */
+    GEMM_KERNEL_SLICED_RAGGED = 8
 } gemm_kernel_kind;
 int gemm_launched_kernel(const gemm_cfg *cfg, int n_groups, const gemm_group_rec *host_table, int32_t out4[4]);
 
 /*
  * BLOCK_M, BLOCK_N and the number of K slices that gemm_run launches for a cfg of one problem or strided batch: the cfg's own,
- * or those of a pipelined kernel that fills the chip better (at most the cfg's K slices, so that its workspace holds them).
+ * or those of a pipelined kernel that fills the chip better (at most the cfg's K slices, so that its workspace holds them), or
+ * 16, 16, 1 where the sliced kernel runs.
  * Errors: as gemm_launched_kernel.
  */
 int gemm_launched_tile(const gemm_cfg *cfg, int32_t out3[3]);

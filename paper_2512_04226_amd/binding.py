@@ -461,7 +461,7 @@ _lib.gemm_run_grouped.argtypes = [ctypes.POINTER(gemm_cfg), _int, ctypes.POINTER
 _lib.gemm_launched_kernel.restype = _int
 _lib.gemm_launched_kernel.argtypes = [ctypes.POINTER(gemm_cfg), _int, ctypes.POINTER(gemm_group_rec),
                                       ctypes.POINTER(ctypes.c_int32)]
-KERNEL_KINDS = ("plain", "ragged", "streaming", "pipelined", "pipelined ragged", "chained", "chained ragged")
+KERNEL_KINDS = ("plain", "ragged", "streaming", "pipelined", "pipelined ragged", "chained", "chained ragged", "sliced", "sliced ragged")
 
 
 def gemm_launched_kernel(cfg, table=None):

@@ -164,8 +164,9 @@ struct Tile {
 #endif
     static_assert(LF_ASKED >= 0 && LF_ASKED <= 7, "unknown K-loop form");
     static_assert(FT == 0 || ES == 2, "fp16 is a 16-bit input type");
-    static constexpr int NW = WM * WN;
+    static constexpr int NW = WM * WN;      // waves of a K slice
     static constexpr int NT = WM * WN * 64;
+    static constexpr int KW = 1;            // K slices of a workgroup (see Sliced)
     // ST_ = 1: the weight-streaming instantiation, which the host launches for a grid of one tile row (M <= BLOCK_M)
     // over weights larger than the memory-side cache.  Every byte of B is then read once: its slab loads carry the non-temporal
     // hint, so that the stream does not push A's panel, which every workgroup re-reads, out of the L2 (5-10 % on
@@ -256,6 +257,15 @@ struct Tile {
         return (((krow / B_ROW_DIV) & B_KEY_MASK) << SEG_BITS) ^ (((krow >> 3) & 1) * B_HALF_FLIP);
     }
     __device__ static inline int b_off(int krow, int nbyte) { return krow * RB + (nbyte ^ b_key(krow)); }
+};
+
+// KW groups of a tile's waves in one workgroup, each with a ring of its own, compute the same tile over KW slices of its K
+// range; the sums are added in LDS in slice order and stored once (see sliced.inc for where it is used).
+template <class T_, int KW_>
+struct Sliced : T_ {
+    static constexpr int KW = KW_, NT = T_::NT * KW_, LDS_BYTES = T_::LDS_BYTES * KW_, MIN_WAVES = NT > 256 ? NT / 256 : 1;
+    static_assert(T_::DIRECT && T_::LF != 7 && NT <= 1024 && LDS_BYTES <= 160 * 1024, "direct kernels of the NS-stage ring");
+    static_assert(KW_ * T_::NW * T_::WTM * (T_::WTN * 4 + 16) <= LDS_BYTES, "the sums of all waves fit the rings");
 };
 
 // Workgroup id -> (tile_m, tile_n, k_slice).  Hardware deals consecutive workgroup ids
@@ -401,7 +411,9 @@ __global__ __launch_bounds__(T::NT, T::MIN_WAVES) void gemm_kernel(const KernelA
 
     const int tid = threadIdx.x;
     const int lane = tid & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);   // wave-uniform, kept scalar
+    // wave-uniform, kept scalar; of its K slice's waves
+    const int wave_wg = __builtin_amdgcn_readfirstlane(tid >> 6), slice = T::KW == 1 ? 0 : wave_wg / T::NW;
+    const int wave = T::KW == 1 ? wave_wg : wave_wg % T::NW;
     const int wm = wave / T::WN, wn = wave % T::WN;
 
     for (int seg = 0; seg < nseg; ++seg) {
@@ -442,7 +454,19 @@ __global__ __launch_bounds__(T::NT, T::MIN_WAVES) void gemm_kernel(const KernelA
         out_mode = (args.split_k > 1) ? 1 : 0;
     }
     const int m0 = tm * BM, n0 = tn * BN;
-    const int kt_count = (k_len + BK - 1) / BK;
+    int kt_count = (k_len + BK - 1) / BK;
+    // the slab that ends the K range (of the slice that has it), and the range's end
+    int last_slab = kt_count - 1, last_slice = 0;
+    const int k_end = k_len;
+    if constexpr (T::KW > 1) {
+        // every slice walks as many slabs; what lies beyond the K range arrives as zeros
+        kt_count = (kt_count + T::KW - 1) / T::KW;
+        last_slice = last_slab / kt_count;
+        last_slab -= last_slice * kt_count;
+        k_begin += slice * kt_count * BK;
+        k_len -= slice * kt_count * BK;
+        k_len = k_len < 0 ? 0 : k_len > kt_count * BK ? kt_count * BK : k_len;
+    }
 
     // ---- global -> LDS bookkeeping ----
     // Load instruction i of wave w fills LDS unit u = i*NW + w of the stage: lane l writes the
@@ -706,7 +730,10 @@ __global__ __launch_bounds__(T::NT, T::MIN_WAVES) void gemm_kernel(const KernelA
         for (int l = 0; l < NL; ++l)
             asm volatile("" ::"v"(diag_regs[l]));
 #endif
-        asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(ALLOW) : "memory");
+        if constexpr (T::KW > 1 && T::NW == 1)      // (a wave that shares its ring with no other waits for nobody)
+            asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"(ALLOW) : "memory");
+        else
+            asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(ALLOW) : "memory");
     };
 
     // The compiler cannot tell which LDS bytes a direct-to-LDS load will write, and before an LDS
@@ -715,7 +742,7 @@ __global__ __launch_bounds__(T::NT, T::MIN_WAVES) void gemm_kernel(const KernelA
     // barriers therefore lives in a function whose two stage pointers are `__restrict__`: it
     // refills only the stage that was just freed and reads only the next one, the two never
     // overlap, and the waits that order refills against reads are the explicit ones of publish().
-    G355_LDS uint8_t *const lds = (G355_LDS uint8_t *)smem;
+    G355_LDS uint8_t *const lds = (G355_LDS uint8_t *)smem + slice * (T::LDS_BYTES / T::KW);
     auto mma_kstep = [&](int buf) __attribute__((always_inline)) {
 #ifndef G355_DIAG_SKIP_MFMA
 #pragma unroll
@@ -830,11 +857,11 @@ __global__ __launch_bounds__(T::NT, T::MIN_WAVES) void gemm_kernel(const KernelA
     // Both operands: a NaN in one's padding times the zero of the other would still be a NaN.  Once per K range: 1501 x
     // 3003 x 2005 bf16 45.6 -> 31.2 us against the register-staged two-stage loop that trimmed every slab before.
     auto trim_last_slab = [&](G355_LDS uint8_t *pa, G355_LDS uint8_t *pb) __attribute__((always_inline)) {
-        const int valid = k_len % EPC;
+        const int valid = k_end % EPC;
         if (T::RG && valid) {
             constexpr int EPD = 4 / ES;                // elements per dword
-            const int chunk = k_len % BK / EPC;
-            for (int r = tid; r < BM + (T::BL == 1 ? BN : 0); r += T::NT) {
+            const int chunk = k_end % BK / EPC;
+            for (int r = (T::KW == 1) ? tid : (slice == last_slice) ? tid % (T::NW * 64) : BM + BN; r < BM + (T::BL == 1 ? BN : 0); r += T::NW * 64) {
                 G355_LDS i32x4 *const c = (G355_LDS i32x4 *)(r < BM ? pa + T::a_off(r, chunk) : pb + T::a_off(r - BM, chunk));
                 i32x4 v = *c;
 #pragma unroll
@@ -1012,7 +1039,7 @@ __global__ __launch_bounds__(T::NT, T::MIN_WAVES) void gemm_kernel(const KernelA
             for (int l = 0; l < NL; ++l)
                 issue_one(mode, std::true_type{}, l, s, lds + s * T::STAGE);
         asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"((T::NS - 1) * FULL) : "memory");
-        if (T::RG && kt_count == 1)
+        if (T::RG && last_slab == 0)
             trim_last_slab(lds, lds + T::A_BYTES);
         if constexpr (LF == 6) {
             // Form 6: B fragments are not double-buffered per k-step but pass through a ring of R6 register
@@ -1108,6 +1135,8 @@ __global__ __launch_bounds__(T::NT, T::MIN_WAVES) void gemm_kernel(const KernelA
         // K-contiguous operand; with them the 256x256 tiles on K-contiguous B spilled); the last NS + 1 do test.
         int kt_main = k_len / BK - T::NS;
         kt_main = kt_main < kt_end ? kt_main : kt_end;
+        if (T::KW > 1 && T::RG)                // (the trimming's barrier: all slices pass it in the same iteration)
+            kt_main = kt_main < last_slab - 1 ? kt_main : last_slab - 1;
         for (; kt < kt_main; ++kt) {
             const int next = (stage + 1 == T::NS) ? 0 : stage + 1;
             after_barrier(mode, std::false_type{}, lds + stage * T::STAGE, lds + next * T::STAGE, kt);
@@ -1115,7 +1144,7 @@ __global__ __launch_bounds__(T::NT, T::MIN_WAVES) void gemm_kernel(const KernelA
         }
         for (; kt < kt_end; ++kt) {
             const int next = (stage + 1 == T::NS) ? 0 : stage + 1;
-            if (T::RG && kt + 2 == kt_count)
+            if (T::RG && kt + 1 == last_slab)
                 trim_last_slab(lds + next * T::STAGE, lds + next * T::STAGE + T::A_BYTES);
             after_barrier(mode, std::true_type{}, lds + stage * T::STAGE, lds + next * T::STAGE, kt);
             stage = next;
@@ -1163,6 +1192,63 @@ __global__ __launch_bounds__(T::NT, T::MIN_WAVES) void gemm_kernel(const KernelA
     constexpr int ST_G = (ST_FIT >= 4 && T::TM % 4 == 0) ? 4 : (ST_FIT >= 2 && T::TM % 2 == 0) ? 2 : 1;
     constexpr int ST_G32 = ST_FIT32 >= ST_G ? ST_G : (ST_FIT32 >= 2 && ST_G % 2 == 0) ? 2 : 1;
     const float alpha = args.alpha, beta = args.beta;
+    if constexpr (T::KW > 1) {
+        // Every wave leaves its sums as fp32 in LDS; then each thread adds the KW slices of 8 consecutive columns.
+        constexpr int ROWB = T::WTN * 4 + 16, PART = T::WTM * ROWB;
+        G355_LDS uint8_t *const sums = (G355_LDS uint8_t *)smem;
+        __syncthreads();
+#pragma unroll
+        for (int i = 0; i < T::TM; ++i)
+#pragma unroll
+            for (int j = 0; j < T::TN; ++j)
+#pragma unroll
+                for (int q = 0; q < T::ACC / 4; ++q) {
+                    f32x4 v;
+#pragma unroll
+                    for (int r = 0; r < 4; ++r)
+                        v[r] = acc[j][i][q * 4 + r];
+                    *(G355_LDS f32x4 *)(sums + wave_wg * PART + (i * MI + lane % MI) * ROWB + (j * MI + q * 8 + 4 * (lane / MI)) * 4) = v;
+                }
+        __syncthreads();
+        constexpr int CPR = BN / 8;
+        for (int c = tid; c < BM * CPR; c += T::NT) {
+            const int row = c / CPR, col = c % CPR * 8, m = m0 + row, n = n0 + col;
+            if (m >= pM || n >= pN)
+                continue;
+            const G355_LDS uint8_t *const src = sums + (row / T::WTM * T::WN + col / T::WTN) * PART + row % T::WTM * ROWB + col % T::WTN * 4;
+            f32x4 lo = *(const G355_LDS f32x4 *)src, hi = *(const G355_LDS f32x4 *)(src + 16);
+#pragma unroll
+            for (int s = 1; s < T::KW; ++s) {
+                lo += *(const G355_LDS f32x4 *)(src + s * (T::NW * PART));
+                hi += *(const G355_LDS f32x4 *)(src + s * (T::NW * PART) + 16);
+            }
+            if (out_mode != 0) {
+                const size_t nw = T::RG ? (size_t)(pN + 7) / 8 * 8 : (size_t)pN;
+                float *const dst = args.ws + ((bz * args.split_k + ks) * pM + m) * nw + n;
+                *(f32x4 *)dst = lo;
+                *(f32x4 *)(dst + 4) = hi;
+                continue;
+            }
+            out_t *const dst = (out_t *)pC + bz * args.stride_c + (size_t)m * pldc + n;
+            out8_t o, cin = {};
+            if (beta != 0.f)
+                cin = *(const out8_t *)dst;
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                o[r] = (out_t)(beta != 0.f ? __builtin_fmaf(beta, (float)cin[r], lo[r] * alpha) : lo[r] * alpha);
+                o[r + 4] = (out_t)(beta != 0.f ? __builtin_fmaf(beta, (float)cin[r + 4], hi[r] * alpha) : hi[r] * alpha);
+            }
+            if (!T::RG || n + 8 <= pN) {
+                *(out8_t *)dst = o;
+            } else {
+#pragma unroll
+                for (int r = 0; r < 8; ++r)
+                    if (n + r < pN)
+                        dst[r] = o[r];
+            }
+        }
+        return;
+    }
     // every wave's requests towards LDS have landed (above) and every wave is past its last fragment read
     __syncthreads();
     const int row0 = m0 + wm * T::WTM, n = n0 + wn * T::WTN + lane % ST_CPR * 8;   // first row of the wave tile, the lane's columns

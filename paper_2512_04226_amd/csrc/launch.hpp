@@ -44,4 +44,6 @@ const VariantFns &kLaunchBf16_0(int, int, int),
 const VariantFns &chained_bf16(int block_m, int block_n, int b_layout, int ragged), &chained_fp16(int, int, int, int), &chained_fp8(int, int, int, int);
 // The pipelined direct kernel of a tile size other than 256x256; launch is null for sizes that have none.
 const VariantFns &pipelined_bf16(int block_m, int block_n, int b_layout, int ragged), &pipelined_fp16(int, int, int, int), &pipelined_fp8(int, int, int, int);
+// The sliced kernel: 16x16 tiles, four K slices in a workgroup.
+const VariantFns &sliced_bf16(int b_layout, int ragged), &sliced_fp16(int, int), &sliced_fp8(int, int);
 }  // namespace g355

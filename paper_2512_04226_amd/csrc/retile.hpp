@@ -1,4 +1,4 @@
-// Which tile, and how many K slices, a launch of one problem or strided batch really runs (host only).
+// Which kernel, tile and K slices a launch of one problem or strided batch really runs (host only).
 //
 // The selector ranks the variants of its table; their tiles halve and double, and so do its K splits, so that a pick can leave
 // a third of the CUs without work, or compute a fifth of its rows for padding.  The pipelined kernels (K-loop form 7, four
@@ -82,6 +82,33 @@ inline Retiled retile(const RetileProblem &p)
         }
     }
     return best.block_m == p.block_m && best.block_n == p.block_n && best.split == p.split ? own : best;
+}
+
+// Whether a launch of few 16x16 tiles runs the sliced kernel (sliced.inc) in place of the cfg's.  At most one of its workgroups
+// per CU; the cfg's own kernel must be one that is picked for such shapes (small tiles, or K slices of several workgroups).
+// Time of the sliced kernel over what ran before, 15 shapes of 12 to 256 tiles (M = 1 to 1000), picks:
+//                      K =  768      1024      1536      2048      3072      4096      8192       16384       28672
+//   16-bit, K-contiguous  .94-1.00  .84- .90  .78-1.01  .73-1.02  .63- .99  .58-1.00  .49- .96   .55-1.17   .82-1.61
+//   16-bit, row-major     .91-1.13  .85-1.10  .81-1.10  .74-1.02  .66-1.04  .40-1.12  .69-1.59  1.37-2.3   1.9-3.1
+//   fp8, K-contiguous    1.15-1.29 1.07-1.13 1.02-1.15  .92- .99  .84-1.13  .75-1.10  .40- .85   .48-1.01   .70-1.26
+//   fp8, row-major       1.09-1.29 1.05-1.30  .99-1.30  .92-1.33  .85-1.33  .79-1.31  .40-1.55   .88-2.0   1.2-2.9
+// Of row-major B a 16-column tile reads 32 (fp8: 16) bytes of each k row: from the L2 that is level, from memory it is not, so
+// only few columns (128 tiles: .81-.98 at K = 1536, .66-.93 at 3072), and not against K slices that spread the reading (8 of them
+// 1.12, 16 and 32 .40-.97).  A launch of most CUs over weights that come from memory is bound by those (1.00-1.13 in one piece).
+// Beyond the last K taken the four chains are longer than the second kernel of K slices.
+inline bool runs_sliced(int64_t M, int64_t N, int64_t K, int64_t batch, bool fp8, bool kc, int block_m, int block_n, int split)
+{
+    const int64_t tiles = (M + 15) / 16 * ((N + 15) / 16) * batch;
+    if (tiles > 256 || (split == 1 ? block_m * block_n > 16 * 64 : split < 4 || block_m * block_n > 64 * 128))
+        return false;
+    if (kc) {
+        if (split == 1 && tiles > 160 && N * K * batch * (fp8 ? 1 : 2) > (8 << 20))
+            return false;
+        return K >= (fp8 ? 2048 : 896) && (split == 1 || K <= (fp8 ? 16384 : 12288));
+    }
+    if (split > 1 && split < 16)
+        return false;
+    return fp8 ? tiles <= 64 && K >= 4096 && K <= 8192 : K >= (tiles <= 128 ? 1536 : 2048) && tiles <= 192 && K <= 4096;
 }
 
 // Band height of the rasterisation: the 32 workgroups that an XCD holds cover a region about as high as it is wide.

@@ -486,6 +486,20 @@ static int plan_launch(const gemm_cfg *cfg, bool aligned, uintptr_t c_address, L
     if (streaming || cfg->stream_k || out->chain)
         return GEMM_OK;
     const int bk = 128 / es;
+    if (runs_sliced(cfg->M, cfg->N, cfg->K, cfg->batch, es == 1, cfg->b_layout == GEMM_B_K_CONTIGUOUS, v.block_m, v.block_n, cfg->split_k)) {
+        // (32-bit offsets as above; a wave's window holds its quarter of K, its ring asks for three slabs more)
+        if (16 * cfg->lda * es >= lim || (cfg->b_layout ? (int64_t)16 : cdiv64(cfg->K, 4) + 8 * bk) * cfg->ldb * es >= lim)
+            return GEMM_OK;
+        out->fns = &(dtype == GEMM_FP16 ? sliced_fp16 : dtype == GEMM_BF16 ? sliced_bf16 : sliced_fp8)(cfg->b_layout, ragged);
+        out->kind = ragged ? GEMM_KERNEL_SLICED_RAGGED : GEMM_KERNEL_SLICED;
+        out->kps = cdiv64(cfg->K, 2 * bk) * (2 * bk);
+        out->tiles_m = cdiv64(cfg->M, 16);
+        out->tiles_n = cdiv64(cfg->N, 16);
+        out->block_m = out->block_n = 16;
+        out->split = 1;
+        out->group_m = retiled_group_m(16, 16);
+        return GEMM_OK;
+    }
     const Retiled r = retile({cfg->M, cfg->N, cfg->batch, cdiv64(cfg->K, bk), v.block_m, v.block_n, cfg->split_k,
                               v.block_m * v.block_n == 128 * 128 && v.stages == 2});
     if (!r.block_m)
