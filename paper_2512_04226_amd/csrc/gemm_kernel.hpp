@@ -186,7 +186,7 @@ struct Tile {
     // 2x2 grid of waves and 128-byte slab rows; a tile that has neither runs form 0 when the form is forced on
     // every tile
     static constexpr bool FITS6 = TN >= 3 && (KSTEPS * TN) % 4 == 0 && KSTEPS >= 2;
-    static constexpr bool FITS7 = BM % 64 == 0 && BN % 128 == 0 && WM == 2 && WN == 2 && BK * ES == 128 && KSTEPS == 2 && (ST == 0 || ST == 3);
+    static constexpr bool FITS7 = BM % 64 == 0 && BN % 128 == 0 && WM == 2 && WN == 2 && BK * ES == 128 && KSTEPS == 2 && (ST == 0 || ST >= 3);
     static constexpr int LF = ((LF_ASKED == 6 && !FITS6) || (LF_ASKED == 7 && !FITS7)) ? 0 : LF_ASKED;
     static constexpr int RA = BK * ES;                      // bytes per A row in LDS
     static constexpr int RB = (BL == 0) ? BN * ES : BK * ES; // bytes per B row in LDS (a k row, or an n row when K-contiguous)
@@ -945,9 +945,9 @@ __global__ __launch_bounds__(T::NT, T::MIN_WAVES) void gemm_kernel(const KernelA
                 const unsigned adv = (T::BL == 0) ? (unsigned)kk * (unsigned)(pldb * ES) : (unsigned)(kk * ES);
                 if constexpr (decltype(tail)::value) {
                     const unsigned off = (T::BL == 0 || b_kcol[i] + kk < k_len) ? b_voff[i] + adv : OOB_OFFSET;
-                    __builtin_amdgcn_raw_ptr_buffer_load_lds(rsB, dst, 16, off, 0, 0, G355_LOAD_DEFAULT);
+                    __builtin_amdgcn_raw_ptr_buffer_load_lds(rsB, dst, 16, off, 0, 0, T::STREAMABLE_B ? G355_LOAD_STREAM : G355_LOAD_DEFAULT);
                 } else {
-                    __builtin_amdgcn_raw_ptr_buffer_load_lds(rsB, dst, 16, b_voff[i], (int)adv, 0, G355_LOAD_DEFAULT);
+                    __builtin_amdgcn_raw_ptr_buffer_load_lds(rsB, dst, 16, b_voff[i], (int)adv, 0, T::STREAMABLE_B ? G355_LOAD_STREAM : G355_LOAD_DEFAULT);
                 }
             };
             // MFMA number m of a k-step: 2x2 blocks of MFMA tiles, walked as a U, so that every MFMA but one in four
@@ -979,20 +979,29 @@ __global__ __launch_bounds__(T::NT, T::MIN_WAVES) void gemm_kernel(const KernelA
             typedef std::integral_constant<int, T::A_LOADS> LA;
             typedef std::integral_constant<int, T::B_LOADS> LB;
             constexpr int ALLOW7 = (NA - 2) * T::A_LOADS + (NB - 2) * T::B_LOADS;
+            // position in K of a slab (streaming: `rot` above)
+            auto at_k = [&](int slab) __attribute__((always_inline)) {
+                if constexpr (T::STREAMABLE_B && T::BL == 1) {
+                    const int p = slab + rot;
+                    return (slab < kt_count ? (p >= kt_count ? p - kt_count : p) : slab) * BK;
+                }
+                return slab * BK;
+            };
             auto slab7 = [&](auto tail, G355_LDS uint8_t *__restrict__ fa, G355_LDS uint8_t *__restrict__ fb,
                              const G355_LDS uint8_t *__restrict__ na, const G355_LDS uint8_t *__restrict__ nb, int s)
                              __attribute__((always_inline)) {
-                kstep7(K1{}, na, nb, LB{}, [&](auto l) __attribute__((always_inline)) { load_b(tail, decltype(l)::value, (s + NB) * BK, fb); });
-                kstep7(K0{}, na, nb, LA{}, [&](auto l) __attribute__((always_inline)) { load_a(tail, decltype(l)::value, (s + NA) * BK, fa); });
+                const int ka = at_k(s + NA), kb = at_k(s + NB);
+                kstep7(K1{}, na, nb, LB{}, [&](auto l) __attribute__((always_inline)) { load_b(tail, decltype(l)::value, kb, fb); });
+                kstep7(K0{}, na, nb, LA{}, [&](auto l) __attribute__((always_inline)) { load_a(tail, decltype(l)::value, ka, fa); });
                 wait_and_barrier<ALLOW7, true>();
             };
             const std::true_type tested{};
             const std::false_type inside{};
             static_for<0, NA>([&](auto uc) __attribute__((always_inline)) {
                 constexpr int u = decltype(uc)::value;
-                static_for<0, T::A_LOADS>([&](auto l) __attribute__((always_inline)) { load_a(tested, decltype(l)::value, u * BK, a_at(u)); });
+                static_for<0, T::A_LOADS>([&](auto l) __attribute__((always_inline)) { load_a(tested, decltype(l)::value, at_k(u), a_at(u)); });
                 if constexpr (u < NB)
-                    static_for<0, T::B_LOADS>([&](auto l) __attribute__((always_inline)) { load_b(tested, decltype(l)::value, u * BK, b_at(u)); });
+                    static_for<0, T::B_LOADS>([&](auto l) __attribute__((always_inline)) { load_b(tested, decltype(l)::value, at_k(u), b_at(u)); });
             });
             wait_and_barrier<(NA - 1) * T::A_LOADS + (NB - 1) * T::B_LOADS, false>();
             if (T::RG && kt_count == 1)
@@ -1002,7 +1011,7 @@ __global__ __launch_bounds__(T::NT, T::MIN_WAVES) void gemm_kernel(const KernelA
             wait_and_barrier<ALLOW7, true>();
             int s = 0;
             const int end = kt_count - 1;
-            const int whole = k_len / BK - NA;      // slabs below this one load only slabs that lie inside the K range
+            const int whole = k_len / BK - NA;      // slabs below this one load only slabs that lie inside the K range (NA >= NB)
             for (; s + PERIOD <= whole; s += PERIOD)
                 static_for<0, PERIOD>([&](auto ic) __attribute__((always_inline)) {
                     constexpr int i = decltype(ic)::value;

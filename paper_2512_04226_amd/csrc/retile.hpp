@@ -84,6 +84,22 @@ inline Retiled retile(const RetileProblem &p)
     return best.block_m == p.block_m && best.block_n == p.block_n && best.split == p.split ? own : best;
 }
 
+// The same for a launch of one tile row over weights beyond the memory-side cache: above 128 rows the pipelined streaming kernel,
+// of 192 rows where they suffice, 128 columns to a tile, whose loads are spread over the matrix instructions.  What bounds it is
+// the CU's vector-memory path, on which A's hits in the L2 wait behind B's misses (256x28672x8192 bf16: A alone 33 us, B alone 74,
+// both 119 without a matrix instruction); a bit less of A is fetched for nothing, and nothing else waits.  Its time over the
+// eight-wave kernel's, bf16 on six and fp8 on two shapes of weights, K splits halved where the cfg's tile has 256 columns:
+//   160 rows  row-major .90-.94 (fp8 1.00-1.01), K-contiguous .86-.99 (fp8 .95)   256 rows  .86-.91 (.88-.89), .86-.97 (.95-.96)
+// At 128 rows and below it is level with the 128x128 tile (.95-1.02) and behind the 128x256 one (1.0-1.25).
+inline Retiled retile_streaming(const RetileProblem &p)
+{
+    const int split = p.block_n == 256 && p.split > 1 ? p.split / 2 : p.split;
+    const int64_t per_slice = (p.slabs + split - 1) / split;
+    if (p.batch != 1 || p.M <= 128 || p.M > 256 || p.block_n < 128 || per_slice < 9 || (p.slabs + per_slice - 1) / per_slice != split)
+        return {0, 0, 0};
+    return {p.M <= 192 ? 192 : 256, 128, split};
+}
+
 // Whether a launch of few 16x16 tiles runs the sliced kernel (sliced.inc) in place of the cfg's.  At most one of its workgroups
 // per CU; the cfg's own kernel must be one that is picked for such shapes (small tiles, or K slices of several workgroups).
 // Time of the sliced kernel over what ran before, 15 shapes of 12 to 256 tiles (M = 1 to 1000), picks:

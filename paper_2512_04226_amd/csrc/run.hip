@@ -249,7 +249,7 @@ int kernel_of(int dtype, int id, int bl, bool ragged, bool streaming, int64_t sl
 inline int64_t cdiv64(int64_t a, int64_t b) { return (a + b - 1) / b; }
 
 // The pipelined kernel of a tile of retile.hpp (nullptr: not built, as in the builds that compare K-loop forms).
-const VariantFns *pipelined_of(int dtype, int block_m, int block_n, int b_layout, int ragged)
+const VariantFns *pipelined_of(int dtype, int block_m, int block_n, int b_layout, int ragged, int streaming)
 {
     const VariantFns *f = nullptr;
     if (block_m == 256 && block_n == 256) {
@@ -259,7 +259,7 @@ const VariantFns *pipelined_of(int dtype, int block_m, int block_n, int b_layout
                 f = &launcher_of(dtype, id, b_layout, ragged ? GEMM_KERNEL_PIPELINED_RAGGED : GEMM_KERNEL_PIPELINED);
         }
     } else {
-        f = &(dtype == GEMM_FP16 ? pipelined_fp16 : dtype == GEMM_BF16 ? pipelined_bf16 : pipelined_fp8)(block_m, block_n, b_layout, ragged);
+        f = &(dtype == GEMM_FP16 ? pipelined_fp16 : dtype == GEMM_BF16 ? pipelined_bf16 : pipelined_fp8)(block_m, block_n, b_layout, ragged, streaming);
     }
     return f && f->launch ? f : nullptr;
 }
@@ -483,10 +483,10 @@ static int plan_launch(const gemm_cfg *cfg, bool aligned, uintptr_t c_address, L
     out->split = cfg->split_k;
     out->group_m = cfg->group_m;
     out->fns = &launcher_of(dtype, cfg->kernel_id, cfg->b_layout, out->kind);
-    if (streaming || cfg->stream_k || out->chain)
+    if (cfg->stream_k || out->chain)
         return GEMM_OK;
     const int bk = 128 / es;
-    if (runs_sliced(cfg->M, cfg->N, cfg->K, cfg->batch, es == 1, cfg->b_layout == GEMM_B_K_CONTIGUOUS, v.block_m, v.block_n, cfg->split_k)) {
+    if (!streaming && runs_sliced(cfg->M, cfg->N, cfg->K, cfg->batch, es == 1, cfg->b_layout == GEMM_B_K_CONTIGUOUS, v.block_m, v.block_n, cfg->split_k)) {
         // (32-bit offsets as above; a wave's window holds its quarter of K, its ring asks for three slabs more)
         if (16 * cfg->lda * es >= lim || (cfg->b_layout ? (int64_t)16 : cdiv64(cfg->K, 4) + 8 * bk) * cfg->ldb * es >= lim)
             return GEMM_OK;
@@ -500,18 +500,19 @@ static int plan_launch(const gemm_cfg *cfg, bool aligned, uintptr_t c_address, L
         out->group_m = retiled_group_m(16, 16);
         return GEMM_OK;
     }
-    const Retiled r = retile({cfg->M, cfg->N, cfg->batch, cdiv64(cfg->K, bk), v.block_m, v.block_n, cfg->split_k,
-                              v.block_m * v.block_n == 128 * 128 && v.stages == 2});
+    const RetileProblem problem = {cfg->M, cfg->N, cfg->batch, cdiv64(cfg->K, bk), v.block_m, v.block_n, cfg->split_k,
+                                   v.block_m * v.block_n == 128 * 128 && v.stages == 2};
+    const Retiled r = streaming ? retile_streaming(problem) : retile(problem);
     if (!r.block_m)
         return GEMM_OK;
-    const VariantFns *const fns = pipelined_of(dtype, r.block_m, r.block_n, cfg->b_layout, ragged);
+    const VariantFns *const fns = pipelined_of(dtype, r.block_m, r.block_n, cfg->b_layout, ragged, streaming);
     const int64_t r_kps = cdiv64(cdiv64(cfg->K, bk), r.split) * bk;
     // (its ring asks for at most six slabs more than the slice has; 32-bit offsets as above)
     if (!fns || (int64_t)r.block_m * cfg->lda * es >= lim ||
         (cfg->b_layout ? (int64_t)r.block_n : r_kps + 6 * bk) * cfg->ldb * es >= lim)
         return GEMM_OK;
     out->fns = fns;
-    out->kind = ragged ? GEMM_KERNEL_PIPELINED_RAGGED : GEMM_KERNEL_PIPELINED;
+    out->kind = streaming ? GEMM_KERNEL_STREAMING : ragged ? GEMM_KERNEL_PIPELINED_RAGGED : GEMM_KERNEL_PIPELINED;
     out->kps = r_kps;
     out->tiles_m = cdiv64(cfg->M, r.block_m);
     out->tiles_n = cdiv64(cfg->N, r.block_n);

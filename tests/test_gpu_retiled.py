@@ -10,7 +10,7 @@ import subprocess
 import pytest
 import torch
 
-from test_gpu_chained import BF16, E4M3, FP16, SLAB, _problem, _run
+from test_gpu_chained import BF16, E4M3, FP16, IN, SLAB, _problem, _run
 from test_kernel_resources import CSRC, HIPCC
 
 # (what runs; the cfg's tile and K slices; M, N, K slabs, batch): the ring's prologue alone and a turn of its period more,
@@ -107,3 +107,34 @@ def test_the_largest_retiled_kernels_keep_no_scratch(tmp_path):
     assert r.returncode == 0, r.stderr[-2000:]
     scratch = [int(x) for x in re.findall(r"ScratchSize \[bytes/lane\]: (\d+)", r.stderr)]
     assert scratch == [0] * 8, scratch
+
+
+# One tile row of 129 to 256 rows over large weights (the threshold lowered, so that small ones count): K walked in a rotated order
+# where the pitch is a power of two of 16 KiB and more, K slices that are halved, a last slab that ends inside the K range
+@pytest.mark.gpu
+@pytest.mark.parametrize("M,N,K_bytes,tile,runs", [(129, 384, 16384, (256, 128, 1), (192, 128, 1)), (192, 400, 16384, (256, 128, 2), (192, 128, 2)),
+                                                   (193, 272, 18432, (256, 256, 2), (256, 128, 1)), (256, 144, 16384 - 96, (256, 256, 4), (256, 128, 2))])
+@pytest.mark.parametrize("dtype", [BF16, E4M3, FP16])
+@pytest.mark.parametrize("bl", [0, 1])
+def test_streaming_launch_of_a_pipelined_tile_is_exact(M, N, K_bytes, tile, runs, dtype, bl):
+    from gpu_util import workspace_for
+    from paper_2512_04226_amd import binding as g
+    K = K_bytes // (1 if dtype == E4M3 else 2)
+    hw = g.gemm_hw_get()
+    hw.mall_bytes = 1 << 20
+    g.gemm_hw_set(hw)
+    try:
+        c = _cfg(g, tile, M, N, K, 1, dtype, bl)
+        gen = torch.Generator(device="cuda").manual_seed(5)
+        A, B = (torch.randint(-3, 4, s, device="cuda", generator=gen).float() for s in ((M, K), (K, N)))
+        ref = (A.double() @ B.double()).to(torch.float16 if dtype == FP16 else torch.bfloat16)
+        A, B = (x.to(IN[dtype]) for x in (A, B.t().contiguous() if bl else B))
+        c.lda, c.ldb, c.ldc = A.stride(0), B.stride(0), N
+        assert g.gemm_launched_kernel(c) == ("streaming", 2, 2, 7) and g.gemm_launched_tile(c) == runs
+        workspace_for(c)
+        C = torch.full((M + 1, N), 99.0, dtype=ref.dtype, device="cuda")
+        g.gemm_run(c, A, B, C)
+        torch.cuda.synchronize()
+        assert torch.equal(C[:M], ref) and bool((C[M] == 99.0).all()), c.describe()
+    finally:
+        g.gemm_hw_reset()
