@@ -229,6 +229,8 @@ int gemm_cfg_at_batched(int idx, int64_t M, int64_t N, int64_t K, int64_t batch,
  *   gemm_grouped_locate  host only: what workgroup `workgroup` of the launch computes, by the
  *                     kernel's own arithmetic: out3 = {record index, tile_m, tile_n}, or {-1,-1,-1}
  *                     for an idle slot.  GEMM_ERR_INDEX beyond the launch's workgroups.
+ *                     (The pipelined kernel may share the tiles of the last slots between two or four
+ *                     workgroups each: those are slots by this count too.)
  * 1 <= n_groups <= 4096.  Errors as for gemm_select / gemm_run; GEMM_ERR_CFG_ILLEGAL also when cfg
  * is not a grouped cfg for n_groups groups or a record does not belong to it.
  */

@@ -57,6 +57,8 @@ struct KernelArgs {
             // above are unused and each workgroup reads its group's record from this device table.
             const GroupRec *groups;
             int n_groups;
+            // pipelined grouped kernel: from slot tail_slot of an XCD on, tail_parts (1, 2 or 4) workgroups share a tile's rows
+            int tail_slot, tail_parts;
         };
         DirectPlan direct;   // general == 0
     };
@@ -143,7 +145,8 @@ typedef float f32x16 __attribute__((ext_vector_type(16)));
 // all others, and once the last slab has landed in LDS its workgroup clears those bytes there (see trim_last_slab);
 // results at the ragged edge of C are stored element by element.  Everything else is shared with the plain form.
 // ST_: 1 = the weight-streaming instantiation for grids of one tile row (see STREAMABLE_B in Tile), 2 = the tile of a
-// chained kernel (chained.hpp), 3 and 4 = 0 and 1 for launches that are neither Stream-K nor grouped (see DIRECT in Tile).
+// chained kernel (chained.hpp), 3 and 4 = 0 and 1 for launches that are neither Stream-K nor grouped (see DIRECT in Tile), 6 = 0
+// for grouped launches only (see GROUPED).
 template <int ES_, int BM_, int BN_, int BK_, int WM_, int WN_, int MI_, int NS_, int BL_, int FT_ = 0, int LF_ = 0, int RG_ = 0, int ST_ = 0>
 struct Tile {
     static constexpr int ES = ES_, BM = BM_, BN = BN_, BK = BK_, WM = WM_, WN = WN_, MI = MI_, NS = NS_, BL = BL_;
@@ -156,7 +159,9 @@ struct Tile {
     // in flight.  The instantiations without the two get there in about 150, with tile coordinates by multiplication
     // (fast_div.hpp).  bf16, row-major B, before and after: 16x64x64 3.1 -> 2.3 us, 512^3 4.4 -> 3.7, 1024^3 7.7 -> 7.0,
     // 2048x2048x512 8.9 -> 8.5, 1501x3003x2005 31.3 -> 30.0, 4096^3 94.1 -> 92.8; K-contiguous 8x4096x4096 9.8 -> 8.5.
-    static constexpr bool DIRECT = ST >= 3;
+    static constexpr bool DIRECT = ST == 3 || ST == 4;
+    // A grouped launch of the pipelined 256x256 tiles: without the Stream-K part, with loops for short last tile rows.
+    static constexpr bool GROUPED = ST == 6;
 #ifdef G355_FORCE_LOOP_FORM
     static constexpr int LF_ASKED = G355_FORCE_LOOP_FORM;
 #else
@@ -195,6 +200,9 @@ struct Tile {
     // form 7: slabs of A and of B that the ring holds, and whether they share five units
     static constexpr int RING_B = (160 * 1024 / STAGE >= 3) ? (160 * 1024 / STAGE < 6 ? 160 * 1024 / STAGE : 6) : 2, RING_A = RING_B > 2 ? RING_B : 3;
     static constexpr bool RING_SHARED = RING_B == 2 && A_BYTES == B_BYTES;
+    // rows from one MFMA row block of a wave to its next.  Grouped: WM blocks, so that the first of them hold a short tile's rows
+    // for all waves alike
+    static constexpr int A_PITCH = GROUPED ? MI * WM : MI, A_FIRST = GROUPED ? MI : WTM;
     static constexpr int LDS_BYTES = (LF == 7) ? RING_A * A_BYTES + RING_B * B_BYTES : NS * STAGE;
     // Waves per SIMD the registers must leave room for.  What a workgroup needs by itself, except in the ragged instantiation
     // of the two-stage 128x64 and 64x128 tiles on eight waves: their 48 KB of LDS let three workgroups share a CU, and the
@@ -373,8 +381,9 @@ __global__ __launch_bounds__(T::NT, T::MIN_WAVES) void gemm_kernel(const KernelA
 
     // Work of this workgroup: one (tile, K slice) for a data-parallel or split-K launch, up to
     // two (tile, slab range) segments for a stream-K worker.
-    const int sk_workers = T::DIRECT ? 0 : args.sk.workers;
-    const bool sk_worker = !T::DIRECT && (int)blockIdx.x < sk_workers;
+    constexpr bool MAY_SPLIT = !T::DIRECT && !T::GROUPED;      // be a Stream-K worker
+    const int sk_workers = MAY_SPLIT ? args.sk.workers : 0;
+    const bool sk_worker = MAY_SPLIT && (int)blockIdx.x < sk_workers;
     SkSegment segs[2];
     int nseg = 1;
     if (sk_worker)
@@ -385,12 +394,20 @@ __global__ __launch_bounds__(T::NT, T::MIN_WAVES) void gemm_kernel(const KernelA
     void *pC = args.C;
     int pM = args.M, pN = args.N, pK = args.K, plda = args.lda, pldb = args.ldb, pldc = args.ldc;
     int g_tm = 0, g_tn = 0;
-    const bool grouped = !T::DIRECT && args.n_groups > 0;
+    int row_part = 0, part_rows = BM;       // grouped: the rows of its tile that the workgroup computes
+    const bool grouped = T::GROUPED || (!T::DIRECT && args.n_groups > 0);
     // one tile row: B is read once; one tile column: A is read once (see Tile::STREAMABLE_*)
     bool stream_a = args.tiles_n == 1, stream_b = T::STREAMABLE_B;
     if (grouped) {
         const int X = args.xcd_remap ? args.n_xcd : 1;
-        const int x = (int)blockIdx.x % X, q = (int)blockIdx.x / X;
+        const int x = (int)blockIdx.x % X;
+        int q = (int)blockIdx.x / X;
+        if (T::GROUPED && q >= args.tail_slot) {
+            const int part = (q - args.tail_slot) & (args.tail_parts - 1);
+            q = args.tail_slot + (q - args.tail_slot) / args.tail_parts;
+            part_rows = BM / args.tail_parts;
+            row_part = part * part_rows;
+        }
         const GroupRec *r = args.groups + group_of(args.groups, args.n_groups, q);
         const int tiles_m = uniform_i32(r->tiles_m), tiles_n = uniform_i32(r->tiles_n);
         stream_a = tiles_n == 1;
@@ -407,6 +424,8 @@ __global__ __launch_bounds__(T::NT, T::MIN_WAVES) void gemm_kernel(const KernelA
         pldb = uniform_i32(r->ldb);
         pldc = uniform_i32(r->ldc);
         logical_tile(tiles_m, tiles_n, uniform_i32(r->group_m), t, g_tm, g_tn);
+        if (T::GROUPED && g_tm * BM + row_part >= pM)
+            return;   // the tile has no rows in this part
     }
 
     const int tid = threadIdx.x;
@@ -453,7 +472,8 @@ __global__ __launch_bounds__(T::NT, T::MIN_WAVES) void gemm_kernel(const KernelA
             k_len = args.k_per_split;
         out_mode = (args.split_k > 1) ? 1 : 0;
     }
-    const int m0 = tm * BM, n0 = tn * BN;
+    const int m0 = tm * BM + (T::GROUPED ? row_part : 0), n0 = tn * BN;
+    const int m_end = T::GROUPED && pM - m0 > part_rows ? m0 + part_rows : pM;     // rows from here on are not this workgroup's
     int kt_count = (k_len + BK - 1) / BK;
     // the slab that ends the K range (of the slice that has it), and the range's end
     int last_slab = kt_count - 1, last_slice = 0;
@@ -488,7 +508,7 @@ __global__ __launch_bounds__(T::NT, T::MIN_WAVES) void gemm_kernel(const KernelA
     const uint8_t *Bbase = (T::BL == 0)
                                ? (const uint8_t *)pB + (bz * args.stride_b + (size_t)k_begin * pldb + n0_ld) * ES
                                : (const uint8_t *)pB + (bz * args.stride_b + (size_t)n0_ld * pldb + k_begin) * ES;
-    const int a_rows_valid = (pM - m0 < BM) ? (pM - m0) : BM;
+    const int a_rows_valid = (m_end - m0 < BM) ? (m_end - m0) : BM;
     const int b_rows_valid = (pN - n0 < BN) ? (pN - n0) : BN;      // K-contiguous B only
     // (ragged instantiation: the window ends with the chunk that holds the last valid element, so that this
     // chunk is fetched whole and trimmed in LDS; rows are a whole number of chunks apart, so it lies
@@ -597,7 +617,7 @@ __global__ __launch_bounds__(T::NT, T::MIN_WAVES) void gemm_kernel(const KernelA
 
     // ---- fragment addressing (per lane, constant over the K loop) ----
     // column operand (from A): lane holds row m = lane % MI, k in [kg*KL, kg*KL + KL)
-    const int a_row = wm * T::WTM + (lane % MI);
+    const int a_row = wm * T::A_FIRST + (lane % MI);
     const int a_kg = lane / MI;
     // row operand (from B, transposed): 16-lane group g, lane i of it supplies the address of
     // k row (i / LPR) and n block (i % LPR); it receives n = i, k = 0 .. 64/16*ES ... of the group
@@ -921,14 +941,6 @@ __global__ __launch_bounds__(T::NT, T::MIN_WAVES) void gemm_kernel(const KernelA
                     dst = __builtin_bit_cast(frag_t, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
                 }
             };
-            auto frag = [&](const G355_LDS uint8_t *pa, const G355_LDS uint8_t *pb, int k, int u) __attribute__((always_inline)) {
-                if (u < T::TM)
-                    kc_frag(af[k][u], pa, fa_off[k], u * MI);
-                else if (T::BL == 1)
-                    kc_frag(bfr[k][u - T::TM], pb, fb_off[k], (u - T::TM) * MI);
-                else
-                    frag_from(pa, pb, k, k, u);
-            };
             // one load instruction of A's (B's) slab at K position kk; a slab wholly inside the K range needs no test and
             // its position is the scalar offset
             auto load_a = [&](auto tail, int i, int kk, G355_LDS uint8_t *unit) __attribute__((always_inline)) {
@@ -950,35 +962,47 @@ __global__ __launch_bounds__(T::NT, T::MIN_WAVES) void gemm_kernel(const KernelA
                     __builtin_amdgcn_raw_ptr_buffer_load_lds(rsB, dst, 16, b_voff[i], (int)adv, 0, T::STREAMABLE_B ? G355_LOAD_STREAM : G355_LOAD_DEFAULT);
                 }
             };
+            // the tile's first TM7 row blocks per wave
+            auto run7 = [&](auto tm7) __attribute__((always_inline)) {
+            constexpr int TM7 = decltype(tm7)::value, MN7 = TM7 * T::TN, NF7 = TM7 + T::TN;
+            constexpr int A7 = TM7 * T::WM * MI * T::RA / 1024 / T::NW;      // loads that hold them
+            auto frag = [&](const G355_LDS uint8_t *pa, const G355_LDS uint8_t *pb, int k, int u) __attribute__((always_inline)) {
+                if (u < TM7)
+                    kc_frag(af[k][u], pa, fa_off[k], u * T::A_PITCH);
+                else if (T::BL == 1)
+                    kc_frag(bfr[k][u - TM7], pb, fb_off[k], (u - TM7) * MI);
+                else
+                    frag_from(pa, pb, k, k, u - TM7 + T::TM);
+            };
             // MFMA number m of a k-step: 2x2 blocks of MFMA tiles, walked as a U, so that every MFMA but one in four
             // shares an operand with the one before (1 % on N(0,1) data against rows of eight: fewer operand changes)
             auto mma_at = [&](int buf, int m) __attribute__((always_inline)) {
-                if constexpr (T::TM % 2 || T::TN % 2) {
-                    mma_one(buf, m / T::TM, (m / T::TM) % 2 ? T::TM - 1 - m % T::TM : m % T::TM);
+                if constexpr (TM7 % 2 || T::TN % 2) {
+                    mma_one(buf, m / TM7, (m / TM7) % 2 ? TM7 - 1 - m % TM7 : m % TM7);
                 } else {
                     const int b = m / 4, q = m % 4;
-                    mma_one(buf, b / (T::TM / 2) * 2 + q / 2, b % (T::TM / 2) * 2 + (q == 1 || q == 2));
+                    mma_one(buf, b / (TM7 / 2) * 2 + q / 2, b % (TM7 / 2) * 2 + (q == 1 || q == 2));
                 }
             };
             // One k-step on the fragments in buffer KB.  Slot m: its share of the other buffer's fragment reads (from
             // pa / pb, spread over the first three quarters), MFMA m, its share of the slab's loads of one operand.
-            constexpr int HR = MN * 3 / 4;
+            constexpr int HR = MN7 * 3 / 4;
             auto kstep7 = [&](auto kb, const G355_LDS uint8_t *pa, const G355_LDS uint8_t *pb, auto loads, auto load) __attribute__((always_inline)) {
                 constexpr int KB = decltype(kb)::value, LPS = decltype(loads)::value;
-                static_for<0, MN>([&](auto mc) __attribute__((always_inline)) {
+                static_for<0, MN7>([&](auto mc) __attribute__((always_inline)) {
                     constexpr int m = decltype(mc)::value;
-                    constexpr int u0 = (m * NF + HR - 1) / HR, u1 = ((m + 1) * NF + HR - 1) / HR;
-                    static_for<(u0 < NF ? u0 : NF), (u1 < NF ? u1 : NF)>(
+                    constexpr int u0 = (m * NF7 + HR - 1) / HR, u1 = ((m + 1) * NF7 + HR - 1) / HR;
+                    static_for<(u0 < NF7 ? u0 : NF7), (u1 < NF7 ? u1 : NF7)>(
                         [&](auto u) __attribute__((always_inline)) { frag(pa, pb, KB ^ 1, decltype(u)::value); });
                     mma_at(KB, m);
-                    static_for<(m * LPS + MN - 1) / MN, ((m + 1) * LPS + MN - 1) / MN>(load);
+                    static_for<(m * LPS + MN7 - 1) / MN7, ((m + 1) * LPS + MN7 - 1) / MN7>(load);
                     __builtin_amdgcn_sched_barrier(0);
                 });
             };
             // from the barrier of slab s to the barrier of slab s + 1 (fa, fb: where A(s+NA) and B(s+NB) go; na, nb: A(s+1), B(s+1))
-            typedef std::integral_constant<int, T::A_LOADS> LA;
+            typedef std::integral_constant<int, A7> LA;
             typedef std::integral_constant<int, T::B_LOADS> LB;
-            constexpr int ALLOW7 = (NA - 2) * T::A_LOADS + (NB - 2) * T::B_LOADS;
+            constexpr int ALLOW7 = (NA - 2) * A7 + (NB - 2) * T::B_LOADS;
             // position in K of a slab (streaming: `rot` above)
             auto at_k = [&](int slab) __attribute__((always_inline)) {
                 if constexpr (T::STREAMABLE_B && T::BL == 1) {
@@ -999,14 +1023,14 @@ __global__ __launch_bounds__(T::NT, T::MIN_WAVES) void gemm_kernel(const KernelA
             const std::false_type inside{};
             static_for<0, NA>([&](auto uc) __attribute__((always_inline)) {
                 constexpr int u = decltype(uc)::value;
-                static_for<0, T::A_LOADS>([&](auto l) __attribute__((always_inline)) { load_a(tested, decltype(l)::value, at_k(u), a_at(u)); });
+                static_for<0, A7>([&](auto l) __attribute__((always_inline)) { load_a(tested, decltype(l)::value, at_k(u), a_at(u)); });
                 if constexpr (u < NB)
                     static_for<0, T::B_LOADS>([&](auto l) __attribute__((always_inline)) { load_b(tested, decltype(l)::value, at_k(u), b_at(u)); });
             });
-            wait_and_barrier<(NA - 1) * T::A_LOADS + (NB - 1) * T::B_LOADS, false>();
+            wait_and_barrier<(NA - 1) * A7 + (NB - 1) * T::B_LOADS, false>();
             if (T::RG && kt_count == 1)
                 trim_last_slab(a_at(0), b_at(0));
-            static_for<0, NF>([&](auto u) __attribute__((always_inline)) { frag(a_at(0), b_at(0), 0, decltype(u)::value); });
+            static_for<0, NF7>([&](auto u) __attribute__((always_inline)) { frag(a_at(0), b_at(0), 0, decltype(u)::value); });
             kstep7(K0{}, a_at(0), b_at(0), std::integral_constant<int, 0>{}, [](auto) {});
             wait_and_barrier<ALLOW7, true>();
             int s = 0;
@@ -1038,7 +1062,26 @@ __global__ __launch_bounds__(T::NT, T::MIN_WAVES) void gemm_kernel(const KernelA
                     ub = nb;
                 }
             }
-            static_for<0, MN>([&](auto mc) __attribute__((always_inline)) { mma_at(1, decltype(mc)::value); });
+            static_for<0, MN7>([&](auto mc) __attribute__((always_inline)) { mma_at(1, decltype(mc)::value); });
+            };
+            // A tile that ends the matrix with a quarter of its rows or less, half or three quarters, runs a loop of that height: the
+            // chip's power goes into rows that exist, and the workgroup ends sooner.  Twelve drawn groups with 0.59 to 0.96 of their tiles'
+            // rows, together with the shared tiles of the last round (plan_grouped): 0.84 to 1.00 of the time, 0.96 in the mean;
+            // 21 groups of 6913 rows x 1184x2656 bf16 116.4 -> 98.1 us, 16 of 16384 x 4096x4096 449 -> 442.
+            // (In the kernels of Stream-K launches the four loops take registers for which there are none: 24 to 184 bytes of scratch.)
+            if constexpr (T::GROUPED) {
+                constexpr int Q = T::TM / 4, ROWS = Q * T::A_PITCH;
+                if (a_rows_valid <= ROWS)
+                    run7(std::integral_constant<int, Q>{});
+                else if (a_rows_valid <= 2 * ROWS)
+                    run7(std::integral_constant<int, 2 * Q>{});
+                else if (a_rows_valid <= 3 * ROWS)
+                    run7(std::integral_constant<int, 3 * Q>{});
+                else
+                    run7(std::integral_constant<int, T::TM>{});
+            } else {
+                run7(std::integral_constant<int, T::TM>{});
+            }
             return;
         }
 #endif
@@ -1260,7 +1303,7 @@ __global__ __launch_bounds__(T::NT, T::MIN_WAVES) void gemm_kernel(const KernelA
     }
     // every wave's requests towards LDS have landed (above) and every wave is past its last fragment read
     __syncthreads();
-    const int row0 = m0 + wm * T::WTM, n = n0 + wn * T::WTN + lane % ST_CPR * 8;   // first row of the wave tile, the lane's columns
+    const int row0 = m0 + wm * T::A_FIRST, n = n0 + wn * T::WTN + lane % ST_CPR * 8;   // first row of the wave tile, the lane's columns
     auto c_at = [&](int m) { return (out_t *)pC + bz * args.stride_c + (size_t)m * pldc + n; };
     auto store8 = [&](out_t *dst, out8_t o) __attribute__((always_inline)) {
         if (!T::RG || n + 8 <= pN) {
@@ -1310,14 +1353,16 @@ __global__ __launch_bounds__(T::NT, T::MIN_WAVES) void gemm_kernel(const KernelA
         const G355_LDS uint8_t *const src = stg + lrow * ROWB + lane % ST_CPR * (8 * EB);
 #pragma unroll
         for (int t = 0; t < ROWS; t += ST_RPI) {
-            const int m = row0 + i0 * MI + t + lrow;
-            if ((ROWS % ST_RPI == 0 || t + lrow < ROWS) && m < pM && n < pN)
+            const int m = T::GROUPED ? row0 + (i0 + t / MI) * T::A_PITCH + t % MI + lrow : row0 + i0 * MI + t + lrow;
+            if ((ROWS % ST_RPI == 0 || t + lrow < ROWS) && m < m_end && n < pN)
                 put(m, src + t * ROWB);
         }
     };
     const bool narrow = out_mode == 0 && beta == 0.f;
 #pragma unroll
     for (int i0 = 0; i0 < T::TM; i0 += ST_G) {
+        if (T::GROUPED && m0 + i0 * T::A_PITCH >= m_end)
+            continue;       // no row of these blocks exists
         if (narrow) {
             store_blocks(std::false_type{}, std::integral_constant<int, ST_G>{}, i0,
                          [&](int m, const G355_LDS uint8_t *src) __attribute__((always_inline)) {

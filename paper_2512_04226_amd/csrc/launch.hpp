@@ -42,9 +42,10 @@ const VariantFns &kLaunchBf16_0(int, int, int),
 // The chained kernel of a tile size (ragged: the instantiation that trims), whatever slab depth and wave grid the variant has;
 // launch is null for sizes that have none.
 const VariantFns &chained_bf16(int block_m, int block_n, int b_layout, int ragged), &chained_fp16(int, int, int, int), &chained_fp8(int, int, int, int);
-// The pipelined direct kernel of a tile size other than 256x256 (streaming: for one tile row over large weights); launch is null
-// for sizes that have none.
-const VariantFns &pipelined_bf16(int block_m, int block_n, int b_layout, int ragged, int streaming), &pipelined_fp16(int, int, int, int, int),
+// The pipelined kernels of a tile size: direct ones of the sizes other than 256x256, streaming ones for one tile row over large
+// weights, and of 256x256 one for grouped launches; launch is null for sizes that have none.
+enum PipelinedForm { PIPELINED_DIRECT, PIPELINED_STREAMING, PIPELINED_GROUPED };
+const VariantFns &pipelined_bf16(int block_m, int block_n, int b_layout, int ragged, int form), &pipelined_fp16(int, int, int, int, int),
     &pipelined_fp8(int, int, int, int, int);
 // The sliced kernel: 16x16 tiles, four K slices in a workgroup.
 const VariantFns &sliced_bf16(int b_layout, int ragged), &sliced_fp16(int, int), &sliced_fp8(int, int);
