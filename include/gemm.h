@@ -264,7 +264,9 @@ int gemm_run_grouped(const gemm_cfg *cfg, int n_groups, const gemm_group_rec *ho
  * Enqueue C = alpha * A * B + beta * C on hip_stream (a hipStream_t; NULL = the default stream) with
  * the kernel cfg names; returns without synchronising.  A variant has several instantiations and the shape decides which
  * runs: where K or N is ragged, where large weights stream, and, for the 256x256 tiles with 128-byte slab rows, from
- * twenty K slabs per workgroup one on four waves (waves_m and waves_n name the plain instantiation's grid).  A, B, C: device pointers,
+ * twenty K slabs per workgroup one on four waves (waves_m and waves_n name the plain instantiation's grid).  A launch of few
+ * 16x16 tiles with a long K, or one that a pipelined kernel of another tile or of fewer K slices does faster, runs that kernel
+ * (gemm_launched_kernel and gemm_launched_tile name it; the workspace asked for is the cfg's all the same).  A, B, C: device pointers,
  * 16-byte aligned; lda, ldb multiples of 16 bytes, ldc a multiple of 8 elements (else GEMM_ERR_ALIGN).  When cfg->split_k > 1 or cfg->stream_k = 1 a workspace of
  * gemm_workspace_bytes(cfg) must have been registered with gemm_set_workspace for the
  * current device.
