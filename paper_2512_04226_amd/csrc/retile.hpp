@@ -111,8 +111,11 @@ inline Retiled retile_streaming(const RetileProblem &p)
 // Of row-major B a 16-column tile reads 32 (fp8: 16) bytes of each k row: from the L2 that is level, from memory it is not, so
 // only few columns (128 tiles: .81-.98 at K = 1536, .66-.93 at 3072), and not against K slices that spread the reading (8 of them
 // 1.12, 16 and 32 .40-.97).  A launch of most CUs over weights that come from memory is bound by those (1.00-1.13 in one piece).
+// One tile row of 120 to 176 tiles in one piece, row-major, K = 1536 to 2816: 1.00-1.07 where the rows of B (b_pitch bytes apart) are
+// not whole KB, .90-.97 where they are (32-byte and wider pieces then meet in the same channels and the cfg's kernel is the slower for
+// it: 16x2304 7.0 us, 16x2560 9.7, sliced 7.3 and 9.0); up to 113 tiles .84-.96 at any pitch, several tile rows .84-1.01.
 // Beyond the last K taken the four chains are longer than the second kernel of K slices.
-inline bool runs_sliced(int64_t M, int64_t N, int64_t K, int64_t batch, bool fp8, bool kc, int block_m, int block_n, int split)
+inline bool runs_sliced(int64_t M, int64_t N, int64_t K, int64_t batch, int64_t b_pitch, bool fp8, bool kc, int block_m, int block_n, int split)
 {
     const int64_t tiles = (M + 15) / 16 * ((N + 15) / 16) * batch;
     if (tiles > 256 || (split == 1 ? block_m * block_n > 16 * 64 : split < 4 || block_m * block_n > 64 * 128))
@@ -123,6 +126,8 @@ inline bool runs_sliced(int64_t M, int64_t N, int64_t K, int64_t batch, bool fp8
         return K >= (fp8 ? 2048 : 896) && (split == 1 || K <= (fp8 ? 16384 : 12288));
     }
     if (split > 1 && split < 16)
+        return false;
+    if (split == 1 && M <= 16 && tiles > 112 && b_pitch % 1024)
         return false;
     return fp8 ? tiles <= 64 && K >= 4096 && K <= 8192 : K >= (tiles <= 128 ? 1536 : 2048) && tiles <= 192 && K <= 4096;
 }

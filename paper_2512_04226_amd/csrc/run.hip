@@ -487,7 +487,7 @@ static int plan_launch(const gemm_cfg *cfg, bool aligned, uintptr_t c_address, L
     if (cfg->stream_k || out->chain)
         return GEMM_OK;
     const int bk = 128 / es;
-    if (!streaming && runs_sliced(cfg->M, cfg->N, cfg->K, cfg->batch, es == 1, cfg->b_layout == GEMM_B_K_CONTIGUOUS, v.block_m, v.block_n, cfg->split_k)) {
+    if (!streaming && runs_sliced(cfg->M, cfg->N, cfg->K, cfg->batch, cfg->ldb * es, es == 1, cfg->b_layout == GEMM_B_K_CONTIGUOUS, v.block_m, v.block_n, cfg->split_k)) {
         // (32-bit offsets as above; a wave's window holds its quarter of K, its ring asks for three slabs more)
         if (16 * cfg->lda * es >= lim || (cfg->b_layout ? (int64_t)16 : cdiv64(cfg->K, 4) + 8 * bk) * cfg->ldb * es >= lim)
             return GEMM_OK;

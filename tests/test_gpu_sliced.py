@@ -69,4 +69,6 @@ def test_where_a_launch_is_sliced():
     assert kind(40, 64, 12288, split=8) == "sliced" and kind(40, 64, 12416, split=8) == "plain" and kind(40, 64, 4096, split=2) == "plain"
     assert kind(16, 4096, 4096) == "plain" and kind(16, 2048, 4096) == "sliced"          # weights from memory on most CUs
     assert kind(100, 240, 4096, bl=0) == "sliced" and kind(100, 240, 4096, bl=0, split=8) == "plain" and kind(250, 240, 4096, bl=0) == "plain"
+    # one tile row of many columns, row-major: only where the rows of B are whole KB apart
+    assert kind(16, 2304, 2048, bl=0) == "plain" and kind(16, 2560, 2048, bl=0) == "sliced" and kind(16, 1776, 2048, bl=0) == "sliced"
     assert kind(64, 128, 2048, E4M3) == "sliced" and kind(64, 128, 1792, E4M3) == "plain" and kind(64, 128, 2048, E4M3, 0) == "plain"
