@@ -125,7 +125,8 @@ typedef struct gemm_cfg {
     uint16_t group_n;         /* cache-tile width f_n = CUs per L2 / f_m (informational) */
     uint8_t xcd_remap;        /* 1: workgroup ids are renumbered so that each XCD owns a contiguous id range */
     uint8_t stages;           /* LDS ring depth: K_T slabs resident or in flight per workgroup */
-    uint16_t reserved1;       /* 0 */
+    uint16_t own_tile;        /* default 0.  Else gemm_run launches the tile and the K slices named here even where a kernel of others would
+                                 run in their place (see gemm_run): for tools that compare cfgs */
     uint8_t b_layout;         /* gemm_b_layout */
     uint8_t stream_k;         /* 1: the last partial wave of tiles is split along K over sk_workers workgroups (needs split_k = 1) */
     uint16_t sk_workers;      /* stream-K workgroups G (= workgroup slots of the device for this variant); 0 when stream_k = 0 */
@@ -266,7 +267,8 @@ int gemm_run_grouped(const gemm_cfg *cfg, int n_groups, const gemm_group_rec *ho
  * runs: where K or N is ragged, where large weights stream, and, for the 256x256 tiles with 128-byte slab rows, from
  * twenty K slabs per workgroup one on four waves (waves_m and waves_n name the plain instantiation's grid).  A launch of few
  * 16x16 tiles with a long K, or one that a pipelined kernel of another tile or of fewer K slices does faster, runs that kernel
- * (gemm_launched_kernel and gemm_launched_tile name it; the workspace asked for is the cfg's all the same).  A, B, C: device pointers,
+ * (gemm_launched_kernel and gemm_launched_tile name it; the workspace asked for is the cfg's all the same, and predicted_us, gemm_predict
+ * and group_m are about the cfg's own tile), unless own_tile is set.  A, B, C: device pointers,
  * 16-byte aligned; lda, ldb multiples of 16 bytes, ldc a multiple of 8 elements (else GEMM_ERR_ALIGN).  When cfg->split_k > 1 or cfg->stream_k = 1 a workspace of
  * gemm_workspace_bytes(cfg) must have been registered with gemm_set_workspace for the
  * current device.

@@ -59,7 +59,7 @@ class gemm_cfg(ctypes.Structure):
                 ("waves_n", ctypes.c_uint8), ("mfma", ctypes.c_uint8), ("k_unroll", ctypes.c_uint8),
                 ("split_k", ctypes.c_uint16), ("group_m", ctypes.c_uint16), ("group_n", ctypes.c_uint16),
                 ("xcd_remap", ctypes.c_uint8), ("stages", ctypes.c_uint8),
-                ("reserved1", ctypes.c_uint16), ("b_layout", ctypes.c_uint8), ("stream_k", ctypes.c_uint8),
+                ("own_tile", ctypes.c_uint16), ("b_layout", ctypes.c_uint8), ("stream_k", ctypes.c_uint8),
                 ("sk_workers", ctypes.c_uint16), ("alpha", ctypes.c_float),
                 ("bottleneck", ctypes.c_int32), ("beta", ctypes.c_float), ("predicted_us", ctypes.c_double),
                 ("batch", ctypes.c_int32), ("groups", ctypes.c_int32), ("stride_a", ctypes.c_int64),

@@ -115,6 +115,12 @@ def _time_plain(cfg, A, B, C, launches=10):
     return e0.elapsed_time(e1) * 1e3 / launches
 
 
+def _own_tile(cfg):
+    """The cfg, launched as the kernel it names also where gemm_run would run another tile in its place."""
+    cfg.own_tile = 1
+    return cfg
+
+
 def measure_slab_clk(dtype, n, b_layout=0, passes=5):
     """Median over `passes` sweeps of the variant list, each in a different order: the chip is
     power-limited on these shapes, so what ran just before moves a timing by a few percent."""
@@ -129,7 +135,7 @@ def measure_slab_clk(dtype, n, b_layout=0, passes=5):
             continue
         seen.add(cfg.kernel_id)
         ws.ensure(cfg)
-        cfgs.append(cfg)
+        cfgs.append(_own_tile(cfg))
     times = {c.kernel_id: [] for c in cfgs}
     rng = np.random.default_rng(0)
     for p in range(passes):
@@ -188,7 +194,7 @@ def compare_loop_forms(lib_paths, n=8192, passes=7):
                 if c is None or c.split_k != 1 or c.stream_k or c.kernel_id in seen:
                     continue
                 seen.add(c.kernel_id)
-                cfgs.append(c)
+                cfgs.append(_own_tile(c))
             for c in cfgs:
                 outs = []
                 for lib in libs:
@@ -259,7 +265,7 @@ def decompose(lib_paths, n=8192):
                 c = g.gemm_cfg_at(idx, n, n, n, dtype)
                 if c is None or not c.describe().startswith(picks[dtype]):
                     continue
-                us = [settled(lib, c, A, B, C) for lib in libs]
+                us = [settled(lib, _own_tile(c), A, B, C) for lib in libs]
                 print("%-4s %-8s %-38s %s" % (label, "zeros" if zeros else "random", c.describe(), "   ".join(
                     "%s %.0f us (%.0f TFLOP/s)" % (nm, t, 2.0 * n ** 3 / t * 1e-6) for nm, t in zip(names, us))), flush=True)
 
@@ -292,7 +298,7 @@ def compare_builds(named_libs, n=8192):
             c = g.gemm_cfg_at(idx, n, n, n, dtype)
             if c is None or not c.describe().startswith(picks[dtype]):
                 continue
-            print("%-4s %-40s %s" % (label, c.describe(), "  ".join("%s %.0f us" % (nm, settled(l, c, A, B, C)) for nm, l in libs)),
+            print("%-4s %-40s %s" % (label, c.describe(), "  ".join("%s %.0f us" % (nm, settled(l, _own_tile(c), A, B, C)) for nm, l in libs)),
                   flush=True)
 
 

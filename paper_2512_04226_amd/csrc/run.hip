@@ -484,7 +484,7 @@ static int plan_launch(const gemm_cfg *cfg, bool aligned, uintptr_t c_address, L
     out->split = cfg->split_k;
     out->group_m = cfg->group_m;
     out->fns = &launcher_of(dtype, cfg->kernel_id, cfg->b_layout, out->kind);
-    if (cfg->stream_k || out->chain)
+    if (cfg->stream_k || out->chain || cfg->own_tile)
         return GEMM_OK;
     const int bk = 128 / es;
     if (!streaming && runs_sliced(cfg->M, cfg->N, cfg->K, cfg->batch, cfg->ldb * es, es == 1, cfg->b_layout == GEMM_B_K_CONTIGUOUS, v.block_m, v.block_n, cfg->split_k)) {

@@ -1,7 +1,8 @@
 """Offline exhaustive sweep of the compiled configuration space (evaluation tool only).
 
 For each problem shape, times every legal (variant, split_k) configuration returned by
-gemm_cfg_at plus the analytical pick of gemm_select, and records the paper's selection
+gemm_cfg_at, each as the kernel it names (own_tile), plus the analytical pick of gemm_select as gemm_run
+launches it, which may be another tile's kernel in its place, and records the paper's selection
 efficiency (Section V-A): throughput of the pick divided by the best throughput found.
 Nothing here is used by gemm_select or gemm_run.
 
@@ -95,26 +96,36 @@ def sweep_shape(M, N, K, dtype, ws, quick=False, b_layout=0):
         cfg = g.gemm_cfg_at_ex(idx, M, N, K, dtype, b_layout)
         if cfg is None:
             continue
+        cfg.own_tile = 1
         us = time_cfg(cfg, A, B, C, ws, min_ms=0.5 if quick else 1.0)
         rows.append({"idx": idx, "cfg": cfg.describe(), "us": us, "pred_us": cfg.predicted_us})
-    # Finalists: the five fastest of the first pass and the analytic pick.  All of them are timed again,
-    # the same number of times, round-robin (so that drift of the chip's state hits all alike), and each
-    # keeps the median of its timings: the pick gets no second chance that the others do not get.
+    # Finalists: the five fastest of the first pass and the analytic pick as gemm_run launches it (one of the rows where
+    # that is the kernel it names).  All of them are timed again, the same number of times, round-robin (so that drift of the
+    # chip's state hits all alike), and each keeps the median of its timings: the pick gets no second chance that the others
+    # do not get.
     pick = g.gemm_select_ex(M, N, K, dtype, b_layout)
-    by_cfg = {r["cfg"]: r for r in rows}
+    own = pick.copy()
+    own.own_tile = 1
+    replaced = (g.gemm_launched_kernel(pick), g.gemm_launched_tile(pick)) != (g.gemm_launched_kernel(own), g.gemm_launched_tile(own))
     finalists = sorted(rows, key=lambda r: r["us"])[:5]
-    if pick.describe() not in [r["cfg"] for r in finalists]:
-        finalists.append(by_cfg[pick.describe()])
-    cfgs = {r["cfg"]: g.gemm_cfg_at_ex(r["idx"], M, N, K, dtype, b_layout) for r in finalists}
-    again = {r["cfg"]: [r["us"]] for r in finalists}
+    if not replaced and pick.describe() not in [r["cfg"] for r in finalists]:
+        finalists.append(next(r for r in rows if r["cfg"] == pick.describe()))
+    cfgs = []
+    for r in finalists:
+        cfgs.append(g.gemm_cfg_at_ex(r["idx"], M, N, K, dtype, b_layout))
+        cfgs[-1].own_tile = 1
+    again = [[r["us"]] for r in finalists]
+    if replaced:
+        cfgs.append(pick)
+        again.append([time_cfg(pick, A, B, C, ws)])
     for _ in range(2):
-        for r in finalists:
-            again[r["cfg"]].append(time_cfg(cfgs[r["cfg"]], A, B, C, ws))
-    final = [dict(r, us=float(np.median(again[r["cfg"]]))) for r in finalists]
+        for cfg, us in zip(cfgs, again):
+            us.append(time_cfg(cfg, A, B, C, ws))
+    final = [dict(r, us=float(np.median(us))) for r, us in zip(finalists, again)]
     best = min(final, key=lambda r: r["us"])
-    pick_us = [r["us"] for r in final if r["cfg"] == pick.describe()][0]
+    pick_us = float(np.median(again[-1])) if replaced else [r["us"] for r in final if r["cfg"] == pick.describe()][0]
     rec = {"M": M, "N": N, "K": K, "dtype": dtype, "b_layout": b_layout, "n_cfgs": len(rows), "best": best, "pick": pick.describe(),
-           "pick_us": pick_us, "pick_pred_us": pick.predicted_us, "efficiency": min(1.0, best["us"] / pick_us),
+           "pick_launched": list(g.gemm_launched_tile(pick)), "pick_us": pick_us, "pick_pred_us": pick.predicted_us, "efficiency": min(1.0, best["us"] / pick_us),
            "best_tflops": flops / best["us"] * 1e-6, "pick_tflops": flops / pick_us * 1e-6,
            "bottleneck": g.BOTTLENECKS[pick.bottleneck],
            "top5": sorted(final, key=lambda r: r["us"])[:5]}
@@ -124,7 +135,7 @@ def sweep_shape(M, N, K, dtype, ws, quick=False, b_layout=0):
 def rerank(paths):
     """Offline: what the selector as it stands now would have scored on recorded sweeps (files written with
     --all-rows).  For every recorded shape the present gemm_select pick is looked up among the recorded
-    timings of all configurations; efficiency = fastest recorded time / the pick's recorded time, one timing
+    timings of all configurations, each of the kernel the configuration names; efficiency = fastest recorded time / the pick's recorded time, one timing
     each, capped at 1.  No GPU is used."""
     for path in paths:
         recs = [json.loads(line) for line in open(path) if line.strip()]

@@ -212,6 +212,68 @@ def test_a_second_build_of_the_library_gets_whole_pointers(tmp_path, monkeypatch
     assert "CDLL" not in open(calibrate.__file__).read()
 
 
+@pytest.fixture
+def timed(monkeypatch):
+    """The cfgs that the calibration and the sweep hand to their timing functions; nothing is launched."""
+    from paper_2512_04226_amd import binding as g, calibrate, sweep
+    cfgs = []
+
+    class Event:
+        def __init__(self, **kw):
+            pass
+
+        record = synchronize = lambda self: None
+        elapsed_time = lambda self, other: 1.0
+
+    def note(cfg, *args, **kw):
+        cfgs.append(cfg.copy())
+        return 1.0 + len(cfgs) % 7
+
+    monkeypatch.setattr(torch.cuda, "Event", Event)
+    monkeypatch.setattr(torch.cuda, "synchronize", lambda: None)
+    monkeypatch.setattr(g, "open_library", lambda path: path)
+    monkeypatch.setattr(calibrate, "run_in", lambda lib, cfg, *args: note(cfg))
+    for tool in (calibrate, sweep):
+        monkeypatch.setattr(tool, "make_operands", lambda *a, **kw: tuple(torch.zeros(2, 2) for _ in range(3)))
+    monkeypatch.setattr(calibrate, "_time_plain", note)
+    monkeypatch.setattr(calibrate.Workspace, "ensure", lambda self, cfg: None)
+    monkeypatch.setattr(sweep, "time_cfg", note)
+    return cfgs
+
+
+def _runs_its_own(g, cfg):
+    return (cfg.stream_k or g.gemm_launched_tile(cfg) == (cfg.block_m, cfg.block_n, cfg.split_k)) and not g.gemm_launched_kernel(cfg)[0].startswith("sliced")
+
+
+def test_calibration_times_the_kernels_that_the_cfgs_name(timed, capsys):
+    """At 4096^3 and 8192^3 gemm_run runs the pipelined 256x256 tile in place of a third of the variants; a slab cost divided by
+    another tile's count says nothing about either."""
+    from paper_2512_04226_amd import binding as g, calibrate
+    rows = sum((calibrate.measure_slab_clk(dt, n, bl, passes=1) for dt in (g.GEMM_BF16, g.GEMM_FP8_E4M3) for n in (4096, 8192) for bl in (0, 1)), [])
+    assert len(rows) == len(timed) and len({id(r[0]) for r in rows}) == len(rows) > 200
+    calibrate.compare_loop_forms(["a", "b"], passes=1)
+    calibrate.decompose(list("abcd"))
+    calibrate.compare_builds(["n=a"])
+    assert all(_runs_its_own(g, c) for c in timed)
+    # (and by themselves some would not)
+    plain = [c.copy() for c in timed]
+    for c in plain:
+        c.own_tile = 0
+    assert not all(_runs_its_own(g, c) for c in plain)
+
+
+@pytest.mark.parametrize("shape,replaced", [((1152, 2240, 11696), True), ((40, 64, 8192), True), ((2304, 5120, 512), False)])
+def test_sweep_times_entries_as_named_and_the_pick_as_launched(timed, shape, replaced):
+    from paper_2512_04226_amd import binding as g, sweep
+    rec, rows = sweep.sweep_shape(*shape, g.GEMM_BF16, None, b_layout=1)
+    assert len(rows) == rec["n_cfgs"] > 50 and all(_runs_its_own(g, c) for c in timed[:len(rows)])
+    pick = g.gemm_select_ex(*shape, g.GEMM_BF16, 1)
+    assert rec["pick"] == pick.describe() and rec["pick_launched"] == list(g.gemm_launched_tile(pick))
+    assert replaced == (not _runs_its_own(g, pick))
+    as_launched = [c for c in timed[len(rows):] if not c.own_tile]
+    assert len(as_launched) == (3 if replaced else 0) and all(c.describe() == pick.describe() for c in as_launched)
+
+
 def test_uniform128_shapes_follow_the_papers_recipe():
     """Section V-A: dimensions are multiples of 128 up to 8192; the sample is seeded."""
     from paper_2512_04226_amd import workloads as wl

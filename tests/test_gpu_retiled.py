@@ -70,6 +70,28 @@ def test_retiled_launch_accumulates(runs, tile, M, N, slabs, batch):
     assert torch.equal(C[..., :N], ref)
 
 
+@pytest.mark.gpu
+@pytest.mark.parametrize("runs,tile,M,N,slabs,batch", [LAUNCHES[1], LAUNCHES[8]])
+def test_own_tile_launches_the_cfgs_kernel(runs, tile, M, N, slabs, batch):
+    """With own_tile the cfg's K slices, all of them, leave their sums in the workspace; the replacement uses fewer."""
+    from gpu_util import workspace_for
+    from paper_2512_04226_amd import binding as g
+    K = slabs * 64
+    c = _cfg(g, tile, M, N, K, batch, BF16, 1)
+    assert g.gemm_launched_tile(c) == runs
+    c.own_tile = 1
+    assert g.gemm_launched_tile(c) == tile and g.gemm_launched_kernel(c)[1:3] == (c.waves_m, c.waves_n)
+    ws = workspace_for(c)
+    if ws is not None:
+        ws.fill_(float("nan"))
+    A, B, ref = _problem(batch, M, N, K, BF16, 1)
+    assert torch.equal(_run(g, c, A, B, M, N, BF16), ref), c.describe()
+    if ws is not None:
+        need = g.gemm_workspace_bytes(c) // 4
+        slices = ws[:need].view(batch * c.split_k, M, -1)[..., :N]
+        assert not bool(torch.isnan(slices).any())
+
+
 def test_a_retiled_launch_fits_what_the_cfg_was_checked_for():
     """Of drawn cfgs: no more K slices than the cfg has (its workspace holds their slabs), none of them empty, nine slabs or more
     each; small grids, small tiles and Stream-K run their own tile."""
