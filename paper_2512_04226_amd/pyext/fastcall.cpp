@@ -133,12 +133,13 @@ inline bool plain(const at::Tensor &t)
            (t.key_set() - known).highestFunctionalityKey() == c10::DispatchKey::Undefined;
 }
 
-// at::empty of whole rows on the current device.  Without the dispatcher (0.25 us), except where a transform is active, which
-// would see the call, or the operator fills new memory.
+// at::empty of whole rows on the current device.  Without the dispatcher (0.25 us), except where something beside the operator
+// would see the call (a transform, a trace, functionalisation, a Python dispatcher: what a thread adds to the keys that are
+// always there), or the operator fills new memory.
 at::Tensor empty_rows(int64_t rows, int64_t columns, at::ScalarType type, at::Device device)
 {
     const auto &context = at::globalContext();
-    if (c10::impl::tls_local_dispatch_key_set().included_.has(c10::DispatchKey::FuncTorchDynamicLayerFrontMode) ||
+    if (!(c10::impl::tls_local_dispatch_key_set().included_ - c10::default_included_set).empty() ||
         (context.deterministicAlgorithms() && context.deterministicFillUninitializedMemory()))
         return at::empty({rows, columns}, at::TensorOptions().dtype(type).device(device));
     return at::Tensor(at::detail::empty_cuda({rows, columns}, type, device, std::nullopt));

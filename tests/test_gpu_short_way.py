@@ -62,6 +62,19 @@ def test_the_short_way_of_matmul_gives_what_the_general_way_gives():
     assert torch.equal(C, api.matmul(A, B))
 
 
+def test_a_trace_sees_the_short_ways_allocation():
+    """A trace records where the result comes from, as it does on the general way; allocated behind its back, the first call's
+    result would stand in the traced program as a constant."""
+    from paper_2512_04226_amd import api
+    A, B = (torch.randn(64, 64, device="cuda").bfloat16() for _ in range(2))
+    graphs = []
+    for way in (lambda a, b: api._fastcall.matmul(a, b, None, 1.0, 0.0, False, None), lambda a, b: api._matmul_general(a, b, None, 1.0, 0.0, False, None)):
+        traced = torch.jit.trace(lambda a, b: way(a, b) + 1, (A, B), check_trace=False)
+        graphs.append([n.kind() for n in traced.graph.nodes() if n.kind() in ("aten::empty", "aten::add")])
+    assert graphs[0] == graphs[1] == ["aten::empty", "aten::add"]
+    assert torch.equal(api._fastcall.matmul(A, B, None, 1.0, 0.0, False, None), api._matmul_general(A, B, None, 1.0, 0.0, False, None))
+
+
 def _operands(M, N, K):
     return tuple(torch.randn(s, device="cuda").bfloat16() for s in ((M, K), (K, N)))
 
