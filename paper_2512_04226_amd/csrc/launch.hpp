@@ -4,6 +4,13 @@
 #include "../../include/gemm.h"
 #include "gemm_kernel.hpp"
 
+// Builds that force a K-loop form or leave a part of the loop out, for comparisons, hold the variants of the table only: neither
+// pipelined instantiations nor sliced ones, so that every launch runs its cfg's own tile.
+#if defined(G355_FORCE_LOOP_FORM) || defined(G355_DIAG_SKIP_FILL) || defined(G355_DIAG_SKIP_FRAG) || \
+    defined(G355_DIAG_SKIP_MFMA) || defined(G355_DIAG_PANEL) || defined(G355_DIAG_FILL_MODE)
+#define G355_COMPARISON_BUILD
+#endif
+
 namespace g355 {
 typedef hipError_t (*LaunchFn)(const KernelArgs &, hipStream_t);
 // One launch by the runtime's own entry: the <<<>>> form pushes its configuration, calls a stub that pops it, and leaves its
@@ -43,10 +50,10 @@ const VariantFns &kLaunchBf16_0(int, int, int),
 // launch is null for sizes that have none.
 const VariantFns &chained_bf16(int block_m, int block_n, int b_layout, int ragged), &chained_fp16(int, int, int, int), &chained_fp8(int, int, int, int);
 // The pipelined kernels of a tile size: direct ones of the sizes other than 256x256, streaming ones for one tile row over large
-// weights, and of 256x256 one for grouped launches; launch is null for sizes that have none.
+// weights, and of 256x256 one for grouped launches; launch is null for sizes that have none, and in a comparison build for all.
 enum PipelinedForm { PIPELINED_DIRECT, PIPELINED_STREAMING, PIPELINED_GROUPED };
 const VariantFns &pipelined_bf16(int block_m, int block_n, int b_layout, int ragged, int form), &pipelined_fp16(int, int, int, int, int),
     &pipelined_fp8(int, int, int, int, int);
-// The sliced kernel: 16x16 tiles, four K slices in a workgroup.
+// The sliced kernel: 16x16 tiles, four K slices in a workgroup (launch: as above).
 const VariantFns &sliced_bf16(int b_layout, int ragged), &sliced_fp16(int, int), &sliced_fp8(int, int);
 }  // namespace g355

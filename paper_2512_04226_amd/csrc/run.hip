@@ -248,7 +248,7 @@ int kernel_of(int dtype, int id, int bl, bool ragged, bool streaming, int64_t sl
 
 inline int64_t cdiv64(int64_t a, int64_t b) { return (a + b - 1) / b; }
 
-// The pipelined kernel of a tile of retile.hpp (nullptr: not built, as in the builds that compare K-loop forms).
+// The pipelined kernel of a tile of retile.hpp (nullptr: a comparison build has none).
 const VariantFns *pipelined_of(int dtype, int block_m, int block_n, int b_layout, int ragged, int streaming)
 {
     const VariantFns *f = nullptr;
@@ -491,7 +491,10 @@ static int plan_launch(const gemm_cfg *cfg, bool aligned, uintptr_t c_address, L
         // (32-bit offsets as above; a wave's window holds its quarter of K, its ring asks for three slabs more)
         if (16 * cfg->lda * es >= lim || (cfg->b_layout ? (int64_t)16 : cdiv64(cfg->K, 4) + 8 * bk) * cfg->ldb * es >= lim)
             return GEMM_OK;
-        out->fns = &(dtype == GEMM_FP16 ? sliced_fp16 : dtype == GEMM_BF16 ? sliced_bf16 : sliced_fp8)(cfg->b_layout, ragged);
+        const VariantFns &sliced = (dtype == GEMM_FP16 ? sliced_fp16 : dtype == GEMM_BF16 ? sliced_bf16 : sliced_fp8)(cfg->b_layout, ragged);
+        if (!sliced.launch)
+            return GEMM_OK;
+        out->fns = &sliced;
         out->kind = ragged ? GEMM_KERNEL_SLICED_RAGGED : GEMM_KERNEL_SLICED;
         out->kps = cdiv64(cfg->K, 2 * bk) * (2 * bk);
         out->tiles_m = cdiv64(cfg->M, 16);

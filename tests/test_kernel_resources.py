@@ -15,9 +15,9 @@ CSRC = os.path.join(ROOT, "paper_2512_04226_amd", "csrc")
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 
 
-def _usage(src):
+def _usage(src, *defines):
     cmd = [HIPCC, "--offload-arch=gfx950", "-O3", "-std=c++17", "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
-           "--cuda-device-only", "-c", "-Rpass-analysis=kernel-resource-usage", "-o", os.devnull, os.path.join(CSRC, src)]
+           "--cuda-device-only", "-c", "-Rpass-analysis=kernel-resource-usage", "-o", os.devnull, *defines, os.path.join(CSRC, src)]
     r = subprocess.run(cmd, capture_output=True, text=True)
     assert r.returncode == 0, r.stderr[-2000:]
     rows, cur = [], None
@@ -134,3 +134,12 @@ def test_chained_kernels_fill_the_cu_as_their_walk_assumes():
         assert r["waves_per_simd"] >= on_a_cu * wm * wn // 4, r
         spills = (es, bm, bn) == (1, 256, 256)
         assert r["scratch"] <= (20 if spills else 0), r
+
+
+@pytest.mark.skipif(shutil.which(HIPCC) is None and not os.path.exists(HIPCC), reason="needs hipcc")
+@pytest.mark.parametrize("define", ["-DG355_FORCE_LOOP_FORM=3", "-DG355_DIAG_SKIP_FILL"])
+def test_comparison_builds_hold_nothing_that_replaces_a_variant(define):
+    """Builds that compare K-loop forms or leave a part of the loop out time the table's variants: were the pipelined tiles and the
+    sliced kernel in them, in the forced form, launches would run those instead."""
+    for src in ("pipelined_bf16.hip", "sliced_bf16.hip"):
+        assert _usage(src, define) == []
