@@ -31,43 +31,69 @@ struct RetileProblem {
     int64_t M, N, batch, slabs;       // slabs: of 128 bytes, in K
     int block_m, block_n, split;      // the cfg's
     bool two_resident;                // two workgroups of the cfg's kernel share a CU
+    bool reads_c;                     // beta != 0: the old C is read, in the store stage or with the slices' sums
 };
 
-inline double pipelined_us(const PipelinedTile &t, const RetileProblem &p, int64_t split, int64_t workgroups, int64_t per_slice)
+constexpr int64_t kRetileCus = 256;
+
+inline double pipelined_us(const PipelinedTile &t, const RetileProblem &p, int64_t split, int64_t workgroups, int64_t per_slice,
+                           int64_t cus = kRetileCus)
 {
-    constexpr int64_t kCus = 256;
-    const int64_t rounds = workgroups / kCus, rest = workgroups % kCus;
+    const int64_t rounds = workgroups / cus, rest = workgroups % cus;
     double us = rounds * (t.fixed + per_slice * t.full);
     if (rest)
-        us += t.fixed + per_slice * std::max(t.alone, t.full * rest / kCus);
+        us += t.fixed + per_slice * std::max(t.alone, t.full * rest / cus);
     // the slices' sums are added by a second kernel: 20 bytes per ps
     return split > 1 ? us + 3.2 + p.batch * p.M * p.N * (4. * split + 2.) * 5e-8 : us;
 }
 
-// Margins, and where the rule does not look, by the measured time over that of the cfg's own kernel (178 drawn launches of
-// these tiles, K-split ones among them; 40 are retiled, to 0.65 - 0.99 of the time and one to 1.02, 0.89 in the mean):
+// Margins, and where the rule does not look, by the measured time over that of the cfg's own kernel, alone and beside another
+// stream's kernel that holds eight CUs.  Of 1669 drawn launches that the price alone retiled 218 took more than 1.03 of it (up to 1.51; 0.91
+// in the mean): what the price leaves out.  Of 1121 others that the lines below leave, 31 (up to 1.13; 0.87 in the mean, beside 0.87).
 //  - fewer than kMinSlabs slabs per workgroup: a pipelined workgroup's prologue and store stage stand alone (0.96 - 1.2 below);
 //  - fewer than kMinGrid workgroups: not what the selector picks these tiles for;
 //  - 256x256 below twenty slabs runs an eight-wave kernel that is up to 8 % faster than the pipelined one it is priced as, and
 //    launches priced between 0.85 and 0.95 went either way (0.85 - 1.09);
-//  - two-stage 128x128 and 64x256 tiles, two to a CU, hide each other's store stage: priced at 0.93 one went to 1.04, up to 0.83 all gained;
-//  - smaller tiles than 128x128 have three and more workgroups on a CU: 0.9 - 1.2.
+//  - two-stage 128x128 tiles, two to a CU, hide each other's store stage: priced at 0.93 one went to 1.04, up to 0.83 all gained.  A
+//    round that nearly fills the chip with them is priced as two (440 to 512 workgroups: 0.98 in the mean, three of 19 above 1.08);
+//  - smaller tiles than 128x128 have three and more workgroups on a CU: 0.9 - 1.2;
+//  - more bytes towards a CU's LDS than the cfg's kernel has: a launch that waits for its loads takes as much longer (fewer workgroups over
+//    the same weights, three 64-row tiles in place of two of 128: by the ratio of the two up to 1.0 0.76 - 0.95 in the mean, from 1.1
+//    0.98 - 1.08, one in two above 1.03; up to 64 rows, whose tiles load the same of B, 0.99 - 1.02 to 1.15);
+//  - an old C that the store stage reads: two workgroups of a CU hide that too (up to 17 slabs 1.13 and 1.10 in the mean, to 23 slabs 0.98,
+//    from 24 0.93, with the last above 1.1 at 27);
+//  - batches: the problems' operands come from memory, and only tiles of 192x256 and 256x256 ask for them less often (0.88 in the mean;
+//    the smaller ones 0.97, one in six above 1.03);
+//  - 64x256 in place of another tile for more than 64 rows: 1.09 in the mean;
+//  - what needs all CUs: the price on 248 of them must hold too (single rounds of 249 to 256 workgroups 1.11 beside).
+// A price of 0.55 and less outweighs the last five, one of 0.65 (0.70 from K slices) that of a batch.
 inline Retiled retile(const RetileProblem &p)
 {
-    constexpr int64_t kMinSlabs = 9, kMinGrid = 64, kMinRetiled = 100;
+    constexpr int64_t kMinSlabs = 9, kMinGrid = 64, kMinRetiled = 100, kMinSlabsReadingC = 32, kHeldCus = 8;
     const Retiled own = {0, 0, 0};
     auto tiles = [&](int bm, int bn) { return (p.M + bm - 1) / bm * ((p.N + bn - 1) / bn) * p.batch; };
     if (p.block_m * p.block_n < 128 * 128 || p.slabs < kMinSlabs || tiles(p.block_m, p.block_n) * p.split < kMinGrid)
         return own;
-    const int64_t own_slabs = (p.slabs + p.split - 1) / p.split;
-    double limit = 0;
+    // rows and columns of a slab that a CU loads over all rounds
+    auto loads = [&](int bm, int bn, int64_t workgroups, int64_t per_slice) {
+        return (workgroups + kRetileCus - 1) / kRetileCus * per_slice * (std::min<int64_t>(bm, p.M) + std::min<int64_t>(bn, p.N));
+    };
+    const int64_t own_slabs = (p.slabs + p.split - 1) / p.split, own_grid = tiles(p.block_m, p.block_n) * p.split;
+    if (p.two_resident && own_grid > 400 && own_grid <= 2 * kRetileCus)
+        return own;
+    double own_us = 0, own_held = 0;
     for (const PipelinedTile &t : kPipelinedTiles)
-        if (t.block_m == p.block_m && t.block_n == p.block_n)
-            limit = pipelined_us(t, p, p.split, tiles(t.block_m, t.block_n) * p.split, own_slabs);
-    limit *= (p.block_m * p.block_n == 256 * 256 && own_slabs < 20) ? 0.85 : p.two_resident ? 0.90 : 0.95;
+        if (t.block_m == p.block_m && t.block_n == p.block_n) {
+            own_us = pipelined_us(t, p, p.split, own_grid, own_slabs);
+            own_held = pipelined_us(t, p, p.split, own_grid, own_slabs, kRetileCus - kHeldCus);
+        }
+    const int64_t own_loads = loads(p.block_m, p.block_n, own_grid, own_slabs);
+    double limit = own_us * ((p.block_m * p.block_n == 256 * 256 && own_slabs < 20) ? 0.85 : p.two_resident ? 0.90 : 0.95);
     Retiled best = own;
     for (const PipelinedTile &t : kPipelinedTiles) {
         const int64_t n = tiles(t.block_m, t.block_n);
+        const bool narrow = t.block_m * t.block_n < 192 * 256;
+        const bool rows64 = t.block_m == 64 && t.block_n == 256 && (p.block_m != 64 || p.block_n != 256) && p.M > 64;
         for (int split = 1; split <= p.split; ++split) {
             const int64_t per_slice = (p.slabs + split - 1) / split;
             if (per_slice < kMinSlabs)
@@ -75,10 +101,15 @@ inline Retiled retile(const RetileProblem &p)
             if (n * split < kMinRetiled || (p.slabs + per_slice - 1) / per_slice != split)     // (no slice may be empty)
                 continue;
             const double us = pipelined_us(t, p, split, n * split, per_slice);
-            if (us <= limit) {
-                limit = us;
-                best = {t.block_m, t.block_n, split};
-            }
+            if (us > limit || (p.batch > 1 && narrow && us > (p.split > 1 ? 0.70 : 0.65) * own_us))
+                continue;
+            if (us > 0.55 * own_us &&
+                (rows64 || (p.reads_c && split == 1 && own_slabs < kMinSlabsReadingC) ||
+                 20 * loads(t.block_m, t.block_n, n * split, per_slice) > (p.M > 64 ? 21 : 23) * own_loads ||
+                 pipelined_us(t, p, split, n * split, per_slice, kRetileCus - kHeldCus) > 0.97 * own_held))
+                continue;
+            limit = us;
+            best = {t.block_m, t.block_n, split};
         }
     }
     return best.block_m == p.block_m && best.block_n == p.block_n && best.split == p.split ? own : best;
@@ -90,12 +121,16 @@ inline Retiled retile(const RetileProblem &p)
 // both 119 without a matrix instruction); a bit less of A is fetched for nothing, and nothing else waits.  Its time over the
 // eight-wave kernel's, bf16 on six and fp8 on two shapes of weights, K splits halved where the cfg's tile has 256 columns:
 //   160 rows  row-major .90-.94 (fp8 1.00-1.01), K-contiguous .86-.99 (fp8 .95)   256 rows  .86-.91 (.88-.89), .86-.97 (.95-.96)
-// At 128 rows and below it is level with the 128x128 tile (.95-1.02) and behind the 128x256 one (1.0-1.25).
-inline Retiled retile_streaming(const RetileProblem &p)
+// At 128 rows and below it is level with the 128x128 tile (.95-1.02) and behind the 128x256 one (1.0-1.25).  Row-major weights whose
+// 128-column tiles take a second round where the cfg's 256-column ones do not: 1.01-1.07 (57344x4096, 448 workgroups for 224; K-contiguous
+// .93-.99).
+inline Retiled retile_streaming(const RetileProblem &p, bool kc)
 {
     const int split = p.block_n == 256 && p.split > 1 ? p.split / 2 : p.split;
     const int64_t per_slice = (p.slabs + split - 1) / split;
     if (p.batch != 1 || p.M <= 128 || p.M > 256 || p.block_n < 128 || per_slice < 9 || (p.slabs + per_slice - 1) / per_slice != split)
+        return {0, 0, 0};
+    if (!kc && p.block_n == 256 && (p.N + 127) / 128 * split > kRetileCus)
         return {0, 0, 0};
     return {p.M <= 192 ? 192 : 256, 128, split};
 }

@@ -505,8 +505,8 @@ static int plan_launch(const gemm_cfg *cfg, bool aligned, uintptr_t c_address, L
         return GEMM_OK;
     }
     const RetileProblem problem = {cfg->M, cfg->N, cfg->batch, cdiv64(cfg->K, bk), v.block_m, v.block_n, cfg->split_k,
-                                   v.block_m * v.block_n == 128 * 128 && v.stages == 2};
-    const Retiled r = streaming ? retile_streaming(problem) : retile(problem);
+                                   v.block_m * v.block_n == 128 * 128 && v.stages == 2, cfg->beta != 0.f};
+    const Retiled r = streaming ? retile_streaming(problem, cfg->b_layout == GEMM_B_K_CONTIGUOUS) : retile(problem);
     if (!r.block_m)
         return GEMM_OK;
     const VariantFns *const fns = pipelined_of(dtype, r.block_m, r.block_n, cfg->b_layout, ragged, streaming);
