@@ -143,28 +143,46 @@ inline Retiled retile_streaming(const RetileProblem &p, bool kc)
 //   16-bit, row-major     .91-1.13  .85-1.10  .81-1.10  .74-1.02  .66-1.04  .40-1.12  .69-1.59  1.37-2.3   1.9-3.1
 //   fp8, K-contiguous    1.15-1.29 1.07-1.13 1.02-1.15  .92- .99  .84-1.13  .75-1.10  .40- .85   .48-1.01   .70-1.26
 //   fp8, row-major       1.09-1.29 1.05-1.30  .99-1.30  .92-1.33  .85-1.33  .79-1.31  .40-1.55   .88-2.0   1.2-2.9
-// Of row-major B a 16-column tile reads 32 (fp8: 16) bytes of each k row: from the L2 that is level, from memory it is not, so
-// only few columns (128 tiles: .81-.98 at K = 1536, .66-.93 at 3072), and not against K slices that spread the reading (8 of them
-// 1.12, 16 and 32 .40-.97).  A launch of most CUs over weights that come from memory is bound by those (1.00-1.13 in one piece).
+// and of 2380 drawn launches that a rule of K and tiles alone sliced, by what that left out:
+//  - K-contiguous B against K slices, which spread a long K over more CUs.  One tile row .70-.88 up to K = 12288 (16-bit) and above; more
+//    than 16 tiles in 2-4 rows .66-.94 up to K = 10000, 1.03 and more in five of 13 beyond; in 5-8 rows .72-.82 up to 8192, 1.09 and 1.14
+//    beyond; in more .86 up to 6000, .99 to 1.15 beyond; fp8 in 5 and more rows .77 up to 11000, .91 to 1.20 beyond; batches .82 and 1.00;
+//  - of row-major B a 16-column tile reads 32 (fp8: 16) bytes of each k row: from the L2 that is level, from memory it is not, so
+//    only few columns (128 tiles: .81-.98 at K = 1536, .66-.93 at 3072), and not against K slices that spread the reading (8 of them
+//    1.12, 16 and 32 .40-.97; one tile row of more than 64 tiles whose rows are an odd number of half KB apart .92-1.07, else .79-.96);
+//  - row-major B that many tile rows read again, or the problems of a batch bring along: nine and more rows of more than 64 tiles
+//    .95 in the mean and one in five above 1.03, batches of 48 tiles and more the same; else .80, three of 430 above 1.03;
+//  - row-major fp8: against 16x64 tiles of four waves and K slices up to 1.38, and so beyond 128 columns (one tile row: 256) and for batches of two dozen
+//    tiles; else .79.
+// A launch of most CUs over weights that come from memory is bound by those (1.00-1.13 in one piece).
 // One tile row of 120 to 176 tiles in one piece, row-major, K = 1536 to 2816: 1.00-1.07 where the rows of B (b_pitch bytes apart) are
 // not whole KB, .90-.97 where they are (32-byte and wider pieces then meet in the same channels and the cfg's kernel is the slower for
 // it: 16x2304 7.0 us, 16x2560 9.7, sliced 7.3 and 9.0); up to 113 tiles .84-.96 at any pitch, several tile rows .84-1.01.
-// Beyond the last K taken the four chains are longer than the second kernel of K slices.
 inline bool runs_sliced(int64_t M, int64_t N, int64_t K, int64_t batch, int64_t b_pitch, bool fp8, bool kc, int block_m, int block_n, int split)
 {
-    const int64_t tiles = (M + 15) / 16 * ((N + 15) / 16) * batch;
+    const int64_t rows = (M + 15) / 16, tiles = rows * ((N + 15) / 16) * batch;
     if (tiles > 256 || (split == 1 ? block_m * block_n > 16 * 64 : split < 4 || block_m * block_n > 64 * 128))
         return false;
     if (kc) {
-        if (split == 1 && tiles > 160 && N * K * batch * (fp8 ? 1 : 2) > (8 << 20))
+        if (K < (fp8 ? 2048 : 896))
             return false;
-        return K >= (fp8 ? 2048 : 896) && (split == 1 || K <= (fp8 ? 16384 : 12288));
+        if (split == 1)
+            return tiles <= 160 || N * K * batch * (fp8 ? 1 : 2) <= (8 << 20);
+        if (batch > 1)
+            return K <= (fp8 ? 10240 : 6144);
+        if (tiles <= 16 || rows == 1)
+            return K <= (fp8 ? 16384 : 12288);
+        return K <= (rows <= 4 ? (fp8 ? 16384 : 10000) : fp8 ? 11264 : rows <= 8 ? 8192 : 6144);
     }
-    if (split > 1 && split < 16)
+    if (fp8)
+        return split == 1 && block_n == 16 && N <= (rows == 1 && batch == 1 ? 256 : 128) && tiles <= (batch > 1 ? 23 : 64) && K >= 4096 && K <= 8192;
+    if (K < (tiles <= 128 ? 1536 : 2048) || K > 4096 || tiles > 192)
         return false;
-    if (split == 1 && M <= 16 && tiles > 112 && b_pitch % 1024)
-        return false;
-    return fp8 ? tiles <= 64 && K >= 4096 && K <= 8192 : K >= (tiles <= 128 ? 1536 : 2048) && tiles <= 192 && K <= 4096;
+    if (split > 1)
+        return split >= 16 && !(rows == 1 && tiles > 64 && b_pitch % 1024 == 512);
+    if (batch > 1)
+        return tiles < 48;
+    return !(rows > 8 && tiles > 64) && !(rows == 1 && tiles > 112 && b_pitch % 1024);
 }
 
 // Band height of the rasterisation: the 32 workgroups that an XCD holds cover a region about as high as it is wide.

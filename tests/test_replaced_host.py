@@ -33,3 +33,20 @@ def test_no_other_tile_where_it_was_slower(call):
                                   (329, 2752, 19584, BF16, 0), (342, 2816, 23680, BF16, 0), (121, 2048, 12288, BF16, 1)])        # .67, .64, .92
 def test_another_tile_where_it_was_faster(call):
     assert _replaced(*call)
+
+
+@pytest.mark.parametrize("call", [
+    (3, 128, 4096, FP8, 0, 7), (46, 224, 7728, FP8, 0), (3, 928, 7936, FP8, 0), (1, 768, 5248, FP8, 0),       # 1.37, 1.38, 1.34, 1.27
+    (208, 80, 11920, BF16, 1), (76, 96, 10735, FP16, 1), (160, 288, 9776, BF16, 1), (160, 80, 8688, BF16, 1),  # 1.21, 1.20, 1.18, 1.14
+    (66, 49, 10496, FP16, 1, 9), (11, 64, 11119, FP16, 1, 7), (142, 106, 14337, FP8, 1, 2),                   # 1.24, 1.23, 1.20
+    (32, 128, 2048, BF16, 0, 12), (62, 70, 3572, BF16, 0, 9), (224, 128, 2592, FP16, 0),                      # 1.13, 1.14, 1.11
+    (5, 1280, 4096, BF16, 0)])                                                                                # 1.06
+def test_not_sliced_where_it_was_slower(call):
+    assert not _replaced(*call)
+
+
+@pytest.mark.parametrize("call", [(40, 64, 8192, BF16, 1), (1, 1024, 4096, BF16, 1), (2, 2048, 9728, BF16, 1), (19, 32, 8064, BF16, 1),   # .54, .59, .61, .54
+                                  (4, 224, 4096, BF16, 0), (5, 1680, 4096, BF16, 0), (2, 128, 4096, FP16, 0),                    # .45, .80, .48
+                                  (37, 16, 6784, FP8, 0), (2, 16, 6121, FP8, 0), (55, 70, 4096, FP8, 1)])                       # .67, .70
+def test_sliced_where_it_was_faster(call):
+    assert _replaced(*call)
