@@ -54,8 +54,8 @@ inline double pipelined_us(const PipelinedTile &t, const RetileProblem &p, int64
 //  - fewer than kMinGrid workgroups: not what the selector picks these tiles for;
 //  - 256x256 below twenty slabs runs an eight-wave kernel that is up to 8 % faster than the pipelined one it is priced as, and
 //    launches priced between 0.85 and 0.95 went either way (0.85 - 1.09);
-//  - two-stage 128x128 tiles, two to a CU, hide each other's store stage: priced at 0.93 one went to 1.04, up to 0.83 all gained.  A
-//    round that nearly fills the chip with them is priced as two (440 to 512 workgroups: 0.98 in the mean, three of 19 above 1.08);
+//  - two-stage 128x128 and 64x256 tiles, two to a CU, hide each other's store stage: priced at 0.93 one went to 1.04, up to 0.83 all
+//    gained.  A round that nearly fills the chip with the former is priced as two (440 to 512 workgroups: 0.98 in the mean, three of 19 above 1.08);
 //  - smaller tiles than 128x128 have three and more workgroups on a CU: 0.9 - 1.2;
 //  - more bytes towards a CU's LDS than the cfg's kernel has: a launch that waits for its loads takes as much longer (fewer workgroups over
 //    the same weights, three 64-row tiles in place of two of 128: by the ratio of the two up to 1.0 0.76 - 0.95 in the mean, from 1.1
@@ -79,7 +79,7 @@ inline Retiled retile(const RetileProblem &p)
         return (workgroups + kRetileCus - 1) / kRetileCus * per_slice * (std::min<int64_t>(bm, p.M) + std::min<int64_t>(bn, p.N));
     };
     const int64_t own_slabs = (p.slabs + p.split - 1) / p.split, own_grid = tiles(p.block_m, p.block_n) * p.split;
-    if (p.two_resident && own_grid > 400 && own_grid <= 2 * kRetileCus)
+    if (p.two_resident && p.block_m == 128 && own_grid > 400 && own_grid <= 2 * kRetileCus)
         return own;
     double own_us = 0, own_held = 0;
     for (const PipelinedTile &t : kPipelinedTiles)

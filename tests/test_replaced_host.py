@@ -30,7 +30,8 @@ def test_no_other_tile_where_it_was_slower(call):
 
 @pytest.mark.parametrize("call", [(1152, 2240, 11696, BF16, 0, 1, 0.5), (1501, 3003, 2005, BF16, 0), (64, 8192, 28672, FP8, 0),   # .86, .85, .99
                                   (256, 28672, 8192, BF16, 0), (226, 57344, 4096, FP16, 1),                                      # .90, .97
-                                  (329, 2752, 19584, BF16, 0), (342, 2816, 23680, BF16, 0), (121, 2048, 12288, BF16, 1)])        # .67, .64, .92
+                                  (329, 2752, 19584, BF16, 0), (342, 2816, 23680, BF16, 0), (121, 2048, 12288, BF16, 1),         # .67, .64, .92
+                                  (576, 14048, 2436, FP8, 1), (944, 8576, 1456, BF16, 1), (315, 736, 3937, FP16, 1, 34)])        # .67, .68, .70
 def test_another_tile_where_it_was_faster(call):
     assert _replaced(*call)
 
