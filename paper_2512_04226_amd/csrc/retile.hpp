@@ -71,7 +71,9 @@ inline Retiled retile(const RetileProblem &p)
 {
     constexpr int64_t kMinSlabs = 9, kMinGrid = 64, kMinRetiled = 100, kMinSlabsReadingC = 32, kHeldCus = 8;
     const Retiled own = {0, 0, 0};
-    auto tiles = [&](int bm, int bn) { return (p.M + bm - 1) / bm * ((p.N + bn - 1) / bn) * p.batch; };
+    auto tiles = [&](int bm, int bn) {      // (M, N and K are at most 2^30)
+        return (int64_t)(((uint32_t)p.M + bm - 1) / (uint32_t)bm) * (((uint32_t)p.N + bn - 1) / (uint32_t)bn) * p.batch;
+    };
     if (p.block_m * p.block_n < 128 * 128 || p.slabs < kMinSlabs || tiles(p.block_m, p.block_n) * p.split < kMinGrid)
         return own;
     // rows and columns of a slab that a CU loads over all rounds
@@ -89,17 +91,37 @@ inline Retiled retile(const RetileProblem &p)
         }
     const int64_t own_loads = loads(p.block_m, p.block_n, own_grid, own_slabs);
     double limit = own_us * ((p.block_m * p.block_n == 256 * 256 && own_slabs < 20) ? 0.85 : p.two_resident ? 0.90 : 0.95);
+    // the K splits that leave no slice empty, with the slabs of a slice (the table's cfgs have up to 32)
+    constexpr int kMaxSplits = 32;
+    int splits[kMaxSplits], n_splits = 0;
+    uint32_t per[kMaxSplits];
+    const uint32_t slabs = (uint32_t)p.slabs;
+    for (uint32_t split = 1; split <= (uint32_t)p.split && n_splits < kMaxSplits;) {
+        const uint32_t per_slice = (slabs + split - 1) / split;
+        if (per_slice < kMinSlabs)
+            break;
+        if ((slabs + per_slice - 1) / per_slice == split) {
+            splits[n_splits] = (int)split;
+            per[n_splits++] = per_slice;
+        }
+        ++split;
+    }
+    const double sum_us = p.batch * p.M * p.N * 5e-8;
     Retiled best = own;
     for (const PipelinedTile &t : kPipelinedTiles) {
         const int64_t n = tiles(t.block_m, t.block_n);
+        // (whatever the split, the matrix cores' time on all CUs)
+        if (t.full * n * p.slabs > 1.001 * kRetileCus * limit)
+            continue;
         const bool narrow = t.block_m * t.block_n < 192 * 256;
         const bool rows64 = t.block_m == 64 && t.block_n == 256 && (p.block_m != 64 || p.block_n != 256) && p.M > 64;
-        for (int split = 1; split <= p.split; ++split) {
-            const int64_t per_slice = (p.slabs + split - 1) / split;
-            if (per_slice < kMinSlabs)
-                break;
-            if (n * split < kMinRetiled || (p.slabs + per_slice - 1) / per_slice != split)     // (no slice may be empty)
+        for (int i = 0; i < n_splits; ++i) {
+            const int split = splits[i];
+            const int64_t per_slice = per[i];
+            if (n * split < kMinRetiled)
                 continue;
+            if (split > 1 && t.fixed + kMinSlabs * t.alone + 3.2 + sum_us * (4. * split + 2.) > 1.001 * limit)
+                break;      // (the more slices, the longer their sums take)
             const double us = pipelined_us(t, p, split, n * split, per_slice);
             if (us > limit || (p.batch > 1 && narrow && us > (p.split > 1 ? 0.70 : 0.65) * own_us))
                 continue;

@@ -1,4 +1,8 @@
 """Which calls run another kernel than their pick names: shapes on which the replacement was measured slower keep their own."""
+import math
+import random
+import time
+
 import pytest
 
 from paper_2512_04226_amd import binding as g
@@ -51,3 +55,85 @@ def test_not_sliced_where_it_was_slower(call):
                                   (37, 16, 6784, FP8, 0), (2, 16, 6121, FP8, 0), (55, 70, 4096, FP8, 1)])                       # .67, .70
 def test_sliced_where_it_was_faster(call):
     assert _replaced(*call)
+
+
+# (fixed, per slab alone, per slab on a full chip) us
+PRICES = {(256, 256): (7.5, 1.20, 1.60), (192, 256): (4.6, 1.00, 1.38), (128, 256): (3.0, 0.76, 1.06), (64, 256): (2.3, 0.55, 0.74),
+          (256, 128): (3.1, 0.77, 1.12), (192, 128): (3.6, 0.60, 0.84), (128, 128): (2.8, 0.46, 0.63), (64, 128): (2.0, 0.29, 0.43)}
+
+
+def _up(a, b):
+    return -(-a // b)
+
+
+def _by_the_rule(c):
+    """The rule of retile.hpp over every tile and K split, none skipped ahead."""
+    slabs, own = _up(c.K, 128 if c.dtype == FP8 else 64), (c.block_m, c.block_n)
+    two = own[0] * own[1] == 128 * 128 and c.stages == 2
+
+    def grid(t):
+        return _up(c.M, t[0]) * _up(c.N, t[1]) * c.batch
+
+    def price(t, split, cus=256):
+        fixed, alone, full = PRICES[t]
+        per = _up(slabs, split)
+        rounds, rest = divmod(grid(t) * split, cus)
+        us = rounds * (fixed + per * full) + (fixed + per * max(alone, full * rest / cus) if rest else 0.0)
+        return us + (3.2 + c.batch * c.M * c.N * (4.0 * split + 2.0) * 5e-8 if split > 1 else 0.0)
+
+    def loads(t, split):
+        return _up(grid(t) * split, 256) * _up(slabs, split) * (min(t[0], c.M) + min(t[1], c.N))
+
+    if own[0] * own[1] < 128 * 128 or slabs < 9 or grid(own) * c.split_k < 64 or (two and own[0] == 128 and 400 < grid(own) * c.split_k <= 512):
+        return own + (c.split_k,)
+    us0, own_slabs = price(own, c.split_k), _up(slabs, c.split_k)
+    limit, best = us0 * (0.85 if own == (256, 256) and own_slabs < 20 else 0.90 if two else 0.95), own + (c.split_k,)
+    for t in PRICES:
+        for split in range(1, c.split_k + 1):
+            per = _up(slabs, split)
+            if per < 9 or grid(t) * split < 100 or _up(slabs, per) != split:
+                continue
+            us = price(t, split)
+            if us > limit or (c.batch > 1 and t[0] * t[1] < 192 * 256 and us > (0.70 if c.split_k > 1 else 0.65) * us0):
+                continue
+            if us > 0.55 * us0 and ((t == (64, 256) != own and c.M > 64) or (c.beta and split == 1 and own_slabs < 32) or
+                                    20 * loads(t, split) > (21 if c.M > 64 else 23) * loads(own, c.split_k) or
+                                    price(t, split, 248) > 0.97 * price(own, c.split_k, 248)):
+                continue
+            limit, best = us, t + (split,)
+    return best
+
+
+def test_the_search_skips_nothing_that_the_rule_takes():
+    """gemm_run goes through the tiles and K splits at every call and skips what cannot win: of drawn cfgs it comes to what the
+    whole search comes to."""
+    rng, taken = random.Random(17), 0
+    for _ in range(3000):
+        dtype, batch = rng.choice((BF16, FP8, FP16)), rng.choice((1, 1, 1, rng.randint(2, 60)))
+        M, N, K = (int(math.exp(rng.uniform(math.log(lo), math.log(12000)))) for lo in (30, 30, 500))
+        bl = rng.randrange(2)
+        c = (g.gemm_select_batched(M, N, K, batch, dtype, bl) if rng.random() < 0.5 else
+             g.gemm_cfg_at_batched(rng.randrange(g.gemm_cfg_count(dtype)), M, N, K, batch, dtype, bl))
+        if c is None or c.stream_k:
+            continue
+        c.beta = rng.choice((0.0, 0.0, 0.5))
+        kind = g.gemm_launched_kernel(c)[0]
+        if kind.startswith(("chained", "sliced", "streaming")):
+            continue
+        want = _by_the_rule(c)
+        assert g.gemm_launched_tile(c) == want, (c.describe(), M, N, K, batch, c.beta, want, g.gemm_launched_tile(c))
+        taken += want != (c.block_m, c.block_n, c.split_k)
+    assert taken > 200
+
+
+def test_a_launch_with_many_k_slices_is_planned_quickly():
+    """20000 slices: the plan of a call does not walk through them (2 ms when it did)."""
+    c = next(c for c in (g.gemm_cfg_at(i, 128, 128, 1 << 26, BF16) for i in range(g.gemm_cfg_count(BF16)))
+             if c is not None and (c.block_m, c.block_n, c.split_k) == (128, 128, 32))
+    c.split_k = 20000
+    took = []
+    for _ in range(20):
+        t0 = time.perf_counter()
+        g.gemm_launched_tile(c)
+        took.append(time.perf_counter() - t0)
+    assert min(took) < 2e-4, min(took)
