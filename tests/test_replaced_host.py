@@ -127,13 +127,13 @@ def test_the_search_skips_nothing_that_the_rule_takes():
 
 
 def test_a_launch_with_many_k_slices_is_planned_quickly():
-    """20000 slices: the plan of a call does not walk through them (2 ms when it did)."""
-    c = next(c for c in (g.gemm_cfg_at(i, 128, 128, 1 << 26, BF16) for i in range(g.gemm_cfg_count(BF16)))
+    """4096 slices: the plan of a call does not walk through them (0.15 ms when it did)."""
+    c = next(c for c in (g.gemm_cfg_at(i, 256, 128, 1 << 22, BF16) for i in range(g.gemm_cfg_count(BF16)))
              if c is not None and (c.block_m, c.block_n, c.split_k) == (128, 128, 32))
-    c.split_k = 20000
+    c.split_k = 4096
     took = []
     for _ in range(20):
         t0 = time.perf_counter()
         g.gemm_launched_tile(c)
         took.append(time.perf_counter() - t0)
-    assert min(took) < 2e-4, min(took)
+    assert min(took) < 3e-5, min(took)
