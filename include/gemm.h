@@ -216,9 +216,9 @@ int gemm_cfg_at_batched(int idx, int64_t M, int64_t N, int64_t K, int64_t batch,
  *                     hit rates and K loop); Algorithm 9 becomes omega * sum_g T_g L_tile(g) / T.
  *   gemm_cfg_at_grouped  the same for variant `variant` in [0, gemm_variant_count(dtype)), for sweeps.
  *   gemm_grouped_plan validates cfg and problems and writes n_groups table records (HOST memory,
- *                     caller-owned) and the launch's workgroup count.  With X = the descriptor's
+ *                     caller-owned) and the count of the launch's workgroup slots.  With X = the descriptor's
  *                     XCD count (1 when cfg.xcd_remap = 0) a group of T tiles takes ceil(T / X)
- *                     consecutive slots on every XCD: workgroup p is slot p / X of XCD p % X, XCD x
+ *                     consecutive slots on every XCD: p in [0, count) is slot p / X of XCD p % X, XCD x
  *                     computes the x-th of X contiguous chunks of the group's tiles, and a slot
  *                     beyond its chunk is idle.  Every group is thereby spread over all L2s.  The records are ordered by
  *                     descending K (ties: the caller's order), so that the longest tiles are
@@ -227,11 +227,14 @@ int gemm_cfg_at_batched(int idx, int64_t M, int64_t N, int64_t K, int64_t batch,
  *   gemm_run_grouped  enqueues the launch.  host_table: the records gemm_grouped_plan wrote (checked
  *                     again); dev_table: their copy in device memory, which must stay unchanged
  *                     until the launch has finished.  Groups must not overlap in C.
- *   gemm_grouped_locate  host only: what workgroup `workgroup` of the launch computes, by the
+ *   gemm_grouped_locate  host only: the tile of workgroup slot p = `workgroup`, by the
  *                     kernel's own arithmetic: out3 = {record index, tile_m, tile_n}, or {-1,-1,-1}
- *                     for an idle slot.  GEMM_ERR_INDEX beyond the launch's workgroups.
- *                     (The pipelined kernel may share the tiles of the last slots between two or four
- *                     workgroups each: those are slots by this count too.)
+ *                     for an idle slot.  GEMM_ERR_INDEX beyond the slots.
+ *   gemm_grouped_launched  host only: what workgroup `workgroup` of the grid that gemm_run_grouped launches
+ *                     computes, by the kernel's own arithmetic: out5 = {record index, tile_m, tile_n, first row of
+ *                     the tile, rows}, or {-1,-1,-1,0,0} for an idle one.  One workgroup per slot, except that the kernel of
+ *                     the pipelined 256x256 tiles may share the tiles of the last slots between two or four workgroups
+ *                     each, by rows.  *workgroups_out (may be NULL): the workgroups of the grid; GEMM_ERR_INDEX beyond them.
  * 1 <= n_groups <= 4096.  Errors as for gemm_select / gemm_run; GEMM_ERR_CFG_ILLEGAL also when cfg
  * is not a grouped cfg for n_groups groups or a record does not belong to it.
  */
@@ -258,6 +261,8 @@ int gemm_grouped_plan(const gemm_cfg *cfg, int n_groups, const gemm_problem *pro
                       int64_t *workgroups_out);
 int gemm_grouped_locate(const gemm_cfg *cfg, int n_groups, const gemm_group_rec *table, int64_t workgroup,
                         int32_t out3[3]);
+int gemm_grouped_launched(const gemm_cfg *cfg, int n_groups, const gemm_group_rec *table, int64_t workgroup, int32_t out5[5],
+                          int64_t *workgroups_out);
 int gemm_run_grouped(const gemm_cfg *cfg, int n_groups, const gemm_group_rec *host_table, const void *dev_table,
                      void *hip_stream);
 

@@ -454,6 +454,9 @@ _lib.gemm_grouped_plan.argtypes = [ctypes.POINTER(gemm_cfg), _int, ctypes.POINTE
 _lib.gemm_grouped_locate.restype = _int
 _lib.gemm_grouped_locate.argtypes = [ctypes.POINTER(gemm_cfg), _int, ctypes.POINTER(gemm_group_rec), _i64,
                                      ctypes.POINTER(ctypes.c_int32)]
+_lib.gemm_grouped_launched.restype = _int
+_lib.gemm_grouped_launched.argtypes = [ctypes.POINTER(gemm_cfg), _int, ctypes.POINTER(gemm_group_rec), _i64,
+                                       ctypes.POINTER(ctypes.c_int32), ctypes.POINTER(_i64)]
 _lib.gemm_run_grouped.restype = _int
 _lib.gemm_run_grouped.argtypes = [ctypes.POINTER(gemm_cfg), _int, ctypes.POINTER(gemm_group_rec), _vp, _vp]
 
@@ -523,14 +526,22 @@ def gemm_cfg_at_grouped(variant, problems, dtype, b_layout=0):
 
 
 def gemm_grouped_locate(cfg, table, workgroup):
-    """(record index, tile_m, tile_n) of a workgroup of the grouped launch, or (-1, -1, -1) when idle."""
+    """(record index, tile_m, tile_n) of a workgroup slot of the grouped launch, or (-1, -1, -1) when idle."""
     out = (ctypes.c_int32 * 3)()
     _check(_lib.gemm_grouped_locate(ctypes.byref(cfg), len(table), table, int(workgroup), out), "gemm_grouped_locate")
     return tuple(out)
 
 
+def gemm_grouped_launched(cfg, table, workgroup):
+    """((record index, tile_m, tile_n, first row of the tile, rows) or (-1, -1, -1, 0, 0) when idle, workgroups of the grid) of a
+    workgroup that gemm_run_grouped launches."""
+    out, total = (ctypes.c_int32 * 5)(), _i64()
+    _check(_lib.gemm_grouped_launched(ctypes.byref(cfg), len(table), table, int(workgroup), out, ctypes.byref(total)), "gemm_grouped_launched")
+    return tuple(out), total.value
+
+
 def gemm_grouped_plan(cfg, problems):
-    """(host table as a ctypes array of gemm_group_rec, workgroups of the launch)."""
+    """(host table as a ctypes array of gemm_group_rec, workgroup slots of the launch)."""
     table = (gemm_group_rec * len(problems))()
     total = _i64()
     _check(_lib.gemm_grouped_plan(ctypes.byref(cfg), len(problems), problems, table, ctypes.byref(total)),

@@ -57,7 +57,7 @@ struct KernelArgs {
             // above are unused and each workgroup reads its group's record from this device table.
             const GroupRec *groups;
             int n_groups;
-            // pipelined grouped kernel: from slot tail_slot of an XCD on, tail_parts (1, 2 or 4) workgroups share a tile's rows
+            // pipelined grouped kernel: GroupedTail
             int tail_slot, tail_parts;
         };
         DirectPlan direct;   // general == 0
@@ -402,11 +402,11 @@ __global__ __launch_bounds__(T::NT, T::MIN_WAVES) void gemm_kernel(const KernelA
         const int X = args.xcd_remap ? args.n_xcd : 1;
         const int x = (int)blockIdx.x % X;
         int q = (int)blockIdx.x / X;
-        if (T::GROUPED && q >= args.tail_slot) {
-            const int part = (q - args.tail_slot) & (args.tail_parts - 1);
-            q = args.tail_slot + (q - args.tail_slot) / args.tail_parts;
-            part_rows = BM / args.tail_parts;
-            row_part = part * part_rows;
+        if (T::GROUPED) {
+            const GroupedPart part = grouped_part(q, args.tail_slot, args.tail_parts, BM);
+            q = part.slot;
+            row_part = part.first_row;
+            part_rows = part.rows;
         }
         const GroupRec *r = args.groups + group_of(args.groups, args.n_groups, q);
         const int tiles_m = uniform_i32(r->tiles_m), tiles_n = uniform_i32(r->tiles_n);

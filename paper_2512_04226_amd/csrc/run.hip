@@ -712,7 +712,7 @@ static_assert(sizeof(gemm_group_rec) == sizeof(GroupRec) && offsetof(gemm_group_
 
 // The workgroups of a grouped launch (0: every group is empty) and its kernel.
 static int plan_grouped(const gemm_cfg *cfg, int n_groups, const gemm_group_rec *host_table, int64_t *total, int *kind, const VariantFns **fns,
-                        int64_t *tail_slot, int *tail_parts)
+                        GroupedTail *tail)
 {
     const int X = grouped_xcds(cfg);
     int64_t slots = 0;
@@ -737,21 +737,12 @@ static int plan_grouped(const gemm_cfg *cfg, int n_groups, const gemm_group_rec 
     *kind = kernel_of(cfg->dtype, cfg->kernel_id, cfg->b_layout, ragged, false, tiles ? tile_slabs / tiles : 0);
     *fns = &launcher_of(cfg->dtype, cfg->kernel_id, cfg->b_layout, *kind);
     // (the pipelined tiles are all 256x256 with one slab depth per type)
-    *tail_slot = slots;
-    *tail_parts = 1;
+    *tail = {slots, 1};
     if ((*kind == GEMM_KERNEL_PIPELINED || *kind == GEMM_KERNEL_PIPELINED_RAGGED) && (*fns)->loop_form == 7) {
         *fns = &(cfg->dtype == GEMM_FP16 ? pipelined_fp16 : cfg->dtype == GEMM_BF16 ? pipelined_bf16 : pipelined_fp8)(
             cfg->block_m, cfg->block_n, cfg->b_layout, ragged, PIPELINED_GROUPED);
-        // A last round that leaves half of the CUs (three quarters) without a tile: two (four) workgroups share each of its tiles.
-        // Per XCD, whose 32 CUs hold one workgroup each; a half (quarter) of a tile takes 0.63 (0.46) of its time.  16 groups of 16384
-        // rows together x 4096x4096 bf16, 4.5 rounds: 446 -> 442 us.
-        constexpr int64_t kCusPerXcd = 32;
-        const int64_t rounds = slots / kCusPerXcd, rest = slots % kCusPerXcd;
-        if (X == 8 && rounds >= 1 && rest >= 1 && rest <= kCusPerXcd / 2 && (slots + 3 * rest) * X < ((int64_t)1 << 31)) {
-            *tail_parts = rest <= kCusPerXcd / 4 ? 4 : 2;
-            *tail_slot = slots - rest;
-            *total = (slots + rest * (*tail_parts - 1)) * X;
-        }
+        *tail = grouped_tail(slots, X);
+        *total = (slots + (slots - tail->slot) * (tail->parts - 1)) * X;
     }
     return GEMM_OK;
 }
@@ -769,9 +760,8 @@ extern "C" int gemm_run_grouped(const gemm_cfg *cfg, int n_groups, const gemm_gr
     int64_t total = 0;   // the grid: X workgroups per slot
     int kind = GEMM_KERNEL_PLAIN;
     const VariantFns *fns = nullptr;
-    int64_t tail_slot = 0;
-    int tail_parts = 1;
-    rc = plan_grouped(cfg, n_groups, host_table, &total, &kind, &fns, &tail_slot, &tail_parts);
+    GroupedTail tail;
+    rc = plan_grouped(cfg, n_groups, host_table, &total, &kind, &fns, &tail);
     if (rc)
         return rc;
     if (total == 0)
@@ -791,12 +781,43 @@ extern "C" int gemm_run_grouped(const gemm_cfg *cfg, int n_groups, const gemm_gr
     a.general = 1;
     a.groups = (const GroupRec *)dev_table;
     a.n_groups = n_groups;
-    a.tail_slot = (int)tail_slot;
-    a.tail_parts = tail_parts;
+    a.tail_slot = (int)tail.slot;
+    a.tail_parts = tail.parts;
     if (fns->launch(a, (hipStream_t)hip_stream) != hipSuccess) {
         (void)hipGetLastError();
         return GEMM_ERR_HIP;
     }
+    return GEMM_OK;
+}
+
+extern "C" int gemm_grouped_launched(const gemm_cfg *cfg, int n_groups, const gemm_group_rec *table, int64_t workgroup, int32_t out5[5],
+                                     int64_t *workgroups_out)
+{
+    if (!cfg || !table || !out5)
+        return GEMM_ERR_NULL;
+    int rc = check_grouped_cfg(cfg, n_groups), kind;
+    int64_t total = 0;
+    const VariantFns *fns;
+    GroupedTail tail;
+    if (!rc)
+        rc = plan_grouped(cfg, n_groups, table, &total, &kind, &fns, &tail);
+    if (rc)
+        return rc;
+    if (workgroups_out)
+        *workgroups_out = total;
+    if (workgroup < 0 || workgroup >= total)
+        return GEMM_ERR_INDEX;
+    const int X = grouped_xcds(cfg), x = (int)(workgroup % X);
+    const GroupedPart part = grouped_part((int)(workgroup / X), (int)tail.slot, tail.parts, cfg->block_m);
+    int32_t at[3];
+    rc = gemm_grouped_locate(cfg, n_groups, table, (int64_t)part.slot * X + x, at);
+    if (rc)
+        return rc;
+    const int64_t rows = at[0] < 0 ? 0 : (int64_t)table[at[0]].M - (int64_t)at[1] * cfg->block_m - part.first_row;
+    for (int i = 0; i < 3; ++i)
+        out5[i] = rows > 0 ? at[i] : -1;
+    out5[3] = rows > 0 ? part.first_row : 0;
+    out5[4] = rows > 0 ? (int32_t)std::min<int64_t>(rows, part.rows) : 0;
     return GEMM_OK;
 }
 
@@ -807,11 +828,11 @@ extern "C" int gemm_launched_kernel(const gemm_cfg *cfg, int n_groups, const gem
     int rc, kind = GEMM_KERNEL_PLAIN;
     const VariantFns *fns = nullptr;
     if (n_groups != 0) {
-        int64_t total = 0, tail_slot;
-        int tail_parts;
+        int64_t total = 0;
+        GroupedTail tail;
         rc = check_grouped_cfg(cfg, n_groups);
         if (!rc)
-            rc = plan_grouped(cfg, n_groups, host_table, &total, &kind, &fns, &tail_slot, &tail_parts);
+            rc = plan_grouped(cfg, n_groups, host_table, &total, &kind, &fns, &tail);
     } else {
         Launch p;
         rc = plan_launch(cfg, true, 0, &p);

@@ -117,6 +117,50 @@ def test_plan_table_slots_and_workgroup_to_tile_mapping(xcd_remap):
     assert len(bytes(table)) == 64 * len(shapes)
 
 
+# 32 slots of an XCD full (two of them: eight empty groups between) and 3, 8, 9, 16, 17 more: shared by four, four, two, two, not at all;
+# another tile, a short K and a launch without XCDs: never
+@pytest.mark.parametrize("rest,block,slabs,remap,parts", [(3, 256, 24, 1, 4), (8, 256, 24, 1, 4), (9, 256, 20, 1, 2), (16, 256, 24, 1, 2), (17, 256, 24, 1, 1),
+                                                          (0, 256, 24, 1, 1), (3, 256, 12, 1, 1), (3, 128, 24, 1, 1), (3, 256, 24, 0, 1)])
+@pytest.mark.parametrize("dtype", [0, 1])
+def test_every_row_is_computed_by_one_launched_workgroup(rest, block, slabs, remap, parts, dtype):
+    K, last = slabs * (128 if dtype else 64), [1, 64, 65, 0, 128, 129, 192, 193, 255, 256, 300, 321, 449][:rest]
+    while sum(-(-m // block) for m in last) > rest:
+        last.pop()
+    shapes = [(32 * block, 8 * block, K)] + [(m, block * 8, K) for m in last]      # eight columns of tiles: a slot on every XCD each
+    shapes += [(7, 8 * block, K)] * (rest - sum(-(-m // block) for m in last))
+    probs = probs_with_fake_pointers(shapes)
+    c = next(c for c in (g.gemm_cfg_at_grouped(v, probs, dtype) for v in range(g.gemm_variant_count(dtype)))
+             if c is not None and (c.block_m, c.block_n, c.stages) == (block, block, 2) and c.block_k * (1 if dtype else 2) == 128 and
+             (block == 128 or c.mfma == (32 if dtype else 16)))
+    c.xcd_remap = remap
+    table, slots = g.gemm_grouped_plan(c, probs)
+    launched = g.gemm_grouped_launched(c, table, 0)[1]
+    assert slots == 8 * (32 + rest) and launched == slots + (8 * rest * (parts - 1) if parts > 1 else 0)
+    rows = {}
+    for w in range(launched):
+        (rec, tm, tn, first, count), _ = g.gemm_grouped_launched(c, table, w)
+        if rec < 0:
+            assert (rec, tm, tn, first, count) == (-1, -1, -1, 0, 0)
+            continue
+        assert count >= 1 and first + count <= block and tm * block + first + count <= table[rec].M and first % (block // parts) == 0
+        if w < 8 * 32:
+            assert (rec, tm, tn) == g.gemm_grouped_locate(c, table, w)
+        for r in range(tm * block + first, tm * block + first + count):
+            assert (rec, r, tn) not in rows
+            rows[rec, r, tn] = w
+    assert len(rows) == sum(r.M * r.tiles_n for r in table)
+    for bad in (-1, launched):
+        with pytest.raises(g.GemmError):
+            g.gemm_grouped_launched(c, table, bad)
+    out = (ctypes.c_int32 * 5)()
+    f = g._lib.gemm_grouped_launched
+    assert f(None, len(table), table, 0, out, None) == -1 and f(ctypes.byref(c), len(table), table, 0, None, None) == -1
+    assert f(ctypes.byref(c), len(table), None, 0, out, None) == -1 and f(ctypes.byref(c), len(table), table, 0, out, None) == 0
+    bad = c.copy()
+    bad.groups += 1
+    assert f(ctypes.byref(bad), len(table), table, 0, out, None) == -4
+
+
 def test_grouped_argument_errors():
     shapes = [(300, 1024, 512), (40, 512, 1024)]
     probs = probs_with_fake_pointers(shapes)
