@@ -124,11 +124,11 @@ typedef float f32x16 __attribute__((ext_vector_type(16)));
 // needs three or more column blocks per wave and a multiple of four blocks per slab, else the tile runs form 0.
 // 7: the pipelined loop of the tiles on four waves, 2x2 (256x256: 128x128 wave tiles, accumulators in AGPRs; smaller ones, see
 // retile.hpp, alike).  One wave per SIMD means that nothing hides a stall, so the loop is arranged to have none: the ring takes
-// most of the LDS (256x256: A and B slabs share five 32 KB units, all 160 KB, two slabs and a half resident or in flight; smaller
-// tiles have three to six slabs of each), the loads of a slab are spread evenly over a WHOLE slab of MFMAs (B's in the second
-// k-step, A's in the next slab's first), the loop is unrolled over the ring so that every offset is a constant, the loads' advance along K is the
-// instruction's scalar offset, and fragment rows are instruction offsets: between two MFMAs there is hardly ever more than
-// one other instruction.  See the comment at the loop for what each of these measured.
+// most of the LDS (256x256: A and B slabs share five 32 KB units, all 160 KB, two slabs and a half resident or in flight; 192x256
+// has three slabs of A and two of B, the smaller tiles three to six of each), the loads of a slab are spread evenly over a WHOLE
+// slab of MFMAs (B's in the second k-step, A's in the next slab's first), the loop is unrolled over the ring so that every offset
+// is a constant, the loads' advance along K is the instruction's scalar offset, and fragment rows are instruction offsets: between
+// two MFMAs there is hardly ever more than one other instruction.  See the comment at the loop for what each of these measured.
 // Building with -DG355_FORCE_LOOP_FORM=k gives every variant form k (how the forms are compared).
 // Timing-only diagnostic builds (their RESULTS ARE WRONG; every access stays in bounds and every wait ends):
 // -DG355_DIAG_SKIP_FILL leaves the refills out of the K loop (the ring keeps its first NS slabs),
@@ -267,13 +267,14 @@ struct Tile {
     __device__ static inline int b_off(int krow, int nbyte) { return krow * RB + (nbyte ^ b_key(krow)); }
 };
 
-// KW groups of a tile's waves in one workgroup, each with a ring of its own, compute the same tile over KW slices of its K
-// range; the sums are added in LDS in slice order and stored once (see sliced.inc for where it is used).
+// KW copies of a tile's one wave in a workgroup, each with a ring of its own, compute the same tile over KW slices of its K
+// range; the sums are added in LDS in slice order and stored once, to C (see sliced.inc for where it is used).
 template <class T_, int KW_>
 struct Sliced : T_ {
     static constexpr int KW = KW_, NT = T_::NT * KW_, LDS_BYTES = T_::LDS_BYTES * KW_, MIN_WAVES = NT > 256 ? NT / 256 : 1;
     static_assert(T_::DIRECT && T_::LF != 7 && NT <= 1024 && LDS_BYTES <= 160 * 1024, "direct kernels of the NS-stage ring");
-    static_assert(KW_ * T_::NW * T_::WTM * (T_::WTN * 4 + 16) <= LDS_BYTES, "the sums of all waves fit the rings");
+    static_assert(T_::NW == 1, "a slice's wave shares its ring with no other: it waits for its own loads only");
+    static_assert(KW_ * T_::BM * (T_::BN * 4 + 16) <= LDS_BYTES, "the sums of all waves fit the rings");
 };
 
 // Workgroup id -> (tile_m, tile_n, k_slice).  Hardware deals consecutive workgroup ids
@@ -431,8 +432,8 @@ __global__ __launch_bounds__(T::NT, T::MIN_WAVES) void gemm_kernel(const KernelA
     const int tid = threadIdx.x;
     const int lane = tid & 63;
     // wave-uniform, kept scalar; of its K slice's waves
-    const int wave_wg = __builtin_amdgcn_readfirstlane(tid >> 6), slice = T::KW == 1 ? 0 : wave_wg / T::NW;
-    const int wave = T::KW == 1 ? wave_wg : wave_wg % T::NW;
+    const int wave_wg = __builtin_amdgcn_readfirstlane(tid >> 6), slice = T::KW == 1 ? 0 : wave_wg;
+    const int wave = T::KW == 1 ? wave_wg : 0;
     const int wm = wave / T::WN, wn = wave % T::WN;
 
     for (int seg = 0; seg < nseg; ++seg) {
@@ -750,7 +751,7 @@ __global__ __launch_bounds__(T::NT, T::MIN_WAVES) void gemm_kernel(const KernelA
         for (int l = 0; l < NL; ++l)
             asm volatile("" ::"v"(diag_regs[l]));
 #endif
-        if constexpr (T::KW > 1 && T::NW == 1)      // (a wave that shares its ring with no other waits for nobody)
+        if constexpr (T::KW > 1)      // (a wave that shares its ring with no other waits for nobody)
             asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"(ALLOW) : "memory");
         else
             asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(ALLOW) : "memory");
@@ -881,7 +882,7 @@ __global__ __launch_bounds__(T::NT, T::MIN_WAVES) void gemm_kernel(const KernelA
         if (T::RG && valid) {
             constexpr int EPD = 4 / ES;                // elements per dword
             const int chunk = k_end % BK / EPC;
-            for (int r = (T::KW == 1) ? tid : (slice == last_slice) ? tid % (T::NW * 64) : BM + BN; r < BM + (T::BL == 1 ? BN : 0); r += T::NW * 64) {
+            for (int r = (T::KW == 1) ? tid : (slice == last_slice) ? lane : BM + BN; r < BM + (T::BL == 1 ? BN : 0); r += T::NW * 64) {
                 G355_LDS i32x4 *const c = (G355_LDS i32x4 *)(r < BM ? pa + T::a_off(r, chunk) : pb + T::a_off(r - BM, chunk));
                 i32x4 v = *c;
 #pragma unroll
@@ -1246,7 +1247,7 @@ __global__ __launch_bounds__(T::NT, T::MIN_WAVES) void gemm_kernel(const KernelA
     const float alpha = args.alpha, beta = args.beta;
     if constexpr (T::KW > 1) {
         // Every wave leaves its sums as fp32 in LDS; then each thread adds the KW slices of 8 consecutive columns.
-        constexpr int ROWB = T::WTN * 4 + 16, PART = T::WTM * ROWB;
+        constexpr int ROWB = BN * 4 + 16, PART = BM * ROWB;
         G355_LDS uint8_t *const sums = (G355_LDS uint8_t *)smem;
         __syncthreads();
 #pragma unroll
@@ -1259,7 +1260,7 @@ __global__ __launch_bounds__(T::NT, T::MIN_WAVES) void gemm_kernel(const KernelA
 #pragma unroll
                     for (int r = 0; r < 4; ++r)
                         v[r] = acc[j][i][q * 4 + r];
-                    *(G355_LDS f32x4 *)(sums + wave_wg * PART + (i * MI + lane % MI) * ROWB + (j * MI + q * 8 + 4 * (lane / MI)) * 4) = v;
+                    *(G355_LDS f32x4 *)(sums + slice * PART + (i * MI + lane % MI) * ROWB + (j * MI + q * 8 + 4 * (lane / MI)) * 4) = v;
                 }
         __syncthreads();
         constexpr int CPR = BN / 8;
@@ -1267,19 +1268,12 @@ __global__ __launch_bounds__(T::NT, T::MIN_WAVES) void gemm_kernel(const KernelA
             const int row = c / CPR, col = c % CPR * 8, m = m0 + row, n = n0 + col;
             if (m >= pM || n >= pN)
                 continue;
-            const G355_LDS uint8_t *const src = sums + (row / T::WTM * T::WN + col / T::WTN) * PART + row % T::WTM * ROWB + col % T::WTN * 4;
+            const G355_LDS uint8_t *const src = sums + row * ROWB + col * 4;
             f32x4 lo = *(const G355_LDS f32x4 *)src, hi = *(const G355_LDS f32x4 *)(src + 16);
 #pragma unroll
             for (int s = 1; s < T::KW; ++s) {
-                lo += *(const G355_LDS f32x4 *)(src + s * (T::NW * PART));
-                hi += *(const G355_LDS f32x4 *)(src + s * (T::NW * PART) + 16);
-            }
-            if (out_mode != 0) {
-                const size_t nw = T::RG ? (size_t)(pN + 7) / 8 * 8 : (size_t)pN;
-                float *const dst = args.ws + ((bz * args.split_k + ks) * pM + m) * nw + n;
-                *(f32x4 *)dst = lo;
-                *(f32x4 *)(dst + 4) = hi;
-                continue;
+                lo += *(const G355_LDS f32x4 *)(src + s * PART);
+                hi += *(const G355_LDS f32x4 *)(src + s * PART + 16);
             }
             out_t *const dst = (out_t *)pC + bz * args.stride_c + (size_t)m * pldc + n;
             out8_t o, cin = {};
