@@ -59,6 +59,31 @@ def test_sliced_in_place_of_k_slices_accumulates(dtype, split, slabs, ragged):
     assert torch.equal(C[:, :N], ref) and torch.equal(C[:, N:], old[:, N:])
 
 
+# row-major B in place of K slices: 16 and 32 of them, the shortest and longest K, tiles of the last column half empty
+@pytest.mark.gpu
+@pytest.mark.parametrize("dtype", [BF16, FP16])
+@pytest.mark.parametrize("split,M,N,slabs", [(16, 5, 208, 16), (16, 33, 72, 32), (32, 2, 24, 32), (32, 47, 80, 32)])
+@pytest.mark.parametrize("ragged", [0, 1])
+@pytest.mark.parametrize("beta", [0.0, 2.0])
+def test_sliced_in_place_of_k_slices_of_row_major_weights(dtype, split, M, N, slabs, ragged, beta):
+    from gpu_util import workspace_for
+    from paper_2512_04226_amd import binding as g
+    N, K = N - 3 * ragged, slabs * SLAB[dtype] - 5 * ragged
+    c = _cfg(g, M, N, K, 1, dtype, 0, split)
+    c.alpha, c.beta = 0.5, beta
+    assert g.gemm_launched_kernel(c)[0] == ("sliced ragged" if ragged else "sliced"), c.describe()
+    workspace_for(c)
+    A, B, _ = _problem(1, M, N, K, dtype, 0)
+    ldc = -(-N // 8) * 8 + 8
+    C = torch.randint(-4, 5, (M + 1, ldc), device="cuda").to(torch.float16 if dtype == FP16 else torch.bfloat16)
+    old = C.clone()
+    ref = (0.5 * (A[0, :, :K].double() @ B[0, :K, :N].double()) + beta * old[:M, :N].double()).to(C.dtype)
+    c.lda, c.ldb, c.ldc = A.stride(1), B.stride(1), ldc
+    g.gemm_run(c, A, B, C)
+    torch.cuda.synchronize()
+    assert torch.equal(C[:M, :N], ref) and torch.equal(C[:, N:], old[:, N:]) and torch.equal(C[M], old[M])
+
+
 def test_where_a_launch_is_sliced():
     """At most 256 tiles, small tiles or K slices, a K between the limits."""
     from paper_2512_04226_amd import binding as g

@@ -16,6 +16,7 @@ HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 
 
 def _usage(src, *defines):
+    """Rows of a file of the library (or of a path of its own)."""
     cmd = [HIPCC, "--offload-arch=gfx950", "-O3", "-std=c++17", "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
            "--cuda-device-only", "-c", "-Rpass-analysis=kernel-resource-usage", "-o", os.devnull, *defines, os.path.join(CSRC, src)]
     r = subprocess.run(cmd, capture_output=True, text=True)
@@ -143,3 +144,26 @@ def test_comparison_builds_hold_nothing_that_replaces_a_variant(define):
     sliced kernel in them, in the forced form, launches would run those instead."""
     for src in ("pipelined_bf16.hip", "sliced_bf16.hip"):
         assert _usage(src, define) == []
+
+
+@pytest.mark.skipif(shutil.which(HIPCC) is None and not os.path.exists(HIPCC), reason="needs hipcc")
+def test_the_kernels_that_replace_a_cfgs_keep_no_scratch(tmp_path):
+    """Grouped launches of the pipelined 256x256 tiles, whose four loops need registers that a Stream-K part would not leave;
+    the streaming tiles of up to 256 rows; the sliced kernel.  (192x256, the largest of the others: with its own tests.)"""
+    kinds = {"grouped": ["Tile<%d, 256, 256, %d, 2, 2, %d, 2, %d, 0, 7, %d, 6>" % (es, 128 // es, 16 if es == 2 else 32, bl, rg)
+                         for es in (1, 2) for bl in (0, 1) for rg in (0, 1)],
+             "streaming": ["Tile<%d, %d, 128, %d, 2, 2, %d, 2, %d, 0, 7, 0, 4>" % (es, bm, 128 // es, 16 if es == 2 else 32, bl)
+                           for es in (1, 2) for bl in (0, 1) for bm in (192, 256)],
+             "sliced": ["Sliced<Tile<%d, 16, 16, %d, 1, 1, 16, 3, %d, 0, 0, %d, 3>, 4>" % (es, 256 // es, bl, rg)
+                        for es in (1, 2) for bl in (0, 1) for rg in (0, 1)]}
+    files = []
+    for kind, tiles in kinds.items():
+        for half in (0, 1):
+            files.append(tmp_path / ("%s%d.hip" % (kind, half)))
+            files[-1].write_text('#include "gemm_kernel.hpp"\nnamespace g355 {\n' + "".join(
+                "template __global__ void gemm_kernel<%s>(const KernelArgs);\n" % t for t in tiles[half::2]) + "}\n")
+    with ThreadPoolExecutor(max_workers=6) as ex:
+        for f, rows in zip(files, ex.map(lambda f: _usage(str(f), "-I", CSRC), files)):
+            assert len(rows) == 4, f
+            for r in rows:
+                assert r["scratch"] == 0, r
