@@ -48,8 +48,8 @@ inline double pipelined_us(const PipelinedTile &t, const RetileProblem &p, int64
 }
 
 // Margins, and where the rule does not look, by the measured time over that of the cfg's own kernel, alone and beside another
-// stream's kernel that holds eight CUs.  Of 1669 drawn launches that the price alone retiled 218 took more than 1.03 of it (up to 1.51; 0.91
-// in the mean): what the price leaves out.  Of 1121 others that the lines below leave, 31 (up to 1.13; 0.87 in the mean, beside 0.87).
+// stream's kernel that holds eight CUs.  Of 1517 drawn launches that the price alone retiled 193 took more than 1.03 of it (up to 1.51; 0.91
+// in the mean): what the price leaves out.  Of 1127 others that the lines below leave, 30 (up to 1.13; 0.87 in the mean, beside 0.87).
 //  - fewer than kMinSlabs slabs per workgroup: a pipelined workgroup's prologue and store stage stand alone (0.96 - 1.2 below);
 //  - fewer than kMinGrid workgroups: not what the selector picks these tiles for;
 //  - 256x256 below twenty slabs runs an eight-wave kernel that is up to 8 % faster than the pipelined one it is priced as, and
@@ -63,7 +63,7 @@ inline double pipelined_us(const PipelinedTile &t, const RetileProblem &p, int64
 //  - an old C that the store stage reads: two workgroups of a CU hide that too (up to 17 slabs 1.13 and 1.10 in the mean, to 23 slabs 0.98,
 //    from 24 0.93, with the last above 1.1 at 27);
 //  - batches: the problems' operands come from memory, and only tiles of 192x256 and 256x256 ask for them less often (0.88 in the mean;
-//    the smaller ones 0.97, one in six above 1.03);
+//    the smaller ones 0.97, one in five above 1.03);
 //  - 64x256 in place of another tile for more than 64 rows: 1.09 in the mean;
 //  - what needs all CUs: the price on 248 of them must hold too (single rounds of 249 to 256 workgroups 1.11 beside).
 // A price of 0.55 and less outweighs the last five, one of 0.65 (0.70 from K slices) that of a batch.
@@ -165,7 +165,8 @@ inline Retiled retile_streaming(const RetileProblem &p, bool kc)
 //   16-bit, row-major     .91-1.13  .85-1.10  .81-1.10  .74-1.02  .66-1.04  .40-1.12  .69-1.59  1.37-2.3   1.9-3.1
 //   fp8, K-contiguous    1.15-1.29 1.07-1.13 1.02-1.15  .92- .99  .84-1.13  .75-1.10  .40- .85   .48-1.01   .70-1.26
 //   fp8, row-major       1.09-1.29 1.05-1.30  .99-1.30  .92-1.33  .85-1.33  .79-1.31  .40-1.55   .88-2.0   1.2-2.9
-// and of 2380 drawn launches that a rule of K and tiles alone sliced, by what that left out:
+// and of 2590 drawn launches that a rule of K and tiles alone sliced, by what that left out (1552 others that these lines leave: 0.77 in the
+// mean, eight above 1.03, up to 1.16):
 //  - K-contiguous B against K slices, which spread a long K over more CUs.  One tile row .70-.88 up to K = 12288 (16-bit) and above; more
 //    than 16 tiles in 2-4 rows .66-.94 up to K = 10000, 1.03 and more in five of 13 beyond; in 5-8 rows .72-.82 up to 8192, 1.09 and 1.14
 //    beyond; in more .86 up to 6000, .99 to 1.15 beyond; fp8 in 5 and more rows .77 up to 11000, .91 to 1.20 beyond; batches .82 and 1.00;
